@@ -42,7 +42,9 @@
  *     (Section 4.2.2: the aligned layouts that permit 128-bit accesses), and a K that is a
  *     multiple of 8.  A real, non-diagonal product that misses any of these (any leading
  *     dimension, pointers aligned to an element only, any K) is computed by a general kernel:
- *     same operation and options, much slower.  Complex, dual and diagonal products have no
+ *     same operation and options through registers instead of direct loads, slower (1531 x 1021 x 2003: 28
+ *     against 20 microseconds for 1536 x 1024 x 2048).  It reads nothing outside the operands; a K split
+ *     that cannot have the workspace (see above) is computed in one pass instead.  Complex, dual and diagonal products have no
  *     general kernel: FG_ERR_ALIGN (FG_ERR_UNSUPPORTED for K).  Pointers that are not aligned to
  *     an element are always FG_ERR_ALIGN.
  *   - Sizes: M and N are arbitrary; tiles that hang over the edge of a matrix are predicated
@@ -232,8 +234,8 @@ fg_status fg_gemm_dual(int64_t M, int64_t N, int64_t K, float alpha,
  * remainder of the last step.)  The row and column extents are otherwise arbitrary: tiles that
  * hang over the merged row or column extent are predicated like the edge tiles of fg_gemm.
  * A description that misses any of these is computed by a general kernel: the same mode mapping
- * with element-wise loads and 64-bit offsets, any strides, any extents, element-aligned pointers,
- * tensors of any size, outer products; much slower.  fg_contract_plan() tells which one serves a
+ * with loads through registers and 64-bit offsets, any strides, any extents, element-aligned pointers,
+ * tensors of any size, outer products; slower, most where a tensor has no mode of stride 1.  fg_contract_plan() tells which one serves a
  * description, and why.
  * Limits of both (FG_ERR_UNSUPPORTED): at most 4 modes of extent above 1 per group (rows, columns,
  * summed, batch); merged extents up to 2^30 and at most 2^20 batch indices; no negative strides.

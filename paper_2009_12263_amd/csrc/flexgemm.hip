@@ -12,6 +12,7 @@
 #include <cstring>
 #include <mutex>
 
+#include "general_kernel.hpp"
 #include "kernel_table.hpp"
 
 namespace {
@@ -367,6 +368,45 @@ fg_status static_scratch(int dev, float **out) {
     return FG_OK;
 }
 
+// The scratch memory of one split call: the workspace (ordered against its previous user on another
+// stream, held until release) or the static array of the allocation-free entry point.
+struct Scratch {
+    float *ptr = nullptr;
+    Workspace *guard = nullptr;          // set when release() has to record the use
+    std::unique_lock<std::mutex> lock{g_ws_mutex, std::defer_lock};
+
+    fg_status acquire(bool static_only, int dev, hipStream_t stream) {
+        if (static_only) return static_scratch(dev, &ptr);
+        lock.lock();
+        if (fg_status st = workspace_locked(dev, stream, true, &guard)) return st;
+        ptr = guard->ptr;
+        if (stream_is_capturing(stream)) guard = nullptr;      // a captured call is ordered by its graph's caller
+        else if (guard->used && guard->last_stream != stream) {
+            hipError_t e = hipStreamWaitEvent(stream, guard->last_use, 0);
+            if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "hipStreamWaitEvent on the workspace's last use failed: %s", hipGetErrorString(e));
+        }
+        return FG_OK;
+    }
+    // for callers that can do without: no error is left behind
+    bool try_acquire(bool static_only, int dev, hipStream_t stream) {
+        char kept[sizeof g_err];
+        memcpy(kept, g_err, sizeof kept);
+        if (acquire(static_only, dev, stream) == FG_OK) return true;
+        memcpy(g_err, kept, sizeof kept);
+        (void)hipGetLastError();
+        guard = nullptr;
+        return false;
+    }
+    fg_status release(hipStream_t stream) {
+        if (!guard) return FG_OK;
+        hipError_t e = hipEventRecord(guard->last_use, stream);
+        if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "hipEventRecord after the split-K reduction failed: %s", hipGetErrorString(e));
+        guard->last_stream = stream;
+        guard->used = true;
+        return FG_OK;
+    }
+};
+
 fg_status launch(const fg::KernelEntry &k, const fg::GemmParams &p, hipStream_t stream) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return fail(FG_ERR_LAUNCH, "no HIP device is current");
@@ -549,6 +589,89 @@ fg_status normalise(int64_t M, int64_t N, int64_t K, float alpha, const fg_matri
 }
 
 
+// ---- general kernel (general_kernel.hpp) --------------------------------------------------------------
+
+// Block tile and K ranges of a product on the general kernel: the smallest estimated time.  Measured
+// with one workgroup per compute unit and little less per workgroup with two: a K step of 64
+// takes 0.9 us with the 128x128 tile, two steps (one per wave group) 0.7 us with the 64x64 tile, a
+// workgroup's start and stores 1 us (64x64) or 2; a split adds a launch and the reduction pass (5 us and its
+// traffic).  Against every tile and split forced over 13 shapes from 195x65x2500 to 4095x4097x4099 the
+// choice is the fastest or within 8 %: 1531x1021x2003 28.0 us (128x128: 35.7), 4095x4097x4099 244 us
+// (64x64: 367), 301x301x6001 split in ten 18 us (one pass: 37).
+// The partial products of a split are kept to the 16 MiB of the static array, so that the
+// allocation-free entry point makes the same plan.
+struct GeneralPlan { int variant, bm, bn, splits; };
+GeneralPlan choose_general(int64_t M, int64_t N, int64_t K, int64_t batches, bool may_split) {
+    static const int edge[fg::GENERAL_COUNT] = {128, 64}, groups[fg::GENERAL_COUNT] = {1, 2};
+    static const double round_us[fg::GENERAL_COUNT] = {0.9, 0.7}, fixed_us[fg::GENERAL_COUNT] = {2, 1};
+    static const int split_options[] = {1, 2, 3, 4, 6, 8, 10, 12, 16, 24, 32, 48, 64};
+    const int64_t nk = (K + 63) / 64;
+    const int ft = g_force_tile.load(std::memory_order_relaxed), fs = g_force_split.load(std::memory_order_relaxed);
+    GeneralPlan best{fg::GENERAL_64x64, 64, 64, 1};
+    double best_cost = -1;
+    for (int v = 0; v < fg::GENERAL_COUNT; ++v) {
+        if (ft == fg::TILE_128x128 && v != fg::GENERAL_128x128) continue;
+        if (ft == fg::TILE_64x64 && v != fg::GENERAL_64x64) continue;
+        const int64_t tiles = ((M + edge[v] - 1) / edge[v]) * ((N + edge[v] - 1) / edge[v]) * batches;
+        const double tile_bytes = 4.0 * edge[v] * edge[v];
+        for (int S : split_options) {
+            if (fs >= 1) { if (S != 1) break; S = fs; }
+            if (S > 1 && (!may_split || S > nk || (fs < 1 && nk / S < 4) || (double)tiles * S * tile_bytes > kStaticScratchBytes)) {
+                if (fs < 1) break;
+                S = 1;
+            }
+            const int64_t steps = (nk + S - 1) / S, load = (tiles * S + kNumCU - 1) / kNumCU;
+            double cost = (double)load * ((double)((steps + groups[v] - 1) / groups[v]) * round_us[v] + fixed_us[v]);
+            if (S > 1) cost += 5 + (2.0 * S + 2) * (double)tiles * tile_bytes / 3e6;
+            if (best_cost < 0 || cost < best_cost) { best = GeneralPlan{v, edge[v], edge[v], S}; best_cost = cost; }
+        }
+    }
+    return best;
+}
+
+fg_status general_gemm(const Problem &q, bool static_only, hipStream_t stream) {
+    fg::GeneralParams f;
+    memset(&f, 0, sizeof f);
+    GeneralPlan plan = choose_general(q.M, q.N, q.K, 1, true);
+    f.M = (int32_t)q.M; f.N = (int32_t)q.N; f.K = (int32_t)q.K;
+    f.A = (const uint16_t *)q.A; f.B = (const uint16_t *)q.B;
+    f.a_rs = q.a_kc ? q.lda : 1; f.a_ks = q.a_kc ? 1 : q.lda;
+    f.b_rs = q.b_kc ? q.ldb : 1; f.b_ks = q.b_kc ? 1 : q.ldb;
+    f.a_span = (q.M - 1) * f.a_rs + (q.K - 1) * f.a_ks + 1; f.b_span = (q.N - 1) * f.b_rs + (q.K - 1) * f.b_ks + 1;
+    f.C = q.C; f.D = q.D; f.ldc = q.ldc; f.ldd = q.ldd;
+    f.bias = q.bias; f.bias_dim = q.bias_dim; f.act = q.act; f.c_act = q.c_act;
+    f.alpha = q.alpha; f.beta = q.beta;
+    f.a_add2 = (uint32_t)q.a_add * 0x10001u; f.b_add2 = (uint32_t)q.b_add * 0x10001u; f.ab_add = q.ab_add;
+    f.batches = 1; f.splits = 1;
+    const int64_t tiles_m = (q.M + plan.bm - 1) / plan.bm, tiles_n = (q.N + plan.bn - 1) / plan.bn;
+    if (tiles_m * tiles_n >= (1ll << 31)) return fail(FG_ERR_UNSUPPORTED, "too many tiles");
+    f.tiles_m = (int32_t)tiles_m; f.tiles_n = (int32_t)tiles_n;
+    const int tiles = (int)(tiles_m * tiles_n);
+    Scratch scratch;
+    if (plan.splits > 1) {
+        // A call that cannot have the scratch memory (a capturing stream before the workspace
+        // exists, no memory left) is computed in one pass.
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return fail(FG_ERR_LAUNCH, "no HIP device is current");
+        if (!scratch.try_acquire(static_only, dev, stream)) plan.splits = 1;
+    }
+    if (plan.splits > 1) {
+        fg::GeneralParams part = f;
+        part.splits = plan.splits;
+        part.split_kt = (int32_t)(((q.K + 63) / 64 + plan.splits - 1) / plan.splits);
+        part.D = scratch.ptr;
+        hipError_t e = fg::launch_gemm_general(part, q.a_kc, q.b_kc, q.bf16, plan.variant, stream);
+        if (e == hipSuccess)
+            e = fg::launch_splitk_reduce(scratch.ptr, plan.splits, 0, tiles, plan.bm, plan.bn, f.tiles_m, f.tiles_n, f.M, f.N, q.alpha, q.beta,
+                                         q.C, q.ldc, q.D, q.ldd, q.bias, q.bias_dim, q.act, q.c_act, stream);
+        if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "launch of the general kernel failed: %s", hipGetErrorString(e));
+        return scratch.release(stream);
+    }
+    hipError_t e = fg::launch_gemm_general(f, q.a_kc, q.b_kc, q.bf16, plan.variant, stream);
+    if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "launch of the general kernel failed: %s", hipGetErrorString(e));
+    return FG_OK;
+}
+
 // ---- tensor contraction -> GEMM description (Section 5.5) -----------------------------------------
 // Modes shared by A and C become GEMM rows (M), modes shared by B and C columns (N), modes
 // shared by A and B the summed index (K).  Inside a merged index the first mode is the fastest
@@ -562,6 +685,10 @@ struct Contraction {
     const void *A, *B;
     bool a_kc, b_kc;
     fg::ModeGroup a_m, a_k, b_n, b_k, c_m, c_n;
+    // general kernel only: true extents of the leading modes, element strides inside a piece, elements
+    // each operand spans
+    int32_t m_ext0, n_ext0, k_ext0;
+    int64_t a_es, b_es, a_span, b_span;
 };
 
 struct TensorView { int32_t n; const int32_t *modes; const int64_t *strides; };
@@ -646,7 +773,6 @@ fg_status plan_contraction(int32_t nA, const int32_t *modesA, const int64_t *str
     c.a_kc = ua >= 0 && is_sum(ua);           // A's contiguous mode is summed over
     c.b_kc = ub >= 0 && is_sum(ub);
     if (c.a_kc && c.b_kc && ua != ub) need_general("A and B are contiguous along different summed modes (%d and %d)", ua, ub);
-    if (c.general) { ua = ub = -1; c.a_kc = c.b_kc = false; }   // the merged indices then follow the tensors' own mode order
 
     // order of the modes inside each merged index
     int32_t m_modes[16], n_modes_[16], k_modes[16], b_modes[16];
@@ -668,10 +794,11 @@ fg_status plan_contraction(int32_t nA, const int32_t *modesA, const int64_t *str
     // Modes of extent 1 carry no index and are dropped.  For the others the kernel divides by the
     // extent with a multiply-high: with 2^s < e <= 2^(s+1) and magic = floor(2^(32+s)/e) + 1,
     // floor(idx / e) == (idx * magic) >> (32 + s) for every 0 <= idx < 2^31.
-    auto fill = [&](fg::ModeGroup &g, const int32_t *modes, int n, const TensorView &t, int64_t &total) {
+    auto fill = [&](fg::ModeGroup &g, const int32_t *modes, int n, const TensorView &t, int64_t &total, bool round_first = false) {
         g.n = 0; total = 1;
         for (int i = 0; i < n; ++i) {
             int64_t e; extent_of(modes[i], e);
+            if (i == 0 && round_first && e > 1) e = (e + 7) / 8 * 8;
             total *= e;
             if (e == 1) continue;
             int k = g.n++;
@@ -696,6 +823,11 @@ fg_status plan_contraction(int32_t nA, const int32_t *modesA, const int64_t *str
     for (int i = 0; i < ta.n; ++i) if (ta.strides[i] < 0) return fail(FG_ERR_UNSUPPORTED, "negative strides are not supported");
     for (int i = 0; i < tb.n; ++i) if (tb.strides[i] < 0) return fail(FG_ERR_UNSUPPORTED, "negative strides are not supported");
     for (int i = 0; i < tc.n; ++i) if (tc.strides[i] < 0) return fail(FG_ERR_UNSUPPORTED, "negative strides are not supported");
+    auto span = [&](const TensorView &t) {
+        int64_t sp = 1;
+        for (int i = 0; i < t.n; ++i) { int64_t e; extent_of(t.modes[i], e); sp += (e - 1) * t.strides[i]; }
+        return sp;
+    };
     if (!c.general) {
         if ((c.a_kc || c.b_kc) && c.a_k.n > 0 && c.a_k.extent[0] % 8) need_general("the leading summed mode (%d) is contiguous in A or B and its extent is not a multiple of 8", k_modes[0]);
         if (c.a_kc && c.a_k.n > 0 && c.a_k.stride[0] != 1) need_general("the leading summed mode is not contiguous in A");
@@ -714,11 +846,6 @@ fg_status plan_contraction(int32_t nA, const int32_t *modesA, const int64_t *str
         if (!strides_ok(c.b_n, c.b_kc ? 0 : 1) || !strides_ok(c.b_k, c.b_kc ? 1 : 0) || !strides_ok(c.b_b, 0))
             need_general("a stride of B other than its contiguous mode's is not a multiple of 8 elements");
         // the tiled kernels address A, B and C with 32-bit byte offsets inside a 2 GiB window
-        auto span = [&](const TensorView &t) {
-            int64_t sp = 1;
-            for (int i = 0; i < t.n; ++i) { int64_t e; extent_of(t.modes[i], e); sp += (e - 1) * t.strides[i]; }
-            return sp;
-        };
         if (span(ta) * 2 >= (1ll << 31) || span(tb) * 2 >= (1ll << 31) || span(tc) * 4 >= (1ll << 31)) need_general("A, B or C spans 2 GiB or more");
     }
     if (!c.general) {
@@ -733,6 +860,63 @@ fg_status plan_contraction(int32_t nA, const int32_t *modesA, const int64_t *str
         c.K = c.K / c.a_k.extent[0] * ((c.a_k.extent[0] + 63) / 64 * 64);
     }
     if (c.M > (1 << 30) || c.N > (1 << 30) || c.K > (1 << 30) || c.batches > (1 << 20)) return fail(FG_ERR_UNSUPPORTED, "merged extents above 2^30 (2^20 for batch modes) are not supported");
+    if (c.general) {
+        // Groups for the general kernel, whose threads fetch pieces of eight elements along one mode
+        // of each operand: the mode with stride 1, as one load per piece.  A unit-stride mode
+        // shorter than 5 would fill its pieces badly, and pieces along the summed modes can follow one mode
+        // only; such an operand is fetched element by element along its longest row or column mode.
+        auto extent = [&](int32_t label) { int64_t e = 1; extent_of(label, e); return e; };
+        auto unit_any = [&](const TensorView &t) {
+            for (int i = 0; i < t.n; ++i)
+                if (t.strides[i] == 1 && extent(t.modes[i]) >= 5 && !is_batch(t.modes[i])) return (int)t.modes[i];
+            return -1;
+        };
+        auto longest = [&](const int32_t *modes, int n) {
+            int best = -1;
+            for (int i = 0; i < n; ++i) if (best < 0 || extent(modes[i]) > extent(best)) best = modes[i];
+            return best;
+        };
+        auto to_front = [](int32_t *modes, int n, int32_t label) {
+            for (int i = 0; i < n; ++i)
+                if (modes[i] == label) { for (; i > 0; --i) modes[i] = modes[i - 1]; modes[0] = label; return; }
+        };
+        int la = unit_any(ta), lb = unit_any(tb);
+        bool have_a = la >= 0, have_b = lb >= 0;
+        c.a_kc = have_a && is_sum(la); c.b_kc = have_b && is_sum(lb);
+        if (c.a_kc && c.b_kc && la != lb) {
+            if (span(ta) >= span(tb)) { c.b_kc = false; have_b = false; }
+            else { c.a_kc = false; have_a = false; }
+        }
+        if (!have_a) la = longest(m_modes, nm);
+        if (!have_b) lb = longest(n_modes_, nn);
+        if (!c.a_kc) to_front(m_modes, nm, la);
+        if (!c.b_kc) to_front(n_modes_, nn, lb);
+        if (c.a_kc) to_front(k_modes, nkk, la);
+        else if (c.b_kc) to_front(k_modes, nkk, lb);
+        const bool k_pad = c.a_kc || c.b_kc;
+        int64_t padded;
+        fill(c.a_m, m_modes, nm, ta, c.M, !c.a_kc); fill(c.c_m, m_modes, nm, tc, padded, !c.a_kc);
+        fill(c.b_n, n_modes_, nn, tb, c.N, !c.b_kc); fill(c.c_n, n_modes_, nn, tc, padded, !c.b_kc);
+        fill(c.a_k, k_modes, nkk, ta, c.K, k_pad); fill(c.b_k, k_modes, nkk, tb, padded, k_pad);
+        // true extent of a group's leading mode, and its stride in the operand; a group without modes has one index
+        auto lead = [&](fg::ModeGroup &g, fg::ModeGroup &other, bool rounded, int label, int64_t &total, int32_t &ext0) {
+            if (g.n == 0 && rounded) {           // one row (or column): a piece with one element
+                g.n = other.n = 1;
+                g.extent[0] = other.extent[0] = 8;
+                g.shift[0] = other.shift[0] = 2;
+                g.magic[0] = other.magic[0] = (uint32_t)((1ull << 34) / 8 + 1);
+                total = 8; ext0 = 1;
+            } else {
+                ext0 = rounded ? (int32_t)extent(label) : g.extent[0];
+            }
+        };
+        lead(c.a_m, c.c_m, !c.a_kc, la, c.M, c.m_ext0);
+        lead(c.b_n, c.c_n, !c.b_kc, lb, c.N, c.n_ext0);
+        lead(c.a_k, c.b_k, k_pad, c.a_kc ? la : lb, c.K, c.k_ext0);
+        auto stride_of = [&](const TensorView &t, int label, bool pseudo) { const int i = pseudo ? -1 : find_mode(t, label); return i < 0 ? (int64_t)1 : t.strides[i]; };
+        c.a_es = stride_of(ta, la, nm == 0 && !c.a_kc); c.b_es = stride_of(tb, lb, nn == 0 && !c.b_kc);
+        c.a_span = span(ta); c.b_span = span(tb);
+    }
     return FG_OK;
 }
 
@@ -782,22 +966,7 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
     Problem q;
     if (fg_status st = normalise(M, N, K, alpha, A, B, beta, C, D, ep, dual, lt, q)) return st;
     if (q.M == 0 || q.N == 0) return FG_OK;
-    if (q.general) {
-        fg::FallbackParams f;
-        memset(&f, 0, sizeof f);
-        f.M = (int32_t)q.M; f.N = (int32_t)q.N; f.K = (int32_t)q.K;
-        f.A = (const uint16_t *)q.A; f.B = (const uint16_t *)q.B;
-        f.a_rs = q.a_kc ? q.lda : 1; f.a_ks = q.a_kc ? 1 : q.lda;
-        f.b_rs = q.b_kc ? q.ldb : 1; f.b_ks = q.b_kc ? 1 : q.ldb;
-        f.C = q.C; f.D = q.D; f.ldc = q.ldc; f.ldd = q.ldd;
-        f.bias = q.bias; f.bias_dim = q.bias_dim; f.act = q.act; f.c_act = q.c_act;
-        f.alpha = q.alpha; f.beta = q.beta;
-        f.a_add = q.a_add; f.b_add = q.b_add; f.ab_add = q.ab_add; f.bf16 = q.bf16;
-        if ((int64_t)((q.M + 63) / 64) * ((q.N + 63) / 64) >= (1ll << 31)) return fail(FG_ERR_UNSUPPORTED, "too many tiles");
-        hipError_t e = fg::launch_gemm_fallback(f, (hipStream_t)hip_stream);
-        if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "launch of the general kernel failed: %s", hipGetErrorString(e));
-        return FG_OK;
-    }
+    if (q.general) return general_gemm(q, static_only, (hipStream_t)hip_stream);
     Plan plan{0, 1, 1};
     const fg::KernelEntry *kp = select_kernel(q, &plan);
     if (!kp) return fail(FG_ERR_UNSUPPORTED, "no kernel for M=%lld, N=%lld", (long long)q.M, (long long)q.N);
@@ -859,25 +1028,12 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
     }
     if (S == 1) return launch(k, p, stream);
     const int64_t need = (int64_t)count * S * k.bm * k.bn * 4;
-    float *ws = nullptr;
-    Workspace *guard = nullptr;
-    std::unique_lock<std::mutex> ws_lock(g_ws_mutex, std::defer_lock);
-    if (static_only) {
-        if (need > kStaticScratchBytes)
-            return fail(FG_ERR_UNSUPPORTED, "this problem is computed as %d partial products over K, which need %lld bytes of scratch memory; the "
-                                            "static scratch array of the allocation-free entry point holds %lld (use fg_gemm_ex)",
-                        S, (long long)need, (long long)kStaticScratchBytes);
-        if (fg_status st = static_scratch(dev, &ws)) return st;
-    } else {
-        ws_lock.lock();
-        if (fg_status st = workspace_locked(dev, stream, true, &guard)) return st;
-        ws = guard->ptr;
-        if (stream_is_capturing(stream)) guard = nullptr;      // a captured call is ordered by its graph's caller
-        else if (guard->used && guard->last_stream != stream) {
-            hipError_t e = hipStreamWaitEvent(stream, guard->last_use, 0);
-            if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "hipStreamWaitEvent on the workspace's last use failed: %s", hipGetErrorString(e));
-        }
-    }
+    if (static_only && need > kStaticScratchBytes)
+        return fail(FG_ERR_UNSUPPORTED, "this problem is computed as %d partial products over K, which need %lld bytes of scratch memory; the "
+                                        "static scratch array of the allocation-free entry point holds %lld (use fg_gemm_ex)",
+                    S, (long long)need, (long long)kStaticScratchBytes);
+    Scratch scratch;
+    if (fg_status st = scratch.acquire(static_only, dev, stream)) return st;
     if (first > 0) {
         fg::GemmParams head = p;
         head.tile_count = first;
@@ -888,19 +1044,13 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
     part.tile_begin = first; part.tile_count = count;
     part.splits = S;
     part.split_kt = (int32_t)((nk + S - 1) / S);
-    part.D = ws;
+    part.D = scratch.ptr;
     part.C = nullptr; part.has_c = 0; part.bias = nullptr; part.act = 0; part.c_act = 0; part.alpha = 1.f; part.beta = 0.f;
     if (fg_status st = launch(k, part, stream)) return st;
-    hipError_t e = fg::launch_splitk_reduce(ws, S, first, count, k.bm, k.bn, p.tiles_m, p.tiles_n, (int)q.M, (int)q.N, q.alpha, q.beta,
+    hipError_t e = fg::launch_splitk_reduce(scratch.ptr, S, first, count, k.bm, k.bn, p.tiles_m, p.tiles_n, (int)q.M, (int)q.N, q.alpha, q.beta,
                                             q.C, q.ldc, q.D, q.ldd, q.bias, q.bias_dim, q.act, q.c_act, stream);
     if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "launch of the split-K reduction failed: %s", hipGetErrorString(e));
-    if (guard) {
-        e = hipEventRecord(guard->last_use, stream);
-        if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "hipEventRecord after the split-K reduction failed: %s", hipGetErrorString(e));
-        guard->last_stream = stream;
-        guard->used = true;
-    }
-    return FG_OK;
+    return scratch.release(stream);
 }
 
 fg_status fg_gemm(int64_t M, int64_t N, int64_t K, float alpha, const fg_matrix *A, const fg_matrix *B,
@@ -961,7 +1111,7 @@ fg_status fg_gemm_plan(int64_t M, int64_t N, int64_t K, int32_t layoutA, int32_t
     if (g_relaxed.status != FG_OK) {
         // K is not a multiple of 8 (alignment is not known to this query)
         if (q.cplx || q.a_diag || q.b_diag || q.cd16) return fail(g_relaxed.status, "%s (complex, dual, diagonal and FG_F16-result products have no general kernel)", g_relaxed.msg);
-        snprintf(buf, (size_t)buf_len, "gemm_general_64x64x32");
+        snprintf(buf, (size_t)buf_len, "gemm_general_64x64x32");     // a fixed name: callers compare it, the tile is choose_general's
         return FG_OK;
     }
     Plan plan{0, 1, 1};
@@ -1013,18 +1163,21 @@ fg_status fg_contract(int32_t nA, const int32_t *modesA, const int64_t *stridesA
     if (c.M == 0 || c.N == 0) return FG_OK;
     const bool use_c = Cin != nullptr && beta != 0.f;        // beta == 0: Cin is never read
     if (c.general) {
-        fg::ContractFallbackParams f;
+        fg::GeneralParams f;
         memset(&f, 0, sizeof f);
-        f.M = (int32_t)c.M; f.N = (int32_t)c.N; f.K = (int32_t)c.K; f.batches = (int32_t)c.batches;
-        f.A = (const _Float16 *)c.A; f.B = (const _Float16 *)c.B;
+        const GeneralPlan plan = choose_general(c.M, c.N, c.K, c.batches, false);
+        f.M = (int32_t)c.M; f.N = (int32_t)c.N; f.K = (int32_t)c.K; f.batches = (int32_t)c.batches; f.splits = 1;
+        f.A = (const uint16_t *)c.A; f.B = (const uint16_t *)c.B;
+        f.a_span = c.a_span; f.b_span = c.b_span; f.a_es = c.a_es; f.b_es = c.b_es;
         f.C = use_c ? Cin : nullptr; f.D = Cout;
         f.a_m = c.a_m; f.a_k = c.a_k; f.b_n = c.b_n; f.b_k = c.b_k; f.c_m = c.c_m; f.c_n = c.c_n;
         f.a_b = c.a_b; f.b_b = c.b_b; f.c_b = c.c_b;
+        f.m_ext0 = c.m_ext0; f.n_ext0 = c.n_ext0; f.k_ext0 = c.k_ext0;
         f.alpha = alpha; f.beta = use_c ? beta : 0.f;
-        f.a_kfast = c.a_k.n > 0 && c.a_k.stride[0] == 1;
-        f.b_kfast = c.b_k.n > 0 && c.b_k.stride[0] == 1;
-        if (((c.M + 63) / 64) * ((c.N + 63) / 64) * c.batches >= (1ll << 31)) return fail(FG_ERR_UNSUPPORTED, "too many tiles");
-        hipError_t e = fg::launch_contract_fallback(f, (hipStream_t)hip_stream);
+        const int64_t tiles_m = (c.M + plan.bm - 1) / plan.bm, tiles_n = (c.N + plan.bn - 1) / plan.bn;
+        if (tiles_m * tiles_n * c.batches >= (1ll << 31)) return fail(FG_ERR_UNSUPPORTED, "too many tiles");
+        f.tiles_m = (int32_t)tiles_m; f.tiles_n = (int32_t)tiles_n;
+        hipError_t e = fg::launch_contract_general(f, c.a_kc, c.b_kc, plan.variant, (hipStream_t)hip_stream);
         if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "launch of the general contraction kernel failed: %s", hipGetErrorString(e));
         return FG_OK;
     }

@@ -1,0 +1,20 @@
+// Instantiations of the general kernel for real matrix products (see general_kernel.hpp): operands
+// with any leading dimension, bases aligned to an element only, any K.
+#include "general_kernel.hpp"
+#include "kernel_table.hpp"
+
+namespace fg {
+namespace {
+
+template <bool BF16>
+GeneralFn pick(bool a_kc, bool b_kc, int variant) {
+    return variant == GENERAL_128x128 ? general_fn<128, 128, 4, 2, 1, BF16, true>(a_kc, b_kc) : general_fn<64, 64, 2, 2, 2, BF16, true>(a_kc, b_kc);
+}
+
+}  // namespace
+
+hipError_t launch_gemm_general(const GeneralParams &p, bool a_kc, bool b_kc, bool bf16, int variant, hipStream_t stream) {
+    return launch_general((bf16 ? pick<true>(a_kc, b_kc, variant) : pick<false>(a_kc, b_kc, variant)), p, stream);
+}
+
+}  // namespace fg

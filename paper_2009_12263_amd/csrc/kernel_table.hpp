@@ -65,36 +65,14 @@ hipError_t launch_splitk_reduce(const float *W, int splits, int tile_begin, int 
                                 int tiles_n, int M, int N, float alpha, float beta, const float *C, int64_t ldc, float *D,
                                 int64_t ldd, const float *bias, int bias_dim, int act, int c_act, hipStream_t stream);
 
-// General kernel for real products with unaligned operands or a K that is not a multiple of 8
-// (gemm_fallback.hip).  D is column-major; A is addressed as A[m * a_rs + k * a_ks], B as
-// B[n * b_rs + k * b_ks] (element strides).
-struct FallbackParams {
-    int32_t M, N, K;
-    const uint16_t *A, *B;
-    int64_t a_rs, a_ks, b_rs, b_ks;
-    const float *C;
-    float *D;
-    int64_t ldc, ldd;
-    const float *bias;
-    int32_t bias_dim, act, c_act;
-    float alpha, beta;
-    uint16_t a_add, b_add;       // FP16 bit patterns added to loaded A and B elements when ab_add
-    bool ab_add, bf16;
-};
-hipError_t launch_gemm_fallback(const FallbackParams &p, hipStream_t stream);
-
-// General kernel for contractions the tiled kernels cannot take (contract_fallback.hip): same
-// mode groups as GemmParams, 64-bit element offsets.
-struct ContractFallbackParams {
-    int32_t M, N, K, batches;
-    const _Float16 *A, *B;
-    const float *C;
-    float *D;
-    ModeGroup a_m, a_k, b_n, b_k, c_m, c_n, a_b, b_b, c_b;
-    float alpha, beta;
-    int32_t a_kfast, b_kfast;    // the operand's leading summed mode has stride 1: load with lanes along k
-};
-hipError_t launch_contract_fallback(const ContractFallbackParams &p, hipStream_t stream);
+// General kernel (general_kernel.hpp): matrices with unaligned operands or a K that is not a multiple
+// of 8 (gemm_general.hip), contractions the tiled kernels cannot take (contract_general.hip).  Two
+// shapes of 512 threads: 128x128 tiles with eight 32x64 waves, and 64x64 tiles whose two groups of
+// four waves take alternate K steps.
+enum GeneralVariant { GENERAL_128x128 = 0, GENERAL_64x64 = 1, GENERAL_COUNT = 2 };
+struct GeneralParams;
+hipError_t launch_gemm_general(const GeneralParams &p, bool a_kc, bool b_kc, bool bf16, int variant, hipStream_t stream);
+hipError_t launch_contract_general(const GeneralParams &p, bool a_kc, bool b_kc, int variant, hipStream_t stream);
 
 // Entry index inside one table of real kernels: three variants per tile.
 enum Variant { VARIANT_MATRIX = 0, VARIANT_CONTRACT = 1, VARIANT_CONTRACT_STREAM = 2, VARIANT_COUNT = 3 };

@@ -1,0 +1,115 @@
+"""GPU parity of the general kernel (operands the tiled kernels cannot take) at the sizes where its
+pieces of eight, its K steps of 64, its two block tiles and its K split can go wrong.  Integer data
+unless stated: every entry must equal the exact result."""
+import itertools
+
+import pytest
+import torch
+
+from paper_2009_12263_amd import binding as fg
+from paper_2009_12263_amd import workloads as W
+from tests.parity import delenv, run_contract_case, run_unaligned_gemm_case, setenv
+
+pytestmark = pytest.mark.gpu
+LAYOUTS = [fg.FG_COL, fg.FG_ROW]
+a, b, c, d, e, f, g = range(7)
+
+
+def say(msg):
+    print("[case] " + msg, flush=True)
+
+
+@pytest.mark.parametrize("tile", ["2", "3"])
+@pytest.mark.parametrize("la,lb", list(itertools.product(LAYOUTS, LAYOUTS)))
+def test_matrix_edges(monkeypatch, tile, la, lb):
+    """K around the 8 k of a piece, the 64 of a step and the 72 from which a step takes unchecked
+    loads; rows around the tiles; operands of fewer than eight elements; tight and padded leading
+    dimensions (a tight one puts the last piece at the very end of the operand)."""
+    setenv(monkeypatch, "FG_FORCE_TILE", tile)
+    for K in (1, 7, 9, 63, 65, 71, 72, 73, 127, 129, 200, 263, 521):
+        for (M, N) in ((1, 1), (3, 65), (129, 7), (200, 131)):
+            say("tile %s %dx%dx%d A=%d B=%d" % (tile, M, N, K, la, lb))
+            run_unaligned_gemm_case(M, N, K, la, lb, pads=(0, 0, 0), offsets=(1, 0, 0))
+            run_unaligned_gemm_case(M, N, K, la, lb, fg.FG_ROW, pads=(1, 3, 2), bias_dim=1, act=fg.FG_ACT_RELU, c_act=fg.FG_ACT_RELU, beta=-2.0)
+    run_unaligned_gemm_case(130, 70, 77, la, lb, bf16=True, pads=(0, 1, 0))
+    run_unaligned_gemm_case(130, 70, 77, la, lb, ab_add=(1.0, -2.0), pads=(0, 1, 0))
+
+
+@pytest.mark.parametrize("tile,splits", [("2", 2), ("2", 5), ("3", 2), ("3", 3), ("3", 9)])
+def test_matrix_k_split(monkeypatch, tile, splits):
+    """Partial products over K ranges, an odd number of steps per range, empty ranges at the end."""
+    setenv(monkeypatch, "FG_FORCE_TILE", tile)
+    setenv(monkeypatch, "FG_FORCE_SPLIT", str(splits))
+    for (M, N, K) in ((70, 45, 1001), (131, 129, 641), (65, 200, 65), (9, 5, 577)):
+        for la, lb in ((fg.FG_COL, fg.FG_COL), (fg.FG_ROW, fg.FG_ROW)):
+            say("tile %s split %d %dx%dx%d" % (tile, splits, M, N, K))
+            run_unaligned_gemm_case(M, N, K, la, lb, bias_dim=0, act=fg.FG_ACT_RELU, beta=0.5)
+            run_unaligned_gemm_case(M, N, K, la, lb, ints=False, ab_add=(0.5, -0.25))
+
+
+def test_planners_own_choices():
+    for (M, N, K) in ((301, 301, 6001), (17, 1025, 4099), (1531, 130, 515), (1100, 1030, 129)):
+        say("%dx%dx%d floats" % (M, N, K))
+        run_unaligned_gemm_case(M, N, K, fg.FG_ROW, fg.FG_COL, ints=False, pads=(0, 0, 0), offsets=(0, 0, 0))
+
+
+def test_leading_dimensions_beyond_the_tiled_kernels():
+    """Offsets that need 64 bits, in every matrix."""
+    run_unaligned_gemm_case(3, 2, 5, fg.FG_COL, fg.FG_COL, pads=((1 << 24) + 1, (1 << 23) + 3, (1 << 22) + 1))
+    run_unaligned_gemm_case(9, 3, 70, fg.FG_ROW, fg.FG_ROW, pads=((1 << 23) + 1, 1, (1 << 22) + 1))
+
+
+def test_split_calls_without_allocation_and_in_a_graph():
+    """The allocation-free entry point makes the same plan (bit-identical floats); a captured split
+    call replays to the eager result."""
+    M, N, K = 301, 99, 4101
+    A = W.uniform_pm1(M * K, 1, device="cuda"); B = W.uniform_pm1(K * N, 2, device="cuda")
+    Cm = W.uniform_pm1(M * N, 3, device="cuda", dtype=torch.float32)
+    want, D = torch.empty_like(Cm), torch.empty_like(Cm)
+    fg.fg_init()
+
+    def call(out, **kw):
+        fg.fg_gemm(M, N, K, 0.5, fg.Matrix(A, fg.FG_COL, M), fg.Matrix(B, fg.FG_COL, K), 1.0, fg.Matrix(Cm, fg.FG_COL, M), fg.Matrix(out, fg.FG_COL, M), **kw)
+    call(want)
+    call(D, noalloc=True)
+    torch.cuda.synchronize()
+    assert torch.equal(D, want)
+    s, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=s):
+            call(D, stream=s)
+    torch.cuda.synchronize()
+    for rep in range(3):
+        D.fill_(float("nan"))
+        call(torch.empty_like(D))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        say("replay %d" % rep)
+        assert torch.equal(D, want)
+
+
+@pytest.mark.parametrize("tile", ["2", "3"])
+def test_contraction_forms(monkeypatch, tile):
+    """Which direction the pieces run along (rows, summed modes, element by element), leading modes
+    that pieces do not divide, several modes per group, batch modes, and strides with gaps that
+    hold NaN."""
+    setenv(monkeypatch, "FG_FORCE_TILE", tile)
+    say("rows x columns"); run_contract_case({a: 13, b: 5, c: 7, d: 11, e: 9, f: 6}, [a, e, b, f], [d, f, c, e], [a, b, c, d], ints=True, beta=1.0)
+    say("both along the summed mode"); run_contract_case({a: 70, b: 131, d: 77}, [d, a], [d, b], [a, b], ints=True)
+    say("along the summed mode and along columns"); run_contract_case({a: 33, b: 21, d: 13, e: 6}, [d, a, e], [b, e, d], [a, b], ints=True, beta=-1.0)
+    say("along two different summed modes"); run_contract_case({a: 33, b: 140, d: 13, e: 11}, [d, e, a], [e, d, b], [a, b], ints=True)
+    say("unit modes of extent 2"); run_contract_case({a: 2, b: 3, c: 65, d: 67, e: 9}, [a, c, e], [b, e, d], [a, c, b, d], ints=True)
+    say("result along the second row mode"); run_contract_case({a: 9, b: 11, c: 70, d: 65}, [b, d, a], [d, c], [a, b, c], ints=True)
+    say("batch modes"); run_contract_case({a: 13, b: 9, d: 65, g: 3, f: 2}, [a, d, f, g], [d, b, g, f], [a, g, b, f], ints=True, beta=2.0)
+    say("one row"); run_contract_case({b: 70, d: 133}, [d], [b, d], [b], ints=True)
+    say("one row, one column"); run_contract_case({d: 300}, [d], [d], [], ints=True)
+    say("no summed mode"); run_contract_case({a: 70, b: 133, g: 2}, [a, g], [b, g], [a, b, g], ints=True)
+    say("operands of a few elements"); run_contract_case({a: 3, b: 2, d: 2}, [a, d], [d, b], [a, b], ints=True)
+    ext = {a: 21, b: 67, c: 3, d: 37}
+    for sA, sB in (([1, 23, 23 * 37 + 5], [1, 39]), ([2, 43, 43 * 37], [3, 113]), ([111, 1, 4441], [201, 3])):
+        say("strides %s %s" % (sA, sB))
+        run_contract_case(ext, [a, d, c], [d, b], [a, b, c], ints=True, beta=1.0, stridesA=sA, stridesB=sB, stridesC=[1, 23, 23 * 67 + 1], poison=True)
+    say("floats"); run_contract_case({a: 37, b: 9, c: 11, d: 15, e: 27, f: 25}, [a, e, b, f], [d, f, c, e], [a, b, c, d], alpha=0.5, beta=1.5)
+    delenv(monkeypatch, "FG_FORCE_TILE")
