@@ -293,13 +293,13 @@ fg_status prepare(const fg::KernelEntry &k, int dev, int &per_cu) {
     std::lock_guard<std::mutex> lock(m);
     per_cu = 0;
     for (int i = 0; i < n_done; ++i)
-        if (done[i].fn == (const void *)k.fn && done[i].dev == dev) per_cu = done[i].per_cu;
+        if (done[i].fn == k.fn && done[i].dev == dev) per_cu = done[i].per_cu;
     if (per_cu == 0) {
-        hipError_t e = hipFuncSetAttribute((const void *)k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.lds_bytes);
+        hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.lds_bytes);
         if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "hipFuncSetAttribute(%s): %s", k.name, hipGetErrorString(e));
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)k.fn, k.threads, (size_t)k.lds_bytes);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k.fn, k.threads, (size_t)k.lds_bytes);
         if (e != hipSuccess || per_cu < 1) return fail(FG_ERR_LAUNCH, "occupancy query for %s failed: %s", k.name, hipGetErrorString(e));
-        if (n_done < 512) { done[n_done].fn = (const void *)k.fn; done[n_done].dev = dev; done[n_done].per_cu = per_cu; ++n_done; }
+        if (n_done < 512) { done[n_done].fn = k.fn; done[n_done].dev = dev; done[n_done].per_cu = per_cu; ++n_done; }
     }
     return FG_OK;
 }
@@ -407,19 +407,19 @@ struct Scratch {
     }
 };
 
-fg_status launch(const fg::KernelEntry &k, const fg::GemmParams &p, hipStream_t stream) {
+// p: the parameters of kernel k, whose size the runtime takes from the kernel.
+fg_status launch(const fg::KernelEntry &k, const fg::GemmParams &p, hipStream_t stream, int batches = 1) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return fail(FG_ERR_LAUNCH, "no HIP device is current");
     int per_cu = 0;
     if (fg_status st = prepare(k, dev, per_cu)) return st;
     // Persistent workgroups: as many as the GPU holds at once; each walks tiles b, b + grid, ...
-    const int ntiles = p.tile_count > 0 ? p.tile_count * (p.splits > 1 ? p.splits : 1)
-                                        : p.tiles_m * p.tiles_n * (p.batches > 1 ? p.batches : 1);
+    const int ntiles = p.tile_count > 0 ? p.tile_count * (p.splits > 1 ? p.splits : 1) : p.tiles_m * p.tiles_n * batches;
     const int resident = per_cu * kNumCU;
     dim3 grid((unsigned)(ntiles < resident ? ntiles : resident)), block((unsigned)k.threads);
-    hipLaunchKernelGGL(k.fn, grid, block, (size_t)k.lds_bytes, stream, p);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "launch of %s failed: %s", k.name, hipGetErrorString(e));
+    void *args[] = {const_cast<fg::GemmParams *>(&p)};
+    hipError_t e = hipLaunchKernel(k.fn, grid, block, args, (size_t)k.lds_bytes, stream);
+    if (e != hipSuccess) { (void)hipGetLastError(); return fail(FG_ERR_LAUNCH, "launch of %s failed: %s", k.name, hipGetErrorString(e)); }
     return FG_OK;
 }
 
@@ -1185,8 +1185,8 @@ fg_status fg_contract(int32_t nA, const int32_t *modesA, const int64_t *stridesA
     const fg::KernelEntry *kp = select_contract_kernel(c, Cin, Cout, &perm_z);
     if (!kp) return fail(FG_ERR_UNSUPPORTED, "internal: no contraction kernel for this tile");
     const fg::KernelEntry &k = *kp;
-    fg::GemmParams p;
-    memset(&p, 0, sizeof p);
+    fg::ContractParams p;
+    memset((void *)&p, 0, sizeof p);
     p.M = (int32_t)c.M; p.N = (int32_t)c.N; p.K = (int32_t)c.K;
     p.tiles_m = (int32_t)((c.M + k.bm - 1) / k.bm); p.tiles_n = (int32_t)((c.N + k.bn - 1) / k.bn);
     p.A = (const _Float16 *)c.A; p.B = (const _Float16 *)c.B;
@@ -1197,7 +1197,7 @@ fg_status fg_contract(int32_t nA, const int32_t *modesA, const int64_t *stridesA
     p.a_b = c.a_b; p.b_b = c.b_b; p.c_b = c.c_b; p.batches = (int32_t)c.batches;
     if ((int64_t)p.tiles_m * p.tiles_n * c.batches >= (1ll << 31)) return fail(FG_ERR_UNSUPPORTED, "too many tiles");
     p.perm_z = perm_z;
-    return launch(k, p, (hipStream_t)hip_stream);
+    return launch(k, p, (hipStream_t)hip_stream, p.batches);
 }
 
 fg_status fg_contract_plan(int32_t nA, const int32_t *modesA, const int64_t *stridesA, const void *A,

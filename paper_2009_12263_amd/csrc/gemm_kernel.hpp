@@ -72,7 +72,15 @@ struct GemmParams {
     // BM x BN partial result (alpha = 1, no C, bias or activation) to slot w of the workspace D.
     int32_t tile_begin, tile_count;
     int32_t splits, split_kt;
-    // tensor contraction: mode groups of each tensor
+    // Matrix kernels: C and D are accessed with the default cache policy instead of the streaming
+    // one (set by the host when the whole problem fits the memory-side cache; see stream_policy).
+    int32_t cd_cached;
+};
+
+// What contractions need besides.  A struct of its own because a launch copies a kernel's arguments
+// through the command path: 1.1 KB of them cost 3.5 us of host time per call, 0.25 KB 2.9 us.
+struct ContractParams : GemmParams {
+    // mode groups of each tensor
     ModeGroup a_m, a_k, b_n, b_k, c_m, c_n;
     // batch modes (present in A, B and C): the launch covers `batches` copies of the tile grid,
     // copy t works on the slices of A, B and C at batch index t
@@ -81,9 +89,6 @@ struct GemmParams {
     // Contractions with an M-contiguous A: order in which the matrix unit sees the rows of a block
     // tile (tile_row below).  1: the order in which they are loaded.
     int32_t perm_z;
-    // Matrix kernels: C and D are accessed with the default cache policy instead of the streaming
-    // one (set by the host when the whole problem fits the memory-side cache; see stream_policy).
-    int32_t cd_cached;
 };
 
 // Row permutation inside a block tile of a contraction (A contiguous along its leading row mode).
@@ -126,6 +131,7 @@ struct TileCfg {
     static constexpr int ACC_LH = M16_ ? 8 : 4;
     static constexpr int acc_col(int r) { return M16_ ? 16 * (r >> 3) + 4 * ((r >> 2) & 1) + (r & 3) : 8 * (r >> 2) + (r & 3); }
     static constexpr bool A_KC = A_KC_, B_KC = B_KC_, STRIDED = STRIDED_;
+    using Params = typename std::conditional<STRIDED_, ContractParams, GemmParams>::type;   // what the kernel takes
     // 0: real; 1: complex (i^2 = -1), 2: dual (eps^2 = 0) numbers in planar-split storage
     static constexpr int CPLX = CPLX_;
     static constexpr bool SPLITK = !STRIDED_ && DIAG_ == 0 && CPLX_ == 0 && !CD16_;   // kernel understands GemmParams::splits
@@ -644,7 +650,7 @@ template <class Cfg>
 constexpr int stream_policy() { return (Cfg::DIAG == 0 && (!Cfg::STRIDED || Cfg::CSTREAM)) ? 2 : 0; }   // gfx950 cache policy: bit 1 = nt
 // `block(i, j)` returns the 32x32 block (i, j) of the wave's results as sixteen registers.
 template <class Cfg, bool HAS_C, class Blocks, bool CACHED = false>
-__device__ __forceinline__ void epilogue(const GemmParams &p, const float *Cp, float *Dp, const Blocks &block,
+__device__ __forceinline__ void epilogue(const typename Cfg::Params &p, const float *Cp, float *Dp, const Blocks &block,
                                          int m_base, int n_base, int lane) {
     constexpr int kStream = CACHED ? 0 : stream_policy<Cfg>();
     const int lm = lane & 31, lh = lane >> 5;
@@ -1042,7 +1048,7 @@ __device__ __forceinline__ floatx16 gather_block(const floatx4 (&a16)[Cfg::FI][C
 }
 
 template <class Cfg>
-__global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const GemmParams p) {
+__global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg::Params p) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     FG_LDS char *smem = (FG_LDS char *)smem_generic;
     constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK;
@@ -1052,7 +1058,9 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const GemmParams p)
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave % Cfg::WGM, wn = wave / Cfg::WGM;
-    const int ntiles = Cfg::SPLITK ? p.tile_count * p.splits : p.tiles_m * p.tiles_n * (Cfg::STRIDED ? p.batches : 1);
+    using Params = typename Cfg::Params;
+    int ntiles = Cfg::SPLITK ? p.tile_count * p.splits : p.tiles_m * p.tiles_n;
+    if constexpr (Cfg::STRIDED) ntiles *= p.batches;
     [[maybe_unused]] const uint32_t xf_a = p.a_add2, xf_b = p.b_add2;   // used by TileCfg::XFORM only
     [[maybe_unused]] const int xf_k = p.K;
 
@@ -1080,7 +1088,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const GemmParams p)
     // start the loads of a tile: point the loaders at its panels and fill the ring
     auto start_tile = [&](int tile_id, int &m0, int &n0, int &split) {
         // parameters are re-read here rather than kept in registers across the K loop
-        const GemmParams tp = load_param<GemmParams>(0);
+        const Params tp = load_param<Params>(0);
         int tm, tn;
         split = 0;
         if constexpr (Cfg::SPLITK) {
@@ -1113,12 +1121,18 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const GemmParams p)
             ap[0] += group_offset(tp.a_b, split);
             bp[0] += group_offset(tp.b_b, split);
         }
+        [[maybe_unused]] const ModeGroup none = {};
 #pragma unroll
         for (int q = 0; q < NLOADERS; ++q) {
+            if constexpr (Cfg::STRIDED) {
+                la[q].init(ap[q], m0, wave, lane, tp.a_rs, tp.a_ks, tp.a_m, tp.a_k, tp.a_span, tp.K, tp.M);
+                lb[q].init(bp[q], n0, wave, lane, tp.b_rs, tp.b_ks, tp.b_n, tp.b_k, tp.b_span, tp.K, tp.N);
+                continue;
+            }
             if constexpr (Cfg::DIAG == 1) la[q].init(ap[q], m0, tp.M < tp.K ? tp.M : tp.K, wave, lane);
-            else la[q].init(ap[q], m0, wave, lane, tp.a_rs, tp.a_ks, tp.a_m, tp.a_k, tp.a_span, tp.K, tp.M);
+            else la[q].init(ap[q], m0, wave, lane, tp.a_rs, tp.a_ks, none, none, tp.a_span, tp.K, tp.M);
             if constexpr (Cfg::DIAG == 2) lb[q].init(bp[q], n0, tp.N < tp.K ? tp.N : tp.K, wave, lane);
-            else lb[q].init(bp[q], n0, wave, lane, tp.b_rs, tp.b_ks, tp.b_n, tp.b_k, tp.b_span, tp.K, tp.N);
+            else lb[q].init(bp[q], n0, wave, lane, tp.b_rs, tp.b_ks, none, none, tp.b_span, tp.K, tp.N);
             if constexpr (Cfg::DIAG != 0 || Cfg::SPLITK) {
                 if (kt0 > 0) { la[q].skip(kt0); lb[q].skip(kt0); }
             }
@@ -1448,7 +1462,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const GemmParams p)
         }
 
         {
-            GemmParams ep = load_param<GemmParams>(0);
+            Params ep = load_param<Params>(0);
             [[maybe_unused]] int mb = m_base, nb = n_base;
             if constexpr (Cfg::SPLITK) {
                 if (ep.splits > 1) {

@@ -20,7 +20,7 @@ enum TileId { TILE_256x256 = 0, TILE_256x128 = 1, TILE_128x128 = 2, TILE_64x64 =
               TILE_256x256_K32 = 5, TILE_COUNT = 6, DIAG_TILE_COUNT = 4 };
 
 struct KernelEntry {
-    void (*fn)(const GemmParams);
+    const void *fn;           // void (*)(const GemmParams), contractions: (const ContractParams)
     const char *name;
     int bm, bn, threads, lds_bytes;
 };
@@ -84,24 +84,24 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
 // the same with 16x16x32 matrix instructions (TileCfg::M16); BF: bfloat16 inputs, H: binary16 C and D
 #define FG_CFG_K32(BM, BN, BK, ST, WGM, WGN, AKC, BKC, BF, H) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, 0, 0, true, BF, false, false, false, H, true>
 #define FG_ENTRY_K32(BM, BN, BK, ST, WGM, WGN, AKC, BKC, BF, H, NAME)                              \
-    { gemm_kernel<FG_CFG_K32(BM, BN, BK, ST, WGM, WGN, AKC, BKC, BF, H)>, NAME, BM, BN,            \
+    { (const void *)gemm_kernel<FG_CFG_K32(BM, BN, BK, ST, WGM, WGN, AKC, BKC, BF, H)>, NAME, BM, BN,            \
       FG_CFG_K32(BM, BN, BK, ST, WGM, WGN, AKC, BKC, BF, H)::NTHREADS,                             \
       FG_CFG_K32(BM, BN, BK, ST, WGM, WGN, AKC, BKC, BF, H)::LDS_BYTES }
 #define FG_ENTRY(BM, BN, BK, ST, WGM, WGN, AKC, BKC, STR, NAME)                                    \
-    { gemm_kernel<FG_CFG(BM, BN, BK, ST, WGM, WGN, AKC, BKC, STR)>, NAME, BM, BN,                  \
+    { (const void *)gemm_kernel<FG_CFG(BM, BN, BK, ST, WGM, WGN, AKC, BKC, STR)>, NAME, BM, BN,                  \
       FG_CFG(BM, BN, BK, ST, WGM, WGN, AKC, BKC, STR)::NTHREADS,                                   \
       FG_CFG(BM, BN, BK, ST, WGM, WGN, AKC, BKC, STR)::LDS_BYTES }
 
 // contraction kernels whose result streams past the L2 (TileCfg::CSTREAM)
 #define FG_CFG_GS(BM, BN, BK, ST, WGM, WGN, AKC, BKC) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, true, 0, 0, true, false, false, false, true>
 #define FG_ENTRY_GS(BM, BN, BK, ST, WGM, WGN, AKC, BKC, NAME)                                      \
-    { gemm_kernel<FG_CFG_GS(BM, BN, BK, ST, WGM, WGN, AKC, BKC)>, NAME, BM, BN,                    \
+    { (const void *)gemm_kernel<FG_CFG_GS(BM, BN, BK, ST, WGM, WGN, AKC, BKC)>, NAME, BM, BN,                    \
       FG_CFG_GS(BM, BN, BK, ST, WGM, WGN, AKC, BKC)::NTHREADS,                                     \
       FG_CFG_GS(BM, BN, BK, ST, WGM, WGN, AKC, BKC)::LDS_BYTES }
 
 #define FG_CFG_BF16(BM, BN, BK, ST, WGM, WGN, AKC, BKC) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, 0, 0, true, true>
 #define FG_ENTRY_BF16(BM, BN, BK, ST, WGM, WGN, AKC, BKC, NAME)                                    \
-    { gemm_kernel<FG_CFG_BF16(BM, BN, BK, ST, WGM, WGN, AKC, BKC)>, NAME, BM, BN,                  \
+    { (const void *)gemm_kernel<FG_CFG_BF16(BM, BN, BK, ST, WGM, WGN, AKC, BKC)>, NAME, BM, BN,                  \
       FG_CFG_BF16(BM, BN, BK, ST, WGM, WGN, AKC, BKC)::NTHREADS,                                   \
       FG_CFG_BF16(BM, BN, BK, ST, WGM, WGN, AKC, BKC)::LDS_BYTES }
 
@@ -120,7 +120,7 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
 
 #define FG_CFG_H16(BM, BN, BK, ST, WGM, WGN, AKC, BKC) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, 0, 0, true, false, false, false, false, true>
 #define FG_ENTRY_H16(BM, BN, BK, ST, WGM, WGN, AKC, BKC, NAME)                                     \
-    { gemm_kernel<FG_CFG_H16(BM, BN, BK, ST, WGM, WGN, AKC, BKC)>, NAME, BM, BN,                   \
+    { (const void *)gemm_kernel<FG_CFG_H16(BM, BN, BK, ST, WGM, WGN, AKC, BKC)>, NAME, BM, BN,                   \
       FG_CFG_H16(BM, BN, BK, ST, WGM, WGN, AKC, BKC)::NTHREADS,                                    \
       FG_CFG_H16(BM, BN, BK, ST, WGM, WGN, AKC, BKC)::LDS_BYTES }
 
@@ -139,7 +139,7 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
 
 #define FG_CFG_XF(BM, BN, BK, ST, WGM, WGN, AKC, BKC) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, 0, 0, true, false, true>
 #define FG_ENTRY_XF(BM, BN, BK, ST, WGM, WGN, AKC, BKC, NAME)                                      \
-    { gemm_kernel<FG_CFG_XF(BM, BN, BK, ST, WGM, WGN, AKC, BKC)>, NAME, BM, BN,                    \
+    { (const void *)gemm_kernel<FG_CFG_XF(BM, BN, BK, ST, WGM, WGN, AKC, BKC)>, NAME, BM, BN,                    \
       FG_CFG_XF(BM, BN, BK, ST, WGM, WGN, AKC, BKC)::NTHREADS,                                     \
       FG_CFG_XF(BM, BN, BK, ST, WGM, WGN, AKC, BKC)::LDS_BYTES }
 
@@ -150,7 +150,7 @@ template <bool AKC, bool BKC>
 inline KernelEntry xf_k32_entry(const char *name) {
     if constexpr (AKC != BKC) {
         using Cfg = TileCfg<256, 256, 64, 2, 2, 4, AKC, BKC, false, 0, 0, true, false, true, false, false, false, true>;
-        return { gemm_kernel<Cfg>, name, 256, 256, Cfg::NTHREADS, Cfg::LDS_BYTES };
+        return { (const void *)gemm_kernel<Cfg>, name, 256, 256, Cfg::NTHREADS, Cfg::LDS_BYTES };
     } else {
         return FG_EMPTY_ENTRY;
     }
@@ -171,12 +171,12 @@ inline KernelEntry xf_k32_entry(const char *name) {
 
 #define FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, 0, 1, false, false, false, true>
 #define FG_ENTRY_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC, NAME)                                      \
-    { gemm_kernel<FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC)>, NAME, BM, BN,                    \
+    { (const void *)gemm_kernel<FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC)>, NAME, BM, BN,                    \
       FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC)::NTHREADS,                                     \
       FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC)::LDS_BYTES }
 
 #define FG_ENTRY_X(BM, BN, BK, ST, WGM, WGN, AKC, BKC, DG, CX, NAME)                                \
-    { gemm_kernel<TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, DG, CX>>, NAME, BM, BN,       \
+    { (const void *)gemm_kernel<TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, DG, CX>>, NAME, BM, BN,       \
       TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, DG, CX>::NTHREADS,                        \
       TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, DG, CX>::LDS_BYTES }
 
