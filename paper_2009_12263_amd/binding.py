@@ -46,6 +46,8 @@ class FlexGemmError(RuntimeError):
         self.status = status
 
 
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda dev: torch.cuda.current_stream(dev).cuda_stream)
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 _lib = None
 
 
@@ -94,6 +96,9 @@ def load_library() -> C.CDLL:
     return _lib
 
 
+_DTYPES = {torch.float16: FG_F16, torch.bfloat16: FG_BF16, torch.float32: FG_F32, torch.complex32: FG_CF16, torch.complex64: FG_CF32}
+
+
 @dataclass
 class Matrix:
     """Host-side description of a device matrix: the tensors only provide the pointers."""
@@ -104,18 +109,11 @@ class Matrix:
     dtype: Optional[int] = None
 
     def _struct(self) -> fg_matrix:
-        m = fg_matrix()
-        m.re = self.re.data_ptr() if self.re is not None else None
-        m.im = self.im.data_ptr() if self.im is not None else None
-        if self.dtype is not None:
-            m.dtype = self.dtype
-        else:
-            t = self.re if self.re is not None else self.im
-            m.dtype = {torch.float16: FG_F16, torch.bfloat16: FG_BF16, torch.float32: FG_F32,
-                       torch.complex32: FG_CF16, torch.complex64: FG_CF32}.get(
-                t.dtype if t is not None else torch.float32, -1)
-        m.layout, m.ld = self.layout, self.ld
-        return m
+        re, im, dtype = self.re, self.im, self.dtype
+        if dtype is None:
+            t = re if re is not None else im
+            dtype = _DTYPES.get(t.dtype if t is not None else torch.float32, -1)
+        return fg_matrix(re.data_ptr() if re is not None else None, im.data_ptr() if im is not None else None, dtype, self.layout, self.ld)
 
 
 def _check_extent(m: Optional["Matrix"], rows: int, cols: int, name: str) -> None:
@@ -126,25 +124,30 @@ def _check_extent(m: Optional["Matrix"], rows: int, cols: int, name: str) -> Non
     left to it."""
     if m is None or rows <= 0 or cols <= 0:
         return
+    layout, ld = m.layout, m.ld
+    if layout == FG_COL:
+        need = (cols - 1) * ld + rows if ld >= rows else 0
+    elif layout == FG_ROW:
+        need = (rows - 1) * ld + cols if ld >= cols else 0
+    elif layout == FG_DIAG:
+        need = min(rows, cols)
+    else:
+        need = 0
     for t in (m.re, m.im):
         if t is None or not getattr(t, "is_cuda", False):     # only real device tensors are checked
             continue
         per_entry = 2 if (m.dtype in (FG_CF16, FG_CF32) and not t.is_complex()) else 1
-        if m.layout == FG_DIAG:
-            need = min(rows, cols)
-        elif m.layout == FG_COL:
-            need = (cols - 1) * m.ld + rows if m.ld >= rows else 0
-        elif m.layout == FG_ROW:
-            need = (rows - 1) * m.ld + cols if m.ld >= cols else 0
-        else:
-            need = 0
         if need * per_entry > t.numel():
             raise ValueError("%s: a %d x %d matrix with leading dimension %d needs %d elements, the tensor has %d"
-                             % (name, rows, cols, m.ld, need * per_entry, t.numel()))
+                             % (name, rows, cols, ld, need * per_entry, t.numel()))
 
 
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
+        if torch.cuda.is_initialized():
+            # the current device's current stream as torch.cuda.current_stream() gives it, without the
+            # Stream object around the handle (0.2 us per call instead of 2.9)
+            return _current_raw_stream(_current_device())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -165,6 +168,10 @@ def fg_init(raise_on_error: bool = True) -> int:
 def fg_reload_tuning() -> None:
     """Re-read the FG_FORCE_* tuning overrides from the environment (read once at load otherwise)."""
     load_library().fg_reload_tuning()
+
+
+def _ref(s):
+    return C.byref(s) if s is not None else None
 
 
 def _check(status: int, raise_on_error: bool) -> int:
@@ -189,10 +196,8 @@ def fg_gemm(M: int, N: int, K: int, alpha: float, A: Optional[Matrix], B: Option
     sd = D._struct() if D is not None else None
     ep = None
     if bias is not None or act != FG_ACT_NONE:
-        ep = fg_epilogue()
-        ep.bias = bias.data_ptr() if bias is not None else None
-        ep.bias_dim, ep.act = bias_dim, act
-    ref = lambda s: C.byref(s) if s is not None else None
+        ep = fg_epilogue(bias.data_ptr() if bias is not None else None, bias_dim, act)
+    ref = _ref
     if noalloc:
         lt = fg_load_transforms(a_add, b_add, c_act)
         st = lib.fg_gemm_noalloc(M, N, K, alpha, ref(sa), ref(sb), beta, ref(sc), ref(sd), ref(ep), C.byref(lt), _stream_handle(stream))
@@ -214,7 +219,7 @@ def fg_gemm_dual(M: int, N: int, K: int, alpha: float, A: Optional[Matrix], B: O
     sb = B._struct() if B is not None else None
     sc = C_._struct() if C_ is not None else None
     sd = D._struct() if D is not None else None
-    ref = lambda s: C.byref(s) if s is not None else None
+    ref = _ref
     st = lib.fg_gemm_dual(M, N, K, alpha, ref(sa), ref(sb), beta, ref(sc), ref(sd), _stream_handle(stream))
     return _check(st, raise_on_error)
 
@@ -227,6 +232,14 @@ def fg_gemm_plan(M: int, N: int, K: int, layoutA: int = FG_COL, layoutB: int = F
     return buf.value.decode()
 
 
+def _i32(xs):
+    return (C.c_int32 * len(xs))(*map(int, xs))
+
+
+def _i64(xs):
+    return (C.c_int64 * len(xs))(*map(int, xs))
+
+
 def fg_contract(modesA: Sequence[int], stridesA: Sequence[int], A: torch.Tensor,
                 modesB: Sequence[int], stridesB: Sequence[int], B: torch.Tensor,
                 modesC: Sequence[int], stridesC: Sequence[int], Cin: Optional[torch.Tensor], Cout: torch.Tensor,
@@ -234,18 +247,21 @@ def fg_contract(modesA: Sequence[int], stridesA: Sequence[int], A: torch.Tensor,
     """Cout = alpha * contraction(A, B) + beta * Cin; see fg_contract in include/flexgemm.h.
     ``extents`` maps each integer mode label to its extent."""
     lib = load_library()
+    positive = all(int(v) > 0 for v in extents.values())
     for name, t, modes, strides in (("A", A, modesA, stridesA), ("B", B, modesB, stridesB), ("Cin", Cin, modesC, stridesC),
                                     ("Cout", Cout, modesC, stridesC)):
         # the same protection as _check_extent: the last element the description reaches must exist
-        if t is not None and getattr(t, "is_cuda", False) and all(int(v) > 0 for v in extents.values()) and len(modes) == len(strides) and all(m in extents and extents[m] > 0 for m in modes) \
-                and all(int(x) >= 0 for x in strides):
-            need = 1 + sum((int(extents[m]) - 1) * int(x) for m, x in zip(modes, strides))
-            if need > t.numel():
-                raise ValueError("%s: the modes and strides reach element %d, the tensor has %d" % (name, need - 1, t.numel()))
-    i32 = lambda xs: (C.c_int32 * len(xs))(*[int(x) for x in xs])
-    i64 = lambda xs: (C.c_int64 * len(xs))(*[int(x) for x in xs])
-    mA, sA, mB, sB, mC, sC = i32(modesA), i64(stridesA), i32(modesB), i64(stridesB), i32(modesC), i64(stridesC)
-    labels, exts = i32(list(extents.keys())), i64([extents[k] for k in extents])
+        if t is not None and positive and getattr(t, "is_cuda", False) and len(modes) == len(strides):
+            need = 1
+            for m, x in zip(modes, strides):
+                if m not in extents or x < 0:
+                    break
+                need += (int(extents[m]) - 1) * int(x)
+            else:
+                if need > t.numel():
+                    raise ValueError("%s: the modes and strides reach element %d, the tensor has %d" % (name, need - 1, t.numel()))
+    mA, sA, mB, sB, mC, sC = _i32(modesA), _i64(stridesA), _i32(modesB), _i64(stridesB), _i32(modesC), _i64(stridesC)
+    labels, exts = _i32(extents.keys()), _i64(extents.values())
     ptr = lambda t: t.data_ptr() if t is not None else None
     st = lib.fg_contract(len(mA), mA, sA, ptr(A), len(mB), mB, sB, ptr(B), len(mC), mC, sC, ptr(Cin), ptr(Cout),
                          len(labels), labels, exts, alpha, beta, _stream_handle(stream))
@@ -256,10 +272,8 @@ def fg_contract_plan(modesA: Sequence[int], stridesA: Sequence[int], A, modesB: 
                      modesC: Sequence[int], stridesC: Sequence[int], Cin, Cout, extents: dict) -> str:
     """Name of the kernel fg_contract would use; see fg_contract_plan in include/flexgemm.h."""
     lib = load_library()
-    i32 = lambda xs: (C.c_int32 * len(xs))(*[int(x) for x in xs])
-    i64 = lambda xs: (C.c_int64 * len(xs))(*[int(x) for x in xs])
-    mA, sA, mB, sB, mC, sC = i32(modesA), i64(stridesA), i32(modesB), i64(stridesB), i32(modesC), i64(stridesC)
-    labels, exts = i32(list(extents.keys())), i64([extents[k] for k in extents])
+    mA, sA, mB, sB, mC, sC = _i32(modesA), _i64(stridesA), _i32(modesB), _i64(stridesB), _i32(modesC), _i64(stridesC)
+    labels, exts = _i32(extents.keys()), _i64(extents.values())
     ptr = lambda t: t.data_ptr() if t is not None else None
     buf = C.create_string_buffer(256)
     st = lib.fg_contract_plan(len(mA), mA, sA, ptr(A), len(mB), mB, sB, ptr(B), len(mC), mC, sC, ptr(Cin), ptr(Cout),
