@@ -48,9 +48,10 @@ void note_relaxed(fg_status st, const char *fmt, ...) {
 
 constexpr int kNumCU = 256;   // MI355X: 8 XCDs x 32 compute units
 
-// Tuning overrides of the planner, from the environment: FG_FORCE_TILE=0..5 picks a tile shape (0..2
+// Tuning overrides of the planner, from the environment: FG_FORCE_TILE=0..7 picks a tile shape (0..2
 // for the three tiles of the complex and dual kernels)
-// (5: the 256x256 tile with the k32 kernel where the family has one), FG_FORCE_SPLIT=n a split of K
+// (5: the 256x256 tile with the k32 kernel where the family has one; 6, 7: the 64x64 tile with two or
+// four K groups), FG_FORCE_SPLIT=n a split of K
 // for every tile, FG_FORCE_TAIL=n a split of K for the tiles of the last round (1: never).  Read
 // when the library is loaded and again by fg_reload_tuning(), not on every call.
 std::atomic<int> g_force_tile{-1}, g_force_split{0}, g_force_tail{0};
@@ -124,15 +125,18 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 // compute units (measured +1 to +5 % from 192 tiles up, K from 1024 to 8192; equal at 176 tiles,
 // -1 to -6 % at 160 and fewer: a partly busy chip is not at its power limit).  k32 == 1: only
 // when forced (A and B both M/N-contiguous: measured 0 to -5 %).
+// allow_groups: the family has the 64x64 tile with K groups.  Their rates are fitted, like the
+// others', to measured times of one and two tiles per unit over K = 256 .. 8192; over 20 shapes from
+// 300x200 to 2048x1536 the choice is the fastest forced tile and split or within 5 %.
 Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_smallest = true, int64_t batches = 1,
-                 bool allow_deep = true, int k32 = 0) {
-    static const int bm[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256};
-    static const int bn[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256};
-    static const int per_cu[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1};
-    static const double rate_shared[fg::TILE_COUNT] = {1.0, 0.8, 0.73, 0.45, 0.57, 1.0};
-    static const double rate_alone[fg::TILE_COUNT] = {1.0, 0.8, 0.43, 0.17, 0.57, 1.0};
+                 bool allow_deep = true, int k32 = 0, bool allow_groups = false) {
+    static const int bm[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64};
+    static const int bn[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64};
+    static const int per_cu[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1};
+    static const double rate_shared[fg::TILE_COUNT] = {1.0, 0.8, 0.73, 0.45, 0.57, 1.0, 0.40, 0.27};
+    static const double rate_alone[fg::TILE_COUNT] = {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0.26, 0.27};
     static const int split_options[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
-    constexpr double cu_flops = 4.7e12, round_fixed = 2e-6, cu_cd_bw = 25e9, reduce_launch = 6e-6, reduce_bw = 3e12;
+    constexpr double cu_flops = 4.7e12, round_fixed = 2e-6, cu_cd_bw = 25e9, reduce_launch = 8.5e-6, reduce_bw = 3e12;
     // tuning overrides (see read_tuning_from_environment)
     int force_tile = -1;
     const int force_split = g_force_split.load(std::memory_order_relaxed), force_tail = g_force_tail.load(std::memory_order_relaxed);
@@ -151,6 +155,7 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
         if (t == fg::TILE_64x64 && !allow_smallest) continue;
         if (t == fg::TILE_128x128_DEEP && !allow_deep) continue;
         if (t == fg::TILE_256x256_K32) continue;
+        if ((t == fg::TILE_64x64_KG2 || t == fg::TILE_64x64_KG4) && !allow_groups) continue;
         const int64_t tiles = ((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]) * batches;
         const int64_t slots = (int64_t)kNumCU * per_cu[t];
         const int64_t slot_bytes = (int64_t)bm[t] * bn[t] * 4;
@@ -168,7 +173,11 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
             return 2.0 * bm[t] * bn[t] * (double)((nk + S - 1) / S) * 64 / (cu_flops * rate) + epilogue;
         };
         auto reduce_time = [&](int64_t ntile, int S) { return reduce_launch + (2.0 * S + 2.0) * (double)ntile * slot_bytes / reduce_bw; };
+        // K groups: at least four K tiles for each, or their reduction costs more than they save (256^3:
+        // 5.0 us on the GPU with one group, 5.3 with two, 6.3 with four; 512^3: 6.2, 6.2, 7.0)
+        const int64_t groups = t == fg::TILE_64x64_KG2 ? 2 : t == fg::TILE_64x64_KG4 ? 4 : 1;
         auto consider = [&](int S, int tail, double cost) {
+            if (groups > 1 && force_tile < 0 && nk / (S * tail) < 4 * groups) return;
             if (best_cost < 0 || cost < best_cost) { best = Plan{t, S, tail}; best_cost = cost; }
         };
         // (a) every tile split S ways (S = 1: the plain launch)
@@ -257,7 +266,7 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     }
     const bool may_split = plan_out && !q.a_diag && !q.b_diag && !q.cd16;   // the reduction pass writes FP32
     const int k32 = (q.a_diag || q.b_diag) ? 0 : q.ab_add ? (q.a_kc != q.b_kc ? 2 : 0) : ((q.a_kc || q.b_kc) ? 2 : 1);
-    const Plan plan = choose_plan(q.M, q.N, q.K, may_split, true, 1, !q.a_diag && !q.b_diag, k32);
+    const Plan plan = choose_plan(q.M, q.N, q.K, may_split, true, 1, !q.a_diag && !q.b_diag, k32, !q.a_diag && !q.b_diag);
     int tile = plan.tile;
     // A product with a diagonal operand is bound by its memory traffic (one pass over the dense
     // operand, C and D; a tile row only meets the K tiles on the diagonal).  While all of it fits the
@@ -1043,7 +1052,8 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
     fg::GemmParams part = p;
     part.tile_begin = first; part.tile_count = count;
     part.splits = S;
-    part.split_kt = (int32_t)((nk + S - 1) / S);
+    const int64_t kg = k.kg > 1 ? k.kg : 1;          // K groups share a range in equal runs
+    part.split_kt = (int32_t)(((nk + S - 1) / S + kg - 1) / kg * kg);
     part.D = scratch.ptr;
     part.C = nullptr; part.has_c = 0; part.bias = nullptr; part.act = 0; part.c_act = 0; part.alpha = 1.f; part.beta = 0.f;
     if (fg_status st = launch(k, part, stream)) return st;

@@ -112,7 +112,7 @@ __device__ __forceinline__ int tile_row(int pos, int rows, int z_count) {
 // B column-major) rather than M/N-contiguous.  STAGES LDS buffers per operand form a ring over K.
 template <int BM_, int BN_, int BK_, int STAGES_, int WGM_, int WGN_, bool A_KC_, bool B_KC_, bool STRIDED_,
           int DIAG_ = 0, int CPLX_ = 0, bool SPREAD_ = false, bool BF16_ = false, bool XFORM_ = false, bool ILV_ = false,
-          bool CSTREAM_ = false, bool CD16_ = false, bool M16_ = false>
+          bool CSTREAM_ = false, bool CD16_ = false, bool M16_ = false, int KG_ = 1>
 struct TileCfg {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, STAGES = STAGES_;
     // M16: the product is made of v_mfma_f32_16x16x32 instructions (16x16 results, 32 k per
@@ -122,7 +122,10 @@ struct TileCfg {
     static constexpr int KSLICE = M16_ ? 32 : 16;                   // k per matrix instruction
     static constexpr int KSTEPS = BK / KSLICE;                      // MFMA k-slices per tile
     static constexpr int WGM = WGM_, WGN = WGN_;
-    static constexpr int NWAVES = WGM * WGN, NTHREADS = 64 * NWAVES;
+    // KG: groups of WGM x WGN waves that share the block tile's K tiles, each with a ring, loads and
+    // accumulators of its own; the groups' results are added up through LDS before the epilogue.
+    static constexpr int KG = KG_;
+    static constexpr int NWAVES = WGM * WGN, NTHREADS = 64 * NWAVES * KG;
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;
     static constexpr int TI = WTM / 32, TJ = WTN / 32;             // 32x32 blocks of results per wave (epilogue)
     static constexpr int FI = M16_ ? 2 * TI : TI, FJ = M16_ ? 2 * TJ : TJ;   // operand fragments per wave and k-slice
@@ -134,7 +137,8 @@ struct TileCfg {
     using Params = typename std::conditional<STRIDED_, ContractParams, GemmParams>::type;   // what the kernel takes
     // 0: real; 1: complex (i^2 = -1), 2: dual (eps^2 = 0) numbers in planar-split storage
     static constexpr int CPLX = CPLX_;
-    static constexpr bool SPLITK = !STRIDED_ && DIAG_ == 0 && CPLX_ == 0 && !CD16_;   // kernel understands GemmParams::splits
+    static constexpr bool SPLITK_KERNEL = !STRIDED_ && DIAG_ == 0 && CPLX_ == 0;
+    static constexpr bool SPLITK = SPLITK_KERNEL && !CD16_;   // kernel understands GemmParams::splits
     static constexpr bool BF16 = BF16_;                             // A, B are bfloat16 instead of binary16
     // XFORM: a constant is added to every element of A and of B after it is loaded (the fragment
     // registers are transformed just before the matrix instructions that consume them)
@@ -164,7 +168,7 @@ struct TileCfg {
     // LDS map: [A plane 0: stage 0 .. S-1 | A plane 1 ... | B plane 0: stage 0 .. S-1 | B plane 1 ...]
     static constexpr int A_PLANE_BYTES = A_TILE_BYTES * STAGES, B_PLANE_BYTES = B_TILE_BYTES * STAGES;
     static constexpr int A_BYTES = A_PLANE_BYTES * PLANES;
-    static constexpr int LDS_BYTES = A_BYTES + B_PLANE_BYTES * PLANES;
+    static constexpr int GROUP_BYTES = A_BYTES + B_PLANE_BYTES * PLANES, LDS_BYTES = GROUP_BYTES * KG;
     static_assert(BK == 32 || BK == 64, "BK must be 32 or 64");
     static_assert((STAGES & (STAGES - 1)) == 0 && STAGES >= 2, "STAGES must be a power of two");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be made of 32x32 accumulators");
@@ -178,6 +182,8 @@ struct TileCfg {
     static_assert(!(CPLX && (DIAG || STRIDED)), "complex products take plain matrices");
     static_assert(!SPREAD || STAGES >= 4 || BK >= 64, "spread refills need slack before the tile is needed");
     static_assert(!M16 || (CPLX == 0 && DIAG == 0 && !ILV && BK == 64), "16x16x32 products: real, non-diagonal operands, two k-slices per tile");
+    static_assert(KG == 1 || (SPLITK_KERNEL && !ILV_ && !M16_), "K groups: plain real matrix kernels");
+    static_assert(KG == 1 || (KG - 1) * BM * BN * 4 <= LDS_BYTES, "the groups' results pass through the rings");
     static_assert(!M16 || !STRIDED, "16x16x32 products: matrix kernels (the contraction kernels measured slower with them and are not built)");
     static_assert(!XFORM || (DIAG == 0 && CPLX == 0 && !BF16 && !STRIDED), "element-wise addition on A and B: plain real FP16 matrices");
     static_assert(!CSTREAM || STRIDED, "the streaming variant is a contraction kernel");
@@ -1056,7 +1062,8 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
     constexpr int S = Cfg::STAGES, KS = Cfg::KSTEPS, L = Cfg::LOADS_PER_TILE, P = Cfg::PLANES;
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int group = Cfg::KG > 1 ? wave_all / Cfg::NWAVES : 0, wave = wave_all - group * Cfg::NWAVES;
     const int wm = wave % Cfg::WGM, wn = wave / Cfg::WGM;
     using Params = typename Cfg::Params;
     int ntiles = Cfg::SPLITK ? p.tile_count * p.splits : p.tiles_m * p.tiles_n;
@@ -1064,8 +1071,8 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
     [[maybe_unused]] const uint32_t xf_a = p.a_add2, xf_b = p.b_add2;   // used by TileCfg::XFORM only
     [[maybe_unused]] const int xf_k = p.K;
 
-    FG_LDS char *lds_a = smem;
-    FG_LDS char *lds_b = smem + Cfg::A_BYTES;
+    FG_LDS char *lds_a = smem + group * Cfg::GROUP_BYTES;
+    FG_LDS char *lds_b = lds_a + Cfg::A_BYTES;
 
     using PlainA = TileLoader<BM, BK, Cfg::A_KC, Cfg::A_SLABS, Cfg::STRIDED, Cfg::ILV ? 2 : 1, Cfg::M16>;
     using PlainB = TileLoader<BN, BK, Cfg::B_KC, Cfg::B_SLABS, Cfg::STRIDED, Cfg::ILV ? 2 : 1, Cfg::M16>;
@@ -1115,6 +1122,14 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
         if constexpr (Cfg::DIAG == 2) { kt0 = n0 / BK; kt1 = (n0 + BN) / BK; }
         if (kt1 > nk) kt1 = nk;
         nkt = kt1 > kt0 ? kt1 - kt0 : 0;
+        if constexpr (Cfg::KG > 1) {
+            // Group g takes the g-th of KG equal runs.  All groups run the same number of K tiles (they
+            // share the barriers); the tiles of the last group past the end of K are loaded as
+            // zeros.  (A K split hands out ranges that are multiples of KG, so only K itself ends a
+            // run early.)
+            nkt = (nkt + Cfg::KG - 1) / Cfg::KG;
+            kt0 += group * nkt;
+        }
         const _Float16 *ap[2] = {tp.A, tp.A_im};
         const _Float16 *bp[2] = {tp.B, tp.B_im};
         if constexpr (Cfg::STRIDED) {
@@ -1133,7 +1148,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
             else la[q].init(ap[q], m0, wave, lane, tp.a_rs, tp.a_ks, none, none, tp.a_span, tp.K, tp.M);
             if constexpr (Cfg::DIAG == 2) lb[q].init(bp[q], n0, tp.N < tp.K ? tp.N : tp.K, wave, lane);
             else lb[q].init(bp[q], n0, wave, lane, tp.b_rs, tp.b_ks, none, none, tp.b_span, tp.K, tp.N);
-            if constexpr (Cfg::DIAG != 0 || Cfg::SPLITK) {
+            if constexpr (Cfg::DIAG != 0 || Cfg::SPLITK_KERNEL) {
                 if (kt0 > 0) { la[q].skip(kt0); lb[q].skip(kt0); }
             }
         }
@@ -1238,9 +1253,10 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                         }
                         uint32_t add_a = 0, add_b = 0;          // two packed halves each
                         if constexpr (Cfg::XFORM) {
-                            // only the last K tile can reach beyond K: before it the addends are
-                            // the same in every lane and stay in scalar registers
-                            const bool in_k = MORE || (kt0 + kt) * BK + ks * 32 + 8 * (lane >> 4) < xf_k;
+                            // only the last K tile can reach beyond K (the last two of a K group, of which
+                            // one can lie beyond it whole): before it the addends are the same in every
+                            // lane and stay in scalar registers
+                            const bool in_k = (MORE && Cfg::KG == 1) || (kt0 + kt) * BK + ks * 32 + 8 * (lane >> 4) < xf_k;
                             add_a = in_k ? xf_a : 0u;
                             add_b = in_k ? xf_b : 0u;
 #pragma unroll
@@ -1358,7 +1374,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                     // addend is zero (a lane's eight values share one k chunk, K is a multiple of 8).
                     uint32_t add_a = 0, add_b = 0;          // two packed halves each
                     if constexpr (Cfg::XFORM) {
-                        const bool in_k = MORE || (kt0 + kt) * BK + ks * Cfg::KSLICE + 8 * (lane / (Cfg::M16 ? 16 : 32)) < xf_k;
+                        const bool in_k = (MORE && Cfg::KG == 1) || (kt0 + kt) * BK + ks * Cfg::KSLICE + 8 * (lane / (Cfg::M16 ? 16 : 32)) < xf_k;
                         add_a = in_k ? xf_a : 0u;
                         add_b = in_k ? xf_b : 0u;
 #pragma unroll
@@ -1450,6 +1466,34 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
             tile_body(nkt - 1, F, F, F);
         }
 
+        if constexpr (Cfg::KG > 1) {
+            // the other groups hand their results to group 0, which adds them in a fixed order
+            constexpr int Q = TI * TJ * 4;                  // quads of registers per wave
+            FG_LDS floatx4 *ex = (FG_LDS floatx4 *)smem;
+            auto at = [&](int g, int q) { return ((g - 1) * Cfg::NWAVES + wave) * Q * 64 + q * 64 + lane; };
+            wait_tile<0>();
+            __builtin_amdgcn_s_barrier();
+            if (group > 0) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const AccT &a = acc[0][q / (4 * TJ)][q / 4 % TJ];
+                    ex[at(group, q)] = floatx4{a[4 * (q & 3)], a[4 * (q & 3) + 1], a[4 * (q & 3) + 2], a[4 * (q & 3) + 3]};
+                }
+            }
+            wait_tile<0>();
+            __builtin_amdgcn_s_barrier();
+            if (group == 0) {
+#pragma unroll
+                for (int g = 1; g < Cfg::KG; ++g)
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) {
+                        const floatx4 v = ex[at(g, q)];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[0][q / (4 * TJ)][q / 4 % TJ][4 * (q & 3) + r] += v[r];
+                    }
+            }
+        }
+
         // next tile of this workgroup: once every wave has read its last fragments the LDS ring is
         // free, so its first loads go out before this tile's results are stored
         const int next = tile + (int)gridDim.x;
@@ -1461,7 +1505,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
             start_tile(next, m1, n1, sp1);
         }
 
-        {
+        if (Cfg::KG == 1 || group == 0) {
             Params ep = load_param<Params>(0);
             [[maybe_unused]] int mb = m_base, nb = n_base;
             if constexpr (Cfg::SPLITK) {

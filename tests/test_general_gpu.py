@@ -113,3 +113,27 @@ def test_contraction_forms(monkeypatch, tile):
         run_contract_case(ext, [a, d, c], [d, b], [a, b, c], ints=True, beta=1.0, stridesA=sA, stridesB=sB, stridesC=[1, 23, 23 * 67 + 1], poison=True)
     say("floats"); run_contract_case({a: 37, b: 9, c: 11, d: 15, e: 27, f: 25}, [a, e, b, f], [d, f, c, e], [a, b, c, d], alpha=0.5, beta=1.5)
     delenv(monkeypatch, "FG_FORCE_TILE")
+
+
+@pytest.mark.parametrize("tile,groups", [("6", 2), ("7", 4)])
+def test_k_groups(monkeypatch, tile, groups):
+    """The 64x64 tile whose groups of waves share its K tiles (tiled kernels): fewer K tiles than
+    groups, runs that do not come out even, a K tail in the last group's last and last but one tile,
+    several tiles per workgroup, K splits, and every option of the families."""
+    from tests.parity import run_gemm_case
+    setenv(monkeypatch, "FG_FORCE_TILE", tile)
+    for la, lb in itertools.product(LAYOUTS, LAYOUTS):
+        for K in (8, 64, 72, 128, 200, 264, 320, 456, 520, 568, 1032):
+            say("tile %s K=%d A=%d B=%d" % (tile, K, la, lb))
+            run_gemm_case(131, 70, K, la, lb, ints=True, pad=8, poison=True, bias_dim=0)
+            run_gemm_case(131, 70, K, la, lb, fg.FG_ROW, ints=True, ab_add=(3.0, -1.0), c_act=fg.FG_ACT_RELU, act=fg.FG_ACT_RELU)
+        run_gemm_case(200, 130, 456, la, lb, ints=True, bf16=True, pad=8)
+        run_gemm_case(200, 130, 456, la, lb, ints=True, cd16=True, pad=8, bias_dim=1)
+    say("several tiles per workgroup"); run_gemm_case(2100, 1400, 328, ints=True, beta=-2.0)
+    for S in (2, 3, 5):
+        setenv(monkeypatch, "FG_FORCE_SPLIT", str(S))
+        say("tile %s split %d" % (tile, S)); run_gemm_case(131, 200, 1160, fg.FG_ROW, fg.FG_COL, ints=True, bias_dim=1, act=fg.FG_ACT_RELU, pad=8, poison=True)
+        run_gemm_case(131, 200, 1160, ints=True, ab_add=(1.0, 2.0))
+    delenv(monkeypatch, "FG_FORCE_SPLIT")
+    delenv(monkeypatch, "FG_FORCE_TILE")
+    say("planner's own choice, floats"); run_gemm_case(1024, 1024, 2048); run_gemm_case(1500, 1000, 2048, fg.FG_ROW, fg.FG_COL, bf16=True)
