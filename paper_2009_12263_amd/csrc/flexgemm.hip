@@ -696,7 +696,7 @@ struct Contraction {
     fg::ModeGroup a_m, a_k, b_n, b_k, c_m, c_n;
     // general kernel only: true extents of the leading modes, element strides inside a piece, elements
     // each operand spans
-    int32_t m_ext0, n_ext0, k_ext0;
+    int32_t m_ext0, n_ext0, k_ext0, m_hi;
     int64_t a_es, b_es, a_span, b_span;
 };
 
@@ -803,6 +803,14 @@ fg_status plan_contraction(int32_t nA, const int32_t *modesA, const int64_t *str
     // Modes of extent 1 carry no index and are dropped.  For the others the kernel divides by the
     // extent with a multiply-high: with 2^s < e <= 2^(s+1) and magic = floor(2^(32+s)/e) + 1,
     // floor(idx / e) == (idx * magic) >> (32 + s) for every 0 <= idx < 2^31.
+    auto set_mode = [](fg::ModeGroup &g, int k, int64_t e, int64_t stride) {
+        uint32_t sh = 0;
+        while ((2ull << sh) < (uint64_t)e) ++sh;              // 2^sh < e <= 2^(sh+1)
+        g.extent[k] = (int32_t)e;
+        g.stride[k] = stride;
+        g.shift[k] = sh;
+        g.magic[k] = (uint32_t)(((1ull << (32 + sh)) / (uint64_t)e) + 1);
+    };
     auto fill = [&](fg::ModeGroup &g, const int32_t *modes, int n, const TensorView &t, int64_t &total, bool round_first = false) {
         g.n = 0; total = 1;
         for (int i = 0; i < n; ++i) {
@@ -810,13 +818,7 @@ fg_status plan_contraction(int32_t nA, const int32_t *modesA, const int64_t *str
             if (i == 0 && round_first && e > 1) e = (e + 7) / 8 * 8;
             total *= e;
             if (e == 1) continue;
-            int k = g.n++;
-            g.extent[k] = (int32_t)e;
-            g.stride[k] = t.strides[find_mode(t, modes[i])];
-            uint32_t sh = 0;
-            while ((2ull << sh) < (uint64_t)e) ++sh;          // 2^sh < e <= 2^(sh+1)
-            g.shift[k] = sh;
-            g.magic[k] = (uint32_t)(((1ull << (32 + sh)) / (uint64_t)e) + 1);
+            set_mode(g, g.n++, e, t.strides[find_mode(t, modes[i])]);
         }
         for (int i = g.n; i < fg::kMaxGroupModes; ++i) { g.extent[i] = 2; g.stride[i] = 0; g.magic[i] = 0; g.shift[i] = 0; }
     };
@@ -898,6 +900,7 @@ fg_status plan_contraction(int32_t nA, const int32_t *modesA, const int64_t *str
         }
         if (!have_a) la = longest(m_modes, nm);
         if (!have_b) lb = longest(n_modes_, nn);
+        if (c_unit >= 0) to_front(m_modes, nm, c_unit);
         if (!c.a_kc) to_front(m_modes, nm, la);
         if (!c.b_kc) to_front(n_modes_, nn, lb);
         if (c.a_kc) to_front(k_modes, nkk, la);
@@ -911,9 +914,8 @@ fg_status plan_contraction(int32_t nA, const int32_t *modesA, const int64_t *str
         auto lead = [&](fg::ModeGroup &g, fg::ModeGroup &other, bool rounded, int label, int64_t &total, int32_t &ext0) {
             if (g.n == 0 && rounded) {           // one row (or column): a piece with one element
                 g.n = other.n = 1;
-                g.extent[0] = other.extent[0] = 8;
-                g.shift[0] = other.shift[0] = 2;
-                g.magic[0] = other.magic[0] = (uint32_t)((1ull << 34) / 8 + 1);
+                set_mode(g, 0, 8, 0);
+                set_mode(other, 0, 8, 0);
                 total = 8; ext0 = 1;
             } else {
                 ext0 = rounded ? (int32_t)extent(label) : g.extent[0];
@@ -922,6 +924,24 @@ fg_status plan_contraction(int32_t nA, const int32_t *modesA, const int64_t *str
         lead(c.a_m, c.c_m, !c.a_kc, la, c.M, c.m_ext0);
         lead(c.b_n, c.c_n, !c.b_kc, lb, c.N, c.n_ext0);
         lead(c.a_k, c.b_k, k_pad, c.a_kc ? la : lb, c.K, c.k_ext0);
+        // The result contiguous along another row mode than A: rows in A's order would put the 64 lanes
+        // of a store (and of a read of Cin) on 64 different lines.  The leading mode is split into
+        // its pieces of eight and the rest, which goes last, so that a tile holds eight rows of it for each of
+        // several values of the result's contiguous mode and a store touches a quarter of the lines.
+        // A is then read in separate pieces, which pays while K is not long against N: D_abc = A_bda B_dc
+        // with (a, b, c, d) = (111, 99, 301, 65) 30.0 -> 23.2 us (49.1 -> 26.4 with Cin, which doubles the
+        // scattered accesses), (63, 31, 511, 373) 16.2 -> 16.2 (20.3 -> 17.4), (211, 55, 65, 201) 15.6 -> 17.9
+        // (23.5 -> 19.4), (99, 201, 33, 501) 17.8 -> 28.2 (21.0 -> 29.2).
+        c.m_hi = 0;
+        if (have_a && c.K <= (Cin ? 4 * c.N : c.N * 3 / 2) && !c.a_kc && c_unit >= 0 && c_unit != la && is_row(c_unit) && extent(c_unit) >= 4 && c.a_m.n >= 2 && c.a_m.n < fg::kMaxGroupModes && c.a_m.extent[0] > 8) {
+            const int hi = c.a_m.n;
+            for (fg::ModeGroup *g : {&c.a_m, &c.c_m}) {
+                set_mode(*g, hi, g->extent[0] / 8, 8 * g->stride[0]);
+                set_mode(*g, 0, 8, g->stride[0]);
+                g->n = hi + 1;
+            }
+            c.m_hi = hi;
+        }
         auto stride_of = [&](const TensorView &t, int label, bool pseudo) { const int i = pseudo ? -1 : find_mode(t, label); return i < 0 ? (int64_t)1 : t.strides[i]; };
         c.a_es = stride_of(ta, la, nm == 0 && !c.a_kc); c.b_es = stride_of(tb, lb, nn == 0 && !c.b_kc);
         c.a_span = span(ta); c.b_span = span(tb);
@@ -1182,7 +1202,7 @@ fg_status fg_contract(int32_t nA, const int32_t *modesA, const int64_t *stridesA
         f.C = use_c ? Cin : nullptr; f.D = Cout;
         f.a_m = c.a_m; f.a_k = c.a_k; f.b_n = c.b_n; f.b_k = c.b_k; f.c_m = c.c_m; f.c_n = c.c_n;
         f.a_b = c.a_b; f.b_b = c.b_b; f.c_b = c.c_b;
-        f.m_ext0 = c.m_ext0; f.n_ext0 = c.n_ext0; f.k_ext0 = c.k_ext0;
+        f.m_ext0 = c.m_ext0; f.n_ext0 = c.n_ext0; f.k_ext0 = c.k_ext0; f.m_hi = c.m_hi;
         f.alpha = alpha; f.beta = use_c ? beta : 0.f;
         const int64_t tiles_m = (c.M + plan.bm - 1) / plan.bm, tiles_n = (c.N + plan.bn - 1) / plan.bn;
         if (tiles_m * tiles_n * c.batches >= (1ll << 31)) return fail(FG_ERR_UNSUPPORTED, "too many tiles");

@@ -43,6 +43,8 @@ struct GeneralParams {
     // so that no piece straddles two values of the next mode, and *_ext0 is the true extent.
     ModeGroup a_m, a_k, b_n, b_k, c_m, c_n, a_b, b_b, c_b;
     int32_t m_ext0, n_ext0, k_ext0;
+    int32_t m_hi;                     // nonzero: the rows' leading mode is split, mode 0 of the groups are its
+                                      // pieces' elements and mode m_hi counts the pieces
     int64_t a_es, b_es;               // element stride inside a piece
     int32_t batches;
 };
@@ -93,6 +95,20 @@ struct KTable {
 // a unit stride and for those of fewer than eight elements.
 enum FetchMode { FETCH_INSIDE, FETCH_CLAMP, FETCH_GATHER };
 
+// Index along a group's leading mode; hi: the mode that counts its pieces of eight, 0 if it is not split.
+__device__ __forceinline__ int leading_index(const ModeGroup &g, int idx, int hi) {
+    int lead = 0;
+#pragma unroll
+    for (int t = 0; t < kMaxGroupModes; ++t) {
+        const int q = (int)(__umulhi((uint32_t)idx, g.magic[t]) >> g.shift[t]);
+        const int digit = idx - q * g.extent[t];
+        if (t == 0) lead = digit;
+        else if (t == hi) lead += 8 * digit;
+        idx = q;
+    }
+    return lead;
+}
+
 template <int R, bool KC, int NT, bool PLAIN>
 struct PieceLoader {
     static constexpr int CH = R * 8 / NT;            // pieces per thread and K step
@@ -106,7 +122,7 @@ struct PieceLoader {
     int left[2][KC ? 1 : CH];       // elements of the staged pieces that are below K (MC: 0 or 8)
     int shift[2][CH];               // CLAMP: how many elements before its place a piece was loaded
 
-    __device__ __forceinline__ void init(const ModeGroup &rg, int ext0, int64_t rs, int row0, int rdim, int tid) {
+    __device__ __forceinline__ void init(const ModeGroup &rg, int ext0, int hi, int64_t rs, int row0, int rdim, int tid) {
         if constexpr (KC) {
             const int r = tid / 8;
             pos = ((tid % 8) ^ kc_swz<64>(r)) * 8;
@@ -129,8 +145,7 @@ struct PieceLoader {
                 rows = rdim - m;
             } else {
                 off[0] = group_offset(rg, m);
-                const int e = rg.extent[0];
-                rows = ext0 - (m - (int)(__umulhi((uint32_t)m, rg.magic[0]) >> rg.shift[0]) * e);
+                rows = ext0 - leading_index(rg, m, hi);
             }
         }
     }
@@ -245,8 +260,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
     }
     PieceLoader<BM, A_KC, NT, PLAIN> la;
     PieceLoader<BN, B_KC, NT, PLAIN> lb;
-    la.init(p.a_m, p.m_ext0, p.a_rs, m0, p.M, tid);
-    lb.init(p.b_n, p.n_ext0, p.b_rs, n0, p.N, tid);
+    la.init(p.a_m, p.m_ext0, p.m_hi, p.a_rs, m0, p.M, tid);
+    lb.init(p.b_n, p.n_ext0, 0, p.b_rs, n0, p.N, tid);
     FragReader<BM, 64, A_KC, TI> fa;
     FragReader<BN, 64, B_KC, TJ> fb;
     fa.init(wm * WTM, lane);
@@ -258,9 +273,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
         if constexpr (!PLAIN) {
             KTable &t = ktab[group][i & 3];
             const int k = kt(i) * 64 + lane;
-            const int e = p.a_k.extent[0];
-            const int d0 = k - (int)(__umulhi((uint32_t)k, p.a_k.magic[0]) >> p.a_k.shift[0]) * e;
-            const int rest = p.k_ext0 - d0;
+            const int rest = p.k_ext0 - leading_index(p.a_k, k, 0);
             const bool ok = k < p.K && rest > 0;
             t.left[lane] = ok ? (rest < 8 ? rest : 8) : 0;
             t.a[lane] = ok ? group_offset(p.a_k, k) : 0;
@@ -441,18 +454,16 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
     } else {
         // mixed-radix offsets: rows per lane; columns decomposed by the lane that holds column l % 32
         // and fetched from there.  Rows and columns that do not exist have offset -1.
-        auto offset_of = [&](const ModeGroup &g, int idx, int extent, int ext0) -> int64_t {
-            const int e = g.extent[0];
-            const int d0 = idx - (int)(__umulhi((uint32_t)idx, g.magic[0]) >> g.shift[0]) * e;
-            return (idx < extent && d0 < ext0) ? group_offset(g, idx) : -1;
+        auto offset_of = [&](const ModeGroup &g, int idx, int extent, int ext0, int hi) -> int64_t {
+            return (idx < extent && leading_index(g, idx, hi) < ext0) ? group_offset(g, idx) : -1;
         };
         const int64_t base = group_offset(p.c_b, batch);
         int64_t row[TI];
 #pragma unroll
-        for (int i = 0; i < TI; ++i) row[i] = offset_of(p.c_m, mb + 32 * i, p.M, p.m_ext0);
+        for (int i = 0; i < TI; ++i) row[i] = offset_of(p.c_m, mb + 32 * i, p.M, p.m_ext0, p.m_hi);
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
-            const int64_t mine = offset_of(p.c_n, n0 + wn * WTN + 32 * j + lm, p.N, p.n_ext0);
+            const int64_t mine = offset_of(p.c_n, n0 + wn * WTN + 32 * j + lm, p.N, p.n_ext0, 0);
             const int lo = (int)(uint32_t)mine, hi = (int)(uint32_t)((uint64_t)mine >> 32);
             int64_t col[RR];
 #pragma unroll

@@ -102,6 +102,10 @@ def test_contraction_forms(monkeypatch, tile):
     say("along two different summed modes"); run_contract_case({a: 33, b: 140, d: 13, e: 11}, [d, e, a], [e, d, b], [a, b], ints=True)
     say("unit modes of extent 2"); run_contract_case({a: 2, b: 3, c: 65, d: 67, e: 9}, [a, c, e], [b, e, d], [a, c, b, d], ints=True)
     say("result along the second row mode"); run_contract_case({a: 9, b: 11, c: 70, d: 65}, [b, d, a], [d, c], [a, b, c], ints=True)
+    for (na, nb) in ((4, 9), (11, 8), (3, 20), (70, 17)):
+        say("... extents %d and %d" % (na, nb)); run_contract_case({a: na, b: nb, c: 6, d: 13}, [b, d, a], [d, c], [a, b, c], ints=True, beta=1.0)
+    say("... three row modes"); run_contract_case({a: 9, b: 21, c: 6, d: 13, e: 5}, [b, d, e, a], [d, c], [a, e, b, c], ints=True, beta=1.0)
+    say("... four row modes"); run_contract_case({a: 9, b: 21, c: 6, d: 13, e: 2, f: 3}, [b, d, e, a, f], [d, c], [a, e, b, f, c], ints=True)
     say("batch modes"); run_contract_case({a: 13, b: 9, d: 65, g: 3, f: 2}, [a, d, f, g], [d, b, g, f], [a, g, b, f], ints=True, beta=2.0)
     say("one row"); run_contract_case({b: 70, d: 133}, [d], [b, d], [b], ints=True)
     say("one row, one column"); run_contract_case({d: 300}, [d], [d], [], ints=True)
