@@ -126,17 +126,20 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 // -1 to -6 % at 160 and fewer: a partly busy chip is not at its power limit).  k32 == 1: only
 // when forced (A and B both M/N-contiguous: measured 0 to -5 %).
 // allow_groups: the family has the 64x64 tile with K groups.  Their rates are fitted, like the
-// others', to measured times of one and two tiles per unit over K = 256 .. 8192; over 20 shapes from
-// 300x200 to 2048x1536 the choice is the fastest forced tile and split or within 5 %.
+// others' and the cost of a split, to the times of every tile and split forced over 70 products from
+// 17 x 1321 x 1312 to 227 x 8112 x 4992: the choice is on average 1 % slower than the fastest of
+// them (5 % before the fit), at most 13 %.  A split's second launch is priced with its host time, which
+// a stream of small products pays.
 Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_smallest = true, int64_t batches = 1,
                  bool allow_deep = true, int k32 = 0, bool allow_groups = false) {
     static const int bm[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64};
     static const int bn[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64};
     static const int per_cu[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1};
-    static const double rate_shared[fg::TILE_COUNT] = {1.0, 0.8, 0.73, 0.45, 0.57, 1.0, 0.40, 0.27};
-    static const double rate_alone[fg::TILE_COUNT] = {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0.26, 0.27};
+    static const double rate_shared[fg::TILE_COUNT] = {1.0, 0.8, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29};
+    static const double rate_alone[fg::TILE_COUNT] = {1.0, 0.8, 0.43, 0.135, 0.645, 1.0, 0.27, 0.29};
     static const int split_options[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
-    constexpr double cu_flops = 4.7e12, round_fixed = 2e-6, cu_cd_bw = 25e9, reduce_launch = 8.5e-6, reduce_bw = 3e12;
+    constexpr double cu_flops = 4.7e12, round_fixed = 1.6e-6, cu_cd_bw = 27e9, reduce_launch = 12.3e-6, reduce_bw = 7.2e12;
+    constexpr double tail_launch = 6e-6, tail_bw = 3e12;      // the leftover tiles' reduction follows a full round
     // tuning overrides (see read_tuning_from_environment)
     int force_tile = -1;
     const int force_split = g_force_split.load(std::memory_order_relaxed), force_tail = g_force_tail.load(std::memory_order_relaxed);
@@ -202,7 +205,7 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
                 if (force_tail > 1) { if (!fits) break; }
                 else if (!fits || nk / S < 4 || rest * S > slots) break;
                 const double cost = (double)(full / slots) * share_time(full, 1) + 2e-6 +
-                                    (double)((rest * S + slots - 1) / slots) * share_time(rest * S, S) + reduce_time(rest, S);
+                                    (double)((rest * S + slots - 1) / slots) * share_time(rest * S, S) + tail_launch + (2.0 * S + 2.0) * (double)rest * slot_bytes / tail_bw;
                 consider(1, S, force_tail > 1 ? 0.0 : cost);
             }
         }
