@@ -700,7 +700,7 @@ struct Contraction {
     // general kernel only: true extents of the leading modes, element strides inside a piece, elements
     // each operand spans
     int32_t m_ext0, n_ext0, k_ext0, m_hi;
-    int64_t a_es, b_es, a_span, b_span;
+    int64_t a_es, b_es, a_span, b_span, a_kmax, b_kmax;
 };
 
 struct TensorView { int32_t n; const int32_t *modes; const int64_t *strides; };
@@ -948,6 +948,11 @@ fg_status plan_contraction(int32_t nA, const int32_t *modesA, const int64_t *str
         auto stride_of = [&](const TensorView &t, int label, bool pseudo) { const int i = pseudo ? -1 : find_mode(t, label); return i < 0 ? (int64_t)1 : t.strides[i]; };
         c.a_es = stride_of(ta, la, nm == 0 && !c.a_kc); c.b_es = stride_of(tb, lb, nn == 0 && !c.b_kc);
         c.a_span = span(ta); c.b_span = span(tb);
+        c.a_kmax = c.b_kmax = 0;
+        for (int i = 0; i < nkk; ++i) {
+            c.a_kmax += (extent(k_modes[i]) - 1) * ta.strides[find_mode(ta, k_modes[i])];
+            c.b_kmax += (extent(k_modes[i]) - 1) * tb.strides[find_mode(tb, k_modes[i])];
+        }
     }
     return FG_OK;
 }
@@ -1201,6 +1206,7 @@ fg_status fg_contract(int32_t nA, const int32_t *modesA, const int64_t *stridesA
         const GeneralPlan plan = choose_general(c.M, c.N, c.K, c.batches, false);
         f.M = (int32_t)c.M; f.N = (int32_t)c.N; f.K = (int32_t)c.K; f.batches = (int32_t)c.batches; f.splits = 1;
         f.A = (const uint16_t *)c.A; f.B = (const uint16_t *)c.B;
+        f.a_kmax = c.a_kmax; f.b_kmax = c.b_kmax; f.k_modes = c.a_k.n > 0 ? c.a_k.n : 1; f.small = c.a_span < (1ll << 31) && c.b_span < (1ll << 31);
         f.a_span = c.a_span; f.b_span = c.b_span; f.a_es = c.a_es; f.b_es = c.b_es;
         f.C = use_c ? Cin : nullptr; f.D = Cout;
         f.a_m = c.a_m; f.a_k = c.a_k; f.b_n = c.b_n; f.b_k = c.b_k; f.c_m = c.c_m; f.c_n = c.c_n;

@@ -46,7 +46,10 @@ struct GeneralParams {
     int32_t m_hi;                     // nonzero: the rows' leading mode is split, mode 0 of the groups are its
                                       // pieces' elements and mode m_hi counts the pieces
     int64_t a_es, b_es;               // element stride inside a piece
+    int64_t a_kmax, b_kmax;           // largest offset of a k in A and in B
     int32_t batches;
+    int32_t k_modes;                  // modes of a_k that count (at least 1)
+    int32_t small;                    // A and B span less than 2^31 elements, i.e. 32-bit byte offsets reach all of them
 };
 
 // Eight 16-bit elements that may start at any element: one 16-byte load (the target runs with
@@ -181,10 +184,20 @@ struct PieceLoader {
             }
         }
     }
-    // Contractions: request the K step whose offsets stand in koff, kleft.
+    // Contractions: request the K step whose offsets stand in koff, kleft.  INSIDE (the wave's pieces
+    // lie inside the operand whatever k is, and its offsets fit 32 bits): `whole` steps, of which every
+    // k is below K, need no kleft.
     template <int MODE>
-    __device__ __forceinline__ void fetch_strided(int slot, const uint16_t *base, int64_t span, int64_t es, const int64_t *koff, const int32_t *kleft) {
-        if constexpr (KC) {
+    __device__ __forceinline__ void fetch_strided(int slot, const uint16_t *base, int64_t span, int64_t es, bool whole, const int64_t *koff, const int32_t *kleft) {
+        if constexpr (MODE == FETCH_INSIDE) {
+            auto piece = [&](int64_t at_row, int64_t at_k) { return load_piece((const uint16_t *)((const char *)base + ((uint32_t)at_row + (uint32_t)at_k) * 2u)); };
+            if (!whole) {
+#pragma unroll
+                for (int s = 0; s < (KC ? 1 : CH); ++s) left[slot][s] = KC ? kleft[pos] : kleft[pos + s * STEP] ? 8 : 0;
+            }
+#pragma unroll
+            for (int s = 0; s < CH; ++s) stage[slot][s] = KC ? piece(off[KC ? s : 0], koff[pos]) : piece(off[0], koff[pos + s * STEP]);
+        } else if constexpr (KC) {
             left[slot][0] = kleft[pos];
             const int64_t k = koff[pos];
 #pragma unroll
@@ -196,6 +209,13 @@ struct PieceLoader {
                 request<MODE>(slot, s, base, off[0] + koff[pos + s * STEP], span, es, left[slot][s] ? rows : 0);
             }
         }
+    }
+    // no piece of this thread reaches past the operand, kmax being the largest offset of a k
+    __device__ __forceinline__ bool always_inside(int64_t kmax, int64_t span) const {
+        bool ok = true;
+#pragma unroll
+        for (int s = 0; s < (KC ? CH : 1); ++s) ok = ok && off[s] + kmax + 8 <= span;
+        return ok;
     }
     // Write the staged pieces to LDS; `whole`: every k of the step is below K.
     template <int MODE>
@@ -212,7 +232,7 @@ struct PieceLoader {
             u32x4 v = stage[slot][s];
             if (moved) v = drop_first(v, shift[slot][s]);
             if (add) v = __builtin_bit_cast(u32x4, add8(__builtin_bit_cast(half8, v), addend));
-            if (MODE != FETCH_INSIDE && !whole) v = keep_first(v, left[slot][KC ? 0 : s]);
+            if ((MODE != FETCH_INSIDE || !PLAIN) && !whole) v = keep_first(v, left[slot][KC ? 0 : s]);
             *(FG_LDS u32x4 *)(tile + (s * NT + tid) * 16) = v;
         }
     }
@@ -273,13 +293,33 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
         if constexpr (!PLAIN) {
             KTable &t = ktab[group][i & 3];
             const int k = kt(i) * 64 + lane;
-            const int rest = p.k_ext0 - leading_index(p.a_k, k, 0);
+            // 32-bit arithmetic where the operands allow it, and no further than the summed modes go: one
+            // wave computes while the others wait for it at the step's barrier
+            int lead, idx = k;
+            int64_t oa = 0, ob = 0;
+            uint32_t oa32 = 0, ob32 = 0;
+            for (int m = 0; m < p.k_modes; ++m) {
+                const int q = (int)(__umulhi((uint32_t)idx, p.a_k.magic[m]) >> p.a_k.shift[m]);
+                const int digit = idx - q * p.a_k.extent[m];
+                if (m == 0) lead = digit;
+                if (p.small) {
+                    oa32 += (uint32_t)digit * (uint32_t)p.a_k.stride[m];
+                    ob32 += (uint32_t)digit * (uint32_t)p.b_k.stride[m];
+                } else {
+                    oa += digit * p.a_k.stride[m];
+                    ob += digit * p.b_k.stride[m];
+                }
+                idx = q;
+            }
+            const int rest = p.k_ext0 - lead;
             const bool ok = k < p.K && rest > 0;
             t.left[lane] = ok ? (rest < 8 ? rest : 8) : 0;
-            t.a[lane] = ok ? group_offset(p.a_k, k) : 0;
-            t.b[lane] = ok ? group_offset(p.b_k, k) : 0;
+            t.a[lane] = ok ? (p.small ? (int64_t)oa32 : oa) : 0;
+            t.b[lane] = ok ? (p.small ? (int64_t)ob32 : ob) : 0;
         }
     };
+    // every k of step i is below K (contractions whose leading summed mode is rounded up have k to clear in every step)
+    auto whole_step = [&](int i) { return (PLAIN || p.k_ext0 == p.a_k.extent[0]) && kt(i) * 64 + 64 <= p.K; };
     auto fetch = [&](auto mode_tag, int i, int slot) {
         constexpr int MODE = decltype(mode_tag)::value;
         if constexpr (PLAIN) {
@@ -287,14 +327,14 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
             lb.template fetch_plain<MODE>(slot, B, b_span, p.b_ks, kt(i), p.K);
         } else {
             const KTable &t = ktab[group][i & 3];
-            la.template fetch_strided<MODE>(slot, A, a_span, p.a_es, t.a, t.left);
-            lb.template fetch_strided<MODE>(slot, B, b_span, p.b_es, t.b, t.left);
+            const bool whole = whole_step(i);
+            la.template fetch_strided<MODE>(slot, A, a_span, p.a_es, whole, t.a, t.left);
+            lb.template fetch_strided<MODE>(slot, B, b_span, p.b_es, whole, t.b, t.left);
         }
     };
     auto commit = [&](auto mode_tag, int i, int slot) {
         constexpr int MODE = decltype(mode_tag)::value;
-        // contractions whose leading summed mode is rounded up have k to clear in every step
-        const bool whole = (PLAIN || p.k_ext0 == p.a_k.extent[0]) && kt(i) * 64 + 64 <= p.K;
+        const bool whole = whole_step(i);
         const bool add = PLAIN && !BF16 && p.ab_add;
         la.template commit<MODE>(slot, lds_a + slot * A_BYTES, tid, whole, add, p.a_add2);
         lb.template commit<MODE>(slot, lds_b + slot * B_BYTES, tid, whole, add, p.b_add2);
@@ -325,7 +365,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
         publish();
         auto step = [&](auto mode_tag, int i, auto cur_tag) {      // step i, from LDS buffer `cur`
             constexpr int cur = decltype(cur_tag)::value, nxt = cur ^ 1;
-            constexpr bool STEADY = decltype(mode_tag)::value == FETCH_INSIDE;
+            constexpr bool STEADY = PLAIN && decltype(mode_tag)::value == FETCH_INSIDE;
             // the buffer of step i+1 was last read in step i-1, before the barrier that ended it
             if (STEADY || kt(i + 1) < kt1) commit(mode_tag, i + 1, nxt);
             if (STEADY || kt(i + 3) < kt1) fetch(mode_tag, i + 3, nxt);
@@ -369,7 +409,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
             publish();
         }
         const bool pieces = (PLAIN || (p.a_es == 1 && p.b_es == 1)) && a_span >= 8 && b_span >= 8;
-        if (pieces) k_loop(std::integral_constant<int, FETCH_CLAMP>{});
+        // (contractions: the waves of a workgroup may take different loops, which have the same barriers)
+        const bool inside = !PLAIN && pieces && p.small &&
+                            __builtin_amdgcn_ballot_w64(!(la.always_inside(p.a_kmax, a_span) && lb.always_inside(p.b_kmax, b_span))) == 0;
+        if (inside) { if constexpr (!PLAIN) k_loop(std::integral_constant<int, FETCH_INSIDE>{}); }
+        else if (pieces) k_loop(std::integral_constant<int, FETCH_CLAMP>{});
         else k_loop(std::integral_constant<int, FETCH_GATHER>{});
     }
 
@@ -457,13 +501,15 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
         auto offset_of = [&](const ModeGroup &g, int idx, int extent, int ext0, int hi) -> int64_t {
             return (idx < extent && leading_index(g, idx, hi) < ext0) ? group_offset(g, idx) : -1;
         };
-        const int64_t base = group_offset(p.c_b, batch);
+        // read again here rather than kept in scalar registers through the K loop
+        const GeneralParams ep = load_param<GeneralParams>(0);
+        const int64_t base = group_offset(ep.c_b, batch);
         int64_t row[TI];
 #pragma unroll
-        for (int i = 0; i < TI; ++i) row[i] = offset_of(p.c_m, mb + 32 * i, p.M, p.m_ext0, p.m_hi);
+        for (int i = 0; i < TI; ++i) row[i] = offset_of(ep.c_m, mb + 32 * i, p.M, p.m_ext0, p.m_hi);
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
-            const int64_t mine = offset_of(p.c_n, n0 + wn * WTN + 32 * j + lm, p.N, p.n_ext0, 0);
+            const int64_t mine = offset_of(ep.c_n, n0 + wn * WTN + 32 * j + lm, p.N, p.n_ext0, 0);
             const int lo = (int)(uint32_t)mine, hi = (int)(uint32_t)((uint64_t)mine >> 32);
             int64_t col[RR];
 #pragma unroll
