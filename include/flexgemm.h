@@ -43,7 +43,8 @@
  *     multiple of 8.  A real, non-diagonal product that misses any of these (any leading
  *     dimension, pointers aligned to an element only, any K) is computed by a general kernel:
  *     same operation and options through registers instead of direct loads, slower (1531 x 1021 x 2003: 28
- *     against 20 microseconds for 1536 x 1024 x 2048).  It reads nothing outside the operands; a K split
+ *     against 20 microseconds for 1536 x 1024 x 2048).  It reads nothing outside the operands but the
+ *     other half of the 4-byte words that hold their first and last elements; a K split
  *     that cannot have the workspace (see above) is computed in one pass instead.  Complex, dual and diagonal products have no
  *     general kernel: FG_ERR_ALIGN (FG_ERR_UNSUPPORTED for K).  Pointers that are not aligned to
  *     an element are always FG_ERR_ALIGN.

@@ -1213,6 +1213,9 @@ fg_status fg_contract(int32_t nA, const int32_t *modesA, const int64_t *stridesA
         f.a_b = c.a_b; f.b_b = c.b_b; f.c_b = c.c_b;
         f.m_ext0 = c.m_ext0; f.n_ext0 = c.n_ext0; f.k_ext0 = c.k_ext0; f.m_hi = c.m_hi;
         f.alpha = alpha; f.beta = use_c ? beta : 0.f;
+        auto odd_strides = [](const fg::ModeGroup &g) { for (int t = 0; t < g.n; ++t) if (g.stride[t] % 2 && g.stride[t] != 1) return true; return false; };
+        f.odd = ((!c.a_kc && c.m_ext0 < 64) || (!c.b_kc && c.n_ext0 < 64)) && ((uintptr_t)f.A % 4 != 0 || (uintptr_t)f.B % 4 != 0 || odd_strides(f.a_m) || odd_strides(f.a_k) || odd_strides(f.a_b) ||
+                odd_strides(f.b_n) || odd_strides(f.b_k) || odd_strides(f.b_b));
         const int64_t tiles_m = (c.M + plan.bm - 1) / plan.bm, tiles_n = (c.N + plan.bn - 1) / plan.bn;
         if (tiles_m * tiles_n * c.batches >= (1ll << 31)) return fail(FG_ERR_UNSUPPORTED, "too many tiles");
         f.tiles_m = (int32_t)tiles_m; f.tiles_n = (int32_t)tiles_n;

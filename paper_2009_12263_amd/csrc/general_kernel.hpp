@@ -49,6 +49,7 @@ struct GeneralParams {
     int64_t a_kmax, b_kmax;           // largest offset of a k in A and in B
     int32_t batches;
     int32_t k_modes;                  // modes of a_k that count (at least 1)
+    int32_t odd;                      // fetch INSIDE_ODD (see FetchMode) where the kernel has it
     int32_t small;                    // A and B span less than 2^31 elements, i.e. 32-bit byte offsets reach all of them
 };
 
@@ -58,6 +59,11 @@ struct __attribute__((packed, aligned(2))) Piece { uint32_t w[4]; };
 __device__ __forceinline__ u32x4 load_piece(const uint16_t *p) {
     const Piece v = *(const Piece *)p;
     return u32x4{v.w[0], v.w[1], v.w[2], v.w[3]};
+}
+// The four words from a word-aligned address on.
+__device__ __forceinline__ u32x4 load_words(const char *p) {
+    typedef uint32_t u32x4_word __attribute__((ext_vector_type(4), aligned(4)));
+    return *(const u32x4_word *)p;
 }
 // The first `count` of eight elements es apart, zeros behind them.  What does not exist is read
 // from element 0 instead and cleared, so that the loads carry no branches.
@@ -96,7 +102,14 @@ struct KTable {
 // branch stands between the load and its use: with one, every step waited for its own loads,
 // 33 against 28 us at 1531x1021x2003).  GATHER: eight element loads per piece, for operands without
 // a unit stride and for those of fewer than eight elements.
-enum FetchMode { FETCH_INSIDE, FETCH_CLAMP, FETCH_GATHER };
+// INSIDE_ODD: INSIDE for operands with pieces that start in the middle of a 4-byte word: the five words
+// that hold the piece are loaded (a word-aligned 16-byte load and a 4-byte one, which the cache serves several
+// lanes of at a time; a 16-byte load in the middle of words goes lane by lane) and shifted by 16 bits
+// when committed.  Contractions on 64x64 tiles whose rows or columns come in runs shorter than the tile
+// (37x29x31x35 over 27x25: 21.3 -> 19.0 us, D_abc = A_bda B_dc with 63, 31, 511, 373: 14.1 -> 13.0);
+// with longer runs, on the larger tile and for matrices it measured 2 to 20 % slower.
+enum FetchMode { FETCH_INSIDE, FETCH_CLAMP, FETCH_GATHER, FETCH_INSIDE_ODD };
+constexpr bool is_inside(int mode) { return mode == FETCH_INSIDE || mode == FETCH_INSIDE_ODD; }
 
 // Index along a group's leading mode; hi: the mode that counts its pieces of eight, 0 if it is not split.
 __device__ __forceinline__ int leading_index(const ModeGroup &g, int idx, int hi) {
@@ -124,6 +137,8 @@ struct PieceLoader {
     u32x4 stage[2][CH];             // the pieces of two K steps in flight
     int left[2][KC ? 1 : CH];       // elements of the staged pieces that are below K (MC: 0 or 8)
     int shift[2][CH];               // CLAMP: how many elements before its place a piece was loaded
+    uint32_t fifth[2][CH];          // INSIDE_ODD: the word after the staged four
+    int skew[2][CH];                // INSIDE_ODD: bytes to drop in front (0 or 2)
 
     __device__ __forceinline__ void init(const ModeGroup &rg, int ext0, int hi, int64_t rs, int row0, int rdim, int tid) {
         if constexpr (KC) {
@@ -172,14 +187,14 @@ struct PieceLoader {
         const int k0 = kt * 64;
         if constexpr (KC) {
             const int n = K - (k0 + pos);
-            if constexpr (MODE != FETCH_INSIDE) left[slot][0] = n < 0 ? 0 : n > 8 ? 8 : n;
+            if constexpr (!is_inside(MODE)) left[slot][0] = n < 0 ? 0 : n > 8 ? 8 : n;
 #pragma unroll
             for (int s = 0; s < CH; ++s) request<MODE>(slot, s, base, off[s] + k0, span, 1, left[slot][0]);
         } else {
             const int64_t mine = off[0] + (int64_t)pos * ks, step = (int64_t)k0 * ks;
 #pragma unroll
             for (int s = 0; s < CH; ++s) {
-                if constexpr (MODE != FETCH_INSIDE) left[slot][s] = k0 + pos + s * STEP < K ? 8 : 0;
+                if constexpr (!is_inside(MODE)) left[slot][s] = k0 + pos + s * STEP < K ? 8 : 0;
                 request<MODE>(slot, s, base, mine + (step + s * STEP * ks), span, 1, left[slot][s] ? rows : 0);
             }
         }
@@ -189,14 +204,28 @@ struct PieceLoader {
     // k is below K, need no kleft.
     template <int MODE>
     __device__ __forceinline__ void fetch_strided(int slot, const uint16_t *base, int64_t span, int64_t es, bool whole, const int64_t *koff, const int32_t *kleft) {
-        if constexpr (MODE == FETCH_INSIDE) {
-            auto piece = [&](int64_t at_row, int64_t at_k) { return load_piece((const uint16_t *)((const char *)base + ((uint32_t)at_row + (uint32_t)at_k) * 2u)); };
+        if constexpr (is_inside(MODE)) {
+            auto piece = [&](int s, int64_t at_row, int64_t at_k) {
+                uint32_t at = ((uint32_t)at_row + (uint32_t)at_k) * 2u;
+                const char *q = (const char *)base;
+                if constexpr (MODE == FETCH_INSIDE) {
+                    stage[slot][s] = load_piece((const uint16_t *)(q + at));
+                } else {
+                    const uint32_t base_skew = (uint32_t)(uintptr_t)q & 2u;    // uniform
+                    q -= base_skew;
+                    at += base_skew;
+                    skew[slot][s] = (int)(at & 2u);
+                    at &= ~3u;
+                    stage[slot][s] = load_words(q + at);
+                    fifth[slot][s] = *(const uint32_t *)(q + at + 16);
+                }
+            };
             if (!whole) {
 #pragma unroll
                 for (int s = 0; s < (KC ? 1 : CH); ++s) left[slot][s] = KC ? kleft[pos] : kleft[pos + s * STEP] ? 8 : 0;
             }
 #pragma unroll
-            for (int s = 0; s < CH; ++s) stage[slot][s] = KC ? piece(off[KC ? s : 0], koff[pos]) : piece(off[0], koff[pos + s * STEP]);
+            for (int s = 0; s < CH; ++s) piece(s, off[KC ? s : 0], KC ? koff[pos] : koff[pos + s * STEP]);
         } else if constexpr (KC) {
             left[slot][0] = kleft[pos];
             const int64_t k = koff[pos];
@@ -230,9 +259,14 @@ struct PieceLoader {
 #pragma unroll
         for (int s = 0; s < CH; ++s) {
             u32x4 v = stage[slot][s];
+            if constexpr (MODE == FETCH_INSIDE_ODD) {
+                const uint32_t sh = (uint32_t)skew[slot][s], last = fifth[slot][s];
+                v = u32x4{__builtin_amdgcn_alignbyte(v[1], v[0], sh), __builtin_amdgcn_alignbyte(v[2], v[1], sh),
+                          __builtin_amdgcn_alignbyte(v[3], v[2], sh), __builtin_amdgcn_alignbyte(last, v[3], sh)};
+            }
             if (moved) v = drop_first(v, shift[slot][s]);
             if (add) v = __builtin_bit_cast(u32x4, add8(__builtin_bit_cast(half8, v), addend));
-            if ((MODE != FETCH_INSIDE || !PLAIN) && !whole) v = keep_first(v, left[slot][KC ? 0 : s]);
+            if ((!is_inside(MODE) || !PLAIN) && !whole) v = keep_first(v, left[slot][KC ? 0 : s]);
             *(FG_LDS u32x4 *)(tile + (s * NT + tid) * 16) = v;
         }
     }
@@ -365,7 +399,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
         publish();
         auto step = [&](auto mode_tag, int i, auto cur_tag) {      // step i, from LDS buffer `cur`
             constexpr int cur = decltype(cur_tag)::value, nxt = cur ^ 1;
-            constexpr bool STEADY = PLAIN && decltype(mode_tag)::value == FETCH_INSIDE;
+            constexpr bool STEADY = PLAIN && is_inside(decltype(mode_tag)::value);
             // the buffer of step i+1 was last read in step i-1, before the barrier that ended it
             if (STEADY || kt(i + 1) < kt1) commit(mode_tag, i + 1, nxt);
             if (STEADY || kt(i + 3) < kt1) fetch(mode_tag, i + 3, nxt);
@@ -412,9 +446,20 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
         // (contractions: the waves of a workgroup may take different loops, which have the same barriers)
         const bool inside = !PLAIN && pieces && p.small &&
                             __builtin_amdgcn_ballot_w64(!(la.always_inside(p.a_kmax, a_span) && lb.always_inside(p.b_kmax, b_span))) == 0;
-        if (inside) { if constexpr (!PLAIN) k_loop(std::integral_constant<int, FETCH_INSIDE>{}); }
-        else if (pieces) k_loop(std::integral_constant<int, FETCH_CLAMP>{});
-        else k_loop(std::integral_constant<int, FETCH_GATHER>{});
+        constexpr std::integral_constant<int, FETCH_INSIDE> INSIDE{};
+        constexpr std::integral_constant<int, FETCH_INSIDE_ODD> INSIDE_ODD{};
+        constexpr std::integral_constant<int, FETCH_CLAMP> CLAMP{};
+        constexpr std::integral_constant<int, FETCH_GATHER> GATHER{};
+        if constexpr (PLAIN) {
+            if (!pieces) k_loop(GATHER);
+            else k_loop(CLAMP);
+        } else {
+            constexpr bool SHORT_RUNS = !(A_KC && B_KC) && BM == 64;
+            if (SHORT_RUNS && inside && p.odd) { if constexpr (SHORT_RUNS) k_loop(INSIDE_ODD); }
+            else if (inside) k_loop(INSIDE);
+            else if (pieces) k_loop(CLAMP);
+            else k_loop(GATHER);
+        }
     }
 
     // ---- the groups' results: register r0 + r of block (i, j) ends up in y[i][j][r] of group r0 / RR ----
