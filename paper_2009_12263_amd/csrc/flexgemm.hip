@@ -95,6 +95,7 @@ struct Problem {
 struct Plan { int tile; int splits; int tail_splits; };
 
 constexpr int64_t kWorkspaceBytes = 64ll << 20;    // split-K partial products, per device
+constexpr int64_t kStaticScratchBytes = 16ll << 20;   // those of the allocation-free entry point
 
 const fg::KernelEntry *table_h16_for(bool a_kc, bool b_kc) {
     if (!a_kc && b_kc) return fg::kernel_table_nn_h16();
@@ -130,15 +131,28 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 // 17 x 1321 x 1312 to 227 x 8112 x 4992: the choice is on average 1 % slower than the fastest of
 // them (5 % before the fit), at most 13 %.  A split's second launch is priced with its host time, which
 // a stream of small products pays.
+constexpr int kTileM[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64};
+constexpr int kTileN[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64};
+constexpr int kTilesPerCU[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1};
+struct Rates {
+    double shared[fg::TILE_COUNT], alone[fg::TILE_COUNT];
+    double round_fixed, cu_cd_bw, reduce_launch, reduce_bw;
+};
+constexpr Rates kRates = {{1.0, 0.8, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29}, {1.0, 0.8, 0.43, 0.135, 0.645, 1.0, 0.27, 0.29}, 1.6e-6, 27e9, 12.3e-6, 7.2e12};
+// The rates that decided what a call needs scratch memory for before the 64x64 tile had K groups
+// (see within_promised_scratch).
+constexpr Rates kPromisedRates = {{1.0, 0.8, 0.73, 0.45, 0.57, 1.0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0}, 2e-6, 25e9, 6e-6, 3e12};
+
 Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_smallest = true, int64_t batches = 1,
-                 bool allow_deep = true, int k32 = 0, bool allow_groups = false) {
-    static const int bm[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64};
-    static const int bn[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64};
-    static const int per_cu[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1};
-    static const double rate_shared[fg::TILE_COUNT] = {1.0, 0.8, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29};
-    static const double rate_alone[fg::TILE_COUNT] = {1.0, 0.8, 0.43, 0.135, 0.645, 1.0, 0.27, 0.29};
+                 bool allow_deep = true, int k32 = 0, bool allow_groups = false, int64_t scratch_bytes = kWorkspaceBytes,
+                 const Rates &rates = kRates) {
+    const auto &bm = kTileM;
+    const auto &bn = kTileN;
+    const auto &per_cu = kTilesPerCU;
+    const auto &rate_shared = rates.shared, &rate_alone = rates.alone;
     static const int split_options[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
-    constexpr double cu_flops = 4.7e12, round_fixed = 1.6e-6, cu_cd_bw = 27e9, reduce_launch = 12.3e-6, reduce_bw = 7.2e12;
+    constexpr double cu_flops = 4.7e12;
+    const double round_fixed = rates.round_fixed, cu_cd_bw = rates.cu_cd_bw, reduce_launch = rates.reduce_launch, reduce_bw = rates.reduce_bw;
     constexpr double tail_launch = 6e-6, tail_bw = 3e12;      // the leftover tiles' reduction follows a full round
     // tuning overrides (see read_tuning_from_environment)
     int force_tile = -1;
@@ -184,7 +198,7 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
             if (best_cost < 0 || cost < best_cost) { best = Plan{t, S, tail}; best_cost = cost; }
         };
         // (a) every tile split S ways (S = 1: the plain launch)
-        auto legal = [&](int S) { return S == 1 || (may_split && S <= nk && tiles * S * slot_bytes <= kWorkspaceBytes); };
+        auto legal = [&](int S) { return S == 1 || (may_split && S <= nk && tiles * S * slot_bytes <= scratch_bytes); };
         const int forced = (force_split >= 1 && legal(force_split)) ? force_split : (force_split >= 1 ? 1 : 0);
         for (int S : split_options) {
             if (forced) { if (S != split_options[0]) break; S = forced; }      // one candidate: the forced split
@@ -201,7 +215,7 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
             for (int S : split_options) {
                 if (S == 1) continue;
                 if (force_tail > 1) { if (S != split_options[1]) break; S = force_tail; }
-                const bool fits = S <= nk && rest * S * slot_bytes <= kWorkspaceBytes;
+                const bool fits = S <= nk && rest * S * slot_bytes <= scratch_bytes;
                 if (force_tail > 1) { if (!fits) break; }
                 else if (!fits || nk / S < 4 || rest * S > slots) break;
                 const double cost = (double)(full / slots) * share_time(full, 1) + 2e-6 +
@@ -222,6 +236,28 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
         if (force_k32 || (k32 == 2 && tiles >= kNumCU * 3 / 4)) best.tile = fg::TILE_256x256_K32;
     }
     return best;
+}
+
+// Scratch bytes that a plan's partial products take.
+int64_t scratch_need(const Plan &plan, int64_t M, int64_t N) {
+    const int t = plan.tile == fg::TILE_256x256_K32 ? fg::TILE_256x256 : plan.tile;
+    const int64_t tiles = ((M + kTileM[t] - 1) / kTileM[t]) * ((N + kTileN[t] - 1) / kTileN[t]), tile_bytes = (int64_t)kTileM[t] * kTileN[t] * 4;
+    if (plan.splits > 1) return tiles * plan.splits * tile_bytes;
+    if (plan.tail_splits > 1) return tiles % (kNumCU * kTilesPerCU[t]) * plan.tail_splits * tile_bytes;
+    return 0;
+}
+
+// What a call needs scratch memory for is part of what it promises: a call that needed none can be
+// captured before the workspace exists, one whose partial products fit the static array can be made
+// without allocation.  A plan that needs more than the plan by the promised rates is
+// therefore replaced by the best one that does not (0.5 % of random shapes).
+Plan within_promised_scratch(Plan plan, int64_t M, int64_t N, int64_t K, int k32) {
+    const int64_t need = scratch_need(plan, M, N);
+    if (need == 0 || g_force_split.load(std::memory_order_relaxed) >= 1 || g_force_tail.load(std::memory_order_relaxed) > 1 ||
+        g_force_tile.load(std::memory_order_relaxed) >= 0) return plan;
+    const int64_t promised = scratch_need(choose_plan(M, N, K, true, true, 1, true, k32, false, kWorkspaceBytes, kPromisedRates), M, N);
+    const int64_t limit = promised == 0 ? 0 : promised <= kStaticScratchBytes ? kStaticScratchBytes : kWorkspaceBytes;
+    return need <= limit ? plan : choose_plan(M, N, K, limit > 0, true, 1, true, k32, true, limit);
 }
 
 // Tile of the complex and dual kernels (256x128, 128x128 with two workgroups per unit, 64x64 with
@@ -269,7 +305,8 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     }
     const bool may_split = plan_out && !q.a_diag && !q.b_diag && !q.cd16;   // the reduction pass writes FP32
     const int k32 = (q.a_diag || q.b_diag) ? 0 : q.ab_add ? (q.a_kc != q.b_kc ? 2 : 0) : ((q.a_kc || q.b_kc) ? 2 : 1);
-    const Plan plan = choose_plan(q.M, q.N, q.K, may_split, true, 1, !q.a_diag && !q.b_diag, k32, !q.a_diag && !q.b_diag);
+    Plan plan = choose_plan(q.M, q.N, q.K, may_split, true, 1, !q.a_diag && !q.b_diag, k32, !q.a_diag && !q.b_diag);
+    if (may_split) plan = within_promised_scratch(plan, q.M, q.N, q.K, k32);
     int tile = plan.tile;
     // A product with a diagonal operand is bound by its memory traffic (one pass over the dense
     // operand, C and D; a tile row only meets the K tiles on the diagonal).  While all of it fits the
@@ -362,7 +399,6 @@ fg_status workspace_locked(int dev, hipStream_t stream, bool may_allocate, Works
 // library's device image, so each GPU the library runs on holds one copy until the process ends.
 // Host code never uses the symbol itself as an address: g_static_scratch[dev] is the array's
 // device address on GPU `dev`, asked for once per device with that device current.
-constexpr int64_t kStaticScratchBytes = 16ll << 20;
 static __device__ __align__(256) float scratch[kStaticScratchBytes / 4];
 float *g_static_scratch[64];
 
