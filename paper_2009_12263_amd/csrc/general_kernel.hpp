@@ -18,6 +18,7 @@
 // 4095x4097x4099: 244 us, 563 TFLOP/s.
 #pragma once
 #include "gemm_kernel.hpp"
+#include "piece_address.hpp"
 
 namespace fg {
 
@@ -206,18 +207,17 @@ struct PieceLoader {
     __device__ __forceinline__ void fetch_strided(int slot, const uint16_t *base, int64_t span, int64_t es, bool whole, const int64_t *koff, const int32_t *kleft) {
         if constexpr (is_inside(MODE)) {
             auto piece = [&](int s, int64_t at_row, int64_t at_k) {
-                uint32_t at = ((uint32_t)at_row + (uint32_t)at_k) * 2u;
+                const uint32_t at = ((uint32_t)at_row + (uint32_t)at_k) * 2u;
                 const char *q = (const char *)base;
                 if constexpr (MODE == FETCH_INSIDE) {
                     stage[slot][s] = load_piece((const uint16_t *)(q + at));
                 } else {
                     const uint32_t base_skew = (uint32_t)(uintptr_t)q & 2u;    // uniform
                     q -= base_skew;
-                    at += base_skew;
-                    skew[slot][s] = (int)(at & 2u);
-                    at &= ~3u;
-                    stage[slot][s] = load_words(q + at);
-                    fifth[slot][s] = *(const uint32_t *)(q + at + 16);
+                    const OddPiece o = odd_piece(at + base_skew);
+                    skew[slot][s] = (int)o.skew;
+                    stage[slot][s] = load_words(q + o.words);
+                    fifth[slot][s] = *(const uint32_t *)(q + o.fifth);
                 }
             };
             if (!whole) {
@@ -243,7 +243,7 @@ struct PieceLoader {
     __device__ __forceinline__ bool always_inside(int64_t kmax, int64_t span) const {
         bool ok = true;
 #pragma unroll
-        for (int s = 0; s < (KC ? CH : 1); ++s) ok = ok && off[s] + kmax + 8 <= span;
+        for (int s = 0; s < (KC ? CH : 1); ++s) ok = ok && piece_inside(off[s], kmax, span);
         return ok;
     }
     // Write the staged pieces to LDS; `whole`: every k of the step is below K.
