@@ -43,9 +43,13 @@
  *     multiple of 8.  A real, non-diagonal product that misses any of these (any leading
  *     dimension, pointers aligned to an element only, any K) is computed by a general kernel:
  *     same operation and options through registers instead of direct loads, slower (1531 x 1021 x 2003: 28
- *     against 20 microseconds for 1536 x 1024 x 2048).  It reads nothing outside the operands but the
- *     other half of the 4-byte words that hold their first and last elements; a K split
- *     that cannot have the workspace (see above) is computed in one pass instead.  Complex, dual and diagonal products have no
+ *     against 20 microseconds for 1536 x 1024 x 2048).  From the first to the last element of an
+ *     operand it may read anything (never past them, but for the other half of the 4-byte words that
+ *     hold them).  It may split K through the workspace like the tiled kernels, but only in calls that the
+ *     library orders against the workspace's other users: on a stream under capture, through
+ *     fg_gemm_noalloc and where the workspace cannot be had, one kernel computes the K ranges
+ *     in turn, uses no scratch memory and gives the same bits (slower: 301 x 301 x 6001 58 microseconds
+ *     against 13).  Complex, dual and diagonal products have no
  *     general kernel: FG_ERR_ALIGN (FG_ERR_UNSUPPORTED for K).  Pointers that are not aligned to
  *     an element are always FG_ERR_ALIGN.
  *   - Sizes: M and N are arbitrary; tiles that hang over the edge of a matrix are predicated
@@ -182,7 +186,8 @@ fg_status fg_gemm_ex(int64_t M, int64_t N, int64_t K, float alpha,
  * For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): fg_gemm_ex with the same arguments, results and errors,
  * except that the partial products of a K split go to a 16 MiB array that is part of the library's
- * device image (one copy per GPU, held until the process ends) instead of the 64 MiB workspace.
+ * device image (one copy per GPU, held until the process ends) instead of the 64 MiB workspace
+ * (products on the general kernel use neither here).
  * The call makes the same plan as fg_gemm_ex, so its result is bit-identical; when that plan's
  * partial products need more than 16 MiB (tiles to split x K ranges x tile bytes, e.g. a 2048 x 2048
  * output split three ways) it returns FG_ERR_UNSUPPORTED and launches nothing.  It never calls

@@ -435,13 +435,17 @@ struct Scratch {
         }
         return FG_OK;
     }
-    // for callers that can do without: no error is left behind
-    bool try_acquire(bool static_only, int dev, hipStream_t stream) {
+    // The workspace where the library orders its use (not on a capturing stream), for callers that can do
+    // without: no error is left behind.
+    bool try_acquire(int dev, hipStream_t stream) {
         char kept[sizeof g_err];
         memcpy(kept, g_err, sizeof kept);
-        if (acquire(static_only, dev, stream) == FG_OK) return true;
-        memcpy(g_err, kept, sizeof kept);
-        (void)hipGetLastError();
+        const fg_status st = acquire(false, dev, stream);
+        if (st == FG_OK && guard) return true;
+        if (st != FG_OK) {
+            memcpy(g_err, kept, sizeof kept);
+            (void)hipGetLastError();
+        }
         guard = nullptr;
         return false;
     }
@@ -646,8 +650,7 @@ fg_status normalise(int64_t M, int64_t N, int64_t K, float alpha, const fg_matri
 // traffic).  Against every tile and split forced over 13 shapes from 195x65x2500 to 4095x4097x4099 the
 // choice is the fastest or within 8 %: 1531x1021x2003 28.0 us (128x128: 35.7), 4095x4097x4099 244 us
 // (64x64: 367), 301x301x6001 split in ten 18 us (one pass: 37).
-// The partial products of a split are kept to the 16 MiB of the static array, so that the
-// allocation-free entry point makes the same plan.
+// The partial products of a split are kept to 16 MiB of the workspace.
 struct GeneralPlan { int variant, bm, bn, splits; };
 GeneralPlan choose_general(int64_t M, int64_t N, int64_t K, int64_t batches, bool may_split) {
     static const int edge[fg::GENERAL_COUNT] = {128, 64}, groups[fg::GENERAL_COUNT] = {1, 2};
@@ -695,27 +698,32 @@ fg_status general_gemm(const Problem &q, bool static_only, hipStream_t stream) {
     if (tiles_m * tiles_n >= (1ll << 31)) return fail(FG_ERR_UNSUPPORTED, "too many tiles");
     f.tiles_m = (int32_t)tiles_m; f.tiles_n = (int32_t)tiles_n;
     const int tiles = (int)(tiles_m * tiles_n);
+    // The K ranges of a split go side by side through the workspace, or one after another in a single
+    // launch without scratch memory: same bits.  The second way serves every call that may overlap with
+    // others on the GPU without being ordered against them -- on a stream under capture and through the
+    // allocation-free entry point -- because products of this kind never shared memory before they were
+    // split, and calls that cannot have the workspace.  It is slower (301x301x6001: 58 us against 13,
+    // 1450 with the element-wise kernel that served these calls before).
     Scratch scratch;
+    bool side_by_side = false;
     if (plan.splits > 1) {
-        // A call that cannot have the scratch memory (a capturing stream before the workspace
-        // exists, no memory left) is computed in one pass.
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess) return fail(FG_ERR_LAUNCH, "no HIP device is current");
-        if (!scratch.try_acquire(static_only, dev, stream)) plan.splits = 1;
+        side_by_side = !static_only && scratch.try_acquire(dev, stream);
+        f.splits = plan.splits;
+        f.split_kt = (int32_t)(((q.K + 63) / 64 + plan.splits - 1) / plan.splits);
     }
-    if (plan.splits > 1) {
+    if (side_by_side) {
         fg::GeneralParams part = f;
-        part.splits = plan.splits;
-        part.split_kt = (int32_t)(((q.K + 63) / 64 + plan.splits - 1) / plan.splits);
         part.D = scratch.ptr;
-        hipError_t e = fg::launch_gemm_general(part, q.a_kc, q.b_kc, q.bf16, plan.variant, stream);
+        hipError_t e = fg::launch_gemm_general(part, q.a_kc, q.b_kc, q.bf16, plan.variant, false, stream);
         if (e == hipSuccess)
             e = fg::launch_splitk_reduce(scratch.ptr, plan.splits, 0, tiles, plan.bm, plan.bn, f.tiles_m, f.tiles_n, f.M, f.N, q.alpha, q.beta,
                                          q.C, q.ldc, q.D, q.ldd, q.bias, q.bias_dim, q.act, q.c_act, stream);
         if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "launch of the general kernel failed: %s", hipGetErrorString(e));
         return scratch.release(stream);
     }
-    hipError_t e = fg::launch_gemm_general(f, q.a_kc, q.b_kc, q.bf16, plan.variant, stream);
+    hipError_t e = fg::launch_gemm_general(f, q.a_kc, q.b_kc, q.bf16, plan.variant, plan.splits > 1, stream);
     if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "launch of the general kernel failed: %s", hipGetErrorString(e));
     return FG_OK;
 }

@@ -275,11 +275,14 @@ struct PieceLoader {
 // KG groups of WGM x WGN waves share a BM x BN tile: group g multiplies the K steps kt0 + g, kt0 + g +
 // KG, ... into accumulators of its own, from LDS buffers of its own, and the groups' results are
 // added up through LDS at the end, each group finishing 1/KG of the registers.
-template <int BM, int BN, int WGM, int WGN, int KG, bool A_KC, bool B_KC, bool BF16, bool PLAIN>
+// RANGES (matrices): a workgroup computes the K ranges of its tile one after another and adds them up as
+// the reduction pass would.  It needs no scratch memory and gives the bits of the split product.
+template <int BM, int BN, int WGM, int WGN, int KG, bool A_KC, bool B_KC, bool BF16, bool PLAIN, bool RANGES = false>
 __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const GeneralParams p) {
     constexpr int NW = WGM * WGN, NT = 64 * NW, WTM = BM / WGM, WTN = BN / WGN, TI = WTM / 32, TJ = WTN / 32;
     constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128, GROUP_BYTES = 2 * (A_BYTES + B_BYTES);
     constexpr int RR = 16 / KG;                         // registers of each 32x32 block that a group finishes
+    static_assert(PLAIN || !RANGES, "contractions are not split");
     static_assert(KG == 1 || KG * NW * TI * TJ * 16 * 64 * 4 <= KG * GROUP_BYTES, "the exchange of the groups' results fits the K loop's buffers");
     __shared__ __attribute__((aligned(1024))) char smem_generic[KG * GROUP_BYTES];
     __shared__ KTable ktab[PLAIN ? 1 : KG][PLAIN ? 1 : 4];
@@ -302,9 +305,13 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
     if constexpr (PLAIN) split = outer;
     else { split = outer / p.batches; batch = outer - split * p.batches; }
     const int nk_all = (p.K + 63) / 64;
-    const int kt0 = p.splits > 1 ? split * p.split_kt : 0;
-    int kt1 = p.splits > 1 ? kt0 + p.split_kt : nk_all;
-    if (kt1 > nk_all) kt1 = nk_all;
+    int kt0, kt1;
+    auto k_range = [&](int s) {
+        kt0 = p.splits > 1 ? s * p.split_kt : 0;
+        kt1 = p.splits > 1 ? kt0 + p.split_kt : nk_all;
+        if (kt1 > nk_all) kt1 = nk_all;
+    };
+    k_range(split);
 
     const uint16_t *A = p.A, *B = p.B;
     int64_t a_span = p.a_span, b_span = p.b_span;
@@ -380,12 +387,15 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
     };
 
     floatx16 acc[TI][TJ];
+    auto clear = [&] {
 #pragma unroll
-    for (int i = 0; i < TI; ++i)
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < TJ; ++j)
+            for (int j = 0; j < TJ; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    };
+    clear();
 
     // The K loop.  EDGE: mode of the steps that may reach past the operands.  Every group runs the
     // same number of steps (barriers); a group's last one may be empty.
@@ -437,69 +447,92 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
             if (i + 1 < steps) step(edge_tag, i + 1, std::integral_constant<int, 1>{});
         }
     };
-    if (kt0 < kt1) {
-        if constexpr (!PLAIN) {
-            for (int i = wave; i < 4; i += NW) fill_table(i);
-            publish();
+    // y: the groups' results, register r0 + r of block (i, j) ends up in y[i][j][r] of group r0 / RR
+    const int r0 = group * RR;
+    float y[TI][TJ][RR], total[TI][TJ][RR] = {};
+    for (;;) {                                          // once, RANGES: once per K range
+        if (kt0 < kt1) {
+            if constexpr (!PLAIN) {
+                for (int i = wave; i < 4; i += NW) fill_table(i);
+                publish();
+            }
+            const bool pieces = (PLAIN || (p.a_es == 1 && p.b_es == 1)) && a_span >= 8 && b_span >= 8;
+            // (contractions: the waves of a workgroup may take different loops, which have the same barriers)
+            const bool inside = !PLAIN && pieces && p.small &&
+                                __builtin_amdgcn_ballot_w64(!(la.always_inside(p.a_kmax, a_span) && lb.always_inside(p.b_kmax, b_span))) == 0;
+            constexpr std::integral_constant<int, FETCH_INSIDE> INSIDE{};
+            constexpr std::integral_constant<int, FETCH_INSIDE_ODD> INSIDE_ODD{};
+            constexpr std::integral_constant<int, FETCH_CLAMP> CLAMP{};
+            constexpr std::integral_constant<int, FETCH_GATHER> GATHER{};
+            if constexpr (PLAIN) {
+                if (!pieces) k_loop(GATHER);
+                else k_loop(CLAMP);
+            } else {
+                constexpr bool SHORT_RUNS = !(A_KC && B_KC) && BM == 64;
+                if (SHORT_RUNS && inside && p.odd) { if constexpr (SHORT_RUNS) k_loop(INSIDE_ODD); }
+                else if (inside) k_loop(INSIDE);
+                else if (pieces) k_loop(CLAMP);
+                else k_loop(GATHER);
+            }
         }
-        const bool pieces = (PLAIN || (p.a_es == 1 && p.b_es == 1)) && a_span >= 8 && b_span >= 8;
-        // (contractions: the waves of a workgroup may take different loops, which have the same barriers)
-        const bool inside = !PLAIN && pieces && p.small &&
-                            __builtin_amdgcn_ballot_w64(!(la.always_inside(p.a_kmax, a_span) && lb.always_inside(p.b_kmax, b_span))) == 0;
-        constexpr std::integral_constant<int, FETCH_INSIDE> INSIDE{};
-        constexpr std::integral_constant<int, FETCH_INSIDE_ODD> INSIDE_ODD{};
-        constexpr std::integral_constant<int, FETCH_CLAMP> CLAMP{};
-        constexpr std::integral_constant<int, FETCH_GATHER> GATHER{};
-        if constexpr (PLAIN) {
-            if (!pieces) k_loop(GATHER);
-            else k_loop(CLAMP);
+        if constexpr (KG == 1) {
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < RR; ++r) y[i][j][r] = acc[i][j][r];
         } else {
-            constexpr bool SHORT_RUNS = !(A_KC && B_KC) && BM == 64;
-            if (SHORT_RUNS && inside && p.odd) { if constexpr (SHORT_RUNS) k_loop(INSIDE_ODD); }
-            else if (inside) k_loop(INSIDE);
-            else if (pieces) k_loop(CLAMP);
-            else k_loop(GATHER);
+            FG_LDS float *ex = (FG_LDS float *)smem;
+            auto at = [&](int from, int i, int j, int r) { return (((from * NW + wave) * TI * TJ + i * TJ + j) * 16 + r) * 64 + lane; };
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) ex[at(group, i, j, r)] = acc[i][j][r];
+            publish();
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < RR; ++r) {
+                        float v = ex[at(0, i, j, r0 + r)];
+#pragma unroll
+                        for (int g = 1; g < KG; ++g) v += ex[at(g, i, j, r0 + r)];
+                        y[i][j][r] = v;
+                    }
+        }
+        if constexpr (!RANGES) {
+            break;
+        } else {
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < RR; ++r) total[i][j][r] += y[i][j][r];
+            if (++split == p.splits) break;
+            k_range(split);
+            clear();
+            publish();                                  // the exchange has been read: the next range may overwrite it
         }
     }
-
-    // ---- the groups' results: register r0 + r of block (i, j) ends up in y[i][j][r] of group r0 / RR ----
-    const int r0 = group * RR;
-    float y[TI][TJ][RR];
-    if constexpr (KG == 1) {
+    if constexpr (RANGES) {
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
             for (int j = 0; j < TJ; ++j)
 #pragma unroll
-                for (int r = 0; r < RR; ++r) y[i][j][r] = acc[i][j][r];
-    } else {
-        FG_LDS float *ex = (FG_LDS float *)smem;
-        auto at = [&](int from, int i, int j, int r) { return (((from * NW + wave) * TI * TJ + i * TJ + j) * 16 + r) * 64 + lane; };
-#pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-            for (int j = 0; j < TJ; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) ex[at(group, i, j, r)] = acc[i][j][r];
-        publish();
-#pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-            for (int j = 0; j < TJ; ++j)
-#pragma unroll
-                for (int r = 0; r < RR; ++r) {
-                    float v = ex[at(0, i, j, r0 + r)];
-#pragma unroll
-                    for (int g = 1; g < KG; ++g) v += ex[at(g, i, j, r0 + r)];
-                    y[i][j][r] = v;
-                }
+                for (int r = 0; r < RR; ++r) y[i][j][r] = total[i][j][r];
     }
 
     // ---- lane l, register r of block (i, j) holds row l % 32, column 8 (r/4) + 4 (l/32) + r % 4 ----
     const int lm = lane & 31, lh = lane >> 5;
     const int mb = m0 + wm * WTM + lm, nb = n0 + wn * WTN + 4 * lh;
     auto col_of = [&](int r) { return 8 * ((r0 + r) >> 2) + ((r0 + r) & 3); };      // RR is a multiple of 4: uniform part + constant
-    if (p.splits > 1) {
+    if (!RANGES && p.splits > 1) {
         // raw partial tile into workspace slot `item`, tile-local coordinates
         float *w = p.D + (int64_t)item * (BM * BN) + (wm * WTM + lm) + (wn * WTN + 4 * lh) * BM;
 #pragma unroll
@@ -534,8 +567,14 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
                 for (int r = 0; r < RR; ++r) {
                     const int n = n1 + col_of(r);
                     if (n >= p.N) continue;
-                    float v = p.alpha * y[i][j][r] + (bias_n_on ? p.bias[n] : bias_mi);
-                    if (p.C) v += p.beta * act_clamp(cv[r], floor_c, pass_c);
+                    const float bias = bias_n_on ? p.bias[n] : bias_mi;
+                    float v;
+                    if constexpr (RANGES) {
+                        v = split_value(y[i][j][r], p.alpha, p.C, p.beta, p.C ? act_clamp(cv[r], floor_c, pass_c) : 0.f, p.bias, bias);
+                    } else {
+                        v = p.alpha * y[i][j][r] + bias;
+                        if (p.C) v += p.beta * act_clamp(cv[r], floor_c, pass_c);
+                    }
                     d[col_of(r) * p.ldd] = act_clamp(v, floor_v, pass_v);
                 }
             }
@@ -584,8 +623,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
 }
 
 // One workgroup per work item, in rows of at most 2^22 (a grid dimension holds 2^32 threads).
-inline hipError_t launch_general(void (*fn)(const GeneralParams), GeneralParams p, hipStream_t stream) {
-    const int64_t items = (int64_t)p.tiles_m * p.tiles_n * p.splits * p.batches;
+// ranges: fn computes all K ranges of a tile.
+inline hipError_t launch_general(void (*fn)(const GeneralParams), GeneralParams p, hipStream_t stream, bool ranges = false) {
+    const int64_t items = (int64_t)p.tiles_m * p.tiles_n * (ranges ? 1 : p.splits) * p.batches;
     const unsigned per_row = (unsigned)(items < (1 << 22) ? items : (1 << 22));
     p.items = (int32_t)items;
     hipLaunchKernelGGL(fn, dim3(per_row, (unsigned)((items + per_row - 1) / per_row)), dim3(512), 0, stream, p);
@@ -593,10 +633,10 @@ inline hipError_t launch_general(void (*fn)(const GeneralParams), GeneralParams 
 }
 
 typedef void (*GeneralFn)(const GeneralParams);
-template <int BM, int BN, int WGM, int WGN, int KG, bool BF16, bool PLAIN>
+template <int BM, int BN, int WGM, int WGN, int KG, bool BF16, bool PLAIN, bool RANGES = false>
 GeneralFn general_fn(bool a_kc, bool b_kc) {
-    return a_kc ? (b_kc ? general_kernel<BM, BN, WGM, WGN, KG, true, true, BF16, PLAIN> : general_kernel<BM, BN, WGM, WGN, KG, true, false, BF16, PLAIN>)
-                : (b_kc ? general_kernel<BM, BN, WGM, WGN, KG, false, true, BF16, PLAIN> : general_kernel<BM, BN, WGM, WGN, KG, false, false, BF16, PLAIN>);
+    return a_kc ? (b_kc ? general_kernel<BM, BN, WGM, WGN, KG, true, true, BF16, PLAIN, RANGES> : general_kernel<BM, BN, WGM, WGN, KG, true, false, BF16, PLAIN, RANGES>)
+                : (b_kc ? general_kernel<BM, BN, WGM, WGN, KG, false, true, BF16, PLAIN, RANGES> : general_kernel<BM, BN, WGM, WGN, KG, false, false, BF16, PLAIN, RANGES>);
 }
 
 }  // namespace fg

@@ -77,7 +77,8 @@ hipError_t launch_splitk_reduce(const float *W, int splits, int tile_begin, int 
 // four waves take alternate K steps.
 enum GeneralVariant { GENERAL_128x128 = 0, GENERAL_64x64 = 1, GENERAL_COUNT = 2 };
 struct GeneralParams;
-hipError_t launch_gemm_general(const GeneralParams &p, bool a_kc, bool b_kc, bool bf16, int variant, hipStream_t stream);
+// ranges: one launch whose workgroups compute the p.splits K ranges of their tiles in turn, into D.
+hipError_t launch_gemm_general(const GeneralParams &p, bool a_kc, bool b_kc, bool bf16, int variant, bool ranges, hipStream_t stream);
 hipError_t launch_contract_general(const GeneralParams &p, bool a_kc, bool b_kc, int variant, hipStream_t stream);
 
 // Entry index inside one table of real kernels: three variants per tile.

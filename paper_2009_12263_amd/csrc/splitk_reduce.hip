@@ -56,10 +56,8 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float *W, int splits,
     float y[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        y[q] = alpha * sum[q];
-        if (C) y[q] += beta * act_clamp(cv[q], floor_c, c_act_none);
-        if (bias) y[q] += bias[bias_dim == 0 ? (q < valid ? m + q : m) : n];
-        y[q] = act_clamp(y[q], floor_v, act_none);
+        const float b = bias ? bias[bias_dim == 0 ? (q < valid ? m + q : m) : n] : 0.f;
+        y[q] = act_clamp(split_value(sum[q], alpha, C, beta, act_clamp(cv[q], floor_c, c_act_none), bias, b), floor_v, act_none);
     }
     float *d = D + m + (int64_t)n * ldd;
     if (whole) *(float4 *)d = make_float4(y[0], y[1], y[2], y[3]);

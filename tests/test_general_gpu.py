@@ -90,6 +90,62 @@ def test_split_calls_without_allocation_and_in_a_graph():
         assert torch.equal(D, want)
 
 
+def captured_nodes(stream, call):
+    """Nodes of the graph that `call` leaves when it is made on a capturing stream (nothing runs)."""
+    import ctypes
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)
+    s, graph, n = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t()
+    assert hip.hipStreamBeginCapture(s, 2) == 0               # relaxed mode
+    call()
+    assert hip.hipStreamEndCapture(s, ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("tile,splits", [("2", 3), ("3", 5)])
+@pytest.mark.parametrize("dt", [torch.float16, torch.bfloat16])
+def test_split_without_scratch_memory_gives_the_same_bits(monkeypatch, tile, splits, dt):
+    """Products of this kernel need no scratch memory where a call may overlap with others that the
+    library does not order against it: captured calls and allocation-free calls are one kernel each, which
+    adds the K ranges up itself.  The result is bit for bit that of the eager call, whose ranges go through
+    the workspace, with every option (floats; an odd number of steps per range, an empty last range)."""
+    setenv(monkeypatch, "FG_FORCE_TILE", tile)
+    setenv(monkeypatch, "FG_FORCE_SPLIT", str(splits))
+    fg.fg_init()
+    s = torch.cuda.Stream()
+    for (M, N, K) in ((131, 67, 1501), (65, 130, 7 * 64 + 1), (9, 5, 4 * splits * 64 - 63)):
+        A = W.uniform_pm1(M * K, 1, device="cuda", dtype=dt); B = W.uniform_pm1(K * N, 2, device="cuda", dtype=dt)
+        Cm = W.uniform_pm1(M * N, 3, device="cuda", dtype=torch.float32); bias = W.uniform_pm1(M + N, 4, device="cuda", dtype=torch.float32)
+        for opts in (dict(), dict(C=True), dict(C=True, bias=bias, bias_dim=0, act=fg.FG_ACT_RELU, c_act=fg.FG_ACT_RELU), dict(bias=bias, bias_dim=1),
+                     dict(C=True, a_add=0.5, b_add=-0.25) if dt == torch.float16 else dict(C=True, bias=bias, bias_dim=1)):
+            opts = dict(opts)
+            C_ = fg.Matrix(Cm, fg.FG_COL, M) if opts.pop("C", False) else None
+            want, D = torch.full_like(Cm, float("nan")), torch.full_like(Cm, float("nan"))
+
+            def call(out, **kw):
+                fg.fg_gemm(M, N, K, 0.3, fg.Matrix(A, fg.FG_COL, M), fg.Matrix(B, fg.FG_ROW, N), 0.7, C_, fg.Matrix(out, fg.FG_COL, M), **opts, **kw)
+            say("tile %s split %d %dx%dx%d %s" % (tile, splits, M, N, K, sorted(opts)))
+            call(want)
+            call(D, noalloc=True)
+            torch.cuda.synchronize()
+            assert torch.isfinite(want).all() and torch.equal(D, want)
+            assert captured_nodes(s, lambda: call(D, stream=s)) == 1
+            assert captured_nodes(s, lambda: call(D, stream=s, noalloc=True)) == 1
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.stream(s):
+                with torch.cuda.graph(graph, stream=s):
+                    call(D, stream=s)
+            torch.cuda.synchronize()
+            for rep in range(2):
+                D.fill_(float("nan"))
+                call(torch.empty_like(D))                     # an eager split call beside the replays
+                graph.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(D, want), "replay %d" % rep
+
+
 @pytest.mark.parametrize("tile", ["2", "3"])
 def test_contraction_forms(monkeypatch, tile):
     """Which direction the pieces run along (rows, summed modes, element by element), leading modes
