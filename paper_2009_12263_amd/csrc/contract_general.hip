@@ -7,12 +7,13 @@ namespace fg {
 
 namespace {
 GeneralFn pick(bool a_kc, bool b_kc, int variant) {
-    return variant == GENERAL_128x128 ? general_fn<128, 128, 4, 2, 1, false, false>(a_kc, b_kc) : general_fn<64, 64, 2, 2, 2, false, false>(a_kc, b_kc);
+    return variant == GENERAL_128x128 ? general_fn<128, 128, 4, 2, 1, false, false>(a_kc, b_kc)
+         : variant == GENERAL_64x64   ? general_fn<64, 64, 2, 2, 2, false, false>(a_kc, b_kc) : general_fn<64, 64, 2, 2, 1, false, false>(a_kc, b_kc);
 }
 }  // namespace
 
 hipError_t launch_contract_general(const GeneralParams &p, bool a_kc, bool b_kc, int variant, hipStream_t stream) {
-    return launch_general(pick(a_kc, b_kc, variant), p, stream);
+    return launch_general(pick(a_kc, b_kc, variant), variant, p, stream);
 }
 
 }  // namespace fg

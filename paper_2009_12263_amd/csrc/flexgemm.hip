@@ -651,23 +651,38 @@ fg_status normalise(int64_t M, int64_t N, int64_t K, float alpha, const fg_matri
 // choice is the fastest or within 8 %: 1531x1021x2003 28.0 us (128x128: 35.7), 4095x4097x4099 244 us
 // (64x64: 367), 301x301x6001 split in ten 18 us (one pass: 37).
 // The partial products of a split are kept to 16 MiB of the workspace.
+//
+// K up to 64 is one step.  The 64x64 tile's second wave group would have nothing to multiply, yet take half of
+// the LDS, an exchange and its waves' slots, so that few tiles run side by side: contractions (many
+// small batches above all) and matrices of more than two tiles per unit have a form with one group and one
+// buffer.  Two groups -> one: 65536 batches of 4x4x4 780 -> 337 us (378 with the element-wise kernel of before), 8192 of
+// 16x16x9 97 -> 45 (59), matrices 3001x2999x3 25 -> 16 (26).  With fewer tiles the second group's threads help to
+// load and store: 301x299x50 5.4 us with two, 6.4 with one.  Where the 128x128 tile begins was read from both
+// forced on 58 calls (4x4x4 to 5001x4999x3, where it takes 38.5 us): contractions pay more per small tile.
 struct GeneralPlan { int variant, bm, bn, splits; };
-GeneralPlan choose_general(int64_t M, int64_t N, int64_t K, int64_t batches, bool may_split) {
-    static const int edge[fg::GENERAL_COUNT] = {128, 64}, groups[fg::GENERAL_COUNT] = {1, 2};
-    static const double round_us[fg::GENERAL_COUNT] = {0.9, 0.7}, fixed_us[fg::GENERAL_COUNT] = {2, 1};
+GeneralPlan choose_general(int64_t M, int64_t N, int64_t K, int64_t batches, bool matrix) {
+    static const int edge[] = {128, 64}, groups[] = {1, 2};           // GENERAL_128x128, GENERAL_64x64
+    static const double round_us[] = {0.9, 0.7}, fixed_us[] = {2, 1};
     static const int split_options[] = {1, 2, 3, 4, 6, 8, 10, 12, 16, 24, 32, 48, 64};
     const int64_t nk = (K + 63) / 64;
     const int ft = g_force_tile.load(std::memory_order_relaxed), fs = g_force_split.load(std::memory_order_relaxed);
+    if (nk <= 1) {
+        const int64_t small = ((M + 63) / 64) * ((N + 63) / 64) * batches, large = ((M + 127) / 128) * ((N + 127) / 128) * batches;
+        const double small_us = 5 + (matrix ? 1.47 : 2.0) * (small > kNumCU ? (double)small / kNumCU : 1.0);
+        const double large_us = 6.5 + 4.6 * (double)((large + kNumCU - 1) / kNumCU);
+        if (ft == fg::TILE_128x128 || (ft != fg::TILE_64x64 && large_us < small_us)) return GeneralPlan{fg::GENERAL_128x128, 128, 128, 1};
+        return GeneralPlan{matrix && small <= 2 * kNumCU ? fg::GENERAL_64x64 : fg::GENERAL_64x64_ONE, 64, 64, 1};
+    }
     GeneralPlan best{fg::GENERAL_64x64, 64, 64, 1};
     double best_cost = -1;
-    for (int v = 0; v < fg::GENERAL_COUNT; ++v) {
+    for (int v = fg::GENERAL_128x128; v <= fg::GENERAL_64x64; ++v) {
         if (ft == fg::TILE_128x128 && v != fg::GENERAL_128x128) continue;
         if (ft == fg::TILE_64x64 && v != fg::GENERAL_64x64) continue;
         const int64_t tiles = ((M + edge[v] - 1) / edge[v]) * ((N + edge[v] - 1) / edge[v]) * batches;
         const double tile_bytes = 4.0 * edge[v] * edge[v];
         for (int S : split_options) {
             if (fs >= 1) { if (S != 1) break; S = fs; }
-            if (S > 1 && (!may_split || S > nk || (fs < 1 && nk / S < 4) || (double)tiles * S * tile_bytes > kStaticScratchBytes)) {
+            if (S > 1 && (!matrix || S > nk || (fs < 1 && nk / S < 4) || (double)tiles * S * tile_bytes > kStaticScratchBytes)) {
                 if (fs < 1) break;
                 S = 1;
             }

@@ -17,7 +17,7 @@
 // 64x64 tile; 449 us with the element-wise FP32 kernel that served these operands before.
 // 4095x4097x4099: 244 us, 563 TFLOP/s.
 #pragma once
-#include "gemm_kernel.hpp"
+#include "kernel_table.hpp"
 #include "piece_address.hpp"
 
 namespace fg {
@@ -275,23 +275,26 @@ struct PieceLoader {
 // KG groups of WGM x WGN waves share a BM x BN tile: group g multiplies the K steps kt0 + g, kt0 + g +
 // KG, ... into accumulators of its own, from LDS buffers of its own, and the groups' results are
 // added up through LDS at the end, each group finishing 1/KG of the registers.
+// ONE (the 64x64 tile with one group): products of one K step, which need no second buffer and no prefetch.
 // RANGES (matrices): a workgroup computes the K ranges of its tile one after another and adds them up as
 // the reduction pass would.  It needs no scratch memory and gives the bits of the split product.
 template <int BM, int BN, int WGM, int WGN, int KG, bool A_KC, bool B_KC, bool BF16, bool PLAIN, bool RANGES = false>
 __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const GeneralParams p) {
     constexpr int NW = WGM * WGN, NT = 64 * NW, WTM = BM / WGM, WTN = BN / WGN, TI = WTM / 32, TJ = WTN / 32;
-    constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128, GROUP_BYTES = 2 * (A_BYTES + B_BYTES);
+    constexpr bool ONE = KG == 1 && BM == 64;
+    constexpr int BUFFERS = ONE ? 1 : 2;
+    constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128, GROUP_BYTES = BUFFERS * (A_BYTES + B_BYTES);
     constexpr int RR = 16 / KG;                         // registers of each 32x32 block that a group finishes
-    static_assert(PLAIN || !RANGES, "contractions are not split");
+    static_assert((PLAIN && !ONE) || !RANGES, "contractions and products of one K step are not split");
     static_assert(KG == 1 || KG * NW * TI * TJ * 16 * 64 * 4 <= KG * GROUP_BYTES, "the exchange of the groups' results fits the K loop's buffers");
     __shared__ __attribute__((aligned(1024))) char smem_generic[KG * GROUP_BYTES];
-    __shared__ KTable ktab[PLAIN ? 1 : KG][PLAIN ? 1 : 4];
+    __shared__ KTable ktab[PLAIN ? 1 : KG][PLAIN || ONE ? 1 : 4];
     const int lane = threadIdx.x & 63;
     const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int group = wave_all / NW, wave = wave_all - group * NW, tid = wave * 64 + lane;
     const int wm = wave % WGM, wn = wave / WGM;
     FG_LDS char *smem = (FG_LDS char *)smem_generic;
-    FG_LDS char *lds_a = smem + group * GROUP_BYTES, *lds_b = lds_a + 2 * A_BYTES;
+    FG_LDS char *lds_a = smem + group * GROUP_BYTES, *lds_b = lds_a + BUFFERS * A_BYTES;
 
     // work item -> (K range or batch index, tile)
     const int tiles = p.tiles_m * p.tiles_n;
@@ -397,9 +400,32 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
     };
     clear();
 
+    auto products = [&](int buffer) {                   // of the K step in an LDS buffer
+        FG_LDS const char *ta = lds_a + buffer * A_BYTES, *tb = lds_b + buffer * B_BYTES;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            half8 af[TI], bf[TJ];
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) bf[j] = fb.read(tb, j, ks);
+#pragma unroll
+            for (int m = 0; m < TI; ++m) af[m] = fa.read(ta, m, ks);
+#pragma unroll
+            for (int m = 0; m < TI; ++m)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) acc[m][j] = mfma<BF16>(bf[j], af[m], acc[m][j]);
+        }
+    };
+
     // The K loop.  EDGE: mode of the steps that may reach past the operands.  Every group runs the
     // same number of steps (barriers); a group's last one may be empty.
     auto k_loop = [&](auto edge_tag) {
+        if constexpr (ONE) {
+            fetch(edge_tag, 0, 0);
+            commit(edge_tag, 0, 0);
+            publish();
+            products(0);
+            return;
+        }
         constexpr std::integral_constant<int, FETCH_INSIDE> INSIDE{};
         const int steps = (kt1 - kt0 + KG - 1) / KG;
         if (kt(0) < kt1) fetch(edge_tag, 0, 0);
@@ -413,21 +439,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
             // the buffer of step i+1 was last read in step i-1, before the barrier that ended it
             if (STEADY || kt(i + 1) < kt1) commit(mode_tag, i + 1, nxt);
             if (STEADY || kt(i + 3) < kt1) fetch(mode_tag, i + 3, nxt);
-            if (STEADY || kt(i) < kt1) {
-                FG_LDS const char *ta = lds_a + cur * A_BYTES, *tb = lds_b + cur * B_BYTES;
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    half8 af[TI], bf[TJ];
-#pragma unroll
-                    for (int j = 0; j < TJ; ++j) bf[j] = fb.read(tb, j, ks);
-#pragma unroll
-                    for (int m = 0; m < TI; ++m) af[m] = fa.read(ta, m, ks);
-#pragma unroll
-                    for (int m = 0; m < TI; ++m)
-#pragma unroll
-                        for (int j = 0; j < TJ; ++j) acc[m][j] = mfma<BF16>(bf[j], af[m], acc[m][j]);
-                }
-            }
+            if (STEADY || kt(i) < kt1) products(cur);
             // offsets of step i+4: their slot was last read for step i
             if constexpr (!PLAIN) { if (wave == i % NW) fill_table(i + 4); }
             publish();
@@ -453,7 +465,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
     for (;;) {                                          // once, RANGES: once per K range
         if (kt0 < kt1) {
             if constexpr (!PLAIN) {
-                for (int i = wave; i < 4; i += NW) fill_table(i);
+                for (int i = wave; i < (ONE ? 1 : 4); i += NW) fill_table(i);
                 publish();
             }
             const bool pieces = (PLAIN || (p.a_es == 1 && p.b_es == 1)) && a_span >= 8 && b_span >= 8;
@@ -624,11 +636,12 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
 
 // One workgroup per work item, in rows of at most 2^22 (a grid dimension holds 2^32 threads).
 // ranges: fn computes all K ranges of a tile.
-inline hipError_t launch_general(void (*fn)(const GeneralParams), GeneralParams p, hipStream_t stream, bool ranges = false) {
+inline hipError_t launch_general(void (*fn)(const GeneralParams), int variant, GeneralParams p, hipStream_t stream, bool ranges = false) {
+    if (variant == GENERAL_64x64_ONE && p.K > 64) return hipErrorInvalidValue;
     const int64_t items = (int64_t)p.tiles_m * p.tiles_n * (ranges ? 1 : p.splits) * p.batches;
     const unsigned per_row = (unsigned)(items < (1 << 22) ? items : (1 << 22));
     p.items = (int32_t)items;
-    hipLaunchKernelGGL(fn, dim3(per_row, (unsigned)((items + per_row - 1) / per_row)), dim3(512), 0, stream, p);
+    hipLaunchKernelGGL(fn, dim3(per_row, (unsigned)((items + per_row - 1) / per_row)), dim3(variant == GENERAL_64x64_ONE ? 256 : 512), 0, stream, p);
     return hipGetLastError();
 }
 

@@ -72,10 +72,10 @@ hipError_t launch_splitk_reduce(const float *W, int splits, int tile_begin, int 
                                 int64_t ldd, const float *bias, int bias_dim, int act, int c_act, hipStream_t stream);
 
 // General kernel (general_kernel.hpp): matrices with unaligned operands or a K that is not a multiple
-// of 8 (gemm_general.hip), contractions the tiled kernels cannot take (contract_general.hip).  Two
-// shapes of 512 threads: 128x128 tiles with eight 32x64 waves, and 64x64 tiles whose two groups of
-// four waves take alternate K steps.
-enum GeneralVariant { GENERAL_128x128 = 0, GENERAL_64x64 = 1, GENERAL_COUNT = 2 };
+// of 8 (gemm_general.hip), contractions the tiled kernels cannot take (contract_general.hip).  128x128
+// tiles with eight 32x64 waves; 64x64 tiles whose two groups of four waves take alternate K steps; 64x64 tiles with one
+// group, for products of one K step.
+enum GeneralVariant { GENERAL_128x128 = 0, GENERAL_64x64 = 1, GENERAL_64x64_ONE = 2, GENERAL_COUNT = 3 };
 struct GeneralParams;
 // ranges: one launch whose workgroups compute the p.splits K ranges of their tiles in turn, into D.
 hipError_t launch_gemm_general(const GeneralParams &p, bool a_kc, bool b_kc, bool bf16, int variant, bool ranges, hipStream_t stream);

@@ -146,6 +146,22 @@ def test_split_without_scratch_memory_gives_the_same_bits(monkeypatch, tile, spl
                 assert torch.equal(D, want), "replay %d" % rep
 
 
+def test_one_k_step():
+    """K up to 64, the planner's own choice: matrices of more than two 64x64 tiles per unit run them with one
+    group of waves, fewer tiles with two, many with the 128x128 tile; contractions always with one group."""
+    for K in (1, 7, 33, 63, 64):
+        for (M, N) in ((1700, 1290), (3, 33001), (130, 70)):
+            say("%dx%dx%d" % (M, N, K))
+            run_unaligned_gemm_case(M, N, K, fg.FG_ROW if K % 2 else fg.FG_COL, fg.FG_COL, pads=(1, 1, 1), bias_dim=1, act=fg.FG_ACT_RELU)
+    run_unaligned_gemm_case(1700, 1290, 30, fg.FG_COL, fg.FG_ROW, bf16=True)
+    run_unaligned_gemm_case(1700, 1290, 30, fg.FG_ROW, fg.FG_ROW, fg.FG_ROW, ints=False, ab_add=(0.5, -0.25), c_act=fg.FG_ACT_RELU)
+    run_unaligned_gemm_case(5001, 4999, 3, fg.FG_COL, fg.FG_COL, pads=(0, 0, 0))
+    for ext in ({a: 4, b: 4, d: 4, g: 1500}, {a: 9, b: 5, d: 64, g: 700}, {a: 66, b: 130, d: 33, g: 70}):
+        for modes in (([a, d, g], [d, b, g], [a, b, g]), ([g, a, d], [g, d, b], [g, a, b]), ([d, a, g], [d, b, g], [b, a, g])):
+            say("batches %s %s" % (ext, modes)); run_contract_case(ext, *modes, ints=True, beta=1.0)
+    say("outer product"); run_contract_case({a: 1023, b: 1025}, [a], [b], [a, b], ints=True)
+
+
 @pytest.mark.parametrize("tile", ["2", "3"])
 def test_contraction_forms(monkeypatch, tile):
     """Which direction the pieces run along (rows, summed modes, element by element), leading modes
