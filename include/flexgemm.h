@@ -259,8 +259,9 @@ fg_status fg_contract(int32_t nA, const int32_t *modesA, const int64_t *stridesA
  * data pointers are only inspected for alignment), as a NUL-terminated string in `buf`:
  * "gett_<layouts>_<tile>" or "gett_stream_..." for the tiled kernels (the latter when whole
  * lines of the result stream past the L2; a tile name ending in "_deep" is the 128x128 tile with a
- * ring of four buffers, for results of at most one such tile per compute unit), or "gett_general_64x64x32 (<reason>)" with the first
- * requirement of the tiled kernels that the description misses.  Returns what fg_contract would
+ * ring of four buffers, for results of at most one such tile per compute unit), or "gett_general_64x64x32 (<reason>; <tile> tiles)" with the first
+ * requirement of the tiled kernels that the description misses and the general kernel's block tile (64x64 or
+ * 128x128; its K step is 64, the name is kept for callers that compare it).  Returns what fg_contract would
  * return for the description.
  */
 fg_status fg_contract_plan(int32_t nA, const int32_t *modesA, const int64_t *stridesA, const void *A,
@@ -305,6 +306,9 @@ fg_status fg_init(void);
  * outputs with a 256x256 tile for at least three quarters of the compute units; the others use 32x32x16 instructions.  Both
  * accumulate the same FP16 products in FP32, in a different order: results agree within the stated
  * tolerance and are bit-identical on integer-valued data.
+ * A name with "_64x64x64" stands for the 64x64 tile whichever number of wave groups (one, two or
+ * four) shares its K.  "gemm_general_64x64x32" and "gemm_general_128x128x64" are the general kernel (K % 8 != 0; both take
+ * K steps of 64); a product that only misses an alignment, which this query does not know, runs there too.
  * This is the "params" choice of Section 4.2.1, made here by an estimate
  * of the run time of every tile shape and split.  `variant` (fg_plan_variant) names the operator: real FP16, planar complex, dual, real BF16,
  * interleaved complex, real FP16 with C and D stored as binary16, or real FP16 with a constant added to the

@@ -1208,7 +1208,11 @@ fg_status fg_gemm_plan(int64_t M, int64_t N, int64_t K, int32_t layoutA, int32_t
     if (g_relaxed.status != FG_OK) {
         // K is not a multiple of 8 (alignment is not known to this query)
         if (q.cplx || q.a_diag || q.b_diag || q.cd16) return fail(g_relaxed.status, "%s (complex, dual, diagonal and FG_F16-result products have no general kernel)", g_relaxed.msg);
-        snprintf(buf, (size_t)buf_len, "gemm_general_64x64x32");     // a fixed name: callers compare it, the tile is choose_general's
+        const GeneralPlan plan = choose_general(q.M, q.N, q.K, 1, true);
+        char split[24] = "";
+        if (plan.splits > 1) snprintf(split, sizeof split, "+splitk%d", plan.splits);
+        // the 64x64 tile keeps the name that callers compare (its K step is 64 now)
+        snprintf(buf, (size_t)buf_len, "gemm_general_%s%s", plan.bm == 128 ? "128x128x64" : "64x64x32", split);
         return FG_OK;
     }
     Plan plan{0, 1, 1};
@@ -1313,7 +1317,11 @@ fg_status fg_contract_plan(int32_t nA, const int32_t *modesA, const int64_t *str
                                         Cin, Cout, n_modes, mode_labels, mode_extents, c))
         return st;
     if (c.M == 0 || c.N == 0) { snprintf(buf, (size_t)buf_len, "nothing to compute"); return FG_OK; }
-    if (c.general) { snprintf(buf, (size_t)buf_len, "gett_general_64x64x32 (%s)", c.why_general); return FG_OK; }
+    if (c.general) {
+        const GeneralPlan plan = choose_general(c.M, c.N, c.K, c.batches, false);
+        snprintf(buf, (size_t)buf_len, "gett_general_64x64x32 (%s; %dx%d tiles)", c.why_general, plan.bm, plan.bn);
+        return FG_OK;
+    }
     int perm_z = 1;
     const fg::KernelEntry *k = select_contract_kernel(c, Cin, Cout, &perm_z);
     if (!k) return fail(FG_ERR_UNSUPPORTED, "internal: no contraction kernel for this tile");

@@ -254,6 +254,18 @@ def test_contraction_descriptions_the_tiled_kernels_cannot_take_go_to_the_genera
     assert general([a, d], [1, 1 << 15], [d, b], [1, 1 << 15], [a, b], [1, 1 << 15], big)
 
 
+def test_plans_of_the_general_kernel_name_the_tile_and_the_split():
+    """A general product that splits K says so, like any other product; the block tile is named."""
+    for (M, N, K) in ((301, 301, 6001), (65, 65, 16385), (17, 1025, 4099)):
+        assert re.match(r"^gemm_general_64x64x32\+splitk\d+$", fg.fg_gemm_plan(M, N, K)), (M, N, K)
+    assert fg.fg_gemm_plan(4095, 4097, 4099) == "gemm_general_128x128x64"
+    assert fg.fg_gemm_plan(1531, 1021, 2003) == "gemm_general_64x64x32"
+    a, b, d = 0, 1, 2
+    for n, tile in ((65, "64x64"), (4001, "128x128")):
+        plan = contract_plan([a, d], [1, n], [d, b], [1, 301], [a, b], [1, n], {a: n, b: n, d: 301})
+        assert plan.startswith("gett_general_64x64x32 (") and plan.endswith("; %s tiles)" % tile), plan
+
+
 def test_contract_argument_errors():
     a, b, c, d = 0, 1, 2, 3
     ext = {a: 64, b: 64, c: 64, d: 64}
