@@ -202,9 +202,10 @@ def run_unaligned_gemm_case(M, N, K, la=fg.FG_COL, lb=fg.FG_COL, ld_layout=fg.FG
 
 def run_contract_case(extents, modesA, modesB, modesC, alpha=1.0, beta=0.0, ints=False, samples: Optional[int] = None,
                       stridesA=None, stridesB=None, stridesC=None, inplace=False, config=5, device="cuda",
-                      seed=W.DEFAULT_SEED, B_override=None, poison=False):
+                      seed=W.DEFAULT_SEED, B_override=None, poison=False, offsets=(0, 0, 0)):
     """Run fg_contract on seeded dense (or explicitly strided) tensors and compare with the oracle.
-    ``poison``: every position of A, B and Cin that the strided tensors do not reach holds NaN."""
+    ``poison``: every position of A, B and Cin that the strided tensors do not reach holds NaN.
+    ``offsets``: how many elements into their allocations A, B and C begin; NaN before and behind A and B."""
     ext = lambda ms: [extents[m] for m in ms]
     sA = list(stridesA) if stridesA else list(W.col_major_strides(tuple(ext(modesA))))
     sB = list(stridesB) if stridesB else list(W.col_major_strides(tuple(ext(modesB))))
@@ -215,8 +216,16 @@ def run_contract_case(extents, modesA, modesB, modesC, alpha=1.0, beta=0.0, ints
     B = gen(span(modesB, sB), W.stream_id(config, "B"), seed=seed, device=device, dtype=torch.float16)
     if B_override is not None:
         B = B_override.to(device)
+    def placed(t, n):
+        whole = torch.full((n + t.numel() + 8,), float("nan"), dtype=t.dtype, device=t.device)
+        whole[n:n + t.numel()] = t
+        return whole[n:n + t.numel()]
+    if offsets[0] or offsets[1]:
+        A, B = placed(A, offsets[0]), placed(B, offsets[1])
     nC = span(modesC, sC)
     Cin = gen(nC, W.stream_id(config, "C"), seed=seed, device=device, dtype=torch.float32) if beta != 0.0 else None
+    if Cin is not None and offsets[2]:
+        Cin = placed(Cin, offsets[2])
     if poison:
         def reached_mask(modes, strides, n):
             idx = torch.zeros(1, dtype=torch.int64)
@@ -229,7 +238,7 @@ def run_contract_case(extents, modesA, modesB, modesC, alpha=1.0, beta=0.0, ints
         B[~reached_mask(modesB, sB, B.numel())] = float("nan")
         if Cin is not None:
             Cin[~reached_mask(modesC, sC, nC)] = float("nan")
-    Cout = Cin if (inplace and Cin is not None) else torch.full((nC,), float("nan"), dtype=torch.float32, device=device)
+    Cout = Cin if (inplace and Cin is not None) else torch.full((nC + offsets[2],), float("nan"), dtype=torch.float32, device=device)[offsets[2]:]
     Cin_host = np16(Cin).copy() if Cin is not None else None
     fg.fg_contract(modesA, sA, A, modesB, sB, B, modesC, sC, Cin, Cout, extents, alpha=alpha, beta=beta)
     torch.cuda.synchronize()

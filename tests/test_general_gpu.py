@@ -2,6 +2,7 @@
 pieces of eight, its K steps of 64, its two block tiles and its K split can go wrong.  Integer data
 unless stated: every entry must equal the exact result."""
 import itertools
+import math
 
 import pytest
 import torch
@@ -189,6 +190,107 @@ def test_contraction_forms(monkeypatch, tile):
         run_contract_case(ext, [a, d, c], [d, b], [a, b, c], ints=True, beta=1.0, stridesA=sA, stridesB=sB, stridesC=[1, 23, 23 * 67 + 1], poison=True)
     say("floats"); run_contract_case({a: 37, b: 9, c: 11, d: 15, e: 27, f: 25}, [a, e, b, f], [d, f, c, e], [a, b, c, d], alpha=0.5, beta=1.5)
     delenv(monkeypatch, "FG_FORCE_TILE")
+
+
+@pytest.mark.parametrize("tile", ["2", "3"])
+def test_contraction_bases_inside_words_and_chunks(monkeypatch, tile):
+    """Bases 1 to 7 elements into 16-byte chunks, so that pieces start inside 4-byte words for every
+    combination of the operands; leading extents that are and are not multiples of eight, whose last piece ends
+    with the operand; NaN right before and behind A and B."""
+    setenv(monkeypatch, "FG_FORCE_TILE", tile)
+    for offsets in ((1, 0, 0), (0, 1, 0), (1, 1, 1), (2, 1, 0), (3, 2, 1), (7, 5, 3)):
+        for ext in ({a: 13, b: 5, c: 7, d: 11, e: 9, f: 6}, {a: 16, b: 5, c: 7, d: 24, e: 10, f: 8}):
+            say("offsets %s rows x columns %s" % (offsets, ext)); run_contract_case(ext, [a, e, b, f], [d, f, c, e], [a, b, c, d], ints=True, beta=1.0, offsets=offsets)
+        say("offsets %s dense 16 x 128 beside odd strides" % (offsets,)); run_contract_case({a: 16, b: 65, d: 128}, [a, d], [b, d], [a, b], ints=True, offsets=offsets)
+        run_contract_case({a: 16, b: 33, c: 3, d: 128}, [a, d], [b, c, d], [a, b, c], ints=True, offsets=offsets)
+        say("offsets %s along the summed mode" % (offsets,)); run_contract_case({a: 33, b: 21, d: 13, e: 6}, [d, a, e], [b, e, d], [a, b], ints=True, beta=-1.0, offsets=offsets)
+        run_contract_case({a: 33, b: 21, d: 72, g: 3}, [d, a, g], [d, b, g], [b, a, g], ints=True, offsets=offsets)
+
+
+@pytest.mark.parametrize("tile", ["2", "3"])
+def test_contraction_spans_of_2_31_elements(monkeypatch, tile):
+    """Offsets that do not fit 32 bits, between rows, between summed indices and between batches: what the
+    strides do not reach is NaN."""
+    setenv(monkeypatch, "FG_FORCE_TILE", tile)
+    far = (1 << 31) + 6
+    for name, ext, mA, sA, mB, sB, mC in (
+            ("rows", {a: 21, c: 2, d: 70, b: 67}, [a, d, c], [1, 23, far + 1], [d, b], [1, 71], [a, b, c]),
+            ("summed indices, A along rows", {a: 21, d: 70, e: 2, b: 67}, [a, d, e], [1, 23, far], [b, d, e], [1, 69, 69 * 70], [a, b]),
+            ("summed indices, A along them", {a: 21, d: 37, e: 2, b: 67}, [d, a, e], [1, 39, far + 1], [d, b, e], [1, 39, 39 * 67], [a, b]),
+            ("batches", {a: 21, d: 70, g: 2, b: 67}, [a, d, g], [1, 21, far], [b, d, g], [1, 67, 67 * 70], [a, b, g])):
+        say(name)
+        shape = lambda ms: [ext[m] for m in ms]
+        span = lambda ms, st: 1 + sum((ext[m] - 1) * s for m, s in zip(ms, st))
+        A = torch.full((span(mA, sA),), float("nan"), dtype=torch.float16, device="cuda")
+        B = torch.full((span(mB, sB),), float("nan"), dtype=torch.float16, device="cuda")
+        va, vb = A.as_strided(shape(mA), sA), B.as_strided(shape(mB), sB)
+        va.copy_(W.small_ints(va.numel(), 1, device="cuda").view(shape(mA)))
+        vb.copy_(W.small_ints(vb.numel(), 2, device="cuda").view(shape(mB)))
+        sC = list(W.col_major_strides(tuple(shape(mC))))
+        D = torch.full((span(mC, sC),), float("nan"), dtype=torch.float32, device="cuda")
+        fg.fg_contract(mA, sA, A, mB, sB, B, mC, sC, None, D, ext)
+        torch.cuda.synchronize()
+        sums = [m for m in mA if m in mB and m not in mC]
+        rows, cols, batch = [m for m in mC if m not in mB], [m for m in mC if m not in mA], [m for m in mC if m in mA and m in mB]
+        n = lambda ms: math.prod(shape(ms))
+        x = va.cpu().double().permute([mA.index(m) for m in batch + rows + sums]).reshape(n(batch), n(rows), n(sums))
+        y = vb.cpu().double().permute([mB.index(m) for m in batch + sums + cols]).reshape(n(batch), n(sums), n(cols))
+        order = batch + rows + cols
+        want = torch.stack([x[i] @ y[i] for i in range(n(batch))]).reshape(shape(order)).permute([order.index(m) for m in mC])
+        got = D.as_strided(shape(mC), sC).cpu().double()
+        del A, B, va, vb
+        torch.cuda.empty_cache()
+        assert torch.equal(got, want), name
+
+
+@pytest.mark.parametrize("tile", ["2", "3"])
+def test_contraction_infinities_and_nan(monkeypatch, tile):
+    """NaN and infinities inside A, B and Cin reach exactly the results they belong to, in every direction
+    that pieces run along, with K tails and rounded leading modes."""
+    setenv(monkeypatch, "FG_FORCE_TILE", tile)
+    inf, nan = float("inf"), float("nan")
+    for K in (13, 70, 133):
+        M, N = 21, 67
+        for mA, mB in (([a, d], [b, d]), ([d, a], [d, b]), ([d, a], [b, d]), ([a, d], [d, b])):
+            say("K=%d A%s B%s" % (K, mA, mB))
+            x, y, z = (W.small_ints(n, i, device="cpu").double() for i, n in ((1, M * K), (2, K * N), (3, M * N)))
+            x, y, z = x.view(M, K), y.view(K, N) + 9, z.view(M, N)          # B has no zeros
+            x[3, 5], x[8, K - 1], x[M - 1, 0], y[2, 6], y[K - 1, N - 1], z[0, 1] = inf, nan, -inf, inf, nan, nan
+            want = x @ y + 2 * z
+            ext = {a: M, b: N, d: K}
+            stored = lambda t, lab, modes: (t if modes[0] != lab else t.T).contiguous().reshape(-1)      # first mode fastest
+            A = stored(x, a, mA).to(torch.float16).cuda(); B = stored(y, d, mB).to(torch.float16).cuda()
+            Cin = z.T.contiguous().reshape(-1).float().cuda()
+            D = torch.zeros(M * N, dtype=torch.float32, device="cuda")
+            st = lambda ms: [1, ext[ms[0]]]
+            fg.fg_contract(mA, st(mA), A, mB, st(mB), B, [a, b], [1, M], Cin, D, ext, beta=2.0)
+            torch.cuda.synchronize()
+            got = D.view(N, M).T.cpu().double()
+            assert torch.equal(torch.isnan(got), torch.isnan(want))
+            assert torch.equal(torch.nan_to_num(got, nan=7.0), torch.nan_to_num(want, nan=7.0))
+
+
+def float_result(M, N, K, la, lb, **kw):
+    A = W.uniform_pm1(M * K, 1, device="cuda"); B = W.uniform_pm1(K * N, 2, device="cuda")
+    D = torch.full((M * N,), float("nan"), dtype=torch.float32, device="cuda")
+    fg.fg_gemm(M, N, K, 1.0, fg.Matrix(A, la, M if la == fg.FG_COL else K), fg.Matrix(B, lb, K if lb == fg.FG_COL else N), 0.0, None, fg.Matrix(D, fg.FG_COL, M), **kw)
+    torch.cuda.synchronize()
+    return D
+
+
+def test_k_group_kernels_run(monkeypatch):
+    """One, two and four K groups add the same products up in different orders: on floats the three tiles
+    differ in the last bits (plan names do not tell them apart), so a tile that silently ran as
+    another one is seen; the planner's choice at 1024^3 is the one with four."""
+    for la, lb in itertools.product(LAYOUTS, LAYOUTS):
+        got = {}
+        for tile in ("3", "6", "7"):
+            setenv(monkeypatch, "FG_FORCE_TILE", tile)
+            got[tile] = float_result(1024, 1024, 1024, la, lb)
+        delenv(monkeypatch, "FG_FORCE_TILE")
+        say("A=%d B=%d" % (la, lb))
+        assert not torch.equal(got["3"], got["6"]) and not torch.equal(got["3"], got["7"]) and not torch.equal(got["6"], got["7"])
+        assert torch.equal(float_result(1024, 1024, 1024, la, lb), got["7"])
 
 
 @pytest.mark.parametrize("tile,groups", [("6", 2), ("7", 4)])
