@@ -130,7 +130,8 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 // others' and the cost of a split, to the times of every tile and split forced over 70 products from
 // 17 x 1321 x 1312 to 227 x 8112 x 4992: the choice is on average 1 % slower than the fastest of
 // them (5 % before the fit), at most 13 %.  A split's second launch is priced with its host time, which
-// a stream of small products pays.
+// a stream of small products pays and a replayed graph does not (12x7894x3184, left whole: 17.6 us per call,
+// 18.2 replayed; split in four, as before the fit: 19.4 and 16.3).
 constexpr int kTileM[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64};
 constexpr int kTileN[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64};
 constexpr int kTilesPerCU[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1};
@@ -247,10 +248,10 @@ int64_t scratch_need(const Plan &plan, int64_t M, int64_t N) {
     return 0;
 }
 
-// What a call needs scratch memory for is part of what it promises: a call that needed none can be
+// Which scratch memory a call needs is part of what it promises: a call that needed none can be
 // captured before the workspace exists, one whose partial products fit the static array can be made
-// without allocation.  A plan that needs more than the plan by the promised rates is
-// therefore replaced by the best one that does not (0.5 % of random shapes).
+// without allocation.  A plan that leaves the class (none, static array, workspace) of the plan by the promised
+// rates is therefore replaced by the best one that does not (0.5 % of random shapes).  Costs a split call 1.5 us on the host.
 Plan within_promised_scratch(Plan plan, int64_t M, int64_t N, int64_t K, int k32) {
     const int64_t need = scratch_need(plan, M, N);
     if (need == 0 || g_force_split.load(std::memory_order_relaxed) >= 1 || g_force_tail.load(std::memory_order_relaxed) > 1 ||
@@ -993,7 +994,9 @@ fg_status plan_contraction(int32_t nA, const int32_t *modesA, const int64_t *str
         // A is then read in separate pieces, which pays while K is not long against N: D_abc = A_bda B_dc
         // with (a, b, c, d) = (111, 99, 301, 65) 30.0 -> 23.2 us (49.1 -> 26.4 with Cin, which doubles the
         // scattered accesses), (63, 31, 511, 373) 16.2 -> 16.2 (20.3 -> 17.4), (211, 55, 65, 201) 15.6 -> 17.9
-        // (23.5 -> 19.4), (99, 201, 33, 501) 17.8 -> 28.2 (21.0 -> 29.2).
+        // (23.5 -> 19.4), (99, 201, 33, 501) 17.8 -> 28.2 (21.0 -> 29.2).  Drawn from these four: elsewhere the line may
+        // lie differently.  (A Cin that beta == 0 leaves unread counts as one; at (99, 201, 100, 301) that is the better
+        // side, 20.6 against 23.6 us.)
         c.m_hi = 0;
         if (have_a && c.K <= (Cin ? 4 * c.N : c.N * 3 / 2) && !c.a_kc && c_unit >= 0 && c_unit != la && is_row(c_unit) && extent(c_unit) >= 4 && c.a_m.n >= 2 && c.a_m.n < fg::kMaxGroupModes && c.a_m.extent[0] > 8) {
             const int hi = c.a_m.n;

@@ -12,9 +12,10 @@
 //
 // What bounds it: the vector-memory path of a compute unit.  A 16-byte load per lane that starts at
 // an odd element costs 52 cache accesses per wave, one at an even element 22, an aligned one 15
-// (TCP_TOTAL_CACHE_ACCESSES over 1531x1021x2003, 1530x1018x2003, 1536x1024x2003: 29.9, 27.0 and 23.9 us;
-// the direct-to-LDS kernels take 20 to 22 us for 1536x1024x2048).  1531x1021x2003: 28 us with the
-// 64x64 tile; 449 us with the element-wise FP32 kernel that served these operands before.
+// (TCP_TOTAL_CACHE_ACCESSES per vector load at 1531x1021x2003, where both operands start odd: 51.8; at 1530x1018x2003
+// and 1536x1024x2003, whose A starts even or aligned and whose B is odd: 36.9 and 33.2; 27.9, 26.2 and 23.7 us;
+// the direct-to-LDS kernels take 20 to 22 us for 1536x1024x2048).  1531x1021x2003: 449 us with the element-wise FP32
+// kernel that served these operands before.
 // 4095x4097x4099: 244 us, 563 TFLOP/s.
 #pragma once
 #include "kernel_table.hpp"
