@@ -448,6 +448,7 @@ struct Scratch {
             (void)hipGetLastError();
         }
         guard = nullptr;
+        lock.unlock();
         return false;
     }
     fg_status release(hipStream_t stream) {

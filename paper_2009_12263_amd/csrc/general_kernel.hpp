@@ -105,7 +105,7 @@ struct KTable {
 // 33 against 28 us at 1531x1021x2003).  GATHER: eight element loads per piece, for operands without
 // a unit stride and for those of fewer than eight elements.
 // INSIDE_ODD: INSIDE for operands with pieces that start in the middle of a 4-byte word: the five words
-// that hold the piece are loaded (a word-aligned 16-byte load and a 4-byte one, which the cache serves several
+// that hold the piece are loaded (a word-aligned 16-byte load and a 4-byte one, see odd_piece, which the cache serves several
 // lanes of at a time; a 16-byte load in the middle of words goes lane by lane) and shifted by 16 bits
 // when committed.  Contractions on 64x64 tiles whose rows or columns come in runs shorter than the tile
 // (37x29x31x35 over 27x25: 21.3 -> 19.0 us, D_abc = A_bda B_dc with 63, 31, 511, 373: 14.1 -> 13.0);
@@ -139,7 +139,7 @@ struct PieceLoader {
     u32x4 stage[2][CH];             // the pieces of two K steps in flight
     int left[2][KC ? 1 : CH];       // elements of the staged pieces that are below K (MC: 0 or 8)
     int shift[2][CH];               // CLAMP: how many elements before its place a piece was loaded
-    uint32_t fifth[2][CH];          // INSIDE_ODD: the word after the staged four
+    uint32_t fifth[2][CH];          // INSIDE_ODD: the word after the staged four, if the piece reaches into it
     int skew[2][CH];                // INSIDE_ODD: bytes to drop in front (0 or 2)
 
     __device__ __forceinline__ void init(const ModeGroup &rg, int ext0, int hi, int64_t rs, int row0, int rdim, int tid) {
@@ -309,13 +309,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
     if constexpr (PLAIN) split = outer;
     else { split = outer / p.batches; batch = outer - split * p.batches; }
     const int nk_all = (p.K + 63) / 64;
-    int kt0, kt1;
-    auto k_range = [&](int s) {
-        kt0 = p.splits > 1 ? s * p.split_kt : 0;
-        kt1 = p.splits > 1 ? kt0 + p.split_kt : nk_all;
-        if (kt1 > nk_all) kt1 = nk_all;
-    };
-    k_range(split);
+    typename std::conditional<RANGES, int, const int>::type kt0 = p.splits > 1 ? split * p.split_kt : 0;
+    int kt1 = p.splits > 1 ? kt0 + p.split_kt : nk_all;
+    if (kt1 > nk_all) kt1 = nk_all;
 
     const uint16_t *A = p.A, *B = p.B;
     int64_t a_span = p.a_span, b_span = p.b_span;
@@ -391,60 +387,55 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
     };
 
     floatx16 acc[TI][TJ];
-    auto clear = [&] {
 #pragma unroll
-        for (int i = 0; i < TI; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-            for (int j = 0; j < TJ; ++j)
+        for (int j = 0; j < TJ; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    };
-    clear();
-
-    auto products = [&](int buffer) {                   // of the K step in an LDS buffer
-        FG_LDS const char *ta = lds_a + buffer * A_BYTES, *tb = lds_b + buffer * B_BYTES;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            half8 af[TI], bf[TJ];
-#pragma unroll
-            for (int j = 0; j < TJ; ++j) bf[j] = fb.read(tb, j, ks);
-#pragma unroll
-            for (int m = 0; m < TI; ++m) af[m] = fa.read(ta, m, ks);
-#pragma unroll
-            for (int m = 0; m < TI; ++m)
-#pragma unroll
-                for (int j = 0; j < TJ; ++j) acc[m][j] = mfma<BF16>(bf[j], af[m], acc[m][j]);
-        }
-    };
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
     // The K loop.  EDGE: mode of the steps that may reach past the operands.  Every group runs the
     // same number of steps (barriers); a group's last one may be empty.
     auto k_loop = [&](auto edge_tag) {
-        if constexpr (ONE) {
-            fetch(edge_tag, 0, 0);
-            commit(edge_tag, 0, 0);
-            publish();
-            products(0);
-            return;
-        }
         constexpr std::integral_constant<int, FETCH_INSIDE> INSIDE{};
         const int steps = (kt1 - kt0 + KG - 1) / KG;
         if (kt(0) < kt1) fetch(edge_tag, 0, 0);
-        if (kt(1) < kt1) fetch(edge_tag, 1, 1);
+        if constexpr (!ONE) { if (kt(1) < kt1) fetch(edge_tag, 1, 1); }
         if (kt(0) < kt1) commit(edge_tag, 0, 0);
-        if (kt(2) < kt1) fetch(edge_tag, 2, 0);
+        if constexpr (!ONE) { if (kt(2) < kt1) fetch(edge_tag, 2, 0); }
         publish();
         auto step = [&](auto mode_tag, int i, auto cur_tag) {      // step i, from LDS buffer `cur`
             constexpr int cur = decltype(cur_tag)::value, nxt = cur ^ 1;
             constexpr bool STEADY = PLAIN && is_inside(decltype(mode_tag)::value);
             // the buffer of step i+1 was last read in step i-1, before the barrier that ended it
-            if (STEADY || kt(i + 1) < kt1) commit(mode_tag, i + 1, nxt);
-            if (STEADY || kt(i + 3) < kt1) fetch(mode_tag, i + 3, nxt);
-            if (STEADY || kt(i) < kt1) products(cur);
+            if constexpr (!ONE) {
+                if (STEADY || kt(i + 1) < kt1) commit(mode_tag, i + 1, nxt);
+                if (STEADY || kt(i + 3) < kt1) fetch(mode_tag, i + 3, nxt);
+            }
+            if (STEADY || kt(i) < kt1) {
+                FG_LDS const char *ta = lds_a + cur * A_BYTES, *tb = lds_b + cur * B_BYTES;
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {
+                    half8 af[TI], bf[TJ];
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j) bf[j] = fb.read(tb, j, ks);
+#pragma unroll
+                    for (int m = 0; m < TI; ++m) af[m] = fa.read(ta, m, ks);
+#pragma unroll
+                    for (int m = 0; m < TI; ++m)
+#pragma unroll
+                        for (int j = 0; j < TJ; ++j) acc[m][j] = mfma<BF16>(bf[j], af[m], acc[m][j]);
+                }
+            }
+            if constexpr (ONE) return;
             // offsets of step i+4: their slot was last read for step i
             if constexpr (!PLAIN) { if (wave == i % NW) fill_table(i + 4); }
             publish();
         };
+        if constexpr (ONE) {
+            step(edge_tag, 0, std::integral_constant<int, 0>{});
+            return;
+        }
         int i = 0;
         if constexpr (PLAIN && decltype(edge_tag)::value == FETCH_CLAMP) {
             // while the fetches of both steps lie inside the operands and inside this work item's K
@@ -460,9 +451,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
             if (i + 1 < steps) step(edge_tag, i + 1, std::integral_constant<int, 1>{});
         }
     };
-    // y: the groups' results, register r0 + r of block (i, j) ends up in y[i][j][r] of group r0 / RR
-    const int r0 = group * RR;
-    float y[TI][TJ][RR], total[TI][TJ][RR] = {};
+    float y[TI][TJ][RR];                                // the groups' results (below)
+    [[maybe_unused]] float total[TI][TJ][RR] = {};      // RANGES: their sum over the K ranges
     for (;;) {                                          // once, RANGES: once per K range
         if (kt0 < kt1) {
             if constexpr (!PLAIN) {
@@ -488,31 +478,34 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
                 else k_loop(GATHER);
             }
         }
+
+        // ---- register r0 + r of block (i, j) ends up in y[i][j][r] of group r0 / RR ----
+        const int r0 = group * RR;
         if constexpr (KG == 1) {
-#pragma unroll
+    #pragma unroll
             for (int i = 0; i < TI; ++i)
-#pragma unroll
+    #pragma unroll
                 for (int j = 0; j < TJ; ++j)
-#pragma unroll
+    #pragma unroll
                     for (int r = 0; r < RR; ++r) y[i][j][r] = acc[i][j][r];
         } else {
             FG_LDS float *ex = (FG_LDS float *)smem;
             auto at = [&](int from, int i, int j, int r) { return (((from * NW + wave) * TI * TJ + i * TJ + j) * 16 + r) * 64 + lane; };
-#pragma unroll
+    #pragma unroll
             for (int i = 0; i < TI; ++i)
-#pragma unroll
+    #pragma unroll
                 for (int j = 0; j < TJ; ++j)
-#pragma unroll
+    #pragma unroll
                     for (int r = 0; r < 16; ++r) ex[at(group, i, j, r)] = acc[i][j][r];
             publish();
-#pragma unroll
+    #pragma unroll
             for (int i = 0; i < TI; ++i)
-#pragma unroll
+    #pragma unroll
                 for (int j = 0; j < TJ; ++j)
-#pragma unroll
+    #pragma unroll
                     for (int r = 0; r < RR; ++r) {
                         float v = ex[at(0, i, j, r0 + r)];
-#pragma unroll
+    #pragma unroll
                         for (int g = 1; g < KG; ++g) v += ex[at(g, i, j, r0 + r)];
                         y[i][j][r] = v;
                     }
@@ -527,8 +520,14 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
 #pragma unroll
                     for (int r = 0; r < RR; ++r) total[i][j][r] += y[i][j][r];
             if (++split == p.splits) break;
-            k_range(split);
-            clear();
+            kt0 += p.split_kt;
+            kt1 = kt0 + p.split_kt < nk_all ? kt0 + p.split_kt : nk_all;
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
             publish();                                  // the exchange has been read: the next range may overwrite it
         }
     }
@@ -542,7 +541,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
     }
 
     // ---- lane l, register r of block (i, j) holds row l % 32, column 8 (r/4) + 4 (l/32) + r % 4 ----
-    const int lm = lane & 31, lh = lane >> 5;
+    const int r0 = group * RR, lm = lane & 31, lh = lane >> 5;
     const int mb = m0 + wm * WTM + lm, nb = n0 + wn * WTN + 4 * lh;
     auto col_of = [&](int r) { return 8 * ((r0 + r) >> 2) + ((r0 + r) & 3); };      // RR is a multiple of 4: uniform part + constant
     if (!RANGES && p.splits > 1) {
