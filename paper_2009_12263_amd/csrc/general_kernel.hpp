@@ -482,30 +482,30 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void general_kernel(const Gene
         // ---- register r0 + r of block (i, j) ends up in y[i][j][r] of group r0 / RR ----
         const int r0 = group * RR;
         if constexpr (KG == 1) {
-    #pragma unroll
+#pragma unroll
             for (int i = 0; i < TI; ++i)
-    #pragma unroll
+#pragma unroll
                 for (int j = 0; j < TJ; ++j)
-    #pragma unroll
+#pragma unroll
                     for (int r = 0; r < RR; ++r) y[i][j][r] = acc[i][j][r];
         } else {
             FG_LDS float *ex = (FG_LDS float *)smem;
             auto at = [&](int from, int i, int j, int r) { return (((from * NW + wave) * TI * TJ + i * TJ + j) * 16 + r) * 64 + lane; };
-    #pragma unroll
+#pragma unroll
             for (int i = 0; i < TI; ++i)
-    #pragma unroll
+#pragma unroll
                 for (int j = 0; j < TJ; ++j)
-    #pragma unroll
+#pragma unroll
                     for (int r = 0; r < 16; ++r) ex[at(group, i, j, r)] = acc[i][j][r];
             publish();
-    #pragma unroll
+#pragma unroll
             for (int i = 0; i < TI; ++i)
-    #pragma unroll
+#pragma unroll
                 for (int j = 0; j < TJ; ++j)
-    #pragma unroll
+#pragma unroll
                     for (int r = 0; r < RR; ++r) {
                         float v = ex[at(0, i, j, r0 + r)];
-    #pragma unroll
+#pragma unroll
                         for (int g = 1; g < KG; ++g) v += ex[at(g, i, j, r0 + r)];
                         y[i][j][r] = v;
                     }
