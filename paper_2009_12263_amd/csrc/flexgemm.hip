@@ -143,6 +143,11 @@ constexpr Rates kRates = {{1.0, 0.8, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29}, {1.0, 
 // The rates that decided what a call needs scratch memory for before the 64x64 tile had K groups
 // (see within_promised_scratch).
 constexpr Rates kPromisedRates = {{1.0, 0.8, 0.73, 0.45, 0.57, 1.0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0}, 2e-6, 25e9, 6e-6, 3e12};
+// Contractions have neither K groups nor splits, which the rates above were fitted with: over 320 contractions those
+// picked the fastest tile to within 2.4 % on average and 44 % at most (192 x 960 rows and columns over 2560: 33.8 us
+// with the deep 128x128 tile, 23.6 with the 64x64 tile), these to within 0.5 % and 43 %, and no tile slower than
+// either those or the promised rates pick (176 batches of 120 x 112 over 320: 11.6 us, 17.2 by the promised rates).
+constexpr Rates kContractRates = {{1.0, 0.8, 0.73, 0.394, 0.57, 1.0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0}, 1.8e-6, 25e9, 0, 1};
 
 Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_smallest = true, int64_t batches = 1,
                  bool allow_deep = true, int k32 = 0, bool allow_groups = false, int64_t scratch_bytes = kWorkspaceBytes,
@@ -1233,7 +1238,7 @@ static const fg::KernelEntry *select_contract_kernel(const Contraction &c, const
     // A result that is not contiguous along the leading row mode is stored in short pieces; the
     // smallest tile makes them shorter still (measured on the paper's D_abc = A_bda B_dc).
     const bool rows_contiguous = c.c_m.n == 0 || c.c_m.stride[0] == 1;
-    const int tile = choose_plan(c.M, c.N, c.K, false, rows_contiguous || c.M < 128 || c.N < 128, c.batches, true).tile;
+    const int tile = choose_plan(c.M, c.N, c.K, false, rows_contiguous || c.M < 128 || c.N < 128, c.batches, true, 0, false, 0, kContractRates).tile;
     // The result streams past the L2 only if every store of 32 consecutive rows is one whole,
     // aligned 128-byte line: leading row mode contiguous with an extent that is a multiple of 32,
     // every other stride of C and its base a multiple of 32 elements.
