@@ -881,8 +881,28 @@ __device__ __forceinline__ void epilogue(const typename Cfg::Params &p, const fl
                     __builtin_amdgcn_sched_barrier(0);
                 }
             };
+            // With nothing to load the batches need no order.  Left to the compiler, with plain masks: 1.7 % faster over 19
+            // ragged real products of 4 to 25 us, 1.2 % over 9 complex and 1.4 % over 15 dual ones.
+            auto run_edge_stores = [&] {
+#pragma unroll
+                for (int i = 0; i < Cfg::TI; ++i) {
+                    const bool m_ok = m_base + 32 * i + lm < p.M;
+                    const uint32_t vd = m_ok ? (uint32_t)voff_d : kOutOfRange;
+                    const float bias_mi = (bias_m_on && m_ok) ? p.bias[m_base + 32 * i + lm] : 0.f;
+#pragma unroll
+                    for (int j = 0; j < Cfg::TJ; ++j) {
+                        const floatx16 acc_ij = block(i, j);
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const bool n_ok = n_base + 32 * j + Cfg::acc_col(r) + Cfg::ACC_LH * lh < p.N;
+                            store_cd<H, kStream>(act_clamp(p.alpha * acc_ij[r] + bias_mi, floor_v, pass_v), rd, n_ok ? vd : kOutOfRange, 32 * ES * i + (32 * j + Cfg::acc_col(r)) * ldd4);
+                        }
+                    }
+                }
+            };
             if (bias_n_on) run_edge(std::true_type{});
-            else run_edge(std::false_type{});
+            else if constexpr (HAS_C) run_edge(std::false_type{});
+            else run_edge_stores();
         }
     } else {
         // tensor contraction: element offsets are mixed-radix sums over C's row and column modes.
