@@ -651,16 +651,6 @@ __device__ __forceinline__ void store_cd(float y, __amdgpu_buffer_rsrc_t r, uint
 // the operands reach D as IEEE arithmetic produces them.  Written with a floor so that both cases
 // are one compare and one select; the uniform flag is merged into the compare's lane mask.
 __device__ __forceinline__ float act_clamp(float v, float floor_v, bool pass) { return ((v > floor_v) | pass) ? v : floor_v; }
-// Result of a product whose K was split, from the sum of its partial products (c, bias: used if there is
-// one).  Each operation is spelt out, so that the reduction pass and the general kernel, which adds the ranges up
-// itself where no scratch memory may be used, round alike.
-__device__ __forceinline__ float split_value(float sum, float alpha, bool has_c, float beta, float c, bool has_bias, float bias) {
-#pragma clang fp contract(off)
-    float y = alpha * sum;
-    if (has_c) y = __builtin_fmaf(beta, c, y);
-    if (has_bias) y = y + bias;
-    return y;
-}
 
 template <class Cfg>
 constexpr int stream_policy() { return (Cfg::DIAG == 0 && (!Cfg::STRIDED || Cfg::CSTREAM)) ? 2 : 0; }   // gfx950 cache policy: bit 1 = nt

@@ -273,6 +273,17 @@ struct PieceLoader {
     }
 };
 
+// Result of a product whose K was split, from the sum of its partial products (c, bias: used if there is
+// one).  Each operation is spelt out as in the reduction pass (splitk_reduce.hip), so that a tile whose ranges
+// are added up here has that pass's bits.
+__device__ __forceinline__ float split_value(float sum, float alpha, bool has_c, float beta, float c, bool has_bias, float bias) {
+#pragma clang fp contract(off)
+    float y = alpha * sum;
+    if (has_c) y = __builtin_fmaf(beta, c, y);
+    if (has_bias) y = y + bias;
+    return y;
+}
+
 // KG groups of WGM x WGN waves share a BM x BN tile: group g multiplies the K steps kt0 + g, kt0 + g +
 // KG, ... into accumulators of its own, from LDS buffers of its own, and the groups' results are
 // added up through LDS at the end, each group finishing 1/KG of the registers.

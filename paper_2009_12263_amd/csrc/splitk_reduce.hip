@@ -19,6 +19,7 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float *W, int splits,
                                                      int tiles_m, int tiles_n, int M, int N, float alpha, float beta,
                                                      const float *C, int64_t ldc, float *D, int64_t ldd, const float *bias,
                                                      int bias_dim, int act, int c_act) {
+#pragma clang fp contract(off)                  // the operations of split_value, one by one
     const int per_tile = (bm / 4) * bn;
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (int64_t)per_tile * tile_count) return;
@@ -56,8 +57,10 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float *W, int splits,
     float y[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const float b = bias ? bias[bias_dim == 0 ? (q < valid ? m + q : m) : n] : 0.f;
-        y[q] = act_clamp(split_value(sum[q], alpha, C, beta, act_clamp(cv[q], floor_c, c_act_none), bias, b), floor_v, act_none);
+        y[q] = alpha * sum[q];
+        if (C) y[q] = __builtin_fmaf(beta, act_clamp(cv[q], floor_c, c_act_none), y[q]);
+        if (bias) y[q] += bias[bias_dim == 0 ? (q < valid ? m + q : m) : n];
+        y[q] = act_clamp(y[q], floor_v, act_none);
     }
     float *d = D + m + (int64_t)n * ldd;
     if (whole) *(float4 *)d = make_float4(y[0], y[1], y[2], y[3]);
