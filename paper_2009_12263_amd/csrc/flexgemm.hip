@@ -151,7 +151,7 @@ constexpr Rates kContractRates = {{1.0, 0.8, 0.73, 0.394, 0.57, 1.0, 0, 0}, {1.0
 
 Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_smallest = true, int64_t batches = 1,
                  bool allow_deep = true, int k32 = 0, bool allow_groups = false, int64_t scratch_bytes = kWorkspaceBytes,
-                 const Rates &rates = kRates) {
+                 const Rates &rates = kRates, int straddling = 0) {
     const auto &bm = kTileM;
     const auto &bn = kTileN;
     const auto &per_cu = kTilesPerCU;
@@ -182,6 +182,16 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
         const int64_t tiles = ((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]) * batches;
         const int64_t slots = (int64_t)kNumCU * per_cu[t];
         const int64_t slot_bytes = (int64_t)bm[t] * bn[t] * 4;
+        // K groups: at least four K tiles for each, or their reduction costs more than they save (256^3:
+        // 5.0 us on the GPU with one group, 5.3 with two, 6.3 with four; 512^3: 6.2, 6.2, 7.0)
+        const int64_t groups = t == fg::TILE_64x64_KG2 ? 2 : t == fg::TILE_64x64_KG4 ? 4 : 1;
+        // A piece of 64 elements lies on two 128-byte lines where its row does not begin on one (straddling: in how many
+        // of A and B), which a K loop of K groups feels: 27.6, 32.0 and 36.5 us at 2240x384, 2256x384 and 2256x360 over
+        // 6208 (split in four on the deep 128x128 tile 26.3, 26.8, 27.2).  Priced where a split is the alternative and the
+        // K loop is long beside its second launch (K from 3905 on; from 2560 on, 11 of 28 products that then take another
+        // plan are slower), and below what it costs: of 110 drawn products that take a split for it, four are slower
+        // by 3 to 12 %, the others up to 43 % faster (mean 15 %; in a replayed graph 28 %); at 15 % from K = 3650 on, six are slower.
+        const double lines = may_split && groups > 1 && nk >= 62 ? 1 + 0.1 * straddling : 1;
         auto share_time = [&](int64_t wgs, int S) {     // one workgroup on 1/S of K, plus its epilogue
             // workgroups that share a compute unit at a time: a unit's rate grows linearly from the
             // lone-workgroup rate to the rate with every slot taken, and is divided among them
@@ -193,12 +203,9 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
             // the C read and D write of a tile stream at what one compute unit gets of the memory
             // bandwidth, divided among the workgroups that share the unit
             const double epilogue = round_fixed + (double)n * 8.0 * bm[t] * bn[t] / cu_cd_bw;
-            return 2.0 * bm[t] * bn[t] * (double)((nk + S - 1) / S) * 64 / (cu_flops * rate) + epilogue;
+            return 2.0 * bm[t] * bn[t] * (double)((nk + S - 1) / S) * 64 / (cu_flops * rate) * (S == 1 ? lines : 1) + epilogue;
         };
         auto reduce_time = [&](int64_t ntile, int S) { return reduce_launch + (2.0 * S + 2.0) * (double)ntile * slot_bytes / reduce_bw; };
-        // K groups: at least four K tiles for each, or their reduction costs more than they save (256^3:
-        // 5.0 us on the GPU with one group, 5.3 with two, 6.3 with four; 512^3: 6.2, 6.2, 7.0)
-        const int64_t groups = t == fg::TILE_64x64_KG2 ? 2 : t == fg::TILE_64x64_KG4 ? 4 : 1;
         auto consider = [&](int S, int tail, double cost) {
             if (groups > 1 && force_tile < 0 && nk / (S * tail) < 4 * groups) return;
             if (best_cost < 0 || cost < best_cost) { best = Plan{t, S, tail}; best_cost = cost; }
@@ -257,13 +264,13 @@ int64_t scratch_need(const Plan &plan, int64_t M, int64_t N) {
 // captured before the workspace exists, one whose partial products fit the static array can be made
 // without allocation.  A plan that leaves the class (none, static array, workspace) of the plan by the promised
 // rates is therefore replaced by the best one that does not (0.5 % of random shapes).  Costs a split call 1.5 us on the host.
-Plan within_promised_scratch(Plan plan, int64_t M, int64_t N, int64_t K, int k32) {
+Plan within_promised_scratch(Plan plan, int64_t M, int64_t N, int64_t K, int k32, int straddling) {
     const int64_t need = scratch_need(plan, M, N);
     if (need == 0 || g_force_split.load(std::memory_order_relaxed) >= 1 || g_force_tail.load(std::memory_order_relaxed) > 1 ||
         g_force_tile.load(std::memory_order_relaxed) >= 0) return plan;
     const int64_t promised = scratch_need(choose_plan(M, N, K, true, true, 1, true, k32, false, kWorkspaceBytes, kPromisedRates), M, N);
     const int64_t limit = promised == 0 ? 0 : promised <= kStaticScratchBytes ? kStaticScratchBytes : kWorkspaceBytes;
-    return need <= limit ? plan : choose_plan(M, N, K, limit > 0, true, 1, true, k32, true, limit);
+    return need <= limit ? plan : choose_plan(M, N, K, limit > 0, true, 1, true, k32, true, limit, kRates, straddling);
 }
 
 // Tile of the complex and dual kernels (256x128, 128x128 with two workgroups per unit, 64x64 with
@@ -311,8 +318,20 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     }
     const bool may_split = plan_out && !q.a_diag && !q.b_diag && !q.cd16;   // the reduction pass writes FP32
     const int k32 = (q.a_diag || q.b_diag) ? 0 : q.ab_add ? (q.a_kc != q.b_kc ? 2 : 0) : ((q.a_kc || q.b_kc) ? 2 : 1);
-    Plan plan = choose_plan(q.M, q.N, q.K, may_split, true, 1, !q.a_diag && !q.b_diag, k32, !q.a_diag && !q.b_diag);
-    if (may_split) plan = within_promised_scratch(plan, q.M, q.N, q.K, k32);
+    auto planned = [&](int straddling) {
+        const bool dense = !q.a_diag && !q.b_diag;
+        const Plan p = choose_plan(q.M, q.N, q.K, may_split, true, 1, dense, k32, dense, kWorkspaceBytes, kRates, straddling);
+        return may_split ? within_promised_scratch(p, q.M, q.N, q.K, k32, straddling) : p;
+    };
+    // Rows off a line: by the extents (a row is whole 16-byte pieces), so that the plan query, which knows no leading
+    // dimensions, says the same.  Rows that begin on half a line are not counted: 8192x243 over 4256, both K-contiguous,
+    // 33.8 us in one pass, 41.7 split in two; 443x4534 33.8, and 35.4.
+    auto off_line = [](int64_t extent) { return (extent + 7) / 8 % 4 != 0; };
+    const int straddling = (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N);
+    Plan plan = planned(straddling);
+    // Only a split is taken in place of a pass of K groups: another tile's one pass measured 1 to 7 % slower (4257x397
+    // over 6600: 60.2 us with K groups, 65.0 on the deep 128x128 tile)
+    if (straddling > 0 && plan.splits == 1 && plan.tail_splits == 1) plan = planned(0);
     int tile = plan.tile;
     // A product with a diagonal operand is bound by its memory traffic (one pass over the dense
     // operand, C and D; a tile row only meets the K tiles on the diagonal).  While all of it fits the
