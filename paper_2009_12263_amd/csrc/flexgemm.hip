@@ -187,11 +187,10 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
         const int64_t groups = t == fg::TILE_64x64_KG2 ? 2 : t == fg::TILE_64x64_KG4 ? 4 : 1;
         // A piece of 64 elements lies on two 128-byte lines where its row does not begin on one (straddling: in how many
         // of A and B), which a K loop of K groups feels: 27.6, 32.0 and 36.5 us at 2240x384, 2256x384 and 2256x360 over
-        // 6208 (split in four on the deep 128x128 tile 26.3, 26.8, 27.2).  Priced where a split is the alternative and the
-        // K loop is long beside its second launch (K from 3905 on; from 2560 on, 11 of 28 products that then take another
-        // plan are slower), and below what it costs: of 110 drawn products that take a split for it, four are slower
-        // by 3 to 12 %, the others up to 43 % faster (mean 15 %; in a replayed graph 28 %); at 15 % from K = 3650 on, six are slower.
-        const double lines = may_split && groups > 1 && nk >= 62 ? 1 + 0.1 * straddling : 1;
+        // 6208 (split in four on the deep 128x128 tile 26.3, 26.8, 27.2).  Priced below
+        // what it costs: of 110 drawn products that take a split for it, four are slower by 3 to 12 %, the others up to 43 %
+        // faster (mean 15 %; in a replayed graph 28 %); at 15 % and from K = 3650 on, six are slower.
+        const double lines = groups > 1 ? 1 + 0.1 * straddling : 1;
         auto share_time = [&](int64_t wgs, int S) {     // one workgroup on 1/S of K, plus its epilogue
             // workgroups that share a compute unit at a time: a unit's rate grows linearly from the
             // lone-workgroup rate to the rate with every slot taken, and is divided among them
@@ -327,7 +326,9 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     // dimensions, says the same.  Rows that begin on half a line are not counted: 8192x243 over 4256, both K-contiguous,
     // 33.8 us in one pass, 41.7 split in two; 443x4534 33.8, and 35.4.
     auto off_line = [](int64_t extent) { return (extent + 7) / 8 % 4 != 0; };
-    const int straddling = (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N);
+    // Asked only where a split is the alternative and the K loop is long beside its second launch: from K = 2560 on, 11 of
+    // 28 products that then take another plan are slower.
+    const int straddling = may_split && q.K > 3904 ? (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N) : 0;
     Plan plan = planned(straddling);
     // Only a split is taken in place of a pass of K groups: another tile's one pass measured 1 to 7 % slower (4257x397
     // over 6600: 60.2 us with K groups, 65.0 on the deep 128x128 tile)
