@@ -139,7 +139,7 @@ struct Rates {
     double shared[fg::TILE_COUNT], alone[fg::TILE_COUNT];
     double round_fixed, cu_cd_bw, reduce_launch, reduce_bw;
 };
-constexpr Rates kRates = {{1.0, 0.8, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29}, {1.0, 0.8, 0.43, 0.135, 0.645, 1.0, 0.27, 0.29}, 1.6e-6, 27e9, 12.3e-6, 7.2e12};
+constexpr Rates kRates = {{1.0, 0.88, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29}, {1.0, 0.88, 0.43, 0.135, 0.645, 1.0, 0.27, 0.29}, 1.6e-6, 27e9, 12.3e-6, 7.2e12};
 // The rates that decided what a call needs scratch memory for before the 64x64 tile had K groups
 // (see within_promised_scratch).
 constexpr Rates kPromisedRates = {{1.0, 0.8, 0.73, 0.45, 0.57, 1.0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0}, 2e-6, 25e9, 6e-6, 3e12};
@@ -223,6 +223,7 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
         }
         // (b) whole rounds in one pass, the tiles of the last, partly filled round split over K
         const int64_t full = tiles / slots * slots, rest = tiles - full;
+        const double tail_round = t == fg::TILE_256x128 ? 1.09 : 1;      // in front of a tail the 256x256 tile is as fast: 4100^2 x 4096 185.0 us, 187.5
         if (may_split && full > 0 && rest > 0 && force_split < 1 && force_tail != 1) {
             for (int S : split_options) {
                 if (S == 1) continue;
@@ -230,7 +231,7 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
                 const bool fits = S <= nk && rest * S * slot_bytes <= scratch_bytes;
                 if (force_tail > 1) { if (!fits) break; }
                 else if (!fits || nk / S < 4 || rest * S > slots) break;
-                const double cost = (double)(full / slots) * share_time(full, 1) + 2e-6 +
+                const double cost = (double)(full / slots) * share_time(full, 1) * tail_round + 2e-6 +
                                     (double)((rest * S + slots - 1) / slots) * share_time(rest * S, S) + tail_launch + (2.0 * S + 2.0) * (double)rest * slot_bytes / tail_bw;
                 consider(1, S, force_tail > 1 ? 0.0 : cost);
             }

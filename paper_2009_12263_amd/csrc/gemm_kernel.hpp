@@ -170,7 +170,7 @@ struct TileCfg {
     static constexpr int A_BYTES = A_PLANE_BYTES * PLANES;
     static constexpr int GROUP_BYTES = A_BYTES + B_PLANE_BYTES * PLANES, LDS_BYTES = GROUP_BYTES * KG;
     static_assert(BK == 32 || BK == 64, "BK must be 32 or 64");
-    static_assert((STAGES & (STAGES - 1)) == 0 && STAGES >= 2, "STAGES must be a power of two");
+    static_assert(STAGES >= 2, "a ring");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be made of 32x32 accumulators");
     static_assert(A_SLABS >= 1 && B_SLABS >= 1, "tile too small for this many waves");
     static_assert(A_TILE_BYTES % (1024 * NWAVES) == 0 && B_TILE_BYTES % (1024 * NWAVES) == 0, "");
@@ -256,6 +256,14 @@ __device__ __forceinline__ void load16_to_lds(u32x4 rsrc, uint32_t lds_addr, uin
 template <int NEWER>
 __device__ __forceinline__ void wait_tile() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NEWER) : "memory");
+}
+
+// The same with the number of younger tiles (at most MOST, L loads each) known at run time only.
+template <int L, int MOST>
+__device__ __forceinline__ void wait_tiles(int newer) {
+    if constexpr (MOST == 0) wait_tile<0>();
+    else if (newer >= MOST) wait_tile<MOST * L>();
+    else wait_tiles<L, MOST - 1>(newer);
 }
 
 // Element offset of merged index idx.  Branch-free: the host pads the unused modes of a group
@@ -1226,7 +1234,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                     for (int r = 0; r < (Cfg::M16 ? 4 : 16); ++r) acc[q][i][j][r] = 0.f;
 
         if (nkt > 0) {
-            if (nkt >= S) wait_tile<(S - 1) * L>(); else wait_tile<0>();
+            wait_tiles<L, S - 1>(nkt - 1);
             __builtin_amdgcn_s_barrier();
 
             // A fragments are reloaded in place (the registers of sub-tile i are free once its
@@ -1246,6 +1254,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                 for (int j = 0; j < TJ; ++j) bf[q][0][j] = fb.read(lds_b + q * Cfg::B_PLANE_BYTES, j, 0);
             }
 
+            [[maybe_unused]] int ring = 0;              // buffer of the current K tile (rings that are not a power of two)
             [[maybe_unused]] bool fetched = false;      // ILV: a K step is waiting in registers
             // one K tile; MORE: another tile follows (publish it, refill the ring, prefetch its
             // first fragments)
@@ -1259,8 +1268,15 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                 constexpr bool MORE = decltype(more_tag)::value;
                 const bool RA = Cfg::ILV ? (kt + S < nkt) : decltype(ra_tag)::value;
                 [[maybe_unused]] constexpr bool RB = decltype(rb_tag)::value;
-                const int cur = kt & (S - 1);
-                const int nxt = (kt + 1) & (S - 1);
+                int cur, nxt, prev;
+                if constexpr ((S & (S - 1)) == 0) {
+                    cur = kt & (S - 1); nxt = (kt + 1) & (S - 1); prev = (kt - 1) & (S - 1);
+                } else {
+                    // counted rather than divided, and opaque: folded into the loop's address registers it spilled
+                    cur = ring; nxt = ring + 1 == S ? 0 : ring + 1; prev = ring == 0 ? S - 1 : ring - 1;
+                    ring = nxt;
+                    asm volatile("" : "+s"(ring));
+                }
                 FG_LDS const char *ta = lds_a + cur * Cfg::A_TILE_BYTES;
                 FG_LDS const char *tb = lds_b + cur * Cfg::B_TILE_BYTES;
                 FG_LDS const char *na = lds_a + nxt * Cfg::A_TILE_BYTES;
@@ -1272,7 +1288,6 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                     // quarters through the tile for the 128-row wave tile).
                     static_assert(KS == 2, "");
                     constexpr int BAR_I = TI - AW;
-                    const int prev = (kt - 1) & (S - 1);
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks) {
                         const int rb = ks & 1, wb = rb ^ 1;
@@ -1304,7 +1319,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                         for (int i = 0; i < TI; ++i) {
                             const int slot = i % AW;
                             if (last && MORE && i == BAR_I) {
-                                if (RA) wait_tile<(S - 2) * L>(); else wait_tile<0>();
+                                if (RA) wait_tile<(S - 2) * L>(); else wait_tiles<L, S - 2>(nkt - 2 - kt);
                                 __builtin_amdgcn_s_barrier();
                                 if (RA) {
                                     if constexpr (Cfg::SPREAD) {
@@ -1367,7 +1382,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                         }
                         // tile kt+1 has landed (for this wave) and all of this wave's reads of tile
                         // kt have returned; after the barrier both hold for every wave
-                        if (RA) wait_tile<(S - 2) * L>(); else wait_tile<0>();
+                        if (RA) wait_tile<(S - 2) * L>(); else wait_tiles<L, S - 2>(nkt - 2 - kt);
                         __builtin_amdgcn_s_barrier();
                         if constexpr (Cfg::ILV) {
                             fetched = RA;
@@ -1457,8 +1472,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                         }
                         if constexpr (Cfg::SPREAD) {
                             // one refill load after the MFMAs of sub-tile row i, evenly over the slice
-                            const int prev = (kt - 1) & (S - 1);
-#pragma unroll
+        #pragma unroll
                             for (int n = 0; n < Cfg::A_SLABS; ++n)
                                 if (refill_a && i == n * TI / Cfg::A_SLABS) {
 #pragma unroll

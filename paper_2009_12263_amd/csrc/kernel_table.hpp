@@ -11,6 +11,11 @@ namespace fg {
 // lone workgroup turns a K tile over too fast for a two-buffer ring to cover the memory latency.
 // (2048^3: 26.5 us against 28.8 us with four waves of 64x64 and the same ring.)  Matrix and
 // contraction kernels; no 16x16x32 form.
+// TILE_256x128: matrix kernels with a ring of three buffers (144 KB).  With two, a K tile has one tile's time to
+// arrive in (0.9 us), which data that comes from memory takes: 8192x1024x4096 with three operand sets in turn 82.5 -> 71.5 us
+// (one set, from the memory-side cache: 69.0 -> 67.2), with C 93.5 -> 80.0, 3000^3 94.1 -> 88.4, 2329x3267x5104 127.8 -> 111;
+// a pass over C and D as before (8192^2 x 64: 97.3, 96.5).  A fourth does not fit.  Contractions measured 0 to 4 % slower
+// with three (extents 192, 72, 200 over 208: 11.3, 11.7) and keep two.
 // TILE_256x256_K32: the 256x256 tile computed with 16x16x32 matrix instructions (TileCfg::M16), for
 // products that fill (most of) the GPU: there the chip runs at its power limit and that instruction shape
 // sustains a higher rate on the same data; on a partly filled GPU the 32x32x16 kernels are faster.
@@ -121,7 +126,7 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
     const KernelEntry *FUNC() {                                                                    \
         static const KernelEntry t[TILE_COUNT] = {                                                 \
             FG_ENTRY_BF16(256, 256, 64, 2, 2, 4, AKC, BKC, "gemm_bf16_" TAG "_256x256x64"),        \
-            FG_ENTRY_BF16(256, 128, 64, 2, 4, 2, AKC, BKC, "gemm_bf16_" TAG "_256x128x64"),        \
+            FG_ENTRY_BF16(256, 128, 64, 3, 4, 2, AKC, BKC, "gemm_bf16_" TAG "_256x128x64"),        \
             FG_ENTRY_BF16(128, 128, 64, 2, 2, 2, AKC, BKC, "gemm_bf16_" TAG "_128x128x64"),        \
             FG_ENTRY_BF16(64, 64, 64, 2, 2, 2, AKC, BKC, "gemm_bf16_" TAG "_64x64x64"),            \
             FG_ENTRY_BF16(128, 128, 64, 4, 4, 2, AKC, BKC, "gemm_bf16_" TAG "_128x128x64_deep"),   \
@@ -142,7 +147,7 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
     const KernelEntry *FUNC() {                                                                    \
         static const KernelEntry t[TILE_COUNT] = {                                                 \
             FG_ENTRY_H16(256, 256, 64, 2, 2, 4, AKC, BKC, "gemm_h16_" TAG "_256x256x64"),          \
-            FG_ENTRY_H16(256, 128, 64, 2, 4, 2, AKC, BKC, "gemm_h16_" TAG "_256x128x64"),          \
+            FG_ENTRY_H16(256, 128, 64, 3, 4, 2, AKC, BKC, "gemm_h16_" TAG "_256x128x64"),          \
             FG_ENTRY_H16(128, 128, 64, 2, 2, 2, AKC, BKC, "gemm_h16_" TAG "_128x128x64"),          \
             FG_ENTRY_H16(64, 64, 64, 2, 2, 2, AKC, BKC, "gemm_h16_" TAG "_64x64x64"),              \
             FG_ENTRY_H16(128, 128, 64, 4, 4, 2, AKC, BKC, "gemm_h16_" TAG "_128x128x64_deep"),     \
@@ -176,7 +181,7 @@ inline KernelEntry xf_k32_entry(const char *name) {
     const KernelEntry *FUNC() {                                                                    \
         static const KernelEntry t[TILE_COUNT] = {                                                 \
             FG_ENTRY_XF(256, 256, 64, 2, 2, 4, AKC, BKC, "gemm_abadd_" TAG "_256x256x64"),         \
-            FG_ENTRY_XF(256, 128, 64, 2, 4, 2, AKC, BKC, "gemm_abadd_" TAG "_256x128x64"),         \
+            FG_ENTRY_XF(256, 128, 64, 3, 4, 2, AKC, BKC, "gemm_abadd_" TAG "_256x128x64"),         \
             FG_ENTRY_XF(128, 128, 64, 2, 2, 2, AKC, BKC, "gemm_abadd_" TAG "_128x128x64"),         \
             FG_ENTRY_XF(64, 64, 64, 2, 2, 2, AKC, BKC, "gemm_abadd_" TAG "_64x64x64"),             \
             FG_ENTRY_XF(128, 128, 64, 4, 4, 2, AKC, BKC, "gemm_abadd_" TAG "_128x128x64_deep"),    \
@@ -204,7 +209,7 @@ inline KernelEntry xf_k32_entry(const char *name) {
             FG_ENTRY(256, 256, 64, 2, 2, 4, AKC, BKC, false, "gemm_" TAG "_256x256x64"),           \
             FG_ENTRY(256, 256, 64, 2, 2, 4, AKC, BKC, true, "gett_" TAG "_256x256x64"),            \
             FG_ENTRY_GS(256, 256, 64, 2, 2, 4, AKC, BKC, "gett_stream_" TAG "_256x256x64"),        \
-            FG_ENTRY(256, 128, 64, 2, 4, 2, AKC, BKC, false, "gemm_" TAG "_256x128x64"),           \
+            FG_ENTRY(256, 128, 64, 3, 4, 2, AKC, BKC, false, "gemm_" TAG "_256x128x64"),           \
             FG_ENTRY(256, 128, 64, 2, 4, 2, AKC, BKC, true, "gett_" TAG "_256x128x64"),            \
             FG_ENTRY_GS(256, 128, 64, 2, 4, 2, AKC, BKC, "gett_stream_" TAG "_256x128x64"),        \
             FG_ENTRY(128, 128, 64, 2, 2, 2, AKC, BKC, false, "gemm_" TAG "_128x128x64"),           \

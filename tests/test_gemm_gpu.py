@@ -484,6 +484,20 @@ def test_every_tile_shape_in_every_kernel_family(monkeypatch):
     run_gemm_case(2048, 2048, 2048, samples=4000)
 
 
+@pytest.mark.parametrize("la,lb", list(itertools.product(LAYOUTS, LAYOUTS)))
+def test_ring_of_three_buffers(monkeypatch, la, lb):
+    """The 256x128 tile's ring is no power of two: K loops shorter than the ring, as long, and ending in each of its
+    buffers, with a K tail and edge tiles, several tiles per workgroup and a K split; integer data, every entry exact."""
+    setenv(monkeypatch, "FG_FORCE_TILE", "1")
+    for K in (8, 64, 128, 136, 192, 256, 320, 384, 456):
+        say("ring of three, K = %d, A=%d B=%d" % (K, la, lb)); run_gemm_case(300, 264, K, la, lb, ints=True, pad=8, poison=True)
+    say("several tiles per workgroup"); run_gemm_case(4100, 2300, 200, la, lb, ints=True, beta=-2.0, samples=4000)
+    setenv(monkeypatch, "FG_FORCE_SPLIT", "3")
+    say("K split in 3"); run_gemm_case(300, 264, 1096, la, lb, ints=True, bias_dim=1, act=fg.FG_ACT_RELU)
+    delenv(monkeypatch, "FG_FORCE_SPLIT")
+    delenv(monkeypatch, "FG_FORCE_TILE")
+
+
 def test_operands_larger_than_2_gib():
     """A (then B) alone spans more than 2 GiB, once with K along columns and once along rows:
     the panels of the later tiles and the later K steps start beyond the reach of a 32-bit byte
