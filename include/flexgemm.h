@@ -279,8 +279,9 @@ const char *fg_last_error(void);
 int32_t fg_version(void);
 
 /*
- * Tuning aid, not part of the method: the planner's overrides FG_FORCE_TILE (0..7: tile shape, 6 and 7 the
- * 64x64 tile with two and four groups of waves that share K; 0..2 for complex and
+ * Tuning aid, not part of the method: the planner's overrides FG_FORCE_TILE (0..8: tile shape, 6 and 7 the
+ * 64x64 tile with two groups of waves that share K and rings of two and four buffers, 8 the 64x128 tile with two
+ * groups; 0..2 for complex and
  * dual products, whose kernels have three),
  * FG_FORCE_SPLIT (n: K ranges for every tile) and FG_FORCE_TAIL (n: K ranges for the tiles of the
  * last round; 1: never) are environment variables read once, when the library is loaded.  This

@@ -48,10 +48,10 @@ void note_relaxed(fg_status st, const char *fmt, ...) {
 
 constexpr int kNumCU = 256;   // MI355X: 8 XCDs x 32 compute units
 
-// Tuning overrides of the planner, from the environment: FG_FORCE_TILE=0..7 picks a tile shape (0..2
+// Tuning overrides of the planner, from the environment: FG_FORCE_TILE=0..8 picks a tile shape (0..2
 // for the three tiles of the complex and dual kernels)
-// (5: the 256x256 tile with the k32 kernel where the family has one; 6, 7: the 64x64 tile with two or
-// four K groups), FG_FORCE_SPLIT=n a split of K
+// (5: the 256x256 tile with the k32 kernel where the family has one; 6, 7: the 64x64 tile with two K
+// groups and rings of two or four buffers, 8: the 64x128 tile with two), FG_FORCE_SPLIT=n a split of K
 // for every tile, FG_FORCE_TAIL=n a split of K for the tiles of the last round (1: never).  Read
 // when the library is loaded and again by fg_reload_tuning(), not on every call.
 std::atomic<int> g_force_tile{-1}, g_force_split{0}, g_force_tail{0};
@@ -114,8 +114,8 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 // The params heuristic (Section 4.2.1 picks the largest tile that fits shared memory; here every
 // tile fits, so the question is which shape, and which split of K, finishes first).  Estimated
 // time = rounds x (time of one workgroup on its share of K + the time of its epilogue) + the cost
-// of the reduction pass if K is split.  `rounds` = ceil(workgroups / slots), slots = 256 compute
-// units x workgroups of that shape per unit; a workgroup's rate is a measured fraction of what a
+// of the reduction pass if K is split.  A round = as many workgroups as there are slots, 256 compute
+// units x workgroups of that shape per unit, the last one with those that it has; a workgroup's rate is a measured fraction of what a
 // compute unit sustains with the 256x256 tile (about 4.7 TFLOP/s), one set for workgroups that
 // share a unit and one for a workgroup that has a unit to itself.  Edge tiles are predicated, so
 // a tile need not divide the problem.  K is split only when the output has too few tiles to fill
@@ -126,28 +126,34 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 // compute units (measured +1 to +5 % from 192 tiles up, K from 1024 to 8192; equal at 176 tiles,
 // -1 to -6 % at 160 and fewer: a partly busy chip is not at its power limit).  k32 == 1: only
 // when forced (A and B both M/N-contiguous: measured 0 to -5 %).
-// allow_groups: the family has the 64x64 tile with K groups.  Their rates are fitted, like the
-// others' and the cost of a split, to the times of every tile and split forced over 70 products from
-// 17 x 1321 x 1312 to 227 x 8112 x 4992: the choice is on average 1 % slower than the fastest of
-// them (5 % before the fit), at most 13 %.  A split's second launch is priced with its host time, which
-// a stream of small products pays and a replayed graph does not (12x7894x3184, left whole: 17.6 us per call,
-// 18.2 replayed; split in four, as before the fit: 19.4 and 16.3).
-constexpr int kTileM[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64};
-constexpr int kTileN[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64};
-constexpr int kTilesPerCU[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1};
+// allow_groups: the family has the tiles with K groups.  The rates, the cost of a split and the prices of rows off the
+// lines are fitted to the times of replayed graphs of every tile and split forced over 190 products (64x64x32768 to
+// 4876x7518x2448): the choice is on average 1.7 % slower than the fastest (5 % with the rates before the larger rings),
+// at most 42 % (6708x5150x96), and over 16 % only with K up to 224.
+constexpr int kTileM[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64, 64};
+constexpr int kTileN[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64, 128};
+constexpr int kTilesPerCU[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1, 1};
 struct Rates {
     double shared[fg::TILE_COUNT], alone[fg::TILE_COUNT];
     double round_fixed, cu_cd_bw, reduce_launch, reduce_bw;
+    // A piece of 64 elements lies on two 128-byte lines where its row does not begin on one, and a line costs a unit's
+    // fill path the same whole or in part (64x64 tiles fetched with rows 5936 bytes apart: 54 GB/s per unit, 4096
+    // apart 128): what the K loop takes longer for each of A and B whose rows are off the lines.
+    double off_line[fg::TILE_COUNT];
+    bool last_round;         // the last, partly filled round is priced with the workgroups that it has
 };
-constexpr Rates kRates = {{1.0, 0.88, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29}, {1.0, 0.88, 0.43, 0.135, 0.645, 1.0, 0.27, 0.29}, 1.6e-6, 27e9, 12.3e-6, 7.2e12};
+constexpr Rates kRates = {{1, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
+                          {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
+                          2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
+                          {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true};
 // The rates that decided what a call needs scratch memory for before the 64x64 tile had K groups
 // (see within_promised_scratch).
-constexpr Rates kPromisedRates = {{1.0, 0.8, 0.73, 0.45, 0.57, 1.0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0}, 2e-6, 25e9, 6e-6, 3e12};
+constexpr Rates kPromisedRates = {{1.0, 0.8, 0.73, 0.45, 0.57, 1.0, 0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0, 0}, 2e-6, 25e9, 6e-6, 3e12, {}, false};
 // Contractions have neither K groups nor splits, which the rates above were fitted with: over 320 contractions those
 // picked the fastest tile to within 2.4 % on average and 44 % at most (192 x 960 rows and columns over 2560: 33.8 us
 // with the deep 128x128 tile, 23.6 with the 64x64 tile), these to within 0.5 % and 43 %, and no tile slower than
 // either those or the promised rates pick (176 batches of 120 x 112 over 320: 11.6 us, 17.2 by the promised rates).
-constexpr Rates kContractRates = {{1.0, 0.8, 0.73, 0.394, 0.57, 1.0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0}, 1.8e-6, 25e9, 0, 1};
+constexpr Rates kContractRates = {{1.0, 0.8, 0.73, 0.394, 0.57, 1.0, 0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0, 0}, 1.8e-6, 25e9, 0, 1, {}, false};
 
 Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_smallest = true, int64_t batches = 1,
                  bool allow_deep = true, int k32 = 0, bool allow_groups = false, int64_t scratch_bytes = kWorkspaceBytes,
@@ -178,19 +184,15 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
         if (t == fg::TILE_64x64 && !allow_smallest) continue;
         if (t == fg::TILE_128x128_DEEP && !allow_deep) continue;
         if (t == fg::TILE_256x256_K32) continue;
-        if ((t == fg::TILE_64x64_KG2 || t == fg::TILE_64x64_KG4) && !allow_groups) continue;
+        if (t >= fg::TILE_64x64_KG2 && !allow_groups) continue;
         const int64_t tiles = ((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]) * batches;
         const int64_t slots = (int64_t)kNumCU * per_cu[t];
         const int64_t slot_bytes = (int64_t)bm[t] * bn[t] * 4;
         // K groups: at least four K tiles for each, or their reduction costs more than they save (256^3:
-        // 5.0 us on the GPU with one group, 5.3 with two, 6.3 with four; 512^3: 6.2, 6.2, 7.0)
-        const int64_t groups = t == fg::TILE_64x64_KG2 ? 2 : t == fg::TILE_64x64_KG4 ? 4 : 1;
-        // A piece of 64 elements lies on two 128-byte lines where its row does not begin on one (straddling: in how many
-        // of A and B), which a K loop of K groups feels: 27.6, 32.0 and 36.5 us at 2240x384, 2256x384 and 2256x360 over
-        // 6208 (split in four on the deep 128x128 tile 26.3, 26.8, 27.2).  Priced below
-        // what it costs: of 110 drawn products that take a split for it, four are slower by 3 to 12 %, the others up to 43 %
-        // faster (mean 15 %; in a replayed graph 28 %); at 15 % and from K = 3650 on, six are slower.
-        const double lines = groups > 1 ? 1 + 0.1 * straddling : 1;
+        // 4.5 us on the GPU with one group, 4.8 with two; 519x736x320: 5.1, 5.5); the larger rings, which take longer to
+        // fill, from six on (128x2752x720, six: 6.1 us with two buffers, 6.5 with four; 704x640x768: 6.7, 6.4)
+        const int64_t groups = t >= fg::TILE_64x64_KG2 ? 2 : 1;
+        const double lines = 1 + rates.off_line[t] * straddling;
         auto share_time = [&](int64_t wgs, int S) {     // one workgroup on 1/S of K, plus its epilogue
             // workgroups that share a compute unit at a time: a unit's rate grows linearly from the
             // lone-workgroup rate to the rate with every slot taken, and is divided among them
@@ -202,11 +204,11 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
             // the C read and D write of a tile stream at what one compute unit gets of the memory
             // bandwidth, divided among the workgroups that share the unit
             const double epilogue = round_fixed + (double)n * 8.0 * bm[t] * bn[t] / cu_cd_bw;
-            return 2.0 * bm[t] * bn[t] * (double)((nk + S - 1) / S) * 64 / (cu_flops * rate) * (S == 1 ? lines : 1) + epilogue;
+            return 2.0 * bm[t] * bn[t] * (double)((nk + S - 1) / S) * 64 / (cu_flops * rate) * lines + epilogue;
         };
         auto reduce_time = [&](int64_t ntile, int S) { return reduce_launch + (2.0 * S + 2.0) * (double)ntile * slot_bytes / reduce_bw; };
         auto consider = [&](int S, int tail, double cost) {
-            if (groups > 1 && force_tile < 0 && nk / (S * tail) < 4 * groups) return;
+            if (groups > 1 && force_tile < 0 && nk / (S * tail) < (t == fg::TILE_64x64_KG2 ? 8 : 12)) return;
             if (best_cost < 0 || cost < best_cost) { best = Plan{t, S, tail}; best_cost = cost; }
         };
         // (a) every tile split S ways (S = 1: the plain launch)
@@ -216,8 +218,9 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
             if (forced) { if (S != split_options[0]) break; S = forced; }      // one candidate: the forced split
             else if (S > 1 && (!legal(S) || nk / S < 4)) break;                   // at least 256 k per share
             const int64_t wgs = tiles * S;
-            const int64_t rounds = (wgs + slots - 1) / slots;
-            double cost = (double)rounds * share_time(wgs, S);
+            const int64_t whole = wgs / slots, last = wgs - whole * slots;
+            double cost = rates.last_round && last > 0 ? (whole > 0 ? (double)whole * share_time(slots, S) : 0.0) + share_time(last, S)
+                                                       : (double)(whole + (last > 0)) * share_time(wgs, S);
             if (S > 1) cost += reduce_time(tiles, S);
             consider(S, 1, cost);
         }
@@ -327,13 +330,7 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     // dimensions, says the same.  Rows that begin on half a line are not counted: 8192x243 over 4256, both K-contiguous,
     // 33.8 us in one pass, 41.7 split in two; 443x4534 33.8, and 35.4.
     auto off_line = [](int64_t extent) { return (extent + 7) / 8 % 4 != 0; };
-    // Asked only where a split is the alternative and the K loop is long beside its second launch: from K = 2560 on, 11 of
-    // 28 products that then take another plan are slower.
-    const int straddling = may_split && q.K > 3904 ? (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N) : 0;
-    Plan plan = planned(straddling);
-    // Only a split is taken in place of a pass of K groups: another tile's one pass measured 1 to 7 % slower (4257x397
-    // over 6600: 60.2 us with K groups, 65.0 on the deep 128x128 tile)
-    if (straddling > 0 && plan.splits == 1 && plan.tail_splits == 1) plan = planned(0);
+    const Plan plan = planned(may_split ? (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N) : 0);
     int tile = plan.tile;
     // A product with a diagonal operand is bound by its memory traffic (one pass over the dense
     // operand, C and D; a tile row only meets the K tiles on the diagonal).  While all of it fits the
@@ -1169,7 +1166,7 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
     fg::GemmParams part = p;
     part.tile_begin = first; part.tile_count = count;
     part.splits = S;
-    const int64_t kg = k.kg > 1 ? k.kg : 1;          // K groups share a range in equal runs
+    const int64_t kg = k.kg > 1 ? k.kg : 1;          // K groups share a range
     part.split_kt = (int32_t)(((nk + S - 1) / S + kg - 1) / kg * kg);
     part.D = scratch.ptr;
     part.C = nullptr; part.has_c = 0; part.bias = nullptr; part.act = 0; part.c_act = 0; part.alpha = 1.f; part.beta = 0.f;

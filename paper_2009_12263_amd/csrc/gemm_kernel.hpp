@@ -112,7 +112,7 @@ __device__ __forceinline__ int tile_row(int pos, int rows, int z_count) {
 // B column-major) rather than M/N-contiguous.  STAGES LDS buffers per operand form a ring over K.
 template <int BM_, int BN_, int BK_, int STAGES_, int WGM_, int WGN_, bool A_KC_, bool B_KC_, bool STRIDED_,
           int DIAG_ = 0, int CPLX_ = 0, bool SPREAD_ = false, bool BF16_ = false, bool XFORM_ = false, bool ILV_ = false,
-          bool CSTREAM_ = false, bool CD16_ = false, bool M16_ = false, int KG_ = 1>
+          bool CSTREAM_ = false, bool CD16_ = false, bool M16_ = false, int KG_ = 1, bool KTURNS_ = false>
 struct TileCfg {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, STAGES = STAGES_;
     // M16: the product is made of v_mfma_f32_16x16x32 instructions (16x16 results, 32 k per
@@ -125,6 +125,10 @@ struct TileCfg {
     // KG: groups of WGM x WGN waves that share the block tile's K tiles, each with a ring, loads and
     // accumulators of its own; the groups' results are added up through LDS before the epilogue.
     static constexpr int KG = KG_;
+    // KTURNS: the groups take the K tiles in turns (group g the tiles g, g + KG, ...) instead of equal runs of them, so
+    // that what a unit fetches at a time lies side by side (192x2496x5368, A and B row-major: 21.3 -> 18.0 us).
+    static constexpr bool KTURNS = KTURNS_;
+    static constexpr int KINC = KTURNS_ ? KG_ : 1;
     static constexpr int NWAVES = WGM * WGN, NTHREADS = 64 * NWAVES * KG;
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;
     static constexpr int TI = WTM / 32, TJ = WTN / 32;             // 32x32 blocks of results per wave (epilogue)
@@ -154,6 +158,10 @@ struct TileCfg {
     // of transforms, Section 4.2.3: lower precision in memory, FP32 in the computation): C is
     // widened exactly when loaded, the FP32 result is rounded to nearest even when stored
     static constexpr bool CD16 = CD16_;
+    // ACC_SETS = 2: the k-slices of a K tile are summed in turns into two sets of accumulators, added up after the K loop.
+    // Half as many roundings follow one another in each sum: the error against 64 bits of 1024^3 is 1.1e-7 with two
+    // groups of two sets, as with the four K groups that served it before, 1.5e-7 with two groups of one.
+    static constexpr int ACC_SETS = !STRIDED_ && DIAG_ == 0 && CPLX_ == 0 && !M16_ && (KTURNS_ || STAGES_ == 4) ? 2 : 1;
     // SPREAD: the refill loads of a ring buffer are issued one at a time between the MFMAs of two
     // k-slices (A's part in the slice after the buffer is retired, B's part in the next one)
     // instead of as one burst: a burst from all waves queues up in the compute unit's single
@@ -310,10 +318,12 @@ __device__ __forceinline__ T load_param(unsigned offset) {
 // fetched into registers (fetch), split, and written into the two planes of the planar LDS
 // layout (commit), the conversion the paper places in the global-to-shared copy.
 // FLIP (M/N-contiguous tiles read as 16-row fragments, TileCfg::M16): see mc_swz.
-template <int R, int BK, bool KC, int SLABS, bool STRIDED, int ES = 1, bool FLIP = false>
+// KINC (plain matrices): advance() moves on by so many K steps.
+template <int R, int BK, bool KC, int SLABS, bool STRIDED, int ES = 1, bool FLIP = false, int KINC = 1>
 struct TileLoader {
     static_assert(ES == 1 || (ES == 2 && !STRIDED), "interleaved elements: plain matrices only");
     static_assert(!FLIP || ES == 1, "");
+    static_assert(KINC == 1 || !STRIDED, "");
     uint32_t voff[SLABS];    // per-lane byte offset from the moving base (per slab)
     u32x4 stage[ES == 2 ? SLABS : 1][2];   // ES == 2: the 32 fetched bytes of each slab's chunk
     const char *base;        // uniform: start of this block's panel at the current K step
@@ -440,8 +450,8 @@ struct TileLoader {
     }
     __device__ __forceinline__ void advance() {
         if constexpr (!STRIDED) {
-            base += kstep_bytes;
-            rem -= kstep_bytes;
+            base += KINC * kstep_bytes;
+            rem -= KINC * kstep_bytes;
         } else {
             // odometer step of BK along the leading summed mode (the steps of one pass cover its
             // extent rounded up to a multiple of BK); a carry moves one step along the next mode
@@ -457,7 +467,7 @@ struct TileLoader {
                 }
             }
         }
-        ++ktile;
+        ktile += KINC;
     }
     __device__ __forceinline__ void issue(FG_LDS char *lds_tile, int wave) {
         begin();
@@ -1119,8 +1129,8 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
     FG_LDS char *lds_a = smem + group * Cfg::GROUP_BYTES;
     FG_LDS char *lds_b = lds_a + Cfg::A_BYTES;
 
-    using PlainA = TileLoader<BM, BK, Cfg::A_KC, Cfg::A_SLABS, Cfg::STRIDED, Cfg::ILV ? 2 : 1, Cfg::M16>;
-    using PlainB = TileLoader<BN, BK, Cfg::B_KC, Cfg::B_SLABS, Cfg::STRIDED, Cfg::ILV ? 2 : 1, Cfg::M16>;
+    using PlainA = TileLoader<BM, BK, Cfg::A_KC, Cfg::A_SLABS, Cfg::STRIDED, Cfg::ILV ? 2 : 1, Cfg::M16, Cfg::KINC>;
+    using PlainB = TileLoader<BN, BK, Cfg::B_KC, Cfg::B_SLABS, Cfg::STRIDED, Cfg::ILV ? 2 : 1, Cfg::M16, Cfg::KINC>;
     constexpr int NLOADERS = Cfg::ILV ? 1 : P;      // an interleaved operand is one array, not one per plane
     using LoaderA = typename std::conditional<Cfg::DIAG == 1, DiagLoader<BM, BK, Cfg::A_SLABS>, PlainA>::type;
     using LoaderB = typename std::conditional<Cfg::DIAG == 2, DiagLoader<BN, BK, Cfg::B_SLABS>, PlainB>::type;
@@ -1168,12 +1178,12 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
         if (kt1 > nk) kt1 = nk;
         nkt = kt1 > kt0 ? kt1 - kt0 : 0;
         if constexpr (Cfg::KG > 1) {
-            // Group g takes the g-th of KG equal runs.  All groups run the same number of K tiles (they
-            // share the barriers); the tiles of the last group past the end of K are loaded as
+            // Group g takes the g-th of KG equal runs, or (KTURNS) every KG-th K tile.  All groups run the same
+            // number of K tiles (they share the barriers); tiles past the end of K are loaded as
             // zeros.  (A K split hands out ranges that are multiples of KG, so only K itself ends a
             // run early.)
             nkt = (nkt + Cfg::KG - 1) / Cfg::KG;
-            kt0 += group * nkt;
+            kt0 += Cfg::KTURNS ? group : group * nkt;
         }
         const _Float16 *ap[2] = {tp.A, tp.A_im};
         const _Float16 *bp[2] = {tp.B, tp.B_im};
@@ -1223,9 +1233,10 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
     while (true) {
         const int m_base = m0 + wm * Cfg::WTM, n_base = n0 + wn * Cfg::WTN;
         using AccT = typename std::conditional<Cfg::M16, floatx4, floatx16>::type;
-        AccT acc[P][TI][TJ];
+        constexpr int SETS = Cfg::ACC_SETS;         // (one plane only if there are two)
+        AccT acc[P * SETS][TI][TJ];
 #pragma unroll
-        for (int q = 0; q < P; ++q)
+        for (int q = 0; q < P * SETS; ++q)
 #pragma unroll
             for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -1308,7 +1319,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                             // only the last K tile can reach beyond K (the last two of a K group, of which
                             // one can lie beyond it whole): before it the addends are the same in every
                             // lane and stay in scalar registers
-                            const bool in_k = (MORE && Cfg::KG == 1) || (kt0 + kt) * BK + ks * 32 + 8 * (lane >> 4) < xf_k;
+                            const bool in_k = (MORE && Cfg::KG == 1) || (kt0 + kt * Cfg::KINC) * BK + ks * 32 + 8 * (lane >> 4) < xf_k;
                             add_a = in_k ? xf_a : 0u;
                             add_b = in_k ? xf_b : 0u;
 #pragma unroll
@@ -1426,7 +1437,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                     // addend is zero (a lane's eight values share one k chunk, K is a multiple of 8).
                     uint32_t add_a = 0, add_b = 0;          // two packed halves each
                     if constexpr (Cfg::XFORM) {
-                        const bool in_k = (MORE && Cfg::KG == 1) || (kt0 + kt) * BK + ks * Cfg::KSLICE + 8 * (lane / (Cfg::M16 ? 16 : 32)) < xf_k;
+                        const bool in_k = (MORE && Cfg::KG == 1) || (kt0 + kt * Cfg::KINC) * BK + ks * Cfg::KSLICE + 8 * (lane / (Cfg::M16 ? 16 : 32)) < xf_k;
                         add_a = in_k ? xf_a : 0u;
                         add_b = in_k ? xf_b : 0u;
 #pragma unroll
@@ -1439,8 +1450,10 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                         // accumulator then run along M, the contiguous direction of D
                         if constexpr (Cfg::CPLX == 0) {
 #pragma unroll
-                            for (int j = 0; j < TJ; ++j)
-                                acc[0][i][j] = mfma<Cfg::BF16>(bf[0][rb][j], af[0][i], acc[0][i][j]);
+                            for (int j = 0; j < TJ; ++j) {
+                                AccT &sum = acc[ks % SETS][i][j];
+                                sum = mfma<Cfg::BF16>(bf[0][rb][j], af[0][i], sum);
+                            }
                         } else if constexpr (Cfg::CPLX == 1) {
                             // (Ar + i Ai)(Br + i Bi): the four real products of Section 5.4
                             const half8 nai = neg8(af[1][i]);
@@ -1517,6 +1530,12 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
             tile_body(nkt - 1, F, F, F);
         }
 
+        if constexpr (SETS == 2) {
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) acc[0][i][j] += acc[1][i][j];
+        }
         if constexpr (Cfg::KG > 1) {
             // the other groups hand their results to group 0, which adds them in a fixed order
             constexpr int Q = TI * TJ * 4;                  // quads of registers per wave

@@ -21,13 +21,19 @@ namespace fg {
 // sustains a higher rate on the same data; on a partly filled GPU the 32x32x16 kernels are faster.
 // Plain, BF16 and binary16-result matrix kernels, and the A/B-addition kernels of two layout pairs
 // (other tables leave the entry empty).
-// TILE_64x64_KG2, TILE_64x64_KG4: the 64x64 tile with two or four groups of four waves that share its K
-// tiles (TileCfg::KG), for outputs of at most two such tiles per unit: one group alone spends most of a
-// K tile in barrier and LDS latency, and two or four turn over as many K tiles in little more time
-// (1024^2 x 4096: 34.9 us with one group, 23.8 with two, 21.6 with four; 1536 x 1024 x 2048, which
-// needs two tiles per unit: 21.3, 17.2, 22.5).  Matrix kernels of real products.
+// TILE_64x64_KG2, TILE_64x64_KG2_DEEP: the 64x64 tile with two groups of four waves that share its K tiles
+// (TileCfg::KG), for outputs of at most two such tiles per unit: one group alone spends most of a K tile in barrier
+// and LDS latency.  DEEP: rings of four, for outputs of at most one tile per unit, whose two-buffer rings wait for
+// their loads (1024^2 x 4096: 34.9 us with one group, 23.9 with two, 21.4 with four groups and
+// two buffers, which this form replaces, 17.8 with two groups and four buffers; 512^2 x 2048: 13.5, 12.8, 10.7; five buffers
+// and one group with eight measured no faster).  The direct-to-LDS path of a unit gives 104 GB/s with all units at it
+// (150 alone); this loop takes 80.
+// TILE_64x128_KG2: the same with 64x128 tiles and rings of three, for outputs between one 64x64 tile per unit and one
+// 128x128 tile: fewer bytes per product, and one tile per unit where the 64x64 tile needs two (1536x1024x2048: 17.5 us
+// with two groups, 15.5; 1895x714x1256: 15.3, 14.0; 128x64 tiles 15.7 and 14.9).
+// All three: matrix kernels of real products.
 enum TileId { TILE_256x256 = 0, TILE_256x128 = 1, TILE_128x128 = 2, TILE_64x64 = 3, TILE_128x128_DEEP = 4,
-              TILE_256x256_K32 = 5, TILE_64x64_KG2 = 6, TILE_64x64_KG4 = 7, TILE_COUNT = 8, DIAG_TILE_COUNT = 4 };
+              TILE_256x256_K32 = 5, TILE_64x64_KG2 = 6, TILE_64x64_KG2_DEEP = 7, TILE_64x128_KG2 = 8, TILE_COUNT = 9, DIAG_TILE_COUNT = 4 };
 
 struct KernelEntry {
     const void *fn;           // void (*)(const GemmParams), contractions: (const ContractParams)
@@ -92,11 +98,11 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
 
 // real kernels with BK = 64: ring refills are spread between the MFMAs (TileCfg::SPREAD)
 #define FG_CFG(BM, BN, BK, ST, WGM, WGN, AKC, BKC, STR) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, STR, 0, 0, true>
-// the 64x64 tile with K groups; BF: bfloat16 inputs, XF: addition on A and B, H: binary16 C and D
-#define FG_CFG_KG(AKC, BKC, BF, XF, H, KG) TileCfg<64, 64, 64, 2, 2, 2, AKC, BKC, false, 0, 0, true, BF, XF, false, false, H, false, KG>
-#define FG_ENTRY_KG(AKC, BKC, BF, XF, H, KG, NAME)                                                 \
-    { (const void *)gemm_kernel<FG_CFG_KG(AKC, BKC, BF, XF, H, KG)>, NAME, 64, 64,                 \
-      FG_CFG_KG(AKC, BKC, BF, XF, H, KG)::NTHREADS, FG_CFG_KG(AKC, BKC, BF, XF, H, KG)::LDS_BYTES, KG }
+// the tiles with two K groups (64 rows; BN columns, ring of ST); BF: bfloat16 inputs, XF: addition on A and B, H: binary16 C and D
+#define FG_CFG_KG(AKC, BKC, BF, XF, H, BN, ST, TURNS) TileCfg<64, BN, 64, ST, 2, 2, AKC, BKC, false, 0, 0, true, BF, XF, false, false, H, false, 2, TURNS>
+#define FG_ENTRY_KG(AKC, BKC, BF, XF, H, BN, ST, TURNS, NAME)                                      \
+    { (const void *)gemm_kernel<FG_CFG_KG(AKC, BKC, BF, XF, H, BN, ST, TURNS)>, NAME, 64, BN,      \
+      FG_CFG_KG(AKC, BKC, BF, XF, H, BN, ST, TURNS)::NTHREADS, FG_CFG_KG(AKC, BKC, BF, XF, H, BN, ST, TURNS)::LDS_BYTES, 2 }
 #define FG_EMPTY_ENTRY { nullptr, nullptr, 0, 0, 0, 0, 0 }
 // the same with 16x16x32 matrix instructions (TileCfg::M16); BF: bfloat16 inputs, H: binary16 C and D
 #define FG_CFG_K32(BM, BN, BK, ST, WGM, WGN, AKC, BKC, BF, H) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, 0, 0, true, BF, false, false, false, H, true>
@@ -131,8 +137,9 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
             FG_ENTRY_BF16(64, 64, 64, 2, 2, 2, AKC, BKC, "gemm_bf16_" TAG "_64x64x64"),            \
             FG_ENTRY_BF16(128, 128, 64, 4, 4, 2, AKC, BKC, "gemm_bf16_" TAG "_128x128x64_deep"),   \
             FG_ENTRY_K32(256, 256, 64, 2, 2, 4, AKC, BKC, true, false, "gemm_bf16_" TAG "_256x256x64_k32"), \
-            FG_ENTRY_KG(AKC, BKC, true, false, false, 2, "gemm_bf16_" TAG "_64x64x64"),            \
-            FG_ENTRY_KG(AKC, BKC, true, false, false, 4, "gemm_bf16_" TAG "_64x64x64"),            \
+            FG_ENTRY_KG(AKC, BKC, true, false, false, 64, 2, false, "gemm_bf16_" TAG "_64x64x64"),            \
+            FG_ENTRY_KG(AKC, BKC, true, false, false, 64, 4, true, "gemm_bf16_" TAG "_64x64x64"),            \
+            FG_ENTRY_KG(AKC, BKC, true, false, false, 128, 3, true, "gemm_bf16_" TAG "_64x128x64"),\
         };                                                                                         \
         return t;                                                                                  \
     }
@@ -152,8 +159,9 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
             FG_ENTRY_H16(64, 64, 64, 2, 2, 2, AKC, BKC, "gemm_h16_" TAG "_64x64x64"),              \
             FG_ENTRY_H16(128, 128, 64, 4, 4, 2, AKC, BKC, "gemm_h16_" TAG "_128x128x64_deep"),     \
             FG_ENTRY_K32(256, 256, 64, 2, 2, 4, AKC, BKC, false, true, "gemm_h16_" TAG "_256x256x64_k32"), \
-            FG_ENTRY_KG(AKC, BKC, false, false, true, 2, "gemm_h16_" TAG "_64x64x64"),             \
-            FG_ENTRY_KG(AKC, BKC, false, false, true, 4, "gemm_h16_" TAG "_64x64x64"),             \
+            FG_ENTRY_KG(AKC, BKC, false, false, true, 64, 2, false, "gemm_h16_" TAG "_64x64x64"),             \
+            FG_ENTRY_KG(AKC, BKC, false, false, true, 64, 4, true, "gemm_h16_" TAG "_64x64x64"),             \
+            FG_ENTRY_KG(AKC, BKC, false, false, true, 128, 3, true, "gemm_h16_" TAG "_64x128x64"), \
         };                                                                                         \
         return t;                                                                                  \
     }
@@ -186,8 +194,9 @@ inline KernelEntry xf_k32_entry(const char *name) {
             FG_ENTRY_XF(64, 64, 64, 2, 2, 2, AKC, BKC, "gemm_abadd_" TAG "_64x64x64"),             \
             FG_ENTRY_XF(128, 128, 64, 4, 4, 2, AKC, BKC, "gemm_abadd_" TAG "_128x128x64_deep"),    \
             xf_k32_entry<AKC, BKC>("gemm_abadd_" TAG "_256x256x64_k32"),                           \
-            FG_ENTRY_KG(AKC, BKC, false, true, false, 2, "gemm_abadd_" TAG "_64x64x64"),           \
-            FG_ENTRY_KG(AKC, BKC, false, true, false, 4, "gemm_abadd_" TAG "_64x64x64"),           \
+            FG_ENTRY_KG(AKC, BKC, false, true, false, 64, 2, false, "gemm_abadd_" TAG "_64x64x64"),           \
+            FG_ENTRY_KG(AKC, BKC, false, true, false, 64, 4, true, "gemm_abadd_" TAG "_64x64x64"),           \
+            FG_ENTRY_KG(AKC, BKC, false, true, false, 128, 3, true, "gemm_abadd_" TAG "_64x128x64"),\
         };                                                                                         \
         return t;                                                                                  \
     }
@@ -223,8 +232,9 @@ inline KernelEntry xf_k32_entry(const char *name) {
             FG_ENTRY_GS(128, 128, 64, 4, 4, 2, AKC, BKC, "gett_stream_" TAG "_128x128x64_deep"),   \
             FG_ENTRY_K32(256, 256, 64, 2, 2, 4, AKC, BKC, false, false, "gemm_" TAG "_256x256x64_k32"), \
             FG_EMPTY_ENTRY, FG_EMPTY_ENTRY,                                                        \
-            FG_ENTRY_KG(AKC, BKC, false, false, false, 2, "gemm_" TAG "_64x64x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
-            FG_ENTRY_KG(AKC, BKC, false, false, false, 4, "gemm_" TAG "_64x64x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
+            FG_ENTRY_KG(AKC, BKC, false, false, false, 64, 2, false, "gemm_" TAG "_64x64x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
+            FG_ENTRY_KG(AKC, BKC, false, false, false, 64, 4, true, "gemm_" TAG "_64x64x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
+            FG_ENTRY_KG(AKC, BKC, false, false, false, 128, 3, true, "gemm_" TAG "_64x128x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY,\
         };                                                                                         \
         return t;                                                                                  \
     }

@@ -293,7 +293,7 @@ def test_k_group_kernels_run(monkeypatch):
         assert torch.equal(float_result(1024, 1024, 1024, la, lb), got["7"])
 
 
-@pytest.mark.parametrize("tile,groups", [("6", 2), ("7", 4)])
+@pytest.mark.parametrize("tile,groups", [("6", 2), ("7", 4), ("8", 2)])
 def test_k_groups(monkeypatch, tile, groups):
     """The 64x64 tile whose groups of waves share its K tiles (tiled kernels): fewer K tiles than
     groups, runs that do not come out even, a K tail in the last group's last and last but one tile,
