@@ -25,7 +25,7 @@
  *     that way ("+splitk<n>" / "+tailsplitk<n>" in the plan name).  All such calls on one GPU share
  *     the workspace: calls on one stream are ordered anyway, and a call on another stream than the
  *     previous user's is made to wait on the device (an event recorded after that user's reduction
- *     pass) until the workspace is free, so calls on different streams may be issued freely; they
+ *     pass; after a call on the default stream, after all that was issued there until then) until the workspace is free, so calls on different streams may be issued freely; they
  *     are serialised, not run side by side.  The exception is a stream under graph capture: the
  *     caller orders captured split-K calls against other users of the workspace, and the workspace
  *     must exist before the capture begins (fg_init(); FG_ERR_UNSUPPORTED otherwise).  The partial

@@ -566,6 +566,27 @@ def test_split_k_calls_on_two_streams_do_not_disturb_each_other():
         assert torch.equal(D, ops[i][5]), "launch %d on stream %d differs from the serial result" % (n, i)
 
 
+def test_split_k_calls_on_the_default_stream_and_another():
+    """Calls on the default stream leave no event behind; one on another stream that follows at once still waits for
+    their partial products, and the other way round."""
+    from paper_2009_12263_amd import workloads as W
+    M, N, K = 512, 512, 16384
+    assert "+splitk" in fg.fg_gemm_plan(M, N, K)
+    A = W.small_ints(M * K, 31, device="cuda"); B = W.small_ints(K * N, 32, device="cuda")
+    new = lambda: torch.full((M * N,), float("nan"), dtype=torch.float32, device="cuda")
+    def call(D, stream=None):
+        fg.fg_gemm(M, N, K, 1.0, fg.Matrix(A, fg.FG_COL, M), fg.Matrix(B, fg.FG_COL, K), 0.0, None, fg.Matrix(D, fg.FG_COL, M), stream=stream)
+    ref = new(); call(ref)
+    outs = [new() for _ in range(60)]
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for i, D in enumerate(outs):
+        call(D, side if i % 3 == 2 else None)
+    torch.cuda.synchronize()
+    for i, D in enumerate(outs):
+        assert torch.equal(D, ref), "call %d differs from the serial result" % i
+
+
 def test_tail_round_split(monkeypatch):
     """More tiles than the persistent grid holds at once, with a small remainder: the full rounds
     run as one pass and only the leftover tiles are split over K (plus the reduction pass).  Forced
