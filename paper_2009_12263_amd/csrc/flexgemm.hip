@@ -1132,10 +1132,18 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
         // other workgroups re-read), unless the whole problem fits the 256 MB memory-side cache: then
         // nothing is displaced for long, and keeping C and D cached measured faster (3000^3: 73.6
         // against 87.4 us, 4096^3: -6 %, 5000 x 3000 x 2000: 76.7 against 103.1 us back to back;
-        // equal on cache-cold operands; from 300 MB up streaming wins by 4 to 9 %).
+        // equal on cache-cold operands; from 300 MB up streaming wins by 4 to 9 %).  Columns that do not begin on a
+        // 128-byte line share lines, which a streamed C fetches from memory once for each: kept in the caches whatever
+        // the size (6708x5150x96 148.7 -> 98.2 us, 8180x6100x512 211.6 -> 171.2, 6008x8000x2000 289 -> 272; without C equal).
         const int64_t es_cd = q.cd16 ? 2 : 4;
         const int64_t bytes = (q.M * q.K + q.K * q.N) * 2 + q.M * q.N * es_cd * (q.C ? 2 : 1);
-        p.cd_cached = bytes <= (256ll << 20);
+        auto off_lines = [&](int64_t elems) { return q.ldd % elems != 0 || (q.C && q.ldc % elems != 0); };
+        if (!q.cplx) p.cd_cached = bytes <= (256ll << 20) || (q.C && off_lines(32));
+        // Complex and dual products, whose planes or pairs double all of it: off the lines likewise, with C or without (4040x2048x400
+        // complex 72.3 -> 62.9 us, without C 52.9 -> 39.0, dual 1532x2368x1112 41.3 -> 34.2), but interleaved columns on
+        // half a line stream (3000x2500x1000 84.5, 88.2 kept).  On the lines kept up to 80 MB and with C only (1536^2 x 512
+        // 24.4 -> 21.6, dual 2048^2 x 512 32.0 -> 29.4; without C 22.4 streamed and 23.6 kept, complex 2048^3, 100 MB, 77.4 and 78.4).
+        else p.cd_cached = off_lines(q.ilv ? 8 : 32) || (q.C && 2 * bytes <= (80ll << 20));
     }
     hipStream_t stream = (hipStream_t)hip_stream;
     if (plan.splits <= 1 && plan.tail_splits <= 1) return launch(k, p, stream);

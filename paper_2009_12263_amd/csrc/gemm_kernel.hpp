@@ -72,8 +72,8 @@ struct GemmParams {
     // BM x BN partial result (alpha = 1, no C, bias or activation) to slot w of the workspace D.
     int32_t tile_begin, tile_count;
     int32_t splits, split_kt;
-    // Matrix kernels: C and D are accessed with the default cache policy instead of the streaming
-    // one (set by the host when the whole problem fits the memory-side cache; see stream_policy).
+    // Matrix, complex and dual kernels: C and D are accessed with the default cache policy instead of the streaming
+    // one (set by the host, gemm_impl; see stream_policy).
     int32_t cd_cached;
 };
 
@@ -986,10 +986,11 @@ __device__ __forceinline__ void epilogue(const typename Cfg::Params &p, const fl
 // 2 (m + n*ld), so a lane reads and writes 8 bytes per element and a half-wave covers 256
 // consecutive bytes.  alpha and beta are real.  Rows and columns past the matrix are masked as in
 // the edge path above; eight elements at a time.
-template <class Cfg, bool HAS_C>
+template <class Cfg, bool HAS_C, bool CACHED>
 __device__ __forceinline__ void epilogue_interleaved(const GemmParams &p, floatx16 (&acc_re)[Cfg::TI][Cfg::TJ],
                                                      floatx16 (&acc_im)[Cfg::TI][Cfg::TJ], int m_base, int n_base, int lane) {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    constexpr int kStream = CACHED ? 0 : stream_policy<Cfg>();
     const int lm = lane & 31, lh = lane >> 5;
     const int voff_c = (lm + 4 * lh * (int)p.ldc) * 8, voff_d = (lm + 4 * lh * (int)p.ldd) * 8;
     const int ldc8 = (int)p.ldc * 8, ldd8 = (int)p.ldd * 8;
@@ -1011,7 +1012,7 @@ __device__ __forceinline__ void epilogue_interleaved(const GemmParams &p, floatx
                         const int r = 8 * h + r8;
                         const bool n_ok = n_base + 32 * j + 8 * (r >> 2) + (r & 3) + 4 * lh < p.N;
                         cv[r8] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(
-                            rc, n_ok ? vc : kOutOfRange, 256 * i + (32 * j + 8 * (r >> 2) + (r & 3)) * ldc8, 2));
+                            rc, n_ok ? vc : kOutOfRange, 256 * i + (32 * j + 8 * (r >> 2) + (r & 3)) * ldc8, kStream));
                     }
                 }
 #pragma unroll
@@ -1025,7 +1026,7 @@ __device__ __forceinline__ void epilogue_interleaved(const GemmParams &p, floatx
                     }
                     u32x2 out = {__builtin_bit_cast(uint32_t, yr), __builtin_bit_cast(uint32_t, yi)};
                     __builtin_amdgcn_raw_buffer_store_b64(out, rd, n_ok ? vd : kOutOfRange,
-                                                          256 * i + (32 * j + 8 * (r >> 2) + (r & 3)) * ldd8, 2);
+                                                          256 * i + (32 * j + 8 * (r >> 2) + (r & 3)) * ldd8, kStream);
                 }
             }
         }
@@ -1592,7 +1593,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                 if (ep.has_c) ep.C += c_off;
             }
             // the matrix kernels that stream C and D have a second copy of the epilogue without the hint
-            constexpr bool TWO_POLICIES = !Cfg::STRIDED && Cfg::DIAG == 0 && Cfg::CPLX == 0 && !Cfg::ILV;
+            constexpr bool TWO_POLICIES = !Cfg::STRIDED && Cfg::DIAG == 0;
             if constexpr (Cfg::M16) {
                 auto blocks = [&](int i, int j) { return gather_block<Cfg>(acc[0], i, j); };
                 if (TWO_POLICIES && ep.cd_cached) {
@@ -1603,8 +1604,12 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                 else epilogue<Cfg, false>(ep, ep.C, ep.D, blocks, mb, nb, lane);
             } else {
                 if constexpr (Cfg::ILV) {
-                    if (ep.has_c) epilogue_interleaved<Cfg, true>(ep, acc[0], acc[1], m_base, n_base, lane);
-                    else epilogue_interleaved<Cfg, false>(ep, acc[0], acc[1], m_base, n_base, lane);
+                    if (ep.cd_cached) {
+                        if (ep.has_c) epilogue_interleaved<Cfg, true, true>(ep, acc[0], acc[1], m_base, n_base, lane);
+                        else epilogue_interleaved<Cfg, false, true>(ep, acc[0], acc[1], m_base, n_base, lane);
+                    } else
+                    if (ep.has_c) epilogue_interleaved<Cfg, true, false>(ep, acc[0], acc[1], m_base, n_base, lane);
+                    else epilogue_interleaved<Cfg, false, false>(ep, acc[0], acc[1], m_base, n_base, lane);
                 } else {
                     auto blocks = [&](int i, int j) -> floatx16 { return acc[0][i][j]; };
                     if (TWO_POLICIES && ep.cd_cached) {
@@ -1616,6 +1621,10 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
                 }
                 if constexpr (Cfg::CPLX && !Cfg::ILV) {
                     auto blocks_im = [&](int i, int j) -> floatx16 { return acc[1][i][j]; };
+                    if (ep.cd_cached) {
+                        if (ep.has_c) epilogue<Cfg, true, decltype(blocks_im), true>(ep, ep.C_im, ep.D_im, blocks_im, m_base, n_base, lane);
+                        else epilogue<Cfg, false, decltype(blocks_im), true>(ep, ep.C_im, ep.D_im, blocks_im, m_base, n_base, lane);
+                    } else
                     if (ep.has_c) epilogue<Cfg, true>(ep, ep.C_im, ep.D_im, blocks_im, m_base, n_base, lane);
                     else epilogue<Cfg, false>(ep, ep.C_im, ep.D_im, blocks_im, m_base, n_base, lane);
                 }

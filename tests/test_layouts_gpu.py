@@ -107,3 +107,14 @@ def test_interleaved_and_planar_matrices_are_not_mixed():
     assert fg.fg_gemm(64, 64, 64, 1.0, fg.Matrix(H, fg.FG_COL, 64), fg.Matrix(H, fg.FG_COL, 64), 0.0, None, il(F, fg.FG_CF32), **kw) == fg.FG_ERR_UNSUPPORTED
     assert fg.fg_gemm(64, 64, 64, 1.0, il(H, fg.FG_CF16), il(H, fg.FG_CF16), 0.0, None, il(F, fg.FG_CF32), act=fg.FG_ACT_RELU, **kw) == fg.FG_ERR_UNSUPPORTED
     assert fg.fg_gemm(64, 64, 64, 1.0, fg.Matrix(H, fg.FG_COL, 64, im=H, dtype=fg.FG_CF16), il(H, fg.FG_CF16), 0.0, None, il(F, fg.FG_CF32), **kw) == fg.FG_ERR_LAYOUT
+
+
+@pytest.mark.parametrize("kind", [dict(), dict(dual=True), dict(interleaved=True)])
+@pytest.mark.parametrize("M", [256, 264, 260])
+def test_cache_policies_of_complex_results(kind, M):
+    """C and D of complex and dual products are kept in the caches or streamed past them (columns on the 128-byte lines,
+    on half lines and off them; with C and without): the same results, interior and edge tiles of every tile shape."""
+    for N, with_c in ((128, True), (128, False), (133, True), (133, False)):
+        say("M=%d N=%d C=%d %s" % (M, N, with_c, kind))
+        run_cgemm_case(M, N, 72, ints=True, alpha=2.0, beta=-1.0, with_c=with_c, **kind)
+        run_cgemm_case(M, N, 72, fg.FG_ROW, fg.FG_ROW, fg.FG_ROW, ints=True, with_c=with_c, **kind)
