@@ -281,8 +281,8 @@ int32_t fg_version(void);
 /*
  * Tuning aid, not part of the method: the planner's overrides FG_FORCE_TILE (0..8: tile shape, 6 and 7 the
  * 64x64 tile with two groups of waves that share K and rings of two and four buffers, 8 the 64x128 tile with two
- * groups; 0..2 for complex and
- * dual products, whose kernels have three),
+ * groups; 0..3 for complex and
+ * dual products, whose kernels have four),
  * FG_FORCE_SPLIT (n: K ranges for every tile) and FG_FORCE_TAIL (n: K ranges for the tiles of the
  * last round; 1: never) are environment variables read once, when the library is loaded.  This
  * call reads them again (for a process that changes its environment afterwards).

@@ -48,8 +48,8 @@ void note_relaxed(fg_status st, const char *fmt, ...) {
 
 constexpr int kNumCU = 256;   // MI355X: 8 XCDs x 32 compute units
 
-// Tuning overrides of the planner, from the environment: FG_FORCE_TILE=0..8 picks a tile shape (0..2
-// for the three tiles of the complex and dual kernels)
+// Tuning overrides of the planner, from the environment: FG_FORCE_TILE=0..8 picks a tile shape (0..3
+// for the four tiles of the complex and dual kernels)
 // (5: the 256x256 tile with the k32 kernel where the family has one; 6, 7: the 64x64 tile with two K
 // groups and rings of two or four buffers, 8: the 64x128 tile with two), FG_FORCE_SPLIT=n a split of K
 // for every tile, FG_FORCE_TAIL=n a split of K for the tiles of the last round (1: never).  Read
@@ -277,25 +277,29 @@ Plan within_promised_scratch(Plan plan, int64_t M, int64_t N, int64_t K, int k32
 }
 
 // Tile of the complex and dual kernels (256x128, 128x128 with two workgroups per unit, 64x64 with
-// four): the one with the smallest estimated time.  Whole rounds run with every slot of a unit
+// four, 64x64 with K groups with one): the one with the smallest estimated time.  Whole rounds run with every slot of a unit
 // taken, the workgroups of the last, partly filled round share a unit with fewer others; a
 // workgroup's rate is a measured fraction of what a unit sustains with the 256x128 tile (4096^3:
 // 455 / 515 / 629 us with the three tiles; alone on a unit: 1024^3 51 / 35 / 18 us).  The estimate
 // reproduces the fastest tile of every measured case but one near-tie (2560^3: 131 us against 156 us
 // for the tile the former rule, "the largest tile with 256 tiles", picked; 3072^3: 276 against 301).
-int choose_ctile(int64_t M, int64_t N) {
-    static const int bm[fg::CTILE_COUNT] = {256, 128, 64};
-    static const int bn[fg::CTILE_COUNT] = {128, 128, 64};
-    static const int per_cu[fg::CTILE_COUNT] = {1, 2, 4};
-    static const double rate_shared[fg::CTILE_COUNT] = {1.0, 0.883, 0.72};
-    static const double rate_alone[fg::CTILE_COUNT] = {1.0, 0.74, 0.45};
-    const int forced = g_force_tile.load(std::memory_order_relaxed);      // tuning override, 0..2 here
+// The 64x64 tile with two K groups: one tile per unit and K steps for both groups, 1024^3 22.4 -> 15.9 us against the tile with
+// one group, 500x700x3000 interleaved 53.5 -> 33.5, 192x640x232 6.5 -> 6.1; with K = 152 the second group does not pay (5.1, 5.6), in a
+// second round neither (1300x1300x800 21.8, 26.4; 1536^2 x 512 21.5, 29.7).
+int choose_ctile(int64_t M, int64_t N, int64_t K) {
+    static const int bm[fg::CTILE_COUNT] = {256, 128, 64, 64};
+    static const int bn[fg::CTILE_COUNT] = {128, 128, 64, 64};
+    static const int per_cu[fg::CTILE_COUNT] = {1, 2, 4, 1};
+    static const double rate_shared[fg::CTILE_COUNT] = {1.0, 0.883, 0.72, 0.7};
+    static const double rate_alone[fg::CTILE_COUNT] = {1.0, 0.74, 0.45, 0.7};
+    const int forced = g_force_tile.load(std::memory_order_relaxed);      // tuning override, 0..3 here
     if (forced >= 0 && forced < fg::CTILE_COUNT) return forced;
     int best = 0;
     double best_cost = -1;
     for (int t = 0; t < fg::CTILE_COUNT; ++t) {
         const int64_t tiles = ((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]);
         const int64_t slots = (int64_t)kNumCU * per_cu[t];
+        if (t == fg::CTILE_64x64_KG2 && (tiles > slots || K <= 160)) continue;
         auto tile_time = [&](int64_t sharing) {     // one tile, `sharing` workgroups on its unit
             const double unit = per_cu[t] == 1 ? rate_alone[t]
                               : rate_alone[t] + (rate_shared[t] - rate_alone[t]) * (double)(sharing - 1) / (per_cu[t] - 1);
@@ -313,7 +317,7 @@ int choose_ctile(int64_t M, int64_t N) {
 const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr) {
     if (plan_out) *plan_out = Plan{0, 1, 1};
     if (q.cplx) {
-        const int t = choose_ctile(q.M, q.N);
+        const int t = choose_ctile(q.M, q.N, q.K);
         if (t < 0) return nullptr;
         const int v = (q.a_kc ? 2 : 0) + (q.b_kc ? 0 : 1);     // nn, nt, tn, tt
         if (q.ilv) return &fg::kernel_table_cplx_il()[t * 4 + v];

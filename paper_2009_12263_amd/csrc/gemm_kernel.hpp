@@ -112,7 +112,7 @@ __device__ __forceinline__ int tile_row(int pos, int rows, int z_count) {
 // B column-major) rather than M/N-contiguous.  STAGES LDS buffers per operand form a ring over K.
 template <int BM_, int BN_, int BK_, int STAGES_, int WGM_, int WGN_, bool A_KC_, bool B_KC_, bool STRIDED_,
           int DIAG_ = 0, int CPLX_ = 0, bool SPREAD_ = false, bool BF16_ = false, bool XFORM_ = false, bool ILV_ = false,
-          bool CSTREAM_ = false, bool CD16_ = false, bool M16_ = false, int KG_ = 1, bool KTURNS_ = false>
+          bool CSTREAM_ = false, bool CD16_ = false, bool M16_ = false, int KG_ = 1, bool KTURNS_ = false, int WAVES_ = 1>
 struct TileCfg {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, STAGES = STAGES_;
     // M16: the product is made of v_mfma_f32_16x16x32 instructions (16x16 results, 32 k per
@@ -128,6 +128,7 @@ struct TileCfg {
     // KTURNS: the groups take the K tiles in turns (group g the tiles g, g + KG, ...) instead of equal runs of them, so
     // that what a unit fetches at a time lies side by side (192x2496x5368, A and B row-major: 21.3 -> 18.0 us).
     static constexpr bool KTURNS = KTURNS_;
+    static constexpr int WAVES = WAVES_;                            // waves per SIMD that the registers are to leave room for
     static constexpr int KINC = KTURNS_ ? KG_ : 1;
     static constexpr int NWAVES = WGM * WGN, NTHREADS = 64 * NWAVES * KG;
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;
@@ -190,8 +191,8 @@ struct TileCfg {
     static_assert(!(CPLX && (DIAG || STRIDED)), "complex products take plain matrices");
     static_assert(!SPREAD || STAGES >= 4 || BK >= 64, "spread refills need slack before the tile is needed");
     static_assert(!M16 || (CPLX == 0 && DIAG == 0 && !ILV && BK == 64), "16x16x32 products: real, non-diagonal operands, two k-slices per tile");
-    static_assert(KG == 1 || (SPLITK_KERNEL && !ILV_ && !M16_), "K groups: plain real matrix kernels");
-    static_assert(KG == 1 || (KG - 1) * BM * BN * 4 <= LDS_BYTES, "the groups' results pass through the rings");
+    static_assert(KG == 1 || (!STRIDED_ && DIAG_ == 0 && !M16_), "K groups: matrix kernels without a diagonal operand");
+    static_assert(KG == 1 || (KG - 1) * BM * BN * 4 * PLANES <= LDS_BYTES, "the groups' results pass through the rings");
     static_assert(!M16 || !STRIDED, "16x16x32 products: matrix kernels (the contraction kernels measured slower with them and are not built)");
     static_assert(!XFORM || (DIAG == 0 && CPLX == 0 && !BF16 && !STRIDED), "element-wise addition on A and B: plain real FP16 matrices");
     static_assert(!CSTREAM || STRIDED, "the streaming variant is a contraction kernel");
@@ -1110,7 +1111,7 @@ __device__ __forceinline__ floatx16 gather_block(const floatx4 (&a16)[Cfg::FI][C
 }
 
 template <class Cfg>
-__global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg::Params p) {
+__global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const typename Cfg::Params p) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     FG_LDS char *smem = (FG_LDS char *)smem_generic;
     constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK;
@@ -1204,7 +1205,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
             else la[q].init(ap[q], m0, wave, lane, tp.a_rs, tp.a_ks, none, none, tp.a_span, tp.K, tp.M);
             if constexpr (Cfg::DIAG == 2) lb[q].init(bp[q], n0, tp.N < tp.K ? tp.N : tp.K, wave, lane);
             else lb[q].init(bp[q], n0, wave, lane, tp.b_rs, tp.b_ks, none, none, tp.b_span, tp.K, tp.N);
-            if constexpr (Cfg::DIAG != 0 || Cfg::SPLITK_KERNEL) {
+            if constexpr (Cfg::DIAG != 0 || Cfg::SPLITK_KERNEL || Cfg::KG > 1) {
                 if (kt0 > 0) { la[q].skip(kt0); lb[q].skip(kt0); }
             }
         }
@@ -1539,7 +1540,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
         }
         if constexpr (Cfg::KG > 1) {
             // the other groups hand their results to group 0, which adds them in a fixed order
-            constexpr int Q = TI * TJ * 4;                  // quads of registers per wave
+            constexpr int Q = P * TI * TJ * 4;              // quads of registers per wave
             FG_LDS floatx4 *ex = (FG_LDS floatx4 *)smem;
             auto at = [&](int g, int q) { return ((g - 1) * Cfg::NWAVES + wave) * Q * 64 + q * 64 + lane; };
             wait_tile<0>();
@@ -1547,7 +1548,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
             if (group > 0) {
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
-                    const AccT &a = acc[0][q / (4 * TJ)][q / 4 % TJ];
+                    const AccT &a = acc[q / (4 * TI * TJ)][q / (4 * TJ) % TI][q / 4 % TJ];
                     ex[at(group, q)] = floatx4{a[4 * (q & 3)], a[4 * (q & 3) + 1], a[4 * (q & 3) + 2], a[4 * (q & 3) + 3]};
                 }
             }
@@ -1559,8 +1560,9 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void gemm_kernel(const typename Cfg:
 #pragma unroll
                     for (int q = 0; q < Q; ++q) {
                         const floatx4 v = ex[at(g, q)];
+                        AccT &a = acc[q / (4 * TI * TJ)][q / (4 * TJ) % TI][q / 4 % TJ];
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) acc[0][q / (4 * TJ)][q / 4 % TJ][4 * (q & 3) + r] += v[r];
+                        for (int r = 0; r < 4; ++r) a[4 * (q & 3) + r] += v[r];
                     }
             }
         }

@@ -69,13 +69,18 @@ const KernelEntry *kernel_table_tt_h16();
 // Diagonal operands: index tile * 4 + {0: A diag, B K-contiguous; 1: A diag, B N-contiguous;
 //                                       2: B diag, A K-contiguous; 3: B diag, A M-contiguous}.
 const KernelEntry *kernel_table_diag();
-// Planar complex: index ctile * 4 + {nn, nt, tn, tt}; ctile 0: 256x128, 1: 128x128, 2: 64x64.
+// Planar complex: index ctile * 4 + {nn, nt, tn, tt}; ctile 0: 256x128, 1: 128x128, 2: 64x64, 3: 64x64 with two K
+// groups (TileCfg::KG), whose K tiles of 64 also fetch K-contiguous operands in whole 128-byte lines (32: 300x400x2048, TN,
+// 26.6 us, 64: 21.5; one group of 32: 33.1).  The 128x128 kernels are held to 256 registers and the planar 64x64 ones to 128
+// (TileCfg::WAVES), so that two and four workgroups fit a unit: left to the compiler they took 496 and 168 (interleaved
+// 3000x2500x1000 on the 128x128 tile 95.0 -> 84.3 us, dual 1532x2368x1112 on the 64x64 tile 42.0 -> 38.9); the interleaved
+// 64x64 kernels, 136, measured 2 to 6 % slower with 128.  Both 64x64 tiles keep the name that callers compare.
 const KernelEntry *kernel_table_cplx();
 // Interleaved complex (real and imaginary part adjacent in A, B, C and D): same indexing.
 const KernelEntry *kernel_table_cplx_il();
 // Planar dual numbers (eps^2 = 0): same indexing as the complex table.
 const KernelEntry *kernel_table_dual();
-enum { CTILE_COUNT = 3 };
+enum { CTILE_64x64_KG2 = 3, CTILE_COUNT = 4 };
 
 // Second pass of a split-K product (splitk_reduce.hip).
 hipError_t launch_splitk_reduce(const float *W, int splits, int tile_begin, int tile_count, int bm, int bn, int tiles_m,
@@ -201,16 +206,18 @@ inline KernelEntry xf_k32_entry(const char *name) {
         return t;                                                                                  \
     }
 
-#define FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, 0, 1, false, false, false, true>
-#define FG_ENTRY_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC, NAME)                                      \
-    { (const void *)gemm_kernel<FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC)>, NAME, BM, BN,                    \
-      FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC)::NTHREADS,                                     \
-      FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC)::LDS_BYTES }
+// KG: K groups (in turns), W: TileCfg::WAVES
+#define FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC, KG, W) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, 0, 1, false, false, false, true, false, false, false, KG, (KG > 1), W>
+#define FG_ENTRY_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC, KG, W, NAME)                               \
+    { (const void *)gemm_kernel<FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC, KG, W)>, NAME, BM, BN,             \
+      FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC, KG, W)::NTHREADS,                              \
+      FG_CFG_IL(BM, BN, BK, ST, WGM, WGN, AKC, BKC, KG, W)::LDS_BYTES }
 
-#define FG_ENTRY_X(BM, BN, BK, ST, WGM, WGN, AKC, BKC, DG, CX, NAME)                                \
-    { (const void *)gemm_kernel<TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, DG, CX>>, NAME, BM, BN,       \
-      TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, DG, CX>::NTHREADS,                        \
-      TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, DG, CX>::LDS_BYTES }
+#define FG_CFG_X(BM, BN, BK, ST, WGM, WGN, AKC, BKC, DG, CX, KG, W) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, DG, CX, false, false, false, false, false, false, false, KG, (KG > 1), W>
+#define FG_ENTRY_X(BM, BN, BK, ST, WGM, WGN, AKC, BKC, DG, CX, KG, W, NAME)                         \
+    { (const void *)gemm_kernel<FG_CFG_X(BM, BN, BK, ST, WGM, WGN, AKC, BKC, DG, CX, KG, W)>, NAME, BM, BN,     \
+      FG_CFG_X(BM, BN, BK, ST, WGM, WGN, AKC, BKC, DG, CX, KG, W)::NTHREADS,                       \
+      FG_CFG_X(BM, BN, BK, ST, WGM, WGN, AKC, BKC, DG, CX, KG, W)::LDS_BYTES }
 
 #define FG_DEFINE_TABLE(FUNC, AKC, BKC, TAG)                                                       \
     const KernelEntry *FUNC() {                                                                    \

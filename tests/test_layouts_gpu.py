@@ -118,3 +118,19 @@ def test_cache_policies_of_complex_results(kind, M):
         say("M=%d N=%d C=%d %s" % (M, N, with_c, kind))
         run_cgemm_case(M, N, 72, ints=True, alpha=2.0, beta=-1.0, with_c=with_c, **kind)
         run_cgemm_case(M, N, 72, fg.FG_ROW, fg.FG_ROW, fg.FG_ROW, ints=True, with_c=with_c, **kind)
+
+
+@pytest.mark.parametrize("kind", [dict(), dict(dual=True), dict(interleaved=True)])
+@pytest.mark.parametrize("la,lb", list(itertools.product(LAYOUTS, LAYOUTS)))
+def test_k_groups_of_complex_products(monkeypatch, kind, la, lb):
+    """The 64x64 tile whose two groups of waves take its K tiles in turns: fewer K tiles than groups, an odd count, a K tail in
+    either group's last tile, edge tiles, several tiles per workgroup; integers, every entry exact."""
+    from tests.parity import delenv, setenv
+    setenv(monkeypatch, "FG_FORCE_TILE", "3")
+    for K in (8, 64, 72, 136, 192, 200, 328):
+        say("K groups K=%d la=%d lb=%d %s" % (K, la, lb, kind))
+        run_cgemm_case(131, 70, K, la, lb, ints=True, pad=8, poison=True, **kind)
+    run_cgemm_case(70, 131, 264, la, lb, fg.FG_ROW, ints=True, alpha=2.0, beta=-1.0, **kind)
+    say("several tiles per workgroup"); run_cgemm_case(1290, 1100, 136, la, lb, ints=True, samples=3000, **kind)
+    delenv(monkeypatch, "FG_FORCE_TILE")
+    say("planner's own choice, floats"); run_cgemm_case(300, 200, 1032, la, lb, **kind)
