@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libflexgemm.so: argument marshalling only.
+"""Thin binding of libflexgemm.so: argument marshalling only, natively for plain device tensors
+(_fastcall.so, csrc/fastcall.cpp), with ctypes for everything else.
 
 The functions have the names and arguments of the C ABI (include/flexgemm.h).  Torch is used
 for device memory and streams; every step of the computation runs in the library's kernels.
@@ -7,6 +8,7 @@ There is no fallback: if the shared library is missing, importing the entry poin
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from dataclasses import dataclass
 from typing import Optional, Sequence
@@ -49,6 +51,7 @@ class FlexGemmError(RuntimeError):
 _current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda dev: torch.cuda.current_stream(dev).cuda_stream)
 _current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 _lib = None
+_fast = None
 
 
 def load_library() -> C.CDLL:
@@ -92,8 +95,22 @@ def load_library() -> C.CDLL:
         lib.fg_probe_mfma_k32.argtypes = [vp, i64, i32, C.POINTER(C.c_int64), vp]
         lib.fg_probe_kloop_mix.restype = C.c_int
         lib.fg_probe_kloop_mix.argtypes = [vp, i64, i32, C.POINTER(C.c_int64), vp]
+        _load_fastcall(lib)
         _lib = lib
     return _lib
+
+
+def _load_fastcall(lib: C.CDLL) -> None:
+    global _fast
+    path = os.path.join(_PKG, "_fastcall.so")
+    if not os.path.exists(path):
+        raise ImportError("_fastcall.so is not built: run `python -m paper_2009_12263_amd.build`")
+    spec = importlib.util.spec_from_file_location(__package__ + "._fastcall", path)
+    fast = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(fast)
+    fast.setup(Matrix, _current_raw_stream, _current_device,
+               *(C.cast(fn, C.c_void_p).value for fn in (lib.fg_gemm, lib.fg_gemm_ex, lib.fg_gemm_noalloc, lib.fg_gemm_dual, lib.fg_contract)))
+    _fast = fast
 
 
 _DTYPES = {torch.float16: FG_F16, torch.bfloat16: FG_BF16, torch.float32: FG_F32, torch.complex32: FG_CF16, torch.complex64: FG_CF32}
@@ -187,7 +204,10 @@ def fg_gemm(M: int, N: int, K: int, alpha: float, A: Optional[Matrix], B: Option
     """D = act(alpha * op(A) * op(B) + beta * C + bias); see fg_gemm in include/flexgemm.h.
     With ``a_add``, ``b_add`` or ``c_act`` the call goes to fg_gemm_ex (transforms on loaded elements);
     with ``noalloc`` to fg_gemm_noalloc (same arguments as fg_gemm_ex)."""
-    lib = load_library()
+    lib = _lib or load_library()
+    st = _fast.gemm(M, N, K, alpha, A, B, beta, C_, D, bias, bias_dim, act, stream, a_add, b_add, c_act, noalloc)
+    if st >= 0:
+        return st if st == FG_OK else _check(st, raise_on_error)
     if M > 0 and N > 0:          # an empty result launches nothing
         _check_extent(A, M, K, "A"); _check_extent(B, K, N, "B"); _check_extent(C_, M, N, "C"); _check_extent(D, M, N, "D")
     sa = A._struct() if A is not None else None
@@ -212,7 +232,10 @@ def fg_gemm(M: int, N: int, K: int, alpha: float, A: Optional[Matrix], B: Option
 def fg_gemm_dual(M: int, N: int, K: int, alpha: float, A: Optional[Matrix], B: Optional[Matrix], beta: float,
                  C_: Optional[Matrix], D: Optional[Matrix], stream=None, raise_on_error: bool = True) -> int:
     """Dual-number product on planar (value, dual part) matrices; see fg_gemm_dual in include/flexgemm.h."""
-    lib = load_library()
+    lib = _lib or load_library()
+    st = _fast.dual(M, N, K, alpha, A, B, beta, C_, D, stream)
+    if st >= 0:
+        return st if st == FG_OK else _check(st, raise_on_error)
     if M > 0 and N > 0:          # an empty result launches nothing
         _check_extent(A, M, K, "A"); _check_extent(B, K, N, "B"); _check_extent(C_, M, N, "C"); _check_extent(D, M, N, "D")
     sa = A._struct() if A is not None else None
@@ -246,7 +269,10 @@ def fg_contract(modesA: Sequence[int], stridesA: Sequence[int], A: torch.Tensor,
                 extents: dict, alpha: float = 1.0, beta: float = 0.0, stream=None, raise_on_error: bool = True) -> int:
     """Cout = alpha * contraction(A, B) + beta * Cin; see fg_contract in include/flexgemm.h.
     ``extents`` maps each integer mode label to its extent."""
-    lib = load_library()
+    lib = _lib or load_library()
+    st = _fast.contract(modesA, stridesA, A, modesB, stridesB, B, modesC, stridesC, Cin, Cout, extents, alpha, beta, stream)
+    if st >= 0:
+        return st if st == FG_OK else _check(st, raise_on_error)
     positive = all(int(v) > 0 for v in extents.values())
     for name, t, modes, strides in (("A", A, modesA, stridesA), ("B", B, modesB, stridesB), ("Cin", Cin, modesC, stridesC),
                                     ("Cout", Cout, modesC, stridesC)):

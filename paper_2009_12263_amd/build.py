@@ -1,4 +1,5 @@
-"""Build libflexgemm.so (HIP kernels + C ABI) for gfx950, in-tree, with hipcc.
+"""Build libflexgemm.so (HIP kernels + C ABI) for gfx950, in-tree, with hipcc, and the binding's native
+marshalling (_fastcall.so, csrc/fastcall.cpp) with the host compiler.
 
 Objects go to ``_build/`` at the repository root; the shared library is written next to this
 file so that it travels with the package.  ``python -m paper_2009_12263_amd.build`` rebuilds.
@@ -10,14 +11,17 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libflexgemm.so")
+FASTCALL = os.path.join(PKG, "_fastcall.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = os.environ.get("CXX", "g++")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-inline-asm",
          "-Wno-unused-command-line-argument",
          # keep the compiler from forming packed-FP32 instructions: some of their forms have given
@@ -50,11 +54,32 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def _build_fastcall(force: bool) -> None:
+    src = os.path.join(CSRC, "fastcall.cpp")
+    if not (force or _stale(FASTCALL, [src] + glob.glob(os.path.join(ROOT, "include", "*.h")))):
+        return
+    import torch
+    base = os.path.dirname(torch.__file__)
+    lib = os.path.join(base, "lib")
+    tmp = FASTCALL + ".tmp.%d" % os.getpid()
+    cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w", src, "-o", tmp,
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"],
+           "-L" + lib, "-Wl,-rpath," + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lpthread"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("%s failed on %s:\n%s" % (CXX, src, r.stdout))
+    os.replace(tmp, FASTCALL)
+
+
 def build(force: bool = False, jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = sources()
-    with cf.ThreadPoolExecutor(max_workers=min(jobs, len(srcs))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(jobs, len(srcs) + 1)) as ex:
+        fastcall = ex.submit(_build_fastcall, force)
         objs = list(ex.map(lambda s: _compile(s, force), srcs))
+        fastcall.result()
     if force or _stale(LIB, objs):
         tmp = LIB + ".tmp.%d" % os.getpid()
         subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)

@@ -339,3 +339,20 @@ def test_planner_over_random_shapes_never_fails_and_its_splits_fit_the_workspace
             tiles = -(-Mn // bm) * -(-Nn // bn)
             assert 2 <= S <= 64 and tiles * S * bm * bn * 4 <= 64 << 20, (plan, M, N, K)
             assert variant in (fg.FG_PLAN_REAL, fg.FG_PLAN_REAL_BF16, fg.FG_PLAN_REAL_AB_ADD), plan     # the reduction pass writes FP32 real results
+
+
+def test_native_marshalling_leaves_everything_but_device_tensors_to_the_binding():
+    import torch
+    fg.load_library()
+    t = torch.zeros(64 * 64, dtype=torch.float16)
+    A, D = fg.Matrix(t, fg.FG_COL, 64), fg.Matrix(t.float(), fg.FG_COL, 64)
+    call = [64, 64, 64, 1.0, A, A, 0.0, None, D, None, 0, 0, None, 0.0, 0.0, 0, False]
+    assert fg._fast.gemm(*call) == -1                                   # host tensors
+    assert fg._fast.gemm(*call[:-1]) == -1 and fg._fast.gemm() == -1
+    for at, v in ((0, "64"), (0, 64.0), (0, True), (0, 1 << 70), (3, None), (4, t), (4, None), (9, t), (16, 0)):
+        assert fg._fast.gemm(*(call[:at] + [v] + call[at + 1:])) == -1, (at, v)
+    assert fg._fast.dual(64, 64, 64, 1.0, A, A, 0.0, None, D, None) == -1
+    ext = {0: 64, 1: 64, 2: 64}
+    assert fg._fast.contract([0, 2], [1, 64], t, [2, 1], [1, 64], t, [0, 1], [1, 64], None, t.float(), ext, 1.0, 0.0, None) == -1
+    with pytest.raises(TypeError):
+        fg._fast.setup(1, 2)

@@ -257,6 +257,44 @@ def test_binding_refuses_tensors_smaller_than_the_matrix():
     assert bool((D == 0.0).all())
 
 
+def test_native_marshalling_takes_plain_device_tensors_only():
+    """Plain calls are marshalled natively (status 0), with the results of the binding's own path; what the binding has to look
+    at itself, or refuse, comes back as -1 before anything is launched."""
+    import numpy as np
+    M, N, K = 96, 80, 64
+    A = torch.randn(M * K, device="cuda").half(); B = torch.randn(K * N, device="cuda").half(); c = torch.randn(M * N, device="cuda")
+    mat = lambda t, ld, **kw: fg.Matrix(t, fg.FG_COL, ld, **kw)
+    def args(D, **kw):
+        d = dict(M=M, N=N, K=K, alpha=0.5, A=mat(A, M), B=mat(B, K), beta=2, C=mat(c, M), D=D, bias=None, bias_dim=0, act=0, stream=None,
+                 a_add=0.0, b_add=0.0, c_act=0, noalloc=False)
+        d.update(kw)
+        return list(d.values())
+    for kw in (dict(), dict(C=None, beta=0.0), dict(bias=c[:M], act=fg.FG_ACT_RELU), dict(bias=c[:N], bias_dim=1), dict(a_add=0.25, c_act=1), dict(noalloc=True)):
+        new = [torch.full((M * N,), float("nan"), device="cuda") for _ in range(2)]
+        assert fg._fast.gemm(*args(mat(new[0], M), **kw)) == 0, kw
+        a = args(mat(new[1], M), **kw)
+        fg.fg_gemm(*a[:12], stream=torch.cuda.current_stream(), a_add=a[13], b_add=a[14], c_act=a[15], noalloc=a[16])   # a stream: the binding's own path
+        assert torch.equal(new[0], new[1]), kw
+    D = torch.empty(M * N, device="cuda")
+    for kw in (dict(A=mat(A[:-1], M)), dict(B=mat(B.cpu(), K)), dict(C=mat(c, M + 1)), dict(M=np.int64(M)), dict(stream=torch.cuda.current_stream()),
+               dict(A=mat(A.double(), M)), dict(A=mat(A.as_subclass(type("T", (torch.Tensor,), {})), M)), dict(act=2), dict(bias=c.cpu()[:M]), dict(M=0)):
+        assert fg._fast.gemm(*args(mat(D, M), **kw)) == -1, kw
+    with pytest.raises(ValueError):
+        fg.fg_gemm(*args(mat(D, M), C=mat(c, M + 1))[:12])
+    with pytest.raises(fg.FlexGemmError):                                # a status other than 0 is raised as before
+        fg.fg_gemm(*args(mat(D, M), A=mat(A, M - 1))[:12])
+    ext = {0: M, 1: N, 2: K}
+    call = [[0, 2], [1, M], A, [2, 1], [1, K], B, [0, 1], [1, M], c, D, ext, 1.0, 1.0, None]
+    assert fg._fast.contract(*call) == 0
+    ref = torch.empty_like(D)
+    fg.fg_contract(*call[:9], ref, ext, 1.0, 1.0, stream=torch.cuda.current_stream())
+    assert torch.equal(D, ref)
+    for at, v in ((1, [1, M + 1]), (2, A[:-1]), (9, D[:-1]), (8, c[:-1]), (10, {0: M, 1: N}), (10, {0: M, 1: N, 2: 0}), (13, torch.cuda.current_stream()), (0, (0.0, 2))):
+        assert fg._fast.contract(*(call[:at] + [v] + call[at + 1:])) == -1, at
+    with pytest.raises(fg.FlexGemmError):
+        fg.fg_contract(*call[:10], {0: M, 1: N}, 1.0, 1.0)
+
+
 def test_transforms_are_rejected_where_unsupported():
     H = torch.zeros(64 * 64, dtype=torch.float16, device="cuda")
     Bf = torch.zeros(64 * 64, dtype=torch.bfloat16, device="cuda")
