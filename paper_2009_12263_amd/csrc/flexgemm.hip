@@ -1149,6 +1149,14 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
         // 24.4 -> 21.6, dual 2048^2 x 512 32.0 -> 29.4; without C 22.4 streamed and 23.6 kept, complex 2048^3, 100 MB, 77.4 and 78.4).
         else p.cd_cached = off_lines(q.ilv ? 8 : 32) || (q.C && 2 * bytes <= (80ll << 20));
     }
+    {
+        // An operand that one row (column) of tiles reads is read once.  From 112 MB on, when little of it is still in the
+        // memory-side cache from the call before, its loads stream past the L2 if its rows are whole lines (a line that two
+        // K tiles share would be fetched twice): three operand sets in turn, 134 MB 45.6 -> 40.8 us, 117 MB 39.7 -> 37.4,
+        // 268 MB 71.1 -> 63.3; 100 MB 34.2, 34.5 and 36.5, 38.0; 67 MB, which stays there, 17.5, 20.2.
+        auto once = [](const void *ptr, int64_t ld, int64_t bytes) { return (uintptr_t)ptr % 128 == 0 && ld % 64 == 0 && bytes >= (112ll << 20); };
+        p.once = p.tiles_m == 1 && once(q.B, q.ldb, q.N * q.K * 2) ? 1 : p.tiles_n == 1 && once(q.A, q.lda, q.M * q.K * 2) ? 2 : 0;
+    }
     hipStream_t stream = (hipStream_t)hip_stream;
     if (plan.splits <= 1 && plan.tail_splits <= 1) return launch(k, p, stream);
 

@@ -61,7 +61,9 @@ struct GemmParams {
     int64_t ldc, ldd;                 // column-major C and D: (m, n) at m + n*ld
     float alpha, beta;
     int32_t bias_dim, act, has_c;
-    int32_t diag_a;                   // A is diagonal: A points at the diagonal entries
+    // Kernels of TileCfg::ONCE: 1: B is fetched by one row of tiles only, 2: A by one column of tiles (set by the host): its
+    // loads stream past the L2.
+    int32_t once;
     // transforms on loaded elements (Section 4.3): C_ij := act(C_ij); with TileCfg::XFORM also
     // A_ik := half(A_ik + a_add), B_kj := half(B_kj + b_add), the addend as two packed halves
     int32_t c_act;
@@ -163,6 +165,10 @@ struct TileCfg {
     // Half as many roundings follow one another in each sum: the error against 64 bits of 1024^3 is 1.1e-7 with two
     // groups of two sets, as with the four K groups that served it before, 1.5e-7 with two groups of one.
     static constexpr int ACC_SETS = !STRIDED_ && DIAG_ == 0 && CPLX_ == 0 && !M16_ && (KTURNS_ || STAGES_ == 4) ? 2 : 1;
+    // ONCE: the kernel has K loops whose loads of A or of B carry the streaming policy, for operands that are read once:
+    // narrow products, bound by reading their large operand, which otherwise displaces the small one that all units share
+    // (128x4096x16384, B 134 MB: 45.6 -> 40.1 us; where other tiles read the operand again it costs: 8192x1024x4096 72 -> 76).
+    static constexpr bool ONCE = ACC_SETS == 2;
     // SPREAD: the refill loads of a ring buffer are issued one at a time between the MFMAs of two
     // k-slices (A's part in the slice after the buffer is retired, B's part in the next one)
     // instead of as one burst: a burst from all waves queues up in the compute unit's single
@@ -253,11 +259,18 @@ constexpr uint32_t kOutOfRange = 0x80000000u;   // a byte offset no descriptor o
 // publishes a tile.  (Written as assembly because the compiler, not knowing which LDS bytes a
 // direct load writes, otherwise drains every outstanding load before any LDS read, which would
 // serialise the prefetch of later tiles with the product of the current one.)
+template <bool STREAM = false>
 __device__ __forceinline__ void load16_to_lds(u32x4 rsrc, uint32_t lds_addr, uint32_t voff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :
-                 : "s"(lds_addr), "v"(voff), "s"(rsrc)
-                 : "memory", "m0");
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+                     :
+                     : "s"(lds_addr), "v"(voff), "s"(rsrc)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                     :
+                     : "s"(lds_addr), "v"(voff), "s"(rsrc)
+                     : "memory", "m0");
 }
 
 // Wait until at most NEWER of this wave's direct loads are still in flight (loads complete in
@@ -436,6 +449,7 @@ struct TileLoader {
             klim = kdim - ktile * BK;
         }
     }
+    template <bool STREAM = false>
     __device__ __forceinline__ void issue_slab(FG_LDS char *lds_tile, int wave, int s) {
         uint32_t dst = (uint32_t)(uintptr_t)lds_tile + (uint32_t)(wave * SLABS + s) * 1024u;
         uint32_t v = voff[s];
@@ -447,7 +461,7 @@ struct TileLoader {
             // multiple of BK the last step of each pass hangs over it: those k are zero-filled
             if (kdigit[0] + kchunk[s] >= kext[0]) v = kOutOfRange;
         }
-        load16_to_lds(rsrc_cur, dst, v);
+        load16_to_lds<STREAM>(rsrc_cur, dst, v);
     }
     __device__ __forceinline__ void advance() {
         if constexpr (!STRIDED) {
@@ -470,10 +484,11 @@ struct TileLoader {
         }
         ktile += KINC;
     }
+    template <bool STREAM = false>
     __device__ __forceinline__ void issue(FG_LDS char *lds_tile, int wave) {
         begin();
 #pragma unroll
-        for (int s = 0; s < SLABS; ++s) issue_slab(lds_tile, wave, s);
+        for (int s = 0; s < SLABS; ++s) issue_slab<STREAM>(lds_tile, wave, s);
         advance();
     }
 
@@ -1217,6 +1232,11 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
                     lb[0].fetch();
                     la[0].commit(lds_a + st * Cfg::A_TILE_BYTES, lds_a + Cfg::A_PLANE_BYTES + st * Cfg::A_TILE_BYTES, wave);
                     lb[0].commit(lds_b + st * Cfg::B_TILE_BYTES, lds_b + Cfg::B_PLANE_BYTES + st * Cfg::B_TILE_BYTES, wave);
+                } else if constexpr (Cfg::ONCE) {
+                    if (tp.once == 2) la[0].template issue<true>(lds_a + st * Cfg::A_TILE_BYTES, wave);
+                    else la[0].issue(lds_a + st * Cfg::A_TILE_BYTES, wave);
+                    if (tp.once == 1) lb[0].template issue<true>(lds_b + st * Cfg::B_TILE_BYTES, wave);
+                    else lb[0].issue(lds_b + st * Cfg::B_TILE_BYTES, wave);
                 } else {
 #pragma unroll
                     for (int q = 0; q < P; ++q) {
@@ -1277,7 +1297,8 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
             // that the steady-state body is straight-line code (8192^3: +5 % over testing them per
             // tile, whose booleans lived in vector registers between the MFMAs); the interleaved
             // complex kernels, short of registers, test RA per tile as before.
-            auto tile_body = [&](int kt, auto more_tag, auto ra_tag, auto rb_tag) {
+            auto tile_body = [&](int kt, auto more_tag, auto ra_tag, auto rb_tag, auto once_tag) {
+                [[maybe_unused]] constexpr int ONCE = decltype(once_tag)::value;      // GemmParams::once
                 constexpr bool MORE = decltype(more_tag)::value;
                 const bool RA = Cfg::ILV ? (kt + S < nkt) : decltype(ra_tag)::value;
                 [[maybe_unused]] constexpr bool RB = decltype(rb_tag)::value;
@@ -1491,15 +1512,19 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
                             for (int n = 0; n < Cfg::A_SLABS; ++n)
                                 if (refill_a && i == n * TI / Cfg::A_SLABS) {
 #pragma unroll
-                                    for (int q = 0; q < P; ++q)
-                                        la[q].issue_slab(lds_a + q * Cfg::A_PLANE_BYTES + cur * Cfg::A_TILE_BYTES, wave, n);
+                                    for (int q = 0; q < P; ++q) {
+                                        if constexpr (ONCE == 2) la[q].template issue_slab<true>(lds_a + q * Cfg::A_PLANE_BYTES + cur * Cfg::A_TILE_BYTES, wave, n);
+                                        else la[q].issue_slab(lds_a + q * Cfg::A_PLANE_BYTES + cur * Cfg::A_TILE_BYTES, wave, n);
+                                    }
                                 }
 #pragma unroll
                             for (int n = 0; n < Cfg::B_SLABS; ++n)
                                 if (refill_b && i == n * TI / Cfg::B_SLABS) {
 #pragma unroll
-                                    for (int q = 0; q < P; ++q)
-                                        lb[q].issue_slab(lds_b + q * Cfg::B_PLANE_BYTES + prev * Cfg::B_TILE_BYTES, wave, n);
+                                    for (int q = 0; q < P; ++q) {
+                                        if constexpr (ONCE == 1) lb[q].template issue_slab<true>(lds_b + q * Cfg::B_PLANE_BYTES + prev * Cfg::B_TILE_BYTES, wave, n);
+                                        else lb[q].issue_slab(lds_b + q * Cfg::B_PLANE_BYTES + prev * Cfg::B_TILE_BYTES, wave, n);
+                                    }
                                 }
                         }
                         __builtin_amdgcn_sched_barrier(0);
@@ -1518,18 +1543,38 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
             };
             constexpr std::true_type T{};
             constexpr std::false_type F{};
+            // (written out for the kernels without ONCE, whose code a lambda around it moved)
+            constexpr std::integral_constant<int, 0> O{};
+            if constexpr (Cfg::ONCE) {
+                auto k_loop = [&](auto once_tag) {
+                    if (nkt > 1) {
+                        if (S < nkt) tile_body(0, T, T, F, once_tag); else tile_body(0, T, F, F, once_tag);
+                        int kt = 1;
+                        for (; kt + S < nkt; ++kt) tile_body(kt, T, T, T, once_tag);
+                        for (; kt + 1 < nkt; ++kt) {
+                            if (kt - 1 + S < nkt) tile_body(kt, T, F, T, once_tag); else tile_body(kt, T, F, F, once_tag);
+                        }
+                    }
+                    tile_body(nkt - 1, F, F, F, once_tag);
+                };
+                const int once = load_param<int32_t>(offsetof(GemmParams, once));
+                if (once == 1) k_loop(std::integral_constant<int, 1>{});
+                else if (once == 2) k_loop(std::integral_constant<int, 2>{});
+                else k_loop(O);
+            } else {
             if constexpr (Cfg::ILV) {
-                for (int kt = 0; kt + 1 < nkt; ++kt) tile_body(kt, T, F, F);     // (RA is evaluated in the body)
+                for (int kt = 0; kt + 1 < nkt; ++kt) tile_body(kt, T, F, F, O);     // (RA is evaluated in the body)
             } else
             if (nkt > 1) {
-                if (S < nkt) tile_body(0, T, T, F); else tile_body(0, T, F, F);
+                if (S < nkt) tile_body(0, T, T, F, O); else tile_body(0, T, F, F, O);
                 int kt = 1;
-                for (; kt + S < nkt; ++kt) tile_body(kt, T, T, T);
+                for (; kt + S < nkt; ++kt) tile_body(kt, T, T, T, O);
                 for (; kt + 1 < nkt; ++kt) {            // at most S - 1 tiles: nothing left to refill with
-                    if (kt - 1 + S < nkt) tile_body(kt, T, F, T); else tile_body(kt, T, F, F);
+                    if (kt - 1 + S < nkt) tile_body(kt, T, F, T, O); else tile_body(kt, T, F, F, O);
                 }
             }
-            tile_body(nkt - 1, F, F, F);
+            tile_body(nkt - 1, F, F, F, O);
+            }
         }
 
         if constexpr (SETS == 2) {

@@ -536,6 +536,21 @@ def test_ring_of_three_buffers(monkeypatch, la, lb):
     delenv(monkeypatch, "FG_FORCE_TILE")
 
 
+@pytest.mark.parametrize("la,lb", list(itertools.product(LAYOUTS, LAYOUTS)))
+def test_operands_that_are_read_once(monkeypatch, la, lb):
+    """A large operand that one row or column of tiles reads is fetched with the streaming policy (K loops of their own): B, then
+    A, on the tiles that have them, with K split and in one pass; sampled entries of integer products, exact."""
+    for tile, small in (("4", 72), ("7", 40), ("8", 40)):
+        setenv(monkeypatch, "FG_FORCE_TILE", tile)
+        for split in ("1", "3"):
+            setenv(monkeypatch, "FG_FORCE_SPLIT", split)
+            say("tile %s split %s la=%d lb=%d: B, A" % (tile, split, la, lb))
+            run_gemm_case(small, 4096, 16384, la, lb, ints=True, samples=1500)
+            run_gemm_case(4096, small, 16384, la, lb, ints=True, samples=1500, bias_dim=0)
+    delenv(monkeypatch, "FG_FORCE_TILE")
+    delenv(monkeypatch, "FG_FORCE_SPLIT")
+
+
 def test_operands_larger_than_2_gib():
     """A (then B) alone spans more than 2 GiB, once with K along columns and once along rows:
     the panels of the later tiles and the later K steps start beyond the reach of a 32-bit byte
