@@ -290,7 +290,7 @@ int choose_ctile(int64_t M, int64_t N, int64_t K) {
     static const int bm[fg::CTILE_COUNT] = {256, 128, 64, 64};
     static const int bn[fg::CTILE_COUNT] = {128, 128, 64, 64};
     static const int per_cu[fg::CTILE_COUNT] = {1, 2, 4, 1};
-    static const double rate_shared[fg::CTILE_COUNT] = {1.0, 0.883, 0.72, 0.7};
+    static const double rate_shared[fg::CTILE_COUNT] = {1.0, 0.94, 0.72, 0.7};
     static const double rate_alone[fg::CTILE_COUNT] = {1.0, 0.74, 0.45, 0.7};
     const int forced = g_force_tile.load(std::memory_order_relaxed);      // tuning override, 0..3 here
     if (forced >= 0 && forced < fg::CTILE_COUNT) return forced;
@@ -308,6 +308,8 @@ int choose_ctile(int64_t M, int64_t N, int64_t K) {
         const int64_t full = tiles / slots, rest = tiles - full * slots;
         double cost = (double)full * tile_time(per_cu[t]);
         if (rest > 0) cost += tile_time((rest + kNumCU - 1) / kNumCU);
+        // more than a round of small tiles: dual 2701x3001x1504 141 us, 126 on the 128x128 tile, complex 151 and 140
+        if (t == 2 && tiles > slots) cost *= 1.29;
         if (best_cost < 0 || cost < best_cost) { best = t; best_cost = cost; }
     }
     return best;
@@ -1138,16 +1140,20 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
         // against 87.4 us, 4096^3: -6 %, 5000 x 3000 x 2000: 76.7 against 103.1 us back to back;
         // equal on cache-cold operands; from 300 MB up streaming wins by 4 to 9 %).  Columns that do not begin on a
         // 128-byte line share lines, which a streamed C fetches from memory once for each: kept in the caches whatever
-        // the size (6708x5150x96 148.7 -> 98.2 us, 8180x6100x512 211.6 -> 171.2, 6008x8000x2000 289 -> 272; without C equal).
+        // the size while A and B, which they push out of the memory-side cache, are not larger than half of it (6708x5150x96 148.7 -> 98.2 us,
+        // 8180x6100x512 211.6 -> 171.2, 5000x6000x4000, A and B 88 MB, 276 -> 270; 5000x5004x7000, 140 MB, 427 streamed, 437; without C equal).
         const int64_t es_cd = q.cd16 ? 2 : 4;
         const int64_t bytes = (q.M * q.K + q.K * q.N) * 2 + q.M * q.N * es_cd * (q.C ? 2 : 1);
         auto off_lines = [&](int64_t elems) { return q.ldd % elems != 0 || (q.C && q.ldc % elems != 0); };
-        if (!q.cplx) p.cd_cached = bytes <= (256ll << 20) || (q.C && off_lines(32));
-        // Complex and dual products, whose planes or pairs double all of it: off the lines likewise, with C or without (4040x2048x400
-        // complex 72.3 -> 62.9 us, without C 52.9 -> 39.0, dual 1532x2368x1112 41.3 -> 34.2), but interleaved columns on
-        // half a line stream (3000x2500x1000 84.5, 88.2 kept).  On the lines kept up to 80 MB and with C only (1536^2 x 512
-        // 24.4 -> 21.6, dual 2048^2 x 512 32.0 -> 29.4; without C 22.4 streamed and 23.6 kept, complex 2048^3, 100 MB, 77.4 and 78.4).
-        else p.cd_cached = off_lines(q.ilv ? 8 : 32) || (q.C && 2 * bytes <= (80ll << 20));
+        if (!q.cplx) p.cd_cached = bytes <= (256ll << 20) || (q.C && off_lines(32) && 2 * (q.M * q.K + q.K * q.N) <= (112ll << 20));
+        // Complex and dual products, whose planes or pairs double all of it, stream what is on the lines, but for products with C up
+        // to 80 MB (1536^2 x 512 24.4 -> 21.6, dual 2048^2 x 512 32.0 -> 29.4; without C 22.4 streamed and 23.6 kept, complex 2048^3,
+        // 100 MB, 77.4 and 78.4).  Off the lines (interleaved: off the half lines; 3000x2500x1000 84.5 streamed, 88.2 kept) up to 80 MB
+        // with C or without (dual 1532x2368x1112 without 41.3 -> 34.2), and above while A and B are small (4040x2048x400 complex
+        // 72.3 -> 62.9): larger ones stay in the memory-side cache only if C and D do not push them out, and the K loop waits for
+        // memory (dual 899x3562x3832, A and B 68 MB: 124 streamed, 156 kept).
+        else p.cd_cached = 2 * bytes <= (80ll << 20) ? q.C || off_lines(q.ilv ? 8 : 32)
+                                                     : off_lines(q.ilv ? 8 : 32) && 4 * (q.M * q.K + q.K * q.N) <= (32ll << 20);
     }
     {
         // An operand that one row (column) of tiles reads is read once.  From 112 MB on, when little of it is still in the
