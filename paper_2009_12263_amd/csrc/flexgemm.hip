@@ -149,6 +149,9 @@ constexpr Rates kRates = {{1, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
 // The rates that decided what a call needs scratch memory for before the 64x64 tile had K groups
 // (see within_promised_scratch).
 constexpr Rates kPromisedRates = {{1.0, 0.8, 0.73, 0.45, 0.57, 1.0, 0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0, 0}, 2e-6, 25e9, 6e-6, 3e12, {}, false};
+// The rates of the planner before the larger rings (four K groups as tile 7, no 64x128 tile): see within_promised_scratch.
+constexpr Rates kFormerRates = {{1.0, 0.8, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29, 0}, {1.0, 0.8, 0.43, 0.135, 0.645, 1.0, 0.27, 0.29, 0}, 1.6e-6, 27e9, 12.3e-6, 7.2e12,
+                                {0, 0, 0, 0, 0, 0, 0.1, 0.1, 0}, false};
 // Contractions have neither K groups nor splits, which the rates above were fitted with: over 320 contractions those
 // picked the fastest tile to within 2.4 % on average and 44 % at most (192 x 960 rows and columns over 2560: 33.8 us
 // with the deep 128x128 tile, 23.6 with the 64x64 tile), these to within 0.5 % and 43 %, and no tile slower than
@@ -184,7 +187,7 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
         if (t == fg::TILE_64x64 && !allow_smallest) continue;
         if (t == fg::TILE_128x128_DEEP && !allow_deep) continue;
         if (t == fg::TILE_256x256_K32) continue;
-        if (t >= fg::TILE_64x64_KG2 && !allow_groups) continue;
+        if (t >= fg::TILE_64x64_KG2 && (!allow_groups || rates.shared[t] == 0)) continue;
         const int64_t tiles = ((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]) * batches;
         const int64_t slots = (int64_t)kNumCU * per_cu[t];
         const int64_t slot_bytes = (int64_t)bm[t] * bn[t] * 4;
@@ -204,11 +207,11 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
             // the C read and D write of a tile stream at what one compute unit gets of the memory
             // bandwidth, divided among the workgroups that share the unit
             const double epilogue = round_fixed + (double)n * 8.0 * bm[t] * bn[t] / cu_cd_bw;
-            return 2.0 * bm[t] * bn[t] * (double)((nk + S - 1) / S) * 64 / (cu_flops * rate) * lines + epilogue;
+            return 2.0 * bm[t] * bn[t] * (double)((nk + S - 1) / S) * 64 / (cu_flops * rate) * (S == 1 || rates.last_round ? lines : 1) + epilogue;
         };
         auto reduce_time = [&](int64_t ntile, int S) { return reduce_launch + (2.0 * S + 2.0) * (double)ntile * slot_bytes / reduce_bw; };
         auto consider = [&](int S, int tail, double cost) {
-            if (groups > 1 && force_tile < 0 && nk / (S * tail) < (t == fg::TILE_64x64_KG2 ? 8 : 12)) return;
+            if (groups > 1 && force_tile < 0 && nk / (S * tail) < (t == fg::TILE_64x64_KG2 ? 8 : rates.last_round ? 12 : 16)) return;
             if (best_cost < 0 || cost < best_cost) { best = Plan{t, S, tail}; best_cost = cost; }
         };
         // (a) every tile split S ways (S = 1: the plain launch)
@@ -226,7 +229,7 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
         }
         // (b) whole rounds in one pass, the tiles of the last, partly filled round split over K
         const int64_t full = tiles / slots * slots, rest = tiles - full;
-        const double tail_round = t == fg::TILE_256x128 ? 1.09 : 1;      // in front of a tail the 256x256 tile is as fast: 4100^2 x 4096 185.0 us, 187.5
+        const double tail_round = rates.last_round && t == fg::TILE_256x128 ? 1.09 : 1;      // in front of a tail the 256x256 tile is as fast: 4100^2 x 4096 185.0 us, 187.5
         if (may_split && full > 0 && rest > 0 && force_split < 1 && force_tail != 1) {
             for (int S : split_options) {
                 if (S == 1) continue;
@@ -264,15 +267,25 @@ int64_t scratch_need(const Plan &plan, int64_t M, int64_t N) {
 }
 
 // Which scratch memory a call needs is part of what it promises: a call that needed none can be
-// captured before the workspace exists, one whose partial products fit the static array can be made
-// without allocation.  A plan that leaves the class (none, static array, workspace) of the plan by the promised
-// rates is therefore replaced by the best one that does not (0.5 % of random shapes).  Costs a split call 1.5 us on the host.
+// captured before the workspace exists and beside others, one whose partial products fit the static array can be made
+// without allocation.  A plan that leaves the class (none, static array, workspace) of the plan that the former planners made
+// (kFormerRates, itself held to the classes of kPromisedRates) is therefore replaced by the best one that does not (6 % of
+// random shapes).  Costs a split call 3 us on the host.
 Plan within_promised_scratch(Plan plan, int64_t M, int64_t N, int64_t K, int k32, int straddling) {
     const int64_t need = scratch_need(plan, M, N);
     if (need == 0 || g_force_split.load(std::memory_order_relaxed) >= 1 || g_force_tail.load(std::memory_order_relaxed) > 1 ||
         g_force_tile.load(std::memory_order_relaxed) >= 0) return plan;
-    const int64_t promised = scratch_need(choose_plan(M, N, K, true, true, 1, true, k32, false, kWorkspaceBytes, kPromisedRates), M, N);
-    const int64_t limit = promised == 0 ? 0 : promised <= kStaticScratchBytes ? kStaticScratchBytes : kWorkspaceBytes;
+    auto limit_of = [](int64_t bytes) { return bytes == 0 ? 0 : bytes <= kStaticScratchBytes ? kStaticScratchBytes : kWorkspaceBytes; };
+    const int64_t promised = limit_of(scratch_need(choose_plan(M, N, K, true, true, 1, true, k32, false, kWorkspaceBytes, kPromisedRates), M, N));
+    auto former_plan = [&](int lines) {
+        const Plan p = choose_plan(M, N, K, true, true, 1, true, k32, true, kWorkspaceBytes, kFormerRates, lines);
+        return scratch_need(p, M, N) <= promised ? p : choose_plan(M, N, K, promised > 0, true, 1, true, k32, true, promised, kFormerRates, lines);
+    };
+    // rows off the lines counted in long K loops only, and only for a split
+    const int lines = K > 3904 ? straddling : 0;
+    Plan former = former_plan(lines);
+    if (lines > 0 && former.splits == 1 && former.tail_splits == 1) former = former_plan(0);
+    const int64_t limit = limit_of(scratch_need(former, M, N));
     return need <= limit ? plan : choose_plan(M, N, K, limit > 0, true, 1, true, k32, true, limit, kRates, straddling);
 }
 

@@ -356,3 +356,10 @@ def test_native_marshalling_leaves_everything_but_device_tensors_to_the_binding(
     assert fg._fast.contract([0, 2], [1, 64], t, [2, 1], [1, 64], t, [0, 1], [1, 64], None, t.float(), ext, 1.0, 0.0, None) == -1
     with pytest.raises(TypeError):
         fg._fast.setup(1, 2)
+
+
+def test_products_that_needed_no_scratch_memory_are_not_split():
+    """Calls that were made in one pass before the larger rings stay free of scratch memory, though a split is now estimated
+    faster: they may be captured before the workspace exists, and beside other calls."""
+    for (M, N, K, la, lb) in ((46, 4275, 3392, 0, 1), (1191, 58, 2728, 1, 0), (784, 16, 2608, 0, 0), (137, 866, 2088, 1, 0), (73, 21, 2184, 0, 0)):
+        assert "split" not in fg.fg_gemm_plan(M, N, K, la, lb), (M, N, K)
