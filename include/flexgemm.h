@@ -16,20 +16,22 @@
  * General conventions
  *   - Every data pointer (matrix/tensor elements, bias) is a DEVICE pointer to memory the
  *     caller owns.  The library never allocates, frees, retains or copies caller memory.
- *   - The library owns one 64 MiB device workspace per GPU, allocated by fg_init() or by the
- *     first fg_gemm / fg_gemm_ex call that needs it and kept until the process ends.  It holds the
- *     partial products of split-K calls (outputs with too few tiles to fill the GPU and a long K,
- *     or the leftover tiles of the last, partly filled round of a larger output, are computed as
- *     partial products over ranges of K plus a reduction pass, the cross-workgroup reduction
- *     use of the epilogue in Section 4.2.5).  fg_gemm_plan() tells whether a problem is computed
- *     that way ("+splitk<n>" / "+tailsplitk<n>" in the plan name).  All such calls on one GPU share
- *     the workspace: calls on one stream are ordered anyway, and a call on another stream than the
- *     previous user's is made to wait on the device (an event recorded after that user's reduction
- *     pass; after a call on the default stream, after all that was issued there until then) until the workspace is free, so calls on different streams may be issued freely; they
- *     are serialised, not run side by side.  The exception is a stream under graph capture: the
- *     caller orders captured split-K calls against other users of the workspace, and the workspace
- *     must exist before the capture begins (fg_init(); FG_ERR_UNSUPPORTED otherwise).  The partial
- *     products are added in a fixed order, so results do not depend on scheduling.
+ *   - The library owns two 64 MiB device workspaces per GPU, one of the default stream and one of
+ *     all others, allocated by fg_init() or by the first fg_gemm / fg_gemm_ex call that needs one
+ *     and kept until the process ends (where there is memory for one only, all streams share it).
+ *     They hold the partial products of split-K calls (outputs with too few tiles to fill the GPU
+ *     and a long K, or the leftover tiles of the last, partly filled round of a larger output, are
+ *     computed as partial products over ranges of K plus a reduction pass, the cross-workgroup
+ *     reduction use of the epilogue in Section 4.2.5).  fg_gemm_plan() tells whether a problem is
+ *     computed that way ("+splitk<n>" / "+tailsplitk<n>" in the plan name).  Calls on one stream are
+ *     ordered anyway, and a call on another stream than the previous user's is made to wait on the
+ *     device (an event recorded after that user's reduction pass) until the workspace is free, so
+ *     calls on different streams may be issued freely; those that share a workspace are serialised,
+ *     not run side by side, and no call waits for, or adds work to, another stream than its own
+ *     beyond that.  The exception is a stream under graph capture: the caller orders captured
+ *     split-K calls against other users of the workspace, and the workspace must exist before the
+ *     capture begins (fg_init(); FG_ERR_UNSUPPORTED otherwise).  The partial products are added in a
+ *     fixed order, so results do not depend on scheduling.
  *   - Every descriptor pointer (fg_matrix, fg_epilogue, mode/extent/stride arrays) is a HOST
  *     pointer, read only during the call.
  *   - Work is enqueued on `hip_stream` (a hipStream_t, NULL = the default stream) and the call

@@ -396,19 +396,22 @@ fg_status prepare(const fg::KernelEntry &k, int dev, int &per_cu) {
     return FG_OK;
 }
 
-// Split-K workspace: one allocation of kWorkspaceBytes per device, made by fg_init() or by the
-// first call that splits K, and kept until the process ends.  Every split-K call on a device
-// uses it.  Calls on one stream are ordered anyway; a call on another stream than the previous
-// user's first waits (on the device, not on the host) for the event that user recorded after its
-// reduction pass, so that calls on different streams cannot overwrite each other's partial
-// products.  A call on the default (null) stream records no event, which costs a call 4 us (one kernel after another
-// on a stream: 2.9 us each, 6.8 with an event in between): that stream exists as long as the process, so the
-// event is recorded there when a call on another stream comes, and orders it after all that was issued until then.  A stream that is being captured into a graph takes no part in this (events recorded
+// Split-K workspace: two allocations of kWorkspaceBytes per device, made by fg_init() or by the
+// first call that splits K, and kept until the process ends.  One belongs to the default (null)
+// stream, whose calls are ordered by it and need nothing else: an event behind each costs a call 4 us
+// (one kernel after another on a stream: 2.9 us each, 6.8 with an event in between).  Every other
+// stream uses the other one: calls on one stream are ordered anyway; a call on another stream than
+// the previous user's first waits (on the device, not on the host) for the event that user recorded
+// after its reduction pass, so that calls on different streams cannot overwrite each other's partial
+// products.  So no call touches a stream but its own: on the default stream an operation from elsewhere
+// would wait for the work of every blocking stream, and break a capture that one of them is under.
+// A stream that is being captured into a graph takes no part in this (events recorded
 // into a graph order nothing outside it): captured split-K calls must be ordered by the caller,
 // and the workspace must exist before the capture starts (fg_init()).
 struct Workspace {
-    float *ptr = nullptr;
-    hipEvent_t last_use = nullptr;       // recorded after the most recent split-K call's reduction pass, or when it is first needed
+    float *ptr = nullptr;                // of every stream but the default one
+    float *of_default = nullptr;         // of the default stream; null: there was no memory for it, and that stream shares ptr
+    hipEvent_t last_use = nullptr;       // recorded after the most recent split-K call's reduction pass in ptr
     hipStream_t last_stream = nullptr;
     bool used = false;
 };
@@ -435,6 +438,8 @@ fg_status workspace_locked(int dev, hipStream_t stream, bool may_allocate, Works
         e = hipEventCreateWithFlags(&w.last_use, hipEventDisableTiming);
         if (e != hipSuccess) { (void)hipFree(ptr); return fail(FG_ERR_LAUNCH, "hipEventCreate for the split-K workspace failed: %s", hipGetErrorString(e)); }
         w.ptr = (float *)ptr;
+        if (hipMalloc(&ptr, (size_t)kWorkspaceBytes) == hipSuccess) w.of_default = (float *)ptr;
+        else (void)hipGetLastError();
     }
     *out = &w;
     return FG_OK;
@@ -465,18 +470,20 @@ fg_status static_scratch(int dev, float **out) {
 // stream, held until release) or the static array of the allocation-free entry point.
 struct Scratch {
     float *ptr = nullptr;
-    Workspace *guard = nullptr;          // set when release() has to record the use
+    Workspace *guard = nullptr;          // set when the library orders the use
+    bool by_stream = false;              // ... by the stream alone: release() has nothing to record
     std::unique_lock<std::mutex> lock{g_ws_mutex, std::defer_lock};
 
     fg_status acquire(bool static_only, int dev, hipStream_t stream) {
         if (static_only) return static_scratch(dev, &ptr);
         lock.lock();
         if (fg_status st = workspace_locked(dev, stream, true, &guard)) return st;
-        ptr = guard->ptr;
+        by_stream = stream == nullptr && guard->of_default;
+        ptr = by_stream ? guard->of_default : guard->ptr;
+        if (by_stream) return FG_OK;                           // (this stream cannot be captured)
         if (stream_is_capturing(stream)) guard = nullptr;      // a captured call is ordered by its graph's caller
         else if (guard->used && guard->last_stream != stream) {
-            hipError_t e = guard->last_stream == nullptr ? hipEventRecord(guard->last_use, nullptr) : hipSuccess;
-            if (e == hipSuccess) e = hipStreamWaitEvent(stream, guard->last_use, 0);
+            hipError_t e = hipStreamWaitEvent(stream, guard->last_use, 0);
             if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "hipStreamWaitEvent on the workspace's last use failed: %s", hipGetErrorString(e));
         }
         return FG_OK;
@@ -497,8 +504,8 @@ struct Scratch {
         return false;
     }
     fg_status release(hipStream_t stream) {
-        if (!guard) return FG_OK;
-        hipError_t e = stream ? hipEventRecord(guard->last_use, stream) : hipSuccess;      // the default stream: when it is needed
+        if (!guard || by_stream) return FG_OK;
+        hipError_t e = hipEventRecord(guard->last_use, stream);
         if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "hipEventRecord after the split-K reduction failed: %s", hipGetErrorString(e));
         guard->last_stream = stream;
         guard->used = true;

@@ -619,25 +619,111 @@ def test_split_k_calls_on_two_streams_do_not_disturb_each_other():
         assert torch.equal(D, ops[i][5]), "launch %d on stream %d differs from the serial result" % (n, i)
 
 
-def test_split_k_calls_on_the_default_stream_and_another():
-    """Calls on the default stream leave no event behind; one on another stream that follows at once still waits for
-    their partial products, and the other way round."""
+def _split_calls(n, first_seed):
+    """n products of two shapes, each with operands of its own (call(stream) -> D) and its serial result."""
     from paper_2009_12263_amd import workloads as W
-    M, N, K = 512, 512, 16384
-    assert "+splitk" in fg.fg_gemm_plan(M, N, K)
-    A = W.small_ints(M * K, 31, device="cuda"); B = W.small_ints(K * N, 32, device="cuda")
-    new = lambda: torch.full((M * N,), float("nan"), dtype=torch.float32, device="cuda")
-    def call(D, stream=None):
-        fg.fg_gemm(M, N, K, 1.0, fg.Matrix(A, fg.FG_COL, M), fg.Matrix(B, fg.FG_COL, K), 0.0, None, fg.Matrix(D, fg.FG_COL, M), stream=stream)
-    ref = new(); call(ref)
-    outs = [new() for _ in range(60)]
+    shapes = [(512, 512, 16384), (300, 200, 8192)]
+    assert all("+splitk" in fg.fg_gemm_plan(*shape) for shape in shapes)
+    calls = []
+    for i in range(n):
+        M, N, K = shapes[i % 2]
+        A = W.small_ints(M * K, first_seed + 2 * i, device="cuda"); B = W.small_ints(K * N, first_seed + 2 * i + 1, device="cuda")
+        ref, D = (torch.full((M * N,), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+        def call(out, stream=None, size=(M, N, K), A=A, B=B):
+            M, N, K = size
+            fg.fg_gemm(M, N, K, 1.0, fg.Matrix(A, fg.FG_ROW, K), fg.Matrix(B, fg.FG_COL, K), 0.0, None, fg.Matrix(out, fg.FG_COL, M), stream=stream)
+        call(ref)
+        torch.cuda.synchronize()
+        calls.append((call, D, ref))
+    return calls
+
+
+def test_split_k_calls_on_the_default_stream_and_another():
+    """Split calls issued in turn on the default stream and on two others, back to back, each with operands and (two by two) a
+    shape of its own, so that partial products of one call in another's result show: every entry equals the call made alone."""
+    calls = _split_calls(18, 200)
+    assert len({tuple(ref[:64].tolist()) for _, _, ref in calls}) == len(calls)          # no two results alike
+    streams = [None, torch.cuda.Stream(), torch.cuda.Stream()]
+    for rep in range(4):
+        for _, D, _ in calls: D.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for i, (call, D, _) in enumerate(calls):
+            call(D, streams[(i + i // 3 * rep) % 3])
+        torch.cuda.synchronize()
+        for i, (_, D, ref) in enumerate(calls):
+            assert torch.equal(D, ref), "round %d: call %d differs from the serial result" % (rep, i)
+
+
+def test_split_k_call_does_not_wait_for_unrelated_work_of_the_default_stream():
+    """After a split call on the default stream, one on another stream has nothing there to wait for: it ends while a
+    long kernel that was issued on the default stream meanwhile still runs."""
+    import time
+    (call, D, ref), (other, D2, ref2) = _split_calls(2, 300)
+    torch.cuda._sleep(1 << 20)
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    torch.cuda._sleep(1 << 24)
+    torch.cuda.synchronize()
+    cycles = int((1 << 24) * 0.4 / (time.perf_counter() - t))         # about 0.4 s
+    def beside_a_long_kernel(launch, stream):
+        torch.cuda.synchronize()
+        done = torch.cuda.Event()
+        call(D)
+        torch.cuda._sleep(cycles)
+        done.record()
+        launch(stream)
+        stream.synchronize()
+        early = not done.query()
+        torch.cuda.synchronize()
+        return early
+    # a stream that shares the default stream's hardware queue would run after it whatever the library does
+    plain = torch.zeros(64, device="cuda")
+    def add(s):
+        with torch.cuda.stream(s): plain.add_(1)
+    streams = [s for s in (torch.cuda.Stream() for _ in range(4)) if beside_a_long_kernel(add, s)]
+    if not streams:
+        pytest.skip("no stream runs beside the default stream here")
+    assert beside_a_long_kernel(lambda s: other(D2, s), streams[0])
+    assert torch.equal(D, ref) and torch.equal(D2, ref2)
+
+
+def test_split_k_call_beside_a_capture_on_a_blocking_stream():
+    """A stream of the kind that waits for the default stream is being captured (global mode) while a split call is made on
+    a third stream, after one on the default stream: the call is made, and the capture is whole."""
+    import ctypes as C
+    (call, D, ref), (other, D2, ref2) = _split_calls(2, 400)
+    with open("/proc/self/maps") as f:
+        hip = C.CDLL(next(l.split()[-1] for l in f if "libamdhip64" in l))
+    def check(status): assert status == 0, status
+    blocking, graph, executable = C.c_void_p(), C.c_void_p(), C.c_void_p()
+    check(hip.hipStreamCreate(C.byref(blocking)))                    # the default flags: ordered against the default stream
     side = torch.cuda.Stream()
+    A = torch.randn(256 * 256, device="cuda").half()
+    out, want = (torch.zeros(256 * 256, device="cuda") for _ in range(2))
+    plain = lambda D, stream=None: fg.fg_gemm(256, 256, 256, 1.0, fg.Matrix(A, fg.FG_COL, 256), fg.Matrix(A, fg.FG_ROW, 256), 0.0, None,
+                                              fg.Matrix(D, fg.FG_COL, 256), stream=stream)
+    plain(want); call(D); other(D2, side)                             # loads every kernel that is used below
     torch.cuda.synchronize()
-    for i, D in enumerate(outs):
-        call(D, side if i % 3 == 2 else None)
+    D.fill_(0); D2.fill_(0)
+    call(D)                                                           # the default stream is the previous user
     torch.cuda.synchronize()
-    for i, D in enumerate(outs):
-        assert torch.equal(D, ref), "call %d differs from the serial result" % i
+    check(hip.hipStreamBeginCapture(blocking, 0))
+    try:
+        plain(out, blocking.value)
+        other(D2, side)
+    finally:
+        status = hip.hipStreamEndCapture(blocking, C.byref(graph))
+    check(status)
+    assert graph.value
+    check(hip.hipGraphInstantiate(C.byref(executable), graph, None, None, C.c_size_t(0)))
+    for rep in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        check(hip.hipGraphLaunch(executable, blocking))
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), rep
+    assert torch.equal(D, ref) and torch.equal(D2, ref2)
+    check(hip.hipGraphExecDestroy(executable)); check(hip.hipGraphDestroy(graph)); check(hip.hipStreamDestroy(blocking))
 
 
 def test_tail_round_split(monkeypatch):
