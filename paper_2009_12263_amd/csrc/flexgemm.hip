@@ -12,6 +12,7 @@
 #include <cstring>
 #include <mutex>
 
+#include "cache_policy.hpp"
 #include "general_kernel.hpp"
 #include "kernel_table.hpp"
 
@@ -1175,14 +1176,8 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
         else p.cd_cached = 2 * bytes <= (80ll << 20) ? q.C || off_lines(q.ilv ? 8 : 32)
                                                      : off_lines(q.ilv ? 8 : 32) && 4 * (q.M * q.K + q.K * q.N) <= (32ll << 20);
     }
-    {
-        // An operand that one row (column) of tiles reads is read once.  From 112 MB on, when little of it is still in the
-        // memory-side cache from the call before, its loads stream past the L2 if its rows are whole lines (a line that two
-        // K tiles share would be fetched twice): three operand sets in turn, 134 MB 45.6 -> 40.8 us, 117 MB 39.7 -> 37.4,
-        // 268 MB 71.1 -> 63.3; 100 MB 34.2, 34.5 and 36.5, 38.0; 67 MB, which stays there, 17.5, 20.2.
-        auto once = [](const void *ptr, int64_t ld, int64_t bytes) { return (uintptr_t)ptr % 128 == 0 && ld % 64 == 0 && bytes >= (112ll << 20); };
-        p.once = p.tiles_m == 1 && once(q.B, q.ldb, q.N * q.K * 2) ? 1 : p.tiles_n == 1 && once(q.A, q.lda, q.M * q.K * 2) ? 2 : 0;
-    }
+    p.once = p.tiles_m == 1 && fg::streams_once((uintptr_t)q.B, q.ldb, q.N * q.K * 2) ? 1
+           : p.tiles_n == 1 && fg::streams_once((uintptr_t)q.A, q.lda, q.M * q.K * 2) ? 2 : 0;
     hipStream_t stream = (hipStream_t)hip_stream;
     if (plan.splits <= 1 && plan.tail_splits <= 1) return launch(k, p, stream);
 

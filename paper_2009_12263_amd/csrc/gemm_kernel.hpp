@@ -62,7 +62,7 @@ struct GemmParams {
     float alpha, beta;
     int32_t bias_dim, act, has_c;
     // Kernels of TileCfg::ONCE: 1: B is fetched by one row of tiles only, 2: A by one column of tiles (set by the host): its
-    // loads stream past the L2.
+    // loads carry the streaming policy.
     int32_t once;
     // transforms on loaded elements (Section 4.3): C_ij := act(C_ij); with TileCfg::XFORM also
     // A_ik := half(A_ik + a_add), B_kj := half(B_kj + b_add), the addend as two packed halves
@@ -166,8 +166,8 @@ struct TileCfg {
     // groups of two sets, as with the four K groups that served it before, 1.5e-7 with two groups of one.
     static constexpr int ACC_SETS = !STRIDED_ && DIAG_ == 0 && CPLX_ == 0 && !M16_ && (KTURNS_ || STAGES_ == 4) ? 2 : 1;
     // ONCE: the kernel has K loops whose loads of A or of B carry the streaming policy, for operands that are read once:
-    // narrow products, bound by reading their large operand, which otherwise displaces the small one that all units share
-    // (128x4096x16384, B 134 MB: 45.6 -> 40.1 us; where other tiles read the operand again it costs: 8192x1024x4096 72 -> 76).
+    // narrow products, bound by reading their large operand (128x16384x12288 122 -> 113 us; where other tiles read the
+    // operand again it costs: 8192x1024x4096 72 -> 76).  From which size on, and why: streams_once (cache_policy.hpp).
     static constexpr bool ONCE = ACC_SETS == 2;
     // SPREAD: the refill loads of a ring buffer are issued one at a time between the MFMAs of two
     // k-slices (A's part in the slice after the buffer is retired, B's part in the next one)

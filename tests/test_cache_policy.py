@@ -1,0 +1,45 @@
+"""CPU test of the rules that say which accesses of the matrix kernels carry the streaming policy: the header that the
+library uses is compiled with the host compiler."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2009_12263_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include "cache_policy.hpp"
+int main(int n, char **v) {
+    auto num = [&](int i) { return (long long)strtoll(v[i], nullptr, 10); };
+    (void)n;
+    if (!strcmp(v[1], "once")) printf("%d\n", (int)fg::streams_once((uint64_t)num(2), num(3), num(4)));
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host compiler")
+    d = tmp_path_factory.mktemp("cache_policy")
+    (d / "t.cpp").write_text(PROGRAM)
+    subprocess.check_call([cxx, "-O1", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(d / "t.cpp"), "-o", str(d / "t")])
+    return lambda *args: int(subprocess.check_output([str(d / "t")] + [str(int(a)) if not isinstance(a, str) else a for a in args]))
+
+
+def test_only_operands_that_no_cache_can_hold_stream(rule):
+    """What the memory-side cache (256 MB) may still hold, from the call before or from the kernel that wrote it, is not
+    streamed: 128 x 4096 x 16384 and 128 x 8320 x 16384 (128 and 260 MB) do not stream, 128 x 16384 x 12288 (384 MB) does, and the
+    operands of test_operands_that_are_read_once do."""
+    MB = 1 << 20
+    for mb, streams in ((64, 0), (128, 0), (192, 0), (256, 0), (260, 0), (383, 0), (384, 1), (1187, 1)):
+        assert rule("once", 4096, 16384, mb * MB) == streams, mb
+    assert rule("once", 4096 + 64, 16384, 1024 * MB) == 0 and rule("once", 4096, 16384 + 32, 1024 * MB) == 0      # rows off the lines
+    assert rule("once", 4096, 16448, 12296 * 16392 * 2) == 1 and rule("once", 4096, 12352, 12296 * 16392 * 2) == 1
+    assert rule("once", 4096, 8256, 24648 * 8200 * 2) == 1 and rule("once", 4096, 24704, 24648 * 8200 * 2) == 1

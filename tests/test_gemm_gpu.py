@@ -538,17 +538,28 @@ def test_ring_of_three_buffers(monkeypatch, la, lb):
 
 @pytest.mark.parametrize("la,lb", list(itertools.product(LAYOUTS, LAYOUTS)))
 def test_operands_that_are_read_once(monkeypatch, la, lb):
-    """A large operand that one row or column of tiles reads is fetched with the streaming policy (K loops of their own): B, then
-    A, on the tiles that have them, with K split and in one pass; sampled entries of integer products, exact."""
-    for tile, small in (("4", 72), ("7", 40), ("8", 40)):
+    """An operand of 384 MB and more that one row or column of tiles reads, its rows whole lines, is fetched with the streaming
+    policy (K loops of their own; test_cache_policy.py checks that these sizes are): B, then A, on the tiles and in the families that
+    have them, with K split and in one pass, a K tail, ragged edges and more tiles than run at a time; sampled entries
+    of integer products, exact."""
+    big, K = 12296, 16392                       # leading dimensions 12352 and 16448, multiples of 64
+    runs = [("4", 72, "1", {}), ("7", 40, "3", {}), ("8", 40, "1", {}), ("4", 72, "3", dict(bf16=True)), ("7", 40, "1", dict(bf16=True)),
+            ("8", 40, "3", dict(bf16=True)), ("4", 72, "1", dict(ab_add=(1.0, -2.0))), ("7", 40, "3", dict(ab_add=(1.0, -2.0))),
+            ("8", 40, "1", dict(ab_add=(0.0, 3.0))), ("4", 72, "1", dict(cd16=True)), ("7", 40, "1", dict(cd16=True)), ("8", 40, "1", dict(cd16=True))]
+    for n, (tile, small, split, kw) in enumerate(runs):
         setenv(monkeypatch, "FG_FORCE_TILE", tile)
-        for split in ("1", "3"):
-            setenv(monkeypatch, "FG_FORCE_SPLIT", split)
-            say("tile %s split %s la=%d lb=%d: B, A" % (tile, split, la, lb))
-            run_gemm_case(small, 4096, 16384, la, lb, ints=True, samples=1500)
-            run_gemm_case(4096, small, 16384, la, lb, ints=True, samples=1500, bias_dim=0)
+        setenv(monkeypatch, "FG_FORCE_SPLIT", split)
+        M, N = (small, big) if (n + la) % 2 else (big, small)
+        say("tile %s split %s la=%d lb=%d %s: %dx%dx%d" % (tile, split, la, lb, kw, M, N, K))
+        run_gemm_case(M, N, K, la, lb, ints=True, samples=1000, pad=56, seed=70 + n, **kw)
+    setenv(monkeypatch, "FG_FORCE_SPLIT", "1")
+    for tile, M, N in (("7", 40, 24648), ("8", 49288, 40)):        # 386 and 771 tiles
+        setenv(monkeypatch, "FG_FORCE_TILE", tile)
+        say("tile %s la=%d lb=%d, several tiles to a workgroup" % (tile, la, lb))
+        run_gemm_case(M, N, 8200, la, lb, ints=True, samples=1000, pad=56, bias_dim=0)
     delenv(monkeypatch, "FG_FORCE_TILE")
     delenv(monkeypatch, "FG_FORCE_SPLIT")
+    torch.cuda.empty_cache()
 
 
 def test_operands_larger_than_2_gib():
