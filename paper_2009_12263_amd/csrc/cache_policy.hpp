@@ -21,4 +21,20 @@ inline bool streams_once(uint64_t address, int64_t ld, int64_t bytes) {
     return address % 128 == 0 && ld % 64 == 0 && 2 * bytes >= 3 * kMemorySideCache;
 }
 
+// C and D of a real product are kept in the caches (default policy) instead of streamed past the L2.  They are touched
+// once and would displace the A and B panels that other workgroups re-read, so they stream, unless
+//  - the whole problem fits the memory-side cache: then nothing is displaced for long (3000^3: 73.6 us against 87.4 streamed,
+//    4096^3: -6 %, 5000x3000x2000: 76.7 against 103.1 back to back; equal on cache-cold operands; from 300 MB up
+//    streaming wins by 4 to 9 %);
+//  - there is a C, columns do not begin on half a 128-byte line, and A and B, which C and D push out of the memory-side cache, take
+//    at most 112 MB: columns that share lines are fetched from memory once for each when streamed.  36 products above 256 MB,
+//    kept / streamed: 0.65 to 0.94 off the half lines with A and B up to 60 MB (6692x6497x248 134.0 / 195.9), 0.92 to 1.03 above
+//    (6856x7081x4064 433 / 442; 3928x6503x4240 285 / 277); on half lines 1.02 to 1.12 (8143x3710x1040 125.1 / 112.1), as on whole
+//    ones (6560x7903x2584 315 / 303).  Binary16 C and D: 0.78 to 1.04 and 1.01 to 1.06.
+// Sizes in bytes; ld: bytes from one column of C (D) to the next.
+inline bool keeps_real_cd(int64_t ab, int64_t cd, bool has_c, int64_t ldc, int64_t ldd) {
+    if (ab + cd <= kMemorySideCache) return true;
+    return has_c && (ldc % 64 != 0 || ldd % 64 != 0) && ab <= (112ll << 20);
+}
+
 }  // namespace fg

@@ -1155,18 +1155,10 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
     const int tiles = (int)tiles64;
     p.tile_begin = 0; p.tile_count = tiles; p.splits = 1;
     {
-        // C and D stream past the L2 (they are touched once and would displace the A and B panels that
-        // other workgroups re-read), unless the whole problem fits the 256 MB memory-side cache: then
-        // nothing is displaced for long, and keeping C and D cached measured faster (3000^3: 73.6
-        // against 87.4 us, 4096^3: -6 %, 5000 x 3000 x 2000: 76.7 against 103.1 us back to back;
-        // equal on cache-cold operands; from 300 MB up streaming wins by 4 to 9 %).  Columns that do not begin on a
-        // 128-byte line share lines, which a streamed C fetches from memory once for each: kept in the caches whatever
-        // the size while A and B, which they push out of the memory-side cache, are not larger than half of it (6708x5150x96 148.7 -> 98.2 us,
-        // 8180x6100x512 211.6 -> 171.2, 5000x6000x4000, A and B 88 MB, 276 -> 270; 5000x5004x7000, 140 MB, 427 streamed, 437; without C equal).
         const int64_t es_cd = q.cd16 ? 2 : 4;
         const int64_t bytes = (q.M * q.K + q.K * q.N) * 2 + q.M * q.N * es_cd * (q.C ? 2 : 1);
         auto off_lines = [&](int64_t elems) { return q.ldd % elems != 0 || (q.C && q.ldc % elems != 0); };
-        if (!q.cplx) p.cd_cached = bytes <= (256ll << 20) || (q.C && off_lines(32) && 2 * (q.M * q.K + q.K * q.N) <= (112ll << 20));
+        if (!q.cplx) p.cd_cached = fg::keeps_real_cd((q.M * q.K + q.K * q.N) * 2, q.M * q.N * es_cd * (q.C ? 2 : 1), q.C != nullptr, q.ldc * es_cd, q.ldd * es_cd);
         // Complex and dual products, whose planes or pairs double all of it, stream what is on the lines, but for products with C up
         // to 80 MB (1536^2 x 512 24.4 -> 21.6, dual 2048^2 x 512 32.0 -> 29.4; without C 22.4 streamed and 23.6 kept, complex 2048^3,
         // 100 MB, 77.4 and 78.4).  Off the lines (interleaved: off the half lines; 3000x2500x1000 84.5 streamed, 88.2 kept) up to 80 MB
