@@ -1155,18 +1155,9 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
     const int tiles = (int)tiles64;
     p.tile_begin = 0; p.tile_count = tiles; p.splits = 1;
     {
-        const int64_t es_cd = q.cd16 ? 2 : 4;
-        const int64_t bytes = (q.M * q.K + q.K * q.N) * 2 + q.M * q.N * es_cd * (q.C ? 2 : 1);
-        auto off_lines = [&](int64_t elems) { return q.ldd % elems != 0 || (q.C && q.ldc % elems != 0); };
-        if (!q.cplx) p.cd_cached = fg::keeps_real_cd((q.M * q.K + q.K * q.N) * 2, q.M * q.N * es_cd * (q.C ? 2 : 1), q.C != nullptr, q.ldc * es_cd, q.ldd * es_cd);
-        // Complex and dual products, whose planes or pairs double all of it, stream what is on the lines, but for products with C up
-        // to 80 MB (1536^2 x 512 24.4 -> 21.6, dual 2048^2 x 512 32.0 -> 29.4; without C 22.4 streamed and 23.6 kept, complex 2048^3,
-        // 100 MB, 77.4 and 78.4).  Off the lines (interleaved: off the half lines; 3000x2500x1000 84.5 streamed, 88.2 kept) up to 80 MB
-        // with C or without (dual 1532x2368x1112 without 41.3 -> 34.2), and above while A and B are small (4040x2048x400 complex
-        // 72.3 -> 62.9): larger ones stay in the memory-side cache only if C and D do not push them out, and the K loop waits for
-        // memory (dual 899x3562x3832, A and B 68 MB: 124 streamed, 156 kept).
-        else p.cd_cached = 2 * bytes <= (80ll << 20) ? q.C || off_lines(q.ilv ? 8 : 32)
-                                                     : off_lines(q.ilv ? 8 : 32) && 4 * (q.M * q.K + q.K * q.N) <= (32ll << 20);
+        const int64_t ab = (q.M * q.K + q.K * q.N) * 2, cd = q.M * q.N * (q.cd16 ? 2 : 4) * (q.C ? 2 : 1), elem = q.ilv ? 8 : q.cd16 ? 2 : 4;
+        p.cd_cached = q.cplx ? fg::keeps_complex_cd(2 * ab, 2 * cd, q.K, q.ilv, q.C != nullptr, q.ldc * elem, q.ldd * elem)
+                             : fg::keeps_real_cd(ab, cd, q.C != nullptr, q.ldc * elem, q.ldd * elem);
     }
     p.once = p.tiles_m == 1 && fg::streams_once((uintptr_t)q.B, q.ldb, q.N * q.K * 2) ? 1
            : p.tiles_n == 1 && fg::streams_once((uintptr_t)q.A, q.lda, q.M * q.K * 2) ? 2 : 0;

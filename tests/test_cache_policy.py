@@ -18,6 +18,7 @@ int main(int n, char **v) {
     (void)n;
     if (!strcmp(v[1], "once")) printf("%d\n", (int)fg::streams_once((uint64_t)num(2), num(3), num(4)));
     if (!strcmp(v[1], "real")) printf("%d\n", (int)fg::keeps_real_cd(num(2), num(3), num(4) != 0, num(5), num(6)));
+    if (!strcmp(v[1], "complex")) printf("%d\n", (int)fg::keeps_complex_cd(num(2), num(3), num(4), num(5) != 0, num(6) != 0, num(7), num(8)));
     return 0;
 }
 """
@@ -60,3 +61,18 @@ def test_real_results_above_the_memory_side_cache_are_kept_only_off_the_half_lin
     for off, kept in ((0, 0), (32, 0), (16, 1), (8, 1)):
         assert keeps(9984 + off, 9000, 400, 2, 9984 + off) == kept, off
     assert keeps(3000, 3000, 3000, 4, 3000) == 1 and keeps(8192, 8192, 8192, 4, 8192) == 0
+
+
+def test_complex_results_of_short_passes_stream(rule):
+    """Complex and dual results on the lines with C: kept up to 80 MB, but streamed where the whole pass is at most 16 MB and K at
+    most 256; off the lines kept; above 80 MB kept only off the lines beside small A and B."""
+    def keeps(M, N, K, ilv=0, c=True, off=0):
+        ld = M + off
+        return rule("complex", (M * K + K * N) * 4, M * N * 8 * (2 if c else 1), K, ilv, c, ld * (8 if ilv else 4), ld * (8 if ilv else 4))
+    assert keeps(1440, 613, 136) == 0 and keeps(1216, 544, 200) == 0 and keeps(704, 810, 120, ilv=1) == 0       # 9 to 14 MB
+    assert keeps(1440, 613, 136, off=8) == 1                                                                 # the same off the lines
+    assert keeps(736, 395, 848, ilv=1) == 1 and keeps(2592, 200, 360, ilv=1) == 1                            # 8 and 11 MB, longer K
+    assert keeps(544, 2711, 192) == 1 and keeps(1408, 2907, 160) == 1                                        # 24 and 65 MB
+    assert keeps(1536, 1536, 512) == 1 and keeps(1536, 1536, 512, c=False) == 0 and keeps(1536, 1536, 512, c=False, off=4) == 1
+    assert keeps(2048, 2048, 2048) == 0 and keeps(4040, 2048, 400, off=8) == 1 and keeps(896, 3562, 3832, off=4) == 0
+    assert keeps(3000, 2500, 1000, ilv=1, off=0) == 0                                                        # on half lines
