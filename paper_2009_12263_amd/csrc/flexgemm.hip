@@ -293,14 +293,16 @@ Plan within_promised_scratch(Plan plan, int64_t M, int64_t N, int64_t K, int k32
 // Tile of the complex and dual kernels (256x128, 128x128 with two workgroups per unit, 64x64 with
 // four, 64x64 with K groups with one): the one with the smallest estimated time.  Whole rounds run with every slot of a unit
 // taken, the workgroups of the last, partly filled round share a unit with fewer others; a
-// workgroup's rate is a measured fraction of what a unit sustains with the 256x128 tile (4096^3:
-// 455 / 515 / 629 us with the three tiles; alone on a unit: 1024^3 51 / 35 / 18 us).  The estimate
-// reproduces the fastest tile of every measured case but one near-tie (2560^3: 131 us against 156 us
-// for the tile the former rule, "the largest tile with 256 tiles", picked; 3072^3: 276 against 301).
+// workgroup's rate is a fraction of what a unit sustains with the 256x128 tile.  Over 130 random products (K 8 to 3000) the choice is
+// 0.4 % slower than the fastest tile on average, over 5 % for four (2.1 % and 18 without the rules on K).
+// A K up to 128 makes the product a pass over C and D, which four small workgroups per unit overlap best (complex
+// 986x5218x88 with C: 23.4 us with the 64x64 tile, 31.5 and 33.9 with the larger ones; dual 2141x1751x8 12.5, 16.6, 18.4; of 79
+// such products the 64x64 tile is more than 2 % slower than another in five, at most 14 %, 6528x2560x24).
 // The 64x64 tile with two K groups: one tile per unit and K steps for both groups, 1024^3 22.4 -> 15.9 us against the tile with
-// one group, 500x700x3000 interleaved 53.5 -> 33.5, 192x640x232 6.5 -> 6.1; with K = 152 the second group does not pay (5.1, 5.6), in a
-// second round neither (1300x1300x800 21.8, 26.4; 1536^2 x 512 21.5, 29.7).
-int choose_ctile(int64_t M, int64_t N, int64_t K) {
+// one group, 500x700x3000 interleaved 53.5 -> 33.5; of planar operands, from K = 264 on (to 216 the second group costs 3 to 18 %, around
+// 250 it is even, 42 products), of interleaved ones from 216 on (10x6993x216 7.7, 6.7; 184 and 192 even); in a second round it
+// does not pay (1300x1300x800 21.8, 26.4; 1536^2 x 512 21.5, 29.7).
+int choose_ctile(int64_t M, int64_t N, int64_t K, bool interleaved) {
     static const int bm[fg::CTILE_COUNT] = {256, 128, 64, 64};
     static const int bn[fg::CTILE_COUNT] = {128, 128, 64, 64};
     static const int per_cu[fg::CTILE_COUNT] = {1, 2, 4, 1};
@@ -308,12 +310,13 @@ int choose_ctile(int64_t M, int64_t N, int64_t K) {
     static const double rate_alone[fg::CTILE_COUNT] = {1.0, 0.74, 0.45, 0.7};
     const int forced = g_force_tile.load(std::memory_order_relaxed);      // tuning override, 0..3 here
     if (forced >= 0 && forced < fg::CTILE_COUNT) return forced;
+    if (K <= 128) return fg::CTILE_64x64;
     int best = 0;
     double best_cost = -1;
     for (int t = 0; t < fg::CTILE_COUNT; ++t) {
         const int64_t tiles = ((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]);
         const int64_t slots = (int64_t)kNumCU * per_cu[t];
-        if (t == fg::CTILE_64x64_KG2 && (tiles > slots || K <= 160)) continue;
+        if (t == fg::CTILE_64x64_KG2 && (tiles > slots || K <= (interleaved ? 208 : 256))) continue;
         auto tile_time = [&](int64_t sharing) {     // one tile, `sharing` workgroups on its unit
             const double unit = per_cu[t] == 1 ? rate_alone[t]
                               : rate_alone[t] + (rate_shared[t] - rate_alone[t]) * (double)(sharing - 1) / (per_cu[t] - 1);
@@ -322,8 +325,10 @@ int choose_ctile(int64_t M, int64_t N, int64_t K) {
         const int64_t full = tiles / slots, rest = tiles - full * slots;
         double cost = (double)full * tile_time(per_cu[t]);
         if (rest > 0) cost += tile_time((rest + kNumCU - 1) / kNumCU);
-        // more than a round of small tiles: dual 2701x3001x1504 141 us, 126 on the 128x128 tile, complex 151 and 140
-        if (t == 2 && tiles > slots) cost *= 1.29;
+        // More than a round of small tiles with a long K: they fall behind the estimate (the next larger tile, of 22 products:
+        // K 144 to 504 0.87 to 1.01 as fast, from 512 on 1.04 to 1.39 but for interleaved ones up to K = 1000, 0.93 to 0.99;
+        // dual 2701x3001x1504 141 us, 126 on the 128x128 tile, 1617x3113x904 60.1 and 43.3)
+        if (t == fg::CTILE_64x64 && tiles > slots && K >= 512) cost *= 1.29;
         if (best_cost < 0 || cost < best_cost) { best = t; best_cost = cost; }
     }
     return best;
@@ -333,7 +338,7 @@ int choose_ctile(int64_t M, int64_t N, int64_t K) {
 const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr) {
     if (plan_out) *plan_out = Plan{0, 1, 1};
     if (q.cplx) {
-        const int t = choose_ctile(q.M, q.N, q.K);
+        const int t = choose_ctile(q.M, q.N, q.K, q.ilv);
         if (t < 0) return nullptr;
         const int v = (q.a_kc ? 2 : 0) + (q.b_kc ? 0 : 1);     // nn, nt, tn, tt
         if (q.ilv) return &fg::kernel_table_cplx_il()[t * 4 + v];

@@ -80,7 +80,7 @@ const KernelEntry *kernel_table_cplx();
 const KernelEntry *kernel_table_cplx_il();
 // Planar dual numbers (eps^2 = 0): same indexing as the complex table.
 const KernelEntry *kernel_table_dual();
-enum { CTILE_64x64_KG2 = 3, CTILE_COUNT = 4 };
+enum { CTILE_64x64 = 2, CTILE_64x64_KG2 = 3, CTILE_COUNT = 4 };
 
 // Second pass of a split-K product (splitk_reduce.hip).
 hipError_t launch_splitk_reduce(const float *W, int splits, int tile_begin, int tile_count, int bm, int bn, int tiles_m,

@@ -363,3 +363,13 @@ def test_products_that_needed_no_scratch_memory_are_not_split():
     faster: they may be captured before the workspace exists, and beside other calls."""
     for (M, N, K, la, lb) in ((46, 4275, 3392, 0, 1), (1191, 58, 2728, 1, 0), (784, 16, 2608, 0, 0), (137, 866, 2088, 1, 0), (73, 21, 2184, 0, 0)):
         assert "split" not in fg.fg_gemm_plan(M, N, K, la, lb), (M, N, K)
+
+
+def test_tiles_of_complex_products_with_a_short_k():
+    """A K up to 128 is a pass over C and D and goes to the 64x64 tile whatever the size; beyond one round of them the larger tiles
+    take over from K = 512 on."""
+    for variant in (fg.FG_PLAN_COMPLEX, fg.FG_PLAN_DUAL, fg.FG_PLAN_COMPLEX_INTERLEAVED):
+        for (M, N, K) in ((986, 5218, 88), (2737, 1520, 32), (2141, 1751, 8), (4495, 3923, 8), (752, 7663, 48), (2560, 3392, 320)):
+            assert fg.fg_gemm_plan(M, N, K, 1, 0, 0, variant).endswith("64x64x32"), (M, N, K, variant)
+        for (M, N, K) in ((2624, 3584, 512), (1617, 3113, 904), (2701, 3001, 1504)):
+            assert "64x64" not in fg.fg_gemm_plan(M, N, K, 0, 0, 0, variant), (M, N, K, variant)
