@@ -373,3 +373,13 @@ def test_tiles_of_complex_products_with_a_short_k():
             assert fg.fg_gemm_plan(M, N, K, 1, 0, 0, variant).endswith("64x64x32"), (M, N, K, variant)
         for (M, N, K) in ((2624, 3584, 512), (1617, 3113, 904), (2701, 3001, 1504)):
             assert "64x64" not in fg.fg_gemm_plan(M, N, K, 0, 0, 0, variant), (M, N, K, variant)
+
+
+def test_tails_of_the_256x128_tile_give_way_to_the_256x256_tile_only():
+    """Whole rounds of the 256x128 tile with a split tail are priced as they run: 7488x1088x6400 takes 126 us that way, 185 in one
+    pass of 64x64 tiles.  The 256x256 tile's tail is preferred where the estimates are close."""
+    assert fg.fg_gemm_plan(7488, 1088, 6400, 0, 1, 0, fg.FG_PLAN_REAL_BF16) == "gemm_bf16_nt_256x128x64+tailsplitk8"
+    assert fg.fg_gemm_plan(8064, 1088, 5632, 0, 0, 0) == "gemm_nn_256x128x64+tailsplitk6"
+    assert "256x128x64+tailsplitk" in fg.fg_gemm_plan(4096, 2304, 5760, 1, 1, 0, fg.FG_PLAN_REAL_BF16)
+    for (M, N, K) in ((4100, 4100, 4096), (6318, 2901, 3304), (4361, 3946, 5016)):
+        assert "256x256x64_k32+tailsplitk" in fg.fg_gemm_plan(M, N, K, 1, 0, 0), (M, N, K)
