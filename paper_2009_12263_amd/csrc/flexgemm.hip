@@ -134,6 +134,7 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 constexpr int kTileM[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64, 64};
 constexpr int kTileN[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64, 128};
 constexpr int kTilesPerCU[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1, 1};
+constexpr int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}, kSplitCount = sizeof kSplits / sizeof *kSplits;
 struct Rates {
     double shared[fg::TILE_COUNT], alone[fg::TILE_COUNT];
     double round_fixed, cu_cd_bw, reduce_launch, reduce_bw;
@@ -159,16 +160,66 @@ constexpr Rates kFormerRates = {{1.0, 0.8, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29, 0
 // either those or the promised rates pick (176 batches of 120 x 112 over 320: 11.6 us, 17.2 by the promised rates).
 constexpr Rates kContractRates = {{1.0, 0.8, 0.73, 0.394, 0.57, 1.0, 0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0, 0}, 1.8e-6, 25e9, 0, 1, {}, false};
 
-Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_smallest = true, int64_t batches = 1,
-                 bool allow_deep = true, int k32 = 0, bool allow_groups = false, int64_t scratch_bytes = kWorkspaceBytes,
-                 const Rates &rates = kRates, int straddling = 0) {
-    const auto &bm = kTileM;
-    const auto &bn = kTileN;
-    const auto &per_cu = kTilesPerCU;
-    const auto &rate_shared = rates.shared, &rate_alone = rates.alone;
-    static const int split_options[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
+// What an estimate takes from the rates alone, seconds; index n: n + 1 workgroups share a compute unit.  A call makes up to
+// seven searches (the former planners' too, see within_promised_scratch), which bounds the host's part of a small or split
+// product; so they have no divisions left in them and skip a tile that cannot win: 256^3 0.46 -> 0.14 us, 1024^3 1.0 -> 0.32,
+// 128x4096x16384 4.9 -> 1.4 (2.7 GHz Xeon).
+struct Prices {
+    bool has[fg::TILE_COUNT];
+    double k_tile[fg::TILE_COUNT][4], epilogue[fg::TILE_COUNT][4];      // of a K tile, and of the rest of a workgroup
+    double unit_k_tile[fg::TILE_COUNT];                                 // a K tile's share of a unit's time, at the least
+    double off_line[fg::TILE_COUNT], reduce_launch, reduce_byte;
+    bool last_round;
+};
+constexpr Prices priced(const Rates &r) {
     constexpr double cu_flops = 4.7e12;
-    const double round_fixed = rates.round_fixed, cu_cd_bw = rates.cu_cd_bw, reduce_launch = rates.reduce_launch, reduce_bw = rates.reduce_bw;
+    Prices p{};
+    for (int t = 0; t < fg::TILE_COUNT; ++t) {
+        p.has[t] = r.shared[t] != 0 && t != fg::TILE_256x256_K32;
+        p.off_line[t] = r.off_line[t];
+        for (int n = 0; n < kTilesPerCU[t] && p.has[t]; ++n) {
+            // workgroups that share a compute unit at a time: a unit's rate grows linearly from the
+            // lone-workgroup rate to the rate with every slot taken, and is divided among them
+            const double unit = kTilesPerCU[t] == 1 ? r.alone[t] : r.alone[t] + (r.shared[t] - r.alone[t]) * n / (kTilesPerCU[t] - 1);
+            p.k_tile[t][n] = 2.0 * kTileM[t] * kTileN[t] * 64 / (cu_flops * unit / (n + 1));
+            // the C read and D write of a tile stream at what one compute unit gets of the memory
+            // bandwidth, divided among the workgroups that share the unit
+            p.epilogue[t][n] = r.round_fixed + (n + 1) * 8.0 * kTileM[t] * kTileN[t] / r.cu_cd_bw;
+            const double share = p.k_tile[t][n] / (n + 1);
+            if (n == 0 || share < p.unit_k_tile[t]) p.unit_k_tile[t] = share;
+        }
+    }
+    p.reduce_launch = r.reduce_launch;
+    p.reduce_byte = 1 / r.reduce_bw;
+    p.last_round = r.last_round;
+    return p;
+}
+constexpr Prices kPrices = priced(kRates), kPromisedPrices = priced(kPromisedRates), kFormerPrices = priced(kFormerRates), kContractPrices = priced(kContractRates);
+
+// The K ranges that a product may be split into: at least four K tiles (256 k) each.
+struct KRanges {
+    int32_t nk;                       // K tiles (every real kernel has BK = 64)
+    int n = 0;
+    int32_t share[kSplitCount];       // K tiles of one of kSplits[i] ranges, i < n
+    explicit KRanges(int64_t K) : nk((int32_t)((K + 63) / 64)) {
+        do { share[n] = (nk + kSplits[n] - 1) / kSplits[n]; ++n; } while (n < kSplitCount && nk >= 4 * kSplits[n]);
+    }
+};
+
+constexpr int log2_of(int x) { return x == 1 ? 0 : 1 + log2_of(x / 2); }
+struct Shifts { int m[fg::TILE_COUNT], n[fg::TILE_COUNT], slots[fg::TILE_COUNT], cu; };
+constexpr Shifts shifts_of_tiles() {
+    Shifts s{};
+    s.cu = log2_of(kNumCU);
+    for (int t = 0; t < fg::TILE_COUNT; ++t) { s.m[t] = log2_of(kTileM[t]); s.n[t] = log2_of(kTileN[t]); s.slots[t] = s.cu + log2_of(kTilesPerCU[t]); }
+    return s;
+}
+constexpr Shifts kShifts = shifts_of_tiles();
+static_assert(1 << kShifts.cu == kNumCU, "the searches shift instead of dividing");
+
+Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bool allow_smallest = true, int64_t batches = 1,
+                 bool allow_deep = true, int k32 = 0, bool allow_groups = false, int64_t scratch_bytes = kWorkspaceBytes,
+                 const Prices &prices = kPrices, int straddling = 0) {
     constexpr double tail_launch = 6e-6, tail_bw = 3e12;      // the leftover tiles' reduction follows a full round
     // tuning overrides (see read_tuning_from_environment)
     int force_tile = -1;
@@ -180,74 +231,73 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
         else forced_plain = (t == fg::TILE_256x256);
         if (t >= 0 && t < fg::TILE_COUNT) force_tile = t;
     }
-    const int64_t nk = (K + 63) / 64;                       // K tiles (every real kernel has BK = 64)
+    const int32_t nk = ranges.nk;
     Plan best{0, 1, 1}, large_tail{0, 1, 1};
     double best_cost = -1, large_tail_cost = -1;
     for (int t = 0; t < fg::TILE_COUNT; ++t) {
         if (force_tile >= 0 && t != force_tile) continue;
         if (t == fg::TILE_64x64 && !allow_smallest) continue;
         if (t == fg::TILE_128x128_DEEP && !allow_deep) continue;
-        if (t == fg::TILE_256x256_K32) continue;
-        if (t >= fg::TILE_64x64_KG2 && (!allow_groups || rates.shared[t] == 0)) continue;
-        const int64_t tiles = ((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]) * batches;
-        const int64_t slots = (int64_t)kNumCU * per_cu[t];
-        const int64_t slot_bytes = (int64_t)bm[t] * bn[t] * 4;
+        if (!prices.has[t] || (t >= fg::TILE_64x64_KG2 && !allow_groups)) continue;
+        const int slot_shift = kShifts.slots[t];
+        const int64_t tiles = ((M + kTileM[t] - 1) >> kShifts.m[t]) * ((N + kTileN[t] - 1) >> kShifts.n[t]) * batches;
+        const int64_t slots = 1ll << slot_shift;
+        const int64_t slot_bytes = (int64_t)kTileM[t] * kTileN[t] * 4;
+        // no plan of this tile can take less than its K tiles at the best rate
+        if (best_cost >= 0 && force_tail < 2 && (double)tiles * nk * prices.unit_k_tile[t] * (1.0 / kNumCU) >= best_cost) continue;
+        const double lines = 1 + prices.off_line[t] * straddling;
+        auto share_time = [&](int64_t wgs, int S, int32_t share) {     // one workgroup on its share of K, plus its epilogue
+            int64_t n = ((wgs + kNumCU - 1) >> kShifts.cu) - 1;
+            if (n >= kTilesPerCU[t]) n = kTilesPerCU[t] - 1;
+            return prices.k_tile[t][n] * share * (S == 1 || prices.last_round ? lines : 1) + prices.epilogue[t][n];
+        };
         // K groups: at least four K tiles for each, or their reduction costs more than they save (256^3:
         // 4.5 us on the GPU with one group, 4.8 with two; 519x736x320: 5.1, 5.5); the larger rings, which take longer to
         // fill, from six on (128x2752x720, six: 6.1 us with two buffers, 6.5 with four; 704x640x768: 6.7, 6.4)
-        const int64_t groups = t >= fg::TILE_64x64_KG2 ? 2 : 1;
-        const double lines = 1 + rates.off_line[t] * straddling;
-        auto share_time = [&](int64_t wgs, int S) {     // one workgroup on 1/S of K, plus its epilogue
-            // workgroups that share a compute unit at a time: a unit's rate grows linearly from the
-            // lone-workgroup rate to the rate with every slot taken, and is divided among them
-            int64_t n = (wgs + kNumCU - 1) / kNumCU;
-            if (n > per_cu[t]) n = per_cu[t];
-            const double unit_rate = per_cu[t] == 1 ? rate_alone[t]
-                                   : rate_alone[t] + (rate_shared[t] - rate_alone[t]) * (double)(n - 1) / (per_cu[t] - 1);
-            const double rate = unit_rate / (double)n;
-            // the C read and D write of a tile stream at what one compute unit gets of the memory
-            // bandwidth, divided among the workgroups that share the unit
-            const double epilogue = round_fixed + (double)n * 8.0 * bm[t] * bn[t] / cu_cd_bw;
-            return 2.0 * bm[t] * bn[t] * (double)((nk + S - 1) / S) * 64 / (cu_flops * rate) * (S == 1 || rates.last_round ? lines : 1) + epilogue;
-        };
-        auto reduce_time = [&](int64_t ntile, int S) { return reduce_launch + (2.0 * S + 2.0) * (double)ntile * slot_bytes / reduce_bw; };
+        const int32_t least = t < fg::TILE_64x64_KG2 || force_tile >= 0 ? 0 : t == fg::TILE_64x64_KG2 ? 8 : prices.last_round ? 12 : 16;
         auto consider = [&](int S, int tail, double cost) {
-            if (groups > 1 && force_tile < 0 && nk / (S * tail) < (t == fg::TILE_64x64_KG2 ? 8 : rates.last_round ? 12 : 16)) return;
+            if (nk < least * S * tail) return;
             if (best_cost < 0 || cost < best_cost) { best = Plan{t, S, tail}; best_cost = cost; }
         };
         // (a) every tile split S ways (S = 1: the plain launch)
-        auto legal = [&](int S) { return S == 1 || (may_split && S <= nk && tiles * S * slot_bytes <= scratch_bytes); };
-        const int forced = (force_split >= 1 && legal(force_split)) ? force_split : (force_split >= 1 ? 1 : 0);
-        for (int S : split_options) {
-            if (forced) { if (S != split_options[0]) break; S = forced; }      // one candidate: the forced split
-            else if (S > 1 && (!legal(S) || nk / S < 4)) break;                   // at least 256 k per share
+        auto split_all = [&](int S, int32_t share) {
             const int64_t wgs = tiles * S;
-            const int64_t whole = wgs / slots, last = wgs - whole * slots;
-            double cost = rates.last_round && last > 0 ? (whole > 0 ? (double)whole * share_time(slots, S) : 0.0) + share_time(last, S)
-                                                       : (double)(whole + (last > 0)) * share_time(wgs, S);
-            if (S > 1) cost += reduce_time(tiles, S);
+            const int64_t whole = wgs >> slot_shift, last = wgs & (slots - 1);
+            double cost = prices.last_round && last > 0 ? (whole > 0 ? (double)whole * share_time(slots, S, share) : 0.0) + share_time(last, S, share)
+                                                        : (double)(whole + (last > 0)) * share_time(wgs, S, share);
+            if (S > 1) cost += prices.reduce_launch + (2.0 * S + 2.0) * (double)(tiles * slot_bytes) * prices.reduce_byte;
             consider(S, 1, cost);
+        };
+        if (force_split >= 1) {                                   // one candidate: the forced split, if it is possible
+            const bool legal = force_split == 1 || (may_split && force_split <= nk && tiles * force_split * slot_bytes <= scratch_bytes);
+            const int S = legal ? force_split : 1;
+            split_all(S, (nk + S - 1) / S);
+            continue;
+        }
+        for (int i = 0; i < ranges.n; ++i) {
+            if (i > 0 && (!may_split || tiles * kSplits[i] * slot_bytes > scratch_bytes)) break;
+            split_all(kSplits[i], ranges.share[i]);
         }
         // (b) whole rounds in one pass, the tiles of the last, partly filled round split over K
-        const int64_t full = tiles / slots * slots, rest = tiles - full;
-        if (may_split && full > 0 && rest > 0 && force_split < 1 && force_tail != 1) {
-            for (int S : split_options) {
-                if (S == 1) continue;
-                if (force_tail > 1) { if (S != split_options[1]) break; S = force_tail; }
-                const bool fits = S <= nk && rest * S * slot_bytes <= scratch_bytes;
-                if (force_tail > 1) { if (!fits) break; }
-                else if (!fits || nk / S < 4 || rest * S > slots) break;
-                const double cost = (double)(full / slots) * share_time(full, 1) + 2e-6 +
-                                    (double)((rest * S + slots - 1) / slots) * share_time(rest * S, S) + tail_launch + (2.0 * S + 2.0) * (double)rest * slot_bytes / tail_bw;
-                consider(1, S, force_tail > 1 ? 0.0 : cost);
-                if (t == fg::TILE_256x256 && (large_tail_cost < 0 || cost < large_tail_cost)) { large_tail = Plan{t, 1, S}; large_tail_cost = cost; }
-            }
+        const int64_t rest = tiles & (slots - 1), full = tiles - rest;
+        if (!may_split || full == 0 || rest == 0 || force_tail == 1) continue;
+        if (force_tail > 1) {
+            if (force_tail <= nk && rest * force_tail * slot_bytes <= scratch_bytes) consider(1, force_tail, 0.0);
+            continue;
+        }
+        const double in_front = (double)(full >> slot_shift) * share_time(full, 1, nk) + 2e-6 + tail_launch;
+        for (int i = 1; i < ranges.n; ++i) {
+            const int S = kSplits[i];
+            if (rest * S > slots || rest * S * slot_bytes > scratch_bytes) break;
+            const double cost = in_front + share_time(rest * S, S, ranges.share[i]) + (2.0 * S + 2.0) * (double)(rest * slot_bytes) * (1 / tail_bw);
+            consider(1, S, cost);
+            if (t == fg::TILE_256x256 && (large_tail_cost < 0 || cost < large_tail_cost)) { large_tail = Plan{t, 1, S}; large_tail_cost = cost; }
         }
     }
     // Of two plans with whole rounds in front of a split tail, the 256x256 tile's runs 4 % faster than the 256x128 tile's whose
     // estimate is up to 9 % lower (36 such products, 0.885 to 1.006: 6318x2901x3304 174.0 -> 153.9 us, 4361x3946x5016 with C 245.5 -> 233.3,
     // 8000x2240x4352 175.4 and 176.5).
-    if (rates.last_round && force_tile < 0 && force_split < 1 && best.tile == fg::TILE_256x128 && best.tail_splits > 1 &&
+    if (prices.last_round && force_tile < 0 && force_split < 1 && best.tile == fg::TILE_256x128 && best.tail_splits > 1 &&
         large_tail_cost >= 0 && large_tail_cost <= 1.09 * best_cost)
         best = large_tail;
     // A short K (up to 256) makes the product a pass over C and D: there the 256x128 tile measured
@@ -266,34 +316,33 @@ Plan choose_plan(int64_t M, int64_t N, int64_t K, bool may_split, bool allow_sma
 
 // Scratch bytes that a plan's partial products take.
 int64_t scratch_need(const Plan &plan, int64_t M, int64_t N) {
-    const int t = plan.tile == fg::TILE_256x256_K32 ? fg::TILE_256x256 : plan.tile;
-    const int64_t tiles = ((M + kTileM[t] - 1) / kTileM[t]) * ((N + kTileN[t] - 1) / kTileN[t]), tile_bytes = (int64_t)kTileM[t] * kTileN[t] * 4;
-    if (plan.splits > 1) return tiles * plan.splits * tile_bytes;
-    if (plan.tail_splits > 1) return tiles % (kNumCU * kTilesPerCU[t]) * plan.tail_splits * tile_bytes;
-    return 0;
+    if (plan.splits <= 1 && plan.tail_splits <= 1) return 0;
+    const int t = plan.tile;
+    const int64_t tiles = ((M + kTileM[t] - 1) >> kShifts.m[t]) * ((N + kTileN[t] - 1) >> kShifts.n[t]), tile_bytes = (int64_t)kTileM[t] * kTileN[t] * 4;
+    return (plan.splits > 1 ? tiles * plan.splits : (tiles & ((1ll << kShifts.slots[t]) - 1)) * plan.tail_splits) * tile_bytes;
 }
 
 // Which scratch memory a call needs is part of what it promises: a call that needed none can be
 // captured before the workspace exists and beside others, one whose partial products fit the static array can be made
 // without allocation.  A plan that leaves the class (none, static array, workspace) of the plan that the former planners made
 // (kFormerRates, itself held to the classes of kPromisedRates) is therefore replaced by the best one that does not (6 % of
-// random shapes).  Costs a split call 3 us on the host.
-Plan within_promised_scratch(Plan plan, int64_t M, int64_t N, int64_t K, int k32, int straddling) {
+// random shapes).  Costs a split call about 1 us on the host.
+Plan within_promised_scratch(Plan plan, int64_t M, int64_t N, int64_t K, const KRanges &ranges, int k32, int straddling) {
     const int64_t need = scratch_need(plan, M, N);
     if (need == 0 || g_force_split.load(std::memory_order_relaxed) >= 1 || g_force_tail.load(std::memory_order_relaxed) > 1 ||
         g_force_tile.load(std::memory_order_relaxed) >= 0) return plan;
     auto limit_of = [](int64_t bytes) { return bytes == 0 ? 0 : bytes <= kStaticScratchBytes ? kStaticScratchBytes : kWorkspaceBytes; };
-    const int64_t promised = limit_of(scratch_need(choose_plan(M, N, K, true, true, 1, true, k32, false, kWorkspaceBytes, kPromisedRates), M, N));
+    const int64_t promised = limit_of(scratch_need(choose_plan(M, N, ranges, true, true, 1, true, k32, false, kWorkspaceBytes, kPromisedPrices), M, N));
     auto former_plan = [&](int lines) {
-        const Plan p = choose_plan(M, N, K, true, true, 1, true, k32, true, kWorkspaceBytes, kFormerRates, lines);
-        return scratch_need(p, M, N) <= promised ? p : choose_plan(M, N, K, promised > 0, true, 1, true, k32, true, promised, kFormerRates, lines);
+        const Plan p = choose_plan(M, N, ranges, true, true, 1, true, k32, true, kWorkspaceBytes, kFormerPrices, lines);
+        return scratch_need(p, M, N) <= promised ? p : choose_plan(M, N, ranges, promised > 0, true, 1, true, k32, true, promised, kFormerPrices, lines);
     };
     // rows off the lines counted in long K loops only, and only for a split
     const int lines = K > 3904 ? straddling : 0;
     Plan former = former_plan(lines);
     if (lines > 0 && former.splits == 1 && former.tail_splits == 1) former = former_plan(0);
     const int64_t limit = limit_of(scratch_need(former, M, N));
-    return need <= limit ? plan : choose_plan(M, N, K, limit > 0, true, 1, true, k32, true, limit, kRates, straddling);
+    return need <= limit ? plan : choose_plan(M, N, ranges, limit > 0, true, 1, true, k32, true, limit, kPrices, straddling);
 }
 
 // Tile of the complex and dual kernels (256x128, 128x128 with two workgroups per unit, 64x64 with
@@ -352,10 +401,11 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     }
     const bool may_split = plan_out && !q.a_diag && !q.b_diag && !q.cd16;   // the reduction pass writes FP32
     const int k32 = (q.a_diag || q.b_diag) ? 0 : q.ab_add ? (q.a_kc != q.b_kc ? 2 : 0) : ((q.a_kc || q.b_kc) ? 2 : 1);
+    const KRanges ranges(q.K);
     auto planned = [&](int straddling) {
         const bool dense = !q.a_diag && !q.b_diag;
-        const Plan p = choose_plan(q.M, q.N, q.K, may_split, true, 1, dense, k32, dense, kWorkspaceBytes, kRates, straddling);
-        return may_split ? within_promised_scratch(p, q.M, q.N, q.K, k32, straddling) : p;
+        const Plan p = choose_plan(q.M, q.N, ranges, may_split, true, 1, dense, k32, dense, kWorkspaceBytes, kPrices, straddling);
+        return may_split ? within_promised_scratch(p, q.M, q.N, q.K, ranges, k32, straddling) : p;
     };
     // Rows off a line: by the extents (a row is whole 16-byte pieces), so that the plan query, which knows no leading
     // dimensions, says the same.  Rows that begin on half a line are not counted: 8192x243 over 4256, both K-contiguous,
@@ -1294,7 +1344,7 @@ static const fg::KernelEntry *select_contract_kernel(const Contraction &c, const
     // A result that is not contiguous along the leading row mode is stored in short pieces; the
     // smallest tile makes them shorter still (measured on the paper's D_abc = A_bda B_dc).
     const bool rows_contiguous = c.c_m.n == 0 || c.c_m.stride[0] == 1;
-    const int tile = choose_plan(c.M, c.N, c.K, false, rows_contiguous || c.M < 128 || c.N < 128, c.batches, true, 0, false, 0, kContractRates).tile;
+    const int tile = choose_plan(c.M, c.N, KRanges(c.K), false, rows_contiguous || c.M < 128 || c.N < 128, c.batches, true, 0, false, 0, kContractPrices).tile;
     // The result streams past the L2 only if every store of 32 consecutive rows is one whole,
     // aligned 128-byte line: leading row mode contiguous with an extent that is a multiple of 32,
     // every other stride of C and its base a multiple of 32 elements.
