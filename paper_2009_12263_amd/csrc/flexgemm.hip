@@ -143,17 +143,24 @@ struct Rates {
     // apart 128): what the K loop takes longer for each of A and B whose rows are off the lines.
     double off_line[fg::TILE_COUNT];
     bool last_round;         // the last, partly filled round is priced with the workgroups that it has
+    // K groups and sets of accumulators per group, which share a workgroup's sum over K (TileCfg::KG, ACC_SETS)
+    int groups[fg::TILE_COUNT] = {1, 1, 1, 1, 1, 1, 1, 1, 1}, sets[fg::TILE_COUNT] = {1, 1, 1, 1, 1, 1, 1, 1, 1};
 };
 constexpr Rates kRates = {{1, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
                           {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
                           2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
-                          {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true};
+                          {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true,
+                          {1, 1, 1, 1, 1, 1, 2, 2, 2}, {1, 1, 1, 1, 2, 1, 1, 2, 2}};
+using fg::TileCfg;
+static_assert(FG_CFG(128, 128, 64, 4, 4, 2, false, true, false)::ACC_SETS == 2 && FG_CFG(256, 128, 64, 3, 4, 2, false, true, false)::ACC_SETS == 1 &&
+              FG_CFG_KG(false, true, false, false, false, 64, 2, false)::ACC_SETS == 1 && FG_CFG_KG(false, true, false, false, false, 64, 4, true)::ACC_SETS == 2 &&
+              FG_CFG_KG(false, true, false, false, false, 128, 3, true)::ACC_SETS == 2, "Rates::sets");
 // The rates that decided what a call needs scratch memory for before the 64x64 tile had K groups
-// (see within_promised_scratch).
+// (see plan_product).
 constexpr Rates kPromisedRates = {{1.0, 0.8, 0.73, 0.45, 0.57, 1.0, 0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0, 0}, 2e-6, 25e9, 6e-6, 3e12, {}, false};
-// The rates of the planner before the larger rings (four K groups as tile 7, no 64x128 tile): see within_promised_scratch.
+// The rates of the planner before the larger rings (four K groups as tile 7, no 64x128 tile): see plan_product.
 constexpr Rates kFormerRates = {{1.0, 0.8, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29, 0}, {1.0, 0.8, 0.43, 0.135, 0.645, 1.0, 0.27, 0.29, 0}, 1.6e-6, 27e9, 12.3e-6, 7.2e12,
-                                {0, 0, 0, 0, 0, 0, 0.1, 0.1, 0}, false};
+                                {0, 0, 0, 0, 0, 0, 0.1, 0.1, 0}, false, {1, 1, 1, 1, 1, 1, 2, 4, 1}};
 // Contractions have neither K groups nor splits, which the rates above were fitted with: over 320 contractions those
 // picked the fastest tile to within 2.4 % on average and 44 % at most (192 x 960 rows and columns over 2560: 33.8 us
 // with the deep 128x128 tile, 23.6 with the 64x64 tile), these to within 0.5 % and 43 %, and no tile slower than
@@ -161,22 +168,26 @@ constexpr Rates kFormerRates = {{1.0, 0.8, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29, 0
 constexpr Rates kContractRates = {{1.0, 0.8, 0.73, 0.394, 0.57, 1.0, 0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0, 0}, 1.8e-6, 25e9, 0, 1, {}, false};
 
 // What an estimate takes from the rates alone, seconds; index n: n + 1 workgroups share a compute unit.  A call makes up to
-// seven searches (the former planners' too, see within_promised_scratch), which bounds the host's part of a small or split
-// product; so they have no divisions left in them and skip a tile that cannot win: 256^3 0.46 -> 0.14 us, 1024^3 1.0 -> 0.32,
-// 128x4096x16384 4.9 -> 1.4 (2.7 GHz Xeon).
+// four searches (the former planners' too, see plan_product), which bounds the host's part of a small or split
+// product; so they have no divisions left in them and skip a tile that cannot win: 256^3
+// 0.20 -> 0.14 us on the host (2.7 GHz Xeon), 128x4096x16384 2.3 -> 1.05; 1024^3, which used to ask one planner, 0.44 and 0.45.
 struct Prices {
     bool has[fg::TILE_COUNT];
     double k_tile[fg::TILE_COUNT][4], epilogue[fg::TILE_COUNT][4];      // of a K tile, and of the rest of a workgroup
     double unit_k_tile[fg::TILE_COUNT];                                 // a K tile's share of a unit's time, at the least
     double off_line[fg::TILE_COUNT], reduce_launch, reduce_byte;
     bool last_round;
+    int8_t group_shift[fg::TILE_COUNT], set_shift[fg::TILE_COUNT];
 };
+constexpr int log2_of(int x) { return x == 1 ? 0 : 1 + log2_of(x / 2); }
 constexpr Prices priced(const Rates &r) {
     constexpr double cu_flops = 4.7e12;
     Prices p{};
     for (int t = 0; t < fg::TILE_COUNT; ++t) {
         p.has[t] = r.shared[t] != 0 && t != fg::TILE_256x256_K32;
         p.off_line[t] = r.off_line[t];
+        p.group_shift[t] = (int8_t)log2_of(r.groups[t]);
+        p.set_shift[t] = (int8_t)log2_of(r.sets[t]);
         for (int n = 0; n < kTilesPerCU[t] && p.has[t]; ++n) {
             // workgroups that share a compute unit at a time: a unit's rate grows linearly from the
             // lone-workgroup rate to the rate with every slot taken, and is divided among them
@@ -202,11 +213,19 @@ struct KRanges {
     int n = 0;
     int32_t share[kSplitCount];       // K tiles of one of kSplits[i] ranges, i < n
     explicit KRanges(int64_t K) : nk((int32_t)((K + 63) / 64)) {
-        do { share[n] = (nk + kSplits[n] - 1) / kSplits[n]; ++n; } while (n < kSplitCount && nk >= 4 * kSplits[n]);
+        // divided by multiplication: nk is below 2^25, so (2^40 / S, rounded up) is off by less than 2^25 / 2^40
+        do { share[n] = (int32_t)(((uint64_t)(nk + kSplits[n] - 1) * kInverse.of[n]) >> 40); ++n; } while (n < kSplitCount && nk >= 4 * kSplits[n]);
     }
+    struct Inverse { uint64_t of[kSplitCount]; };
+    static constexpr Inverse inverses() {
+        Inverse v{};
+        for (int i = 0; i < kSplitCount; ++i) v.of[i] = ((1ull << 40) + kSplits[i] - 1) / kSplits[i];
+        return v;
+    }
+    static const Inverse kInverse;
 };
+constexpr KRanges::Inverse KRanges::kInverse = KRanges::inverses();
 
-constexpr int log2_of(int x) { return x == 1 ? 0 : 1 + log2_of(x / 2); }
 struct Shifts { int m[fg::TILE_COUNT], n[fg::TILE_COUNT], slots[fg::TILE_COUNT], cu; };
 constexpr Shifts shifts_of_tiles() {
     Shifts s{};
@@ -217,9 +236,16 @@ constexpr Shifts shifts_of_tiles() {
 constexpr Shifts kShifts = shifts_of_tiles();
 static_assert(1 << kShifts.cu == kNumCU, "the searches shift instead of dividing");
 
+// The longest sum that a plan adds up one product after another, in halves of a K tile, from the K tiles of one range.
+int32_t sum_length(const Prices &prices, int tile, int32_t share) {
+    const int g = prices.group_shift[tile];
+    return ((share + (1 << g) - 1) >> g) * 2 >> prices.set_shift[tile];
+}
+
+// longest: no plan whose sums are longer (sum_length).
 Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bool allow_smallest = true, int64_t batches = 1,
                  bool allow_deep = true, int k32 = 0, bool allow_groups = false, int64_t scratch_bytes = kWorkspaceBytes,
-                 const Prices &prices = kPrices, int straddling = 0) {
+                 const Prices &prices = kPrices, int straddling = 0, int32_t longest = INT32_MAX) {
     constexpr double tail_launch = 6e-6, tail_bw = 3e12;      // the leftover tiles' reduction follows a full round
     // tuning overrides (see read_tuning_from_environment)
     int force_tile = -1;
@@ -233,7 +259,8 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
     }
     const int32_t nk = ranges.nk;
     Plan best{0, 1, 1}, large_tail{0, 1, 1};
-    double best_cost = -1, large_tail_cost = -1;
+    constexpr double never = 1e300;
+    double best_cost = never, large_tail_cost = never;
     for (int t = 0; t < fg::TILE_COUNT; ++t) {
         if (force_tile >= 0 && t != force_tile) continue;
         if (t == fg::TILE_64x64 && !allow_smallest) continue;
@@ -244,10 +271,10 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
         const int64_t slots = 1ll << slot_shift;
         const int64_t slot_bytes = (int64_t)kTileM[t] * kTileN[t] * 4;
         // no plan of this tile can take less than its K tiles at the best rate
-        if (best_cost >= 0 && force_tail < 2 && (double)tiles * nk * prices.unit_k_tile[t] * (1.0 / kNumCU) >= best_cost) continue;
+        if (force_tail < 2 && (double)tiles * nk * prices.unit_k_tile[t] * (1.0 / kNumCU) >= best_cost) continue;
         const double lines = 1 + prices.off_line[t] * straddling;
         auto share_time = [&](int64_t wgs, int S, int32_t share) {     // one workgroup on its share of K, plus its epilogue
-            int64_t n = ((wgs + kNumCU - 1) >> kShifts.cu) - 1;
+            int64_t n = wgs <= kNumCU ? 0 : (wgs - 1) >> kShifts.cu;         // (no workgroups at all: the plan query of an empty result)
             if (n >= kTilesPerCU[t]) n = kTilesPerCU[t] - 1;
             return prices.k_tile[t][n] * share * (S == 1 || prices.last_round ? lines : 1) + prices.epilogue[t][n];
         };
@@ -255,9 +282,10 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
         // 4.5 us on the GPU with one group, 4.8 with two; 519x736x320: 5.1, 5.5); the larger rings, which take longer to
         // fill, from six on (128x2752x720, six: 6.1 us with two buffers, 6.5 with four; 704x640x768: 6.7, 6.4)
         const int32_t least = t < fg::TILE_64x64_KG2 || force_tile >= 0 ? 0 : t == fg::TILE_64x64_KG2 ? 8 : prices.last_round ? 12 : 16;
-        auto consider = [&](int S, int tail, double cost) {
-            if (nk < least * S * tail) return;
-            if (best_cost < 0 || cost < best_cost) { best = Plan{t, S, tail}; best_cost = cost; }
+        auto consider = [&](int S, int tail, int32_t share, double cost) {
+            if (cost >= best_cost || nk < least * S * tail || sum_length(prices, t, share) > longest) return;
+            best = Plan{t, S, tail};
+            best_cost = cost;
         };
         // (a) every tile split S ways (S = 1: the plain launch)
         auto split_all = [&](int S, int32_t share) {
@@ -266,7 +294,7 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
             double cost = prices.last_round && last > 0 ? (whole > 0 ? (double)whole * share_time(slots, S, share) : 0.0) + share_time(last, S, share)
                                                         : (double)(whole + (last > 0)) * share_time(wgs, S, share);
             if (S > 1) cost += prices.reduce_launch + (2.0 * S + 2.0) * (double)(tiles * slot_bytes) * prices.reduce_byte;
-            consider(S, 1, cost);
+            consider(S, 1, share, cost);
         };
         if (force_split >= 1) {                                   // one candidate: the forced split, if it is possible
             const bool legal = force_split == 1 || (may_split && force_split <= nk && tiles * force_split * slot_bytes <= scratch_bytes);
@@ -282,7 +310,7 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
         const int64_t rest = tiles & (slots - 1), full = tiles - rest;
         if (!may_split || full == 0 || rest == 0 || force_tail == 1) continue;
         if (force_tail > 1) {
-            if (force_tail <= nk && rest * force_tail * slot_bytes <= scratch_bytes) consider(1, force_tail, 0.0);
+            if (force_tail <= nk && rest * force_tail * slot_bytes <= scratch_bytes) consider(1, force_tail, nk, 0.0);
             continue;
         }
         const double in_front = (double)(full >> slot_shift) * share_time(full, 1, nk) + 2e-6 + tail_launch;
@@ -290,15 +318,15 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
             const int S = kSplits[i];
             if (rest * S > slots || rest * S * slot_bytes > scratch_bytes) break;
             const double cost = in_front + share_time(rest * S, S, ranges.share[i]) + (2.0 * S + 2.0) * (double)(rest * slot_bytes) * (1 / tail_bw);
-            consider(1, S, cost);
-            if (t == fg::TILE_256x256 && (large_tail_cost < 0 || cost < large_tail_cost)) { large_tail = Plan{t, 1, S}; large_tail_cost = cost; }
+            consider(1, S, nk, cost);
+            if (t == fg::TILE_256x256 && sum_length(prices, t, nk) <= longest && cost < large_tail_cost) { large_tail = Plan{t, 1, S}; large_tail_cost = cost; }
         }
     }
     // Of two plans with whole rounds in front of a split tail, the 256x256 tile's runs 4 % faster than the 256x128 tile's whose
     // estimate is up to 9 % lower (36 such products, 0.885 to 1.006: 6318x2901x3304 174.0 -> 153.9 us, 4361x3946x5016 with C 245.5 -> 233.3,
     // 8000x2240x4352 175.4 and 176.5).
     if (prices.last_round && force_tile < 0 && force_split < 1 && best.tile == fg::TILE_256x128 && best.tail_splits > 1 &&
-        large_tail_cost >= 0 && large_tail_cost <= 1.09 * best_cost)
+        large_tail_cost <= 1.09 * best_cost)
         best = large_tail;
     // A short K (up to 256) makes the product a pass over C and D: there the 256x128 tile measured
     // 4 to 15 % faster than the 256x256 tile the estimate picks (8192^2 x 64: 95.7 against 100.3 us,
@@ -322,27 +350,36 @@ int64_t scratch_need(const Plan &plan, int64_t M, int64_t N) {
     return (plan.splits > 1 ? tiles * plan.splits : (tiles & ((1ll << kShifts.slots[t]) - 1)) * plan.tail_splits) * tile_bytes;
 }
 
-// Which scratch memory a call needs is part of what it promises: a call that needed none can be
-// captured before the workspace exists and beside others, one whose partial products fit the static array can be made
-// without allocation.  A plan that leaves the class (none, static array, workspace) of the plan that the former planners made
-// (kFormerRates, itself held to the classes of kPromisedRates) is therefore replaced by the best one that does not (6 % of
-// random shapes).  Costs a split call about 1 us on the host.
-Plan within_promised_scratch(Plan plan, int64_t M, int64_t N, int64_t K, const KRanges &ranges, int k32, int straddling) {
-    const int64_t need = scratch_need(plan, M, N);
-    if (need == 0 || g_force_split.load(std::memory_order_relaxed) >= 1 || g_force_tail.load(std::memory_order_relaxed) > 1 ||
-        g_force_tile.load(std::memory_order_relaxed) >= 0) return plan;
+// What the planner before the larger rings chose (kFormerRates, four K groups as tile 7, itself held to the scratch classes of
+// kPromisedRates), as far as calls still depend on it.
+struct Former { int64_t scratch; int32_t longest; };
+Former former_plan(int64_t M, int64_t N, int64_t K, const KRanges &ranges, bool may_split, int k32, int straddling) {
     auto limit_of = [](int64_t bytes) { return bytes == 0 ? 0 : bytes <= kStaticScratchBytes ? kStaticScratchBytes : kWorkspaceBytes; };
-    const int64_t promised = limit_of(scratch_need(choose_plan(M, N, ranges, true, true, 1, true, k32, false, kWorkspaceBytes, kPromisedPrices), M, N));
-    auto former_plan = [&](int lines) {
-        const Plan p = choose_plan(M, N, ranges, true, true, 1, true, k32, true, kWorkspaceBytes, kFormerPrices, lines);
-        return scratch_need(p, M, N) <= promised ? p : choose_plan(M, N, ranges, promised > 0, true, 1, true, k32, true, promised, kFormerPrices, lines);
-    };
-    // rows off the lines counted in long K loops only, and only for a split
-    const int lines = K > 3904 ? straddling : 0;
-    Plan former = former_plan(lines);
-    if (lines > 0 && former.splits == 1 && former.tail_splits == 1) former = former_plan(0);
-    const int64_t limit = limit_of(scratch_need(former, M, N));
-    return need <= limit ? plan : choose_plan(M, N, ranges, limit > 0, true, 1, true, k32, true, limit, kPrices, straddling);
+    const int64_t promised = !may_split ? 0 : limit_of(scratch_need(choose_plan(M, N, ranges, true, true, 1, true, k32, false, kWorkspaceBytes, kPromisedPrices), M, N));
+    // (the best plan within the promised class; rows off the lines counted in long K loops only, and only for a split)
+    auto plan_of = [&](int lines) { return choose_plan(M, N, ranges, promised > 0, true, 1, true, k32, true, promised, kFormerPrices, lines); };
+    const int lines = promised > 0 && K > 3904 ? straddling : 0;
+    Plan former = plan_of(lines);
+    if (lines > 0 && former.splits == 1 && former.tail_splits == 1) former = plan_of(0);
+    return Former{limit_of(scratch_need(former, M, N)), sum_length(kFormerPrices, former.tile, (ranges.nk + former.splits - 1) / former.splits)};
+}
+
+// Plan of a real product without a diagonal operand.  Two things that the former planner chose hold still:
+// - Which scratch memory a call needs is part of what it promises: a call that needed none can be captured before the
+//   workspace exists and beside others, one whose partial products fit the static array can be made without allocation.  So no plan
+//   leaves the class (none, static array, workspace) of the former one (6 % of random shapes).
+// - No sum over K is longer: fewer partial sums mean a larger error (0.7 % of random shapes, sums 1.33 to 3 times as long; of 48 of them
+//   the error against 64 bits grew by 19 % on average, 408x8792x12960 4.2e-7 -> 7.2e-7, and they were 6 % slower than by the former
+//   plan; held to it they are 3 % faster and their error is 8 % smaller).
+// The former plan's own tile and split are always among the candidates (the larger ring with two groups of two sums in place of
+// the four groups).  Products of fewer than eight K tiles have neither splits nor groups and need not ask.  Costs about 1 us on the host.
+Plan plan_product(int64_t M, int64_t N, int64_t K, bool may_split, int k32, int straddling) {
+    const KRanges ranges(K);
+    const bool forced = g_force_split.load(std::memory_order_relaxed) >= 1 || g_force_tail.load(std::memory_order_relaxed) > 1 ||
+                        g_force_tile.load(std::memory_order_relaxed) >= 0;
+    if (forced || ranges.n == 1) return choose_plan(M, N, ranges, may_split, true, 1, true, k32, true, kWorkspaceBytes, kPrices, straddling);
+    const Former former = former_plan(M, N, K, ranges, may_split, k32, straddling);
+    return choose_plan(M, N, ranges, former.scratch > 0, true, 1, true, k32, true, former.scratch, kPrices, straddling, former.longest);
 }
 
 // Tile of the complex and dual kernels (256x128, 128x128 with two workgroups per unit, 64x64 with
@@ -401,17 +438,13 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     }
     const bool may_split = plan_out && !q.a_diag && !q.b_diag && !q.cd16;   // the reduction pass writes FP32
     const int k32 = (q.a_diag || q.b_diag) ? 0 : q.ab_add ? (q.a_kc != q.b_kc ? 2 : 0) : ((q.a_kc || q.b_kc) ? 2 : 1);
-    const KRanges ranges(q.K);
-    auto planned = [&](int straddling) {
-        const bool dense = !q.a_diag && !q.b_diag;
-        const Plan p = choose_plan(q.M, q.N, ranges, may_split, true, 1, dense, k32, dense, kWorkspaceBytes, kPrices, straddling);
-        return may_split ? within_promised_scratch(p, q.M, q.N, q.K, ranges, k32, straddling) : p;
-    };
     // Rows off a line: by the extents (a row is whole 16-byte pieces), so that the plan query, which knows no leading
     // dimensions, says the same.  Rows that begin on half a line are not counted: 8192x243 over 4256, both K-contiguous,
     // 33.8 us in one pass, 41.7 split in two; 443x4534 33.8, and 35.4.
     auto off_line = [](int64_t extent) { return (extent + 7) / 8 % 4 != 0; };
-    const Plan plan = planned(may_split ? (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N) : 0);
+    const int straddling = may_split ? (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N) : 0;
+    const Plan plan = q.a_diag || q.b_diag ? choose_plan(q.M, q.N, KRanges(q.K), false, true, 1, false)
+                                           : plan_product(q.M, q.N, q.K, may_split, k32, straddling);
     int tile = plan.tile;
     // A product with a diagonal operand is bound by its memory traffic (one pass over the dense
     // operand, C and D; a tile row only meets the K tiles on the diagonal).  While all of it fits the

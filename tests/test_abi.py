@@ -383,3 +383,18 @@ def test_tails_of_the_256x128_tile_give_way_to_the_256x256_tile_only():
     assert "256x128x64+tailsplitk" in fg.fg_gemm_plan(4096, 2304, 5760, 1, 1, 0, fg.FG_PLAN_REAL_BF16)
     for (M, N, K) in ((4100, 4100, 4096), (6318, 2901, 3304), (4361, 3946, 5016)):
         assert "256x256x64_k32+tailsplitk" in fg.fg_gemm_plan(M, N, K, 1, 0, 0), (M, N, K)
+
+
+def test_no_sum_over_k_is_longer_than_before_the_larger_rings():
+    """Products that were split into more ranges before the planner was fitted again: fewer would mean longer sums and a larger error
+    (408x8792x12960: 4.2e-7 in three ranges, 7.2e-7 in one pass).  (sizes, A and B K-contiguous, variant, K tiles in a range at most)"""
+    import re
+    real, bf16 = fg.FG_PLAN_REAL, fg.FG_PLAN_REAL_BF16
+    for (M, N, K, a_kc, b_kc, variant, most) in ((832, 4928, 15680, 0, 0, real, 82), (8815, 161, 15696, 1, 1, bf16, 41), (8768, 192, 15296, 0, 0, real, 40),
+                                                 (7203, 379, 16640, 0, 0, bf16, 65), (408, 8792, 12960, 0, 1, real, 68), (933, 2176, 7032, 0, 1, real, 37),
+                                                 (4394, 406, 7736, 0, 1, real, 41), (3712, 960, 13312, 1, 0, bf16, 52), (384, 7424, 14016, 0, 0, real, 55)):
+        plan = fg.fg_gemm_plan(M, N, K, fg.FG_ROW if a_kc else fg.FG_COL, fg.FG_COL if b_kc else fg.FG_ROW, fg.FG_COL, variant)
+        assert "64x64x64" not in plan, plan                      # (its name does not tell how many K groups it has)
+        split = re.search(r"\+splitk(\d+)$", plan)
+        ranges = int(split.group(1)) if split else 1
+        assert -(-(-(-K // 64)) // ranges) <= most * (2 if "_deep" in plan else 1), (M, N, K, plan)        # deep: two sums of half the length
