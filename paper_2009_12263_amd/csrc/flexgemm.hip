@@ -386,15 +386,16 @@ Plan plan_product(int64_t M, int64_t N, int64_t K, bool may_split, int k32, int 
 // four, 64x64 with K groups with one): the one with the smallest estimated time.  Whole rounds run with every slot of a unit
 // taken, the workgroups of the last, partly filled round share a unit with fewer others; a
 // workgroup's rate is a fraction of what a unit sustains with the 256x128 tile.  Over 130 random products (K 8 to 3000) the choice is
-// 0.4 % slower than the fastest tile on average, over 5 % for four (2.1 % and 18 without the rules on K).
+// 0.7 % slower than the fastest tile on average, over 5 % for nine (2.1 % and 18 without the rules on K).
 // A K up to 128 makes the product a pass over C and D, which four small workgroups per unit overlap best (complex
 // 986x5218x88 with C: 23.4 us with the 64x64 tile, 31.5 and 33.9 with the larger ones; dual 2141x1751x8 12.5, 16.6, 18.4; of 79
 // such products the 64x64 tile is more than 2 % slower than another in five, at most 14 %, 6528x2560x24).
 // The 64x64 tile with two K groups: one tile per unit and K steps for both groups, 1024^3 22.4 -> 15.9 us against the tile with
-// one group, 500x700x3000 interleaved 53.5 -> 33.5; of planar operands, from K = 264 on (to 216 the second group costs 3 to 18 %, around
-// 250 it is even, 42 products), of interleaved ones from 216 on (10x6993x216 7.7, 6.7; 184 and 192 even); in a second round it
-// does not pay (1300x1300x800 21.8, 26.4; 1536^2 x 512 21.5, 29.7).
-int choose_ctile(int64_t M, int64_t N, int64_t K, bool interleaved) {
+// one group, 500x700x3000 interleaved 53.5 -> 33.5, and sums half as long: the error against 64 bits is 0.73 to 0.78 of one group's.
+// For that it is taken from K = 168 on, though up to 216 the second group costs planar operands 3 to 10 % (196x702x176 5.6, 6.1; around 250
+// it is even, interleaved ones gain from 216 on; 42 products); to 160 it costs up to 35 %, in a second round it does not pay (1300x1300x800
+// 21.8, 26.4; 1536^2 x 512 21.5, 29.7).
+int choose_ctile(int64_t M, int64_t N, int64_t K) {
     static const int bm[fg::CTILE_COUNT] = {256, 128, 64, 64};
     static const int bn[fg::CTILE_COUNT] = {128, 128, 64, 64};
     static const int per_cu[fg::CTILE_COUNT] = {1, 2, 4, 1};
@@ -408,7 +409,7 @@ int choose_ctile(int64_t M, int64_t N, int64_t K, bool interleaved) {
     for (int t = 0; t < fg::CTILE_COUNT; ++t) {
         const int64_t tiles = ((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]);
         const int64_t slots = (int64_t)kNumCU * per_cu[t];
-        if (t == fg::CTILE_64x64_KG2 && (tiles > slots || K <= (interleaved ? 208 : 256))) continue;
+        if (t == fg::CTILE_64x64_KG2 && (tiles > slots || K <= 160)) continue;
         auto tile_time = [&](int64_t sharing) {     // one tile, `sharing` workgroups on its unit
             const double unit = per_cu[t] == 1 ? rate_alone[t]
                               : rate_alone[t] + (rate_shared[t] - rate_alone[t]) * (double)(sharing - 1) / (per_cu[t] - 1);
@@ -430,7 +431,7 @@ int choose_ctile(int64_t M, int64_t N, int64_t K, bool interleaved) {
 const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr) {
     if (plan_out) *plan_out = Plan{0, 1, 1};
     if (q.cplx) {
-        const int t = choose_ctile(q.M, q.N, q.K, q.ilv);
+        const int t = choose_ctile(q.M, q.N, q.K);
         if (t < 0) return nullptr;
         const int v = (q.a_kc ? 2 : 0) + (q.b_kc ? 0 : 1);     // nn, nt, tn, tt
         if (q.ilv) return &fg::kernel_table_cplx_il()[t * 4 + v];
