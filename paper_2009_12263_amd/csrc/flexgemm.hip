@@ -150,10 +150,10 @@ constexpr Rates kRates = {{1, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
                           {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
                           2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
                           {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true,
-                          {1, 1, 1, 1, 1, 1, 2, 2, 2}, {1, 1, 1, 1, 2, 1, 1, 2, 2}};
+                          {1, 1, 1, 1, 1, 1, 2, 2, 2}, {1, 1, 1, 1, 2, 1, 2, 2, 2}};
 using fg::TileCfg;
 static_assert(FG_CFG(128, 128, 64, 4, 4, 2, false, true, false)::ACC_SETS == 2 && FG_CFG(256, 128, 64, 3, 4, 2, false, true, false)::ACC_SETS == 1 &&
-              FG_CFG_KG(false, true, false, false, false, 64, 2, false)::ACC_SETS == 1 && FG_CFG_KG(false, true, false, false, false, 64, 4, true)::ACC_SETS == 2 &&
+              FG_CFG_KG(false, true, false, false, false, 64, 2, false)::ACC_SETS == 2 && FG_CFG_KG(false, true, false, false, false, 64, 4, true)::ACC_SETS == 2 &&
               FG_CFG_KG(false, true, false, false, false, 128, 3, true)::ACC_SETS == 2, "Rates::sets");
 // The rates that decided what a call needs scratch memory for before the 64x64 tile had K groups
 // (see plan_product).
@@ -280,10 +280,13 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
         };
         // K groups: at least four K tiles for each, or their reduction costs more than they save (256^3:
         // 4.5 us on the GPU with one group, 4.8 with two; 519x736x320: 5.1, 5.5); the larger rings, which take longer to
-        // fill, from six on (128x2752x720, six: 6.1 us with two buffers, 6.5 with four; 704x640x768: 6.7, 6.4)
+        // fill, from six on.  In one pass of fewer than 56 tiles the ring of four buffers takes eight: with few workgroups at the memory
+        // the ring of two does not wait (47 such products of twelve to fifteen K tiles 3 to 12 % faster with it, 184x9x864 6.9 -> 6.1 us, with
+        // 52 to 57 tiles even, from 60 on 1 to 13 % slower, 4291x17x912 7.2 and 8.1; split ranges of that length 2 to 9 % faster with four).
         const int32_t least = t < fg::TILE_64x64_KG2 || force_tile >= 0 ? 0 : t == fg::TILE_64x64_KG2 ? 8 : prices.last_round ? 12 : 16;
+        const int32_t least_whole = t == fg::TILE_64x64_KG2_DEEP && force_tile < 0 && tiles < 56 ? 16 : least;
         auto consider = [&](int S, int tail, int32_t share, double cost) {
-            if (cost >= best_cost || nk < least * S * tail || sum_length(prices, t, share) > longest) return;
+            if (cost >= best_cost || nk < (S * tail > 1 ? least : least_whole) * S * tail || sum_length(prices, t, share) > longest) return;
             best = Plan{t, S, tail};
             best_cost = cost;
         };

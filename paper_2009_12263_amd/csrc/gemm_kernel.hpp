@@ -163,12 +163,14 @@ struct TileCfg {
     static constexpr bool CD16 = CD16_;
     // ACC_SETS = 2: the k-slices of a K tile are summed in turns into two sets of accumulators, added up after the K loop.
     // Half as many roundings follow one another in each sum: the error against 64 bits of 1024^3 is 1.1e-7 with two
-    // groups of two sets, as with the four K groups that served it before, 1.5e-7 with two groups of one.
-    static constexpr int ACC_SETS = !STRIDED_ && DIAG_ == 0 && CPLX_ == 0 && !M16_ && (KTURNS_ || STAGES_ == 4) ? 2 : 1;
+    // groups of two sets, as with the four K groups that served it before, 1.5e-7 with two groups of one; no time is lost
+    // (64x64 tile with two buffers: 81 -> 87 registers, 24 products equal within 1 %).
+    static constexpr bool PLAIN_REAL = !STRIDED_ && DIAG_ == 0 && CPLX_ == 0 && !M16_;
+    static constexpr int ACC_SETS = PLAIN_REAL && (KG_ > 1 || STAGES_ == 4) ? 2 : 1;
     // ONCE: the kernel has K loops whose loads of A or of B carry the streaming policy, for operands that are read once:
     // narrow products, bound by reading their large operand (128x16384x12288 122 -> 113 us; where other tiles read the
     // operand again it costs: 8192x1024x4096 72 -> 76).  From which size on, and why: streams_once (cache_policy.hpp).
-    static constexpr bool ONCE = ACC_SETS == 2;
+    static constexpr bool ONCE = PLAIN_REAL && (KTURNS_ || STAGES_ == 4);
     // SPREAD: the refill loads of a ring buffer are issued one at a time between the MFMAs of two
     // k-slices (A's part in the slice after the buffer is retired, B's part in the next one)
     // instead of as one burst: a burst from all waves queues up in the compute unit's single

@@ -279,9 +279,10 @@ def float_result(M, N, K, la, lb, **kw):
 
 
 def test_k_group_kernels_run(monkeypatch):
-    """One, two and four K groups add the same products up in different orders: on floats the three tiles
-    differ in the last bits (plan names do not tell them apart), so a tile that silently ran as
-    another one is seen; the planner's choice at 1024^3 is the one with four."""
+    """One K group, two that take equal runs of the K tiles (ring of two) and two that take them in turns (ring of four) add the
+    same products up in different orders: on floats the three tiles differ in the last bits (plan names do not tell them
+    apart), so a tile that silently ran as another one is seen; the planner's choice at 1024^3 is the ring of four, and for
+    fewer than 56 tiles of twelve to fifteen K tiles, which wait for nothing, the ring of two."""
     for la, lb in itertools.product(LAYOUTS, LAYOUTS):
         got = {}
         for tile in ("3", "6", "7"):
@@ -291,11 +292,18 @@ def test_k_group_kernels_run(monkeypatch):
         say("A=%d B=%d" % (la, lb))
         assert not torch.equal(got["3"], got["6"]) and not torch.equal(got["3"], got["7"]) and not torch.equal(got["6"], got["7"])
         assert torch.equal(float_result(1024, 1024, 1024, la, lb), got["7"])
+        for M, N, tile in ((184, 104, "6"), (64, 1728, "6"), (1024, 512, "7")):
+            small = {}
+            for t in ("6", "7"):
+                setenv(monkeypatch, "FG_FORCE_TILE", t)
+                small[t] = float_result(M, N, 864, la, lb)
+            delenv(monkeypatch, "FG_FORCE_TILE")
+            assert not torch.equal(small["6"], small["7"]) and torch.equal(float_result(M, N, 864, la, lb), small[tile]), (M, N)
 
 
-@pytest.mark.parametrize("tile,groups", [("6", 2), ("7", 4), ("8", 2)])
-def test_k_groups(monkeypatch, tile, groups):
-    """The 64x64 tile whose groups of waves share its K tiles (tiled kernels): fewer K tiles than
+@pytest.mark.parametrize("tile", ["6", "7", "8"])
+def test_k_groups(monkeypatch, tile):
+    """The tiles whose two groups of waves share their K tiles (tiled kernels): fewer K tiles than
     groups, runs that do not come out even, a K tail in the last group's last and last but one tile,
     several tiles per workgroup, K splits, and every option of the families."""
     from tests.parity import run_gemm_case
