@@ -155,6 +155,17 @@ using fg::TileCfg;
 static_assert(FG_CFG(128, 128, 64, 4, 4, 2, false, true, false)::ACC_SETS == 2 && FG_CFG(256, 128, 64, 3, 4, 2, false, true, false)::ACC_SETS == 1 &&
               FG_CFG_KG(false, true, false, false, false, 64, 2, false)::ACC_SETS == 2 && FG_CFG_KG(false, true, false, false, false, 64, 4, true)::ACC_SETS == 2 &&
               FG_CFG_KG(false, true, false, false, false, 128, 3, true)::ACC_SETS == 2, "Rates::sets");
+// Binary16 C and D with K from 512 on: a tile's C and D at three quarters of the bytes (they are half, in lines that are accessed
+// all the same), and rows off the lines priced for the tiles without K groups (these products cannot be split, and were priced
+// without).  30 of 35 changed products are faster, 13 % on average, none over 5 % slower (3817x2363x1944 66.8 -> 53.2 us, 1600x5376x768 with C
+// 32.6 -> 27.8); of 70 large random ones the choice is 1.4 % slower than the fastest tile on average (2.9 %).  With a price on the
+// K groups too, long narrow products leave the 64x128 tile for the deep 128x128 one, which has half as many workgroups
+// (8799x66x14168 94.7 and 175.3 us; 19 of 19 slower).  A shorter K keeps the rates above: these chose tiles 17 to 44 % slower there.
+constexpr Rates kRates16 = {{1, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
+                            {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
+                            2.07e-6, 26.8e9 * 4 / 3, 6.92e-6, 8.7e12,
+                            {0, 0.022, 0, 0.0446, 0.0395, 0, 0, 0, 0}, true,
+                            {1, 1, 1, 1, 1, 1, 2, 2, 2}, {1, 1, 1, 1, 2, 1, 2, 2, 2}};
 // The rates that decided what a call needs scratch memory for before the 64x64 tile had K groups
 // (see plan_product).
 constexpr Rates kPromisedRates = {{1.0, 0.8, 0.73, 0.45, 0.57, 1.0, 0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0, 0}, 2e-6, 25e9, 6e-6, 3e12, {}, false};
@@ -205,7 +216,7 @@ constexpr Prices priced(const Rates &r) {
     p.last_round = r.last_round;
     return p;
 }
-constexpr Prices kPrices = priced(kRates), kPromisedPrices = priced(kPromisedRates), kFormerPrices = priced(kFormerRates), kContractPrices = priced(kContractRates);
+constexpr Prices kPrices = priced(kRates), kPrices16 = priced(kRates16), kPromisedPrices = priced(kPromisedRates), kFormerPrices = priced(kFormerRates), kContractPrices = priced(kContractRates);
 
 // The K ranges that a product may be split into: at least four K tiles (256 k) each.
 struct KRanges {
@@ -376,13 +387,13 @@ Former former_plan(int64_t M, int64_t N, int64_t K, const KRanges &ranges, bool 
 //   plan; held to it they are 3 % faster and their error is 8 % smaller).
 // The former plan's own tile and split are always among the candidates (the larger ring with two groups of two sums in place of
 // the four groups).  Products of fewer than eight K tiles have neither splits nor groups and need not ask.  Costs about 1 us on the host.
-Plan plan_product(int64_t M, int64_t N, int64_t K, bool may_split, int k32, int straddling) {
+Plan plan_product(int64_t M, int64_t N, int64_t K, bool may_split, int k32, int straddling, const Prices &prices) {
     const KRanges ranges(K);
     const bool forced = g_force_split.load(std::memory_order_relaxed) >= 1 || g_force_tail.load(std::memory_order_relaxed) > 1 ||
                         g_force_tile.load(std::memory_order_relaxed) >= 0;
-    if (forced || ranges.n == 1) return choose_plan(M, N, ranges, may_split, true, 1, true, k32, true, kWorkspaceBytes, kPrices, straddling);
+    if (forced || ranges.n == 1) return choose_plan(M, N, ranges, may_split, true, 1, true, k32, true, kWorkspaceBytes, prices, straddling);
     const Former former = former_plan(M, N, K, ranges, may_split, k32, straddling);
-    return choose_plan(M, N, ranges, former.scratch > 0, true, 1, true, k32, true, former.scratch, kPrices, straddling, former.longest);
+    return choose_plan(M, N, ranges, former.scratch > 0, true, 1, true, k32, true, former.scratch, prices, straddling, former.longest);
 }
 
 // Tile of the complex and dual kernels (256x128, 128x128 with two workgroups per unit, 64x64 with
@@ -446,9 +457,10 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     // dimensions, says the same.  Rows that begin on half a line are not counted: 8192x243 over 4256, both K-contiguous,
     // 33.8 us in one pass, 41.7 split in two; 443x4534 33.8, and 35.4.
     auto off_line = [](int64_t extent) { return (extent + 7) / 8 % 4 != 0; };
-    const int straddling = may_split ? (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N) : 0;
+    const bool long16 = q.cd16 && q.K >= 512;               // (see kRates16)
+    const int straddling = may_split || long16 ? (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N) : 0;
     const Plan plan = q.a_diag || q.b_diag ? choose_plan(q.M, q.N, KRanges(q.K), false, true, 1, false)
-                                           : plan_product(q.M, q.N, q.K, may_split, k32, straddling);
+                                           : plan_product(q.M, q.N, q.K, may_split, k32, straddling, long16 ? kPrices16 : kPrices);
     int tile = plan.tile;
     // A product with a diagonal operand is bound by its memory traffic (one pass over the dense
     // operand, C and D; a tile row only meets the K tiles on the diagonal).  While all of it fits the
