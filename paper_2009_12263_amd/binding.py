@@ -1,5 +1,5 @@
 """Thin binding of libflexgemm.so: argument marshalling only, natively for plain device tensors
-(_fastcall.so, csrc/fastcall.cpp), with ctypes for everything else.
+(csrc/fastcall.cpp, where it is built), with ctypes for everything else.
 
 The functions have the names and arguments of the C ABI (include/flexgemm.h).  Torch is used
 for device memory and streams; every step of the computation runs in the library's kernels.
@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes as C
 import importlib.util
 import os
+import sysconfig
 from dataclasses import dataclass
 from typing import Optional, Sequence
 
@@ -17,6 +18,8 @@ import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libflexgemm.so")
+# The native marshalling uses Python's and torch's C++ interfaces: it is built for one version of each, which its name holds.
+FASTCALL_PATH = os.path.join(_PKG, "_fastcall.%s.torch-%s.so" % (sysconfig.get_config_var("SOABI"), torch.__version__))
 
 FG_OK = 0
 FG_ERR_NULL, FG_ERR_SHAPE, FG_ERR_LAYOUT, FG_ERR_ALIGN, FG_ERR_UNSUPPORTED, FG_ERR_MODES, FG_ERR_LAUNCH = range(1, 8)
@@ -100,12 +103,17 @@ def load_library() -> C.CDLL:
     return _lib
 
 
+class _CtypesOnly:
+    """In place of the native marshalling where it is not built: leaves every call to the binding (4 to 8 us more each)."""
+    gemm = dual = contract = staticmethod(lambda *args: -1)
+
+
 def _load_fastcall(lib: C.CDLL) -> None:
     global _fast
-    path = os.path.join(_PKG, "_fastcall.so")
-    if not os.path.exists(path):
-        raise ImportError("_fastcall.so is not built: run `python -m paper_2009_12263_amd.build`")
-    spec = importlib.util.spec_from_file_location(__package__ + "._fastcall", path)
+    if not os.path.exists(FASTCALL_PATH):
+        _fast = _CtypesOnly
+        return
+    spec = importlib.util.spec_from_file_location(__package__ + "._fastcall", FASTCALL_PATH)
     fast = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(fast)
     fast.setup(Matrix, _current_raw_stream, _current_device,

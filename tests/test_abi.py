@@ -358,6 +358,27 @@ def test_native_marshalling_leaves_everything_but_device_tensors_to_the_binding(
         fg._fast.setup(1, 2)
 
 
+def test_binding_works_without_the_native_marshalling(monkeypatch, tmp_path):
+    """Where _fastcall is not built, or only for another Python or torch, whose versions its name holds, calls are marshalled with ctypes."""
+    import sysconfig
+    import torch
+    lib = fg.load_library()
+    assert sysconfig.get_config_var("SOABI") in fg.FASTCALL_PATH and torch.__version__ in fg.FASTCALL_PATH and os.path.exists(fg.FASTCALL_PATH)
+    native = fg._fast
+    t = torch.zeros(64 * 64, dtype=torch.float16)
+    A, D = fg.Matrix(t, fg.FG_COL, 64), fg.Matrix(t.float(), fg.FG_COL, 64)
+    try:
+        monkeypatch.setattr(fg, "FASTCALL_PATH", str(tmp_path / "_fastcall.so"))
+        fg._load_fastcall(lib)
+        assert fg._fast is not native
+        assert fg.fg_gemm(64, 64, 64, 1.0, A, None, 0.0, None, D, raise_on_error=False) == fg.FG_ERR_NULL
+        assert fg.fg_gemm_dual(64, 64, 64, 1.0, A, A, 0.0, None, None, raise_on_error=False) == fg.FG_ERR_NULL
+        with pytest.raises(fg.FlexGemmError):
+            fg.fg_contract([0, 2], [1, 64], t, [2, 1], [1, 64], t, [0, 1], [1, 64], None, t.float(), {0: 64, 1: 64})
+    finally:
+        fg._fast = native
+
+
 def test_products_that_needed_no_scratch_memory_are_not_split():
     """Calls that were made in one pass before the larger rings stay free of scratch memory, though a split is now estimated
     faster: they may be captured before the workspace exists, and beside other calls."""
