@@ -103,6 +103,9 @@ def load_library() -> C.CDLL:
     return _lib
 
 
+_in_bad_fork = getattr(torch._C, "_cuda_isInBadFork", lambda: False)
+
+
 class _CtypesOnly:
     """In place of the native marshalling where it is not built: leaves every call to the binding (4 to 8 us more each)."""
     gemm = dual = contract = staticmethod(lambda *args: -1)
@@ -110,7 +113,9 @@ class _CtypesOnly:
 
 def _load_fastcall(lib: C.CDLL) -> None:
     global _fast
-    if not os.path.exists(FASTCALL_PATH):
+    # A child of fork() cannot use its parent's GPU tensors.  torch says so when the binding asks for the stream; the native
+    # marshalling, which does not ask that way, sees a fork that comes after it is loaded, but not one before.
+    if not os.path.exists(FASTCALL_PATH) or _in_bad_fork():
         _fast = _CtypesOnly
         return
     spec = importlib.util.spec_from_file_location(__package__ + "._fastcall", FASTCALL_PATH)

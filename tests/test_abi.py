@@ -379,6 +379,20 @@ def test_binding_works_without_the_native_marshalling(monkeypatch, tmp_path):
         fg._fast = native
 
 
+def test_native_marshalling_stays_out_of_a_forked_child(monkeypatch):
+    """A process that forks after it has used the GPU, and whose child loads the library first: every call there goes the binding's way,
+    where torch refuses it."""
+    lib = fg.load_library()
+    native = fg._fast
+    assert native is not fg._CtypesOnly
+    try:
+        monkeypatch.setattr(fg, "_in_bad_fork", lambda: True)
+        fg._load_fastcall(lib)
+        assert fg._fast is fg._CtypesOnly and fg._fast.gemm(1, 2, 3) == -1
+    finally:
+        fg._fast = native
+
+
 def test_products_that_needed_no_scratch_memory_are_not_split():
     """Calls that were made in one pass before the larger rings stay free of scratch memory, though a split is now estimated
     faster: they may be captured before the workspace exists, and beside other calls."""
