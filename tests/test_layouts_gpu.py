@@ -109,15 +109,73 @@ def test_interleaved_and_planar_matrices_are_not_mixed():
     assert fg.fg_gemm(64, 64, 64, 1.0, fg.Matrix(H, fg.FG_COL, 64, im=H, dtype=fg.FG_CF16), il(H, fg.FG_CF16), 0.0, None, il(F, fg.FG_CF32), **kw) == fg.FG_ERR_LAYOUT
 
 
-@pytest.mark.parametrize("kind", [dict(), dict(dual=True), dict(interleaved=True)])
-@pytest.mark.parametrize("M", [256, 264, 260])
-def test_cache_policies_of_complex_results(kind, M):
-    """C and D of complex and dual products are kept in the caches or streamed past them (columns on the 128-byte lines,
-    on half lines and off them; with C and without): the same results, interior and edge tiles of every tile shape."""
-    for N, with_c in ((128, True), (128, False), (133, True), (133, False)):
-        say("M=%d N=%d C=%d %s" % (M, N, with_c, kind))
-        run_cgemm_case(M, N, 72, ints=True, alpha=2.0, beta=-1.0, with_c=with_c, **kind)
-        run_cgemm_case(M, N, 72, fg.FG_ROW, fg.FG_ROW, fg.FG_ROW, ints=True, with_c=with_c, **kind)
+KINDS = [dict(), dict(dual=True), dict(interleaved=True)]
+TILES = ["0", "1", "2", "3"]           # 256x128, 128x128, 64x64, 64x64 with two K groups
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("tile", TILES)
+def test_cache_policies_of_complex_results(monkeypatch, kind, tile):
+    """C and D of complex and dual products are kept in the caches or streamed past them: the same results on interior and edge
+    tiles of every tile shape, with C and without, for columns on the lines, on half lines and off them.  Small passes on
+    the lines stream up to K = 256 and are kept above; of the large ones (over 80 MB), those beside large A and B stream and those
+    off the lines beside small ones are kept (test_cache_policy.py has the rule)."""
+    from tests.parity import delenv, setenv
+    setenv(monkeypatch, "FG_FORCE_TILE", tile)
+    for M, N, K, with_c in itertools.product((256, 264, 260), (128, 133), (72, 264), (True, False)):
+        say("tile %s M=%d N=%d K=%d C=%d %s" % (tile, M, N, K, with_c, kind))
+        run_cgemm_case(M, N, K, ints=True, alpha=2.0, beta=-1.0, with_c=with_c, **kind)
+    run_cgemm_case(133, 264, 72, fg.FG_ROW, fg.FG_ROW, fg.FG_ROW, ints=True, **kind)
+    for M, N, K in ((1504, 2003, 2800), (1507, 2003, 2800), (2052, 2603, 72)):
+        say("tile %s M=%d N=%d K=%d C=1 %s" % (tile, M, N, K, kind))
+        run_cgemm_case(M, N, K, fg.FG_ROW, fg.FG_COL, ints=True, alpha=2.0, beta=-1.0, samples=3000, **kind)
+    delenv(monkeypatch, "FG_FORCE_TILE")
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("tile", TILES)
+def test_every_complex_tile_shape(monkeypatch, kind, tile):
+    """Every tile of the complex, dual and interleaved kernels over all layouts: less than a tile, ragged M and N, short and
+    long K with a tail, several tiles; integers, every entry exact, and floats."""
+    from tests.parity import delenv, setenv
+    setenv(monkeypatch, "FG_FORCE_TILE", tile)
+    for la, lb in itertools.product(LAYOUTS, LAYOUTS):
+        say("tile %s la=%d lb=%d %s" % (tile, la, lb, kind))
+        run_cgemm_case(70, 45, 8, la, lb, ints=True, pad=8, poison=True, **kind)
+        run_cgemm_case(300, 270, 136, la, lb, ints=True, pad=8, poison=True, beta=-2.0, **kind)
+        run_cgemm_case(270, 131, 1032, la, lb, fg.FG_ROW, ints=True, with_c=False, **kind)
+        run_cgemm_case(513, 260, 40, la, lb, ints=True, **kind)
+        run_cgemm_case(261, 200, 328, la, lb, alpha=0.5, beta=2.0, **kind)
+    delenv(monkeypatch, "FG_FORCE_TILE")
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_two_64x64_tiles_of_complex_products_are_told_apart(monkeypatch, kind):
+    """One K group and two (which share a plan name) add the same products up in different orders: on floats their results
+    differ in the last bits, so one that silently ran as the other is seen.  The planner takes one up to K = 160, two above."""
+    import torch
+    from paper_2009_12263_amd import workloads as W
+    from tests.parity import delenv, setenv
+    def result(M, N, K):
+        planes = 1 if kind.get("interleaved") else 2
+        def mat(rows, cols, stream, dtype, code):
+            n = rows * cols * (2 if planes == 1 else 1)
+            t = [W.uniform_pm1(n, stream + i, device="cuda", dtype=dtype) for i in range(planes)]
+            return fg.Matrix(t[0], fg.FG_COL, rows, im=t[1] if planes == 2 else None, dtype=code if planes == 1 else None)
+        A, B = mat(M, K, 1, torch.float16, fg.FG_CF16), mat(K, N, 3, torch.float16, fg.FG_CF16)
+        D = mat(M, N, 5, torch.float32, fg.FG_CF32)
+        (fg.fg_gemm_dual if kind.get("dual") else fg.fg_gemm)(M, N, K, 1.0, A, B, 0.0, None, D)
+        torch.cuda.synchronize()
+        return torch.cat([D.re, D.im]) if planes == 2 else D.re
+    for M, N, K, planned in ((200, 136, 96, "2"), (200, 136, 160, "2"), (200, 136, 168, "3"), (304, 200, 1032, "3")):
+        got = {}
+        for tile in ("2", "3"):
+            setenv(monkeypatch, "FG_FORCE_TILE", tile)
+            got[tile] = result(M, N, K)
+        delenv(monkeypatch, "FG_FORCE_TILE")
+        say("M=%d N=%d K=%d %s" % (M, N, K, kind))
+        assert not torch.equal(got["2"], got["3"])
+        assert torch.equal(result(M, N, K), got[planned]), (M, N, K)
 
 
 @pytest.mark.parametrize("kind", [dict(), dict(dual=True), dict(interleaved=True)])
