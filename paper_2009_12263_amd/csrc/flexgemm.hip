@@ -318,6 +318,10 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
         }
         for (int i = 0; i < ranges.n; ++i) {
             if (i > 0 && (!may_split || tiles * kSplits[i] * slot_bytes > scratch_bytes)) break;
+            // The rates of the plain 64x64 tile were fitted to whole products.  Split, it is overrated: 60 plans that it won take 0.90 of its
+            // time on the tiles with K groups or the deep 128x128 one (157x4293x12808 75.7 -> 56.4 us, 5219x11x14856 43.7 -> 36.6; two are 3
+            // and 5 % slower), so it is left to ranges that are too short for K groups.
+            if (i > 0 && t == fg::TILE_64x64 && allow_groups && prices.last_round && nk >= 8 * kSplits[i]) continue;
             split_all(kSplits[i], ranges.share[i]);
         }
         // (b) whole rounds in one pass, the tiles of the last, partly filled round split over K

@@ -443,3 +443,14 @@ def test_tiles_of_binary16_results():
                                         (4608, 1024, 192, 1, 1, "64x64x64")):
         plan = fg.fg_gemm_plan(M, N, K, fg.FG_ROW if a_kc else fg.FG_COL, fg.FG_COL if b_kc else fg.FG_ROW, fg.FG_COL, fg.FG_PLAN_REAL_F16_CD)
         assert plan.split("_")[-1] == tile or plan.endswith(tile + "_k32"), (M, N, K, plan)
+
+
+def test_the_plain_64x64_tile_is_not_split_where_k_groups_can_be():
+    """Split products that the planner gave to the plain 64x64 tile, by an estimate for whole products, 4 to 34 % slower than before."""
+    bf16, add = fg.FG_PLAN_REAL_BF16, fg.FG_PLAN_REAL_AB_ADD
+    for (M, N, K, a_kc, b_kc, variant, plan) in ((157, 4293, 12808, 0, 0, bf16, "gemm_bf16_nt_128x128x64_deep+splitk3"),
+                                                 (3017, 280, 6296, 0, 0, bf16, "gemm_bf16_nt_128x128x64_deep+splitk3"),
+                                                 (1654, 565, 6064, 1, 0, add, "gemm_abadd_tt_128x128x64_deep+splitk3"),
+                                                 (192, 6272, 4840, 1, 1, fg.FG_PLAN_REAL, "gemm_tn_128x128x64_deep+splitk2"),
+                                                 (64, 8320, 8576, 0, 0, fg.FG_PLAN_REAL, "gemm_nt_64x128x64+splitk3")):
+        assert fg.fg_gemm_plan(M, N, K, fg.FG_ROW if a_kc else fg.FG_COL, fg.FG_COL if b_kc else fg.FG_ROW, fg.FG_COL, variant) == plan, (M, N, K)
