@@ -156,12 +156,12 @@ static_assert(FG_CFG(128, 128, 64, 4, 4, 2, false, true, false)::ACC_SETS == 2 &
               FG_CFG_KG(false, true, false, false, false, 64, 2, false)::ACC_SETS == 2 && FG_CFG_KG(false, true, false, false, false, 64, 4, true)::ACC_SETS == 2 &&
               FG_CFG_KG(false, true, false, false, false, 128, 3, true)::ACC_SETS == 2, "Rates::sets");
 // Binary16 C and D with K from 512 on: a tile's C and D at three quarters of the bytes (they are half, in lines that are accessed
-// all the same), and rows off the lines priced for the tiles without K groups (these products cannot be split, and were priced
-// without).  30 of 35 changed products are faster, 13 % on average, none over 5 % slower (3817x2363x1944 66.8 -> 53.2 us, 1600x5376x768 with C
-// 32.6 -> 27.8); of 70 large random ones the choice is 1.4 % slower than the fastest tile on average (2.9 %).  With a price on the
-// K groups too, long narrow products leave the 64x128 tile for the deep 128x128 one, which has half as many workgroups
+// all the same), rows off the lines priced for the tiles without K groups (these products cannot be split, and were priced
+// without), and the 64x64 tile at its former shared rate.  216 random products: 0.6 % slower than the fastest tile on average, over 5 % for
+// 11 (without all that 2.4 % and 39: 3817x2363x1944 66.8 -> 53.2 us, 6308x2574x1016 77.1 -> 56.7, 1600x5376x768 with C 32.6 -> 27.8).
+// With a price on the K groups too, long narrow products leave the 64x128 tile for the deep 128x128 one, which has half as many workgroups
 // (8799x66x14168 94.7 and 175.3 us; 19 of 19 slower).  A shorter K keeps the rates above: these chose tiles 17 to 44 % slower there.
-constexpr Rates kRates16 = {{1, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
+constexpr Rates kRates16 = {{1, 0.88, 0.732, 0.40, 0.74, 1, 0.373, 0.367, 0.384},
                             {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
                             2.07e-6, 26.8e9 * 4 / 3, 6.92e-6, 8.7e12,
                             {0, 0.022, 0, 0.0446, 0.0395, 0, 0, 0, 0}, true,
