@@ -247,10 +247,12 @@ constexpr Shifts shifts_of_tiles() {
 constexpr Shifts kShifts = shifts_of_tiles();
 static_assert(1 << kShifts.cu == kNumCU, "the searches shift instead of dividing");
 
-// The longest sum that a plan adds up one product after another, in halves of a K tile, from the K tiles of one range.
-int32_t sum_length(const Prices &prices, int tile, int32_t share) {
+// How many additions follow one another in an entry of a plan of S ranges of `share` K tiles: four matrix instructions to a K
+// tile in one accumulator, and the partial products of the ranges.  The error against 64 bits goes with the square root: with T products
+// in all, the rounding of T / n sums of n adds T * n, that of adding them up T * (T / n).
+int32_t sum_length(const Prices &prices, int tile, int S, int32_t share) {
     const int g = prices.group_shift[tile];
-    return ((share + (1 << g) - 1) >> g) * 2 >> prices.set_shift[tile];
+    return (((share + (1 << g) - 1) >> g) * 4 >> prices.set_shift[tile]) + S;
 }
 
 // longest: no plan whose sums are longer (sum_length).
@@ -291,13 +293,14 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
         };
         // K groups: at least four K tiles for each, or their reduction costs more than they save (256^3:
         // 4.5 us on the GPU with one group, 4.8 with two; 519x736x320: 5.1, 5.5); the larger rings, which take longer to
-        // fill, from six on.  In one pass of fewer than 56 tiles the ring of four buffers takes eight: with few workgroups at the memory
-        // the ring of two does not wait (47 such products of twelve to fifteen K tiles 3 to 12 % faster with it, 184x9x864 6.9 -> 6.1 us, with
-        // 52 to 57 tiles even, from 60 on 1 to 13 % slower, 4291x17x912 7.2 and 8.1; split ranges of that length 2 to 9 % faster with four).
+        // fill, from six on.  With fewer than 56 workgroups the ring of four buffers takes eight: with few at the memory
+        // the ring of two does not wait (47 products of fewer tiles and twelve to fifteen K tiles 3 to 12 % faster with it, 184x9x864
+        // 6.9 -> 6.1 us, 52 to 57 tiles even, from 60 on 1 to 13 % slower, 4291x17x912 7.2 and 8.1; split ranges of that length: 20
+        // products of 4 to 48 workgroups up to 21 % faster with the ring of two, 30x284x3768 9.9 -> 8.4, with more 2 to 9 % slower).
         const int32_t least = t < fg::TILE_64x64_KG2 || force_tile >= 0 ? 0 : t == fg::TILE_64x64_KG2 ? 8 : prices.last_round ? 12 : 16;
-        const int32_t least_whole = t == fg::TILE_64x64_KG2_DEEP && force_tile < 0 && tiles < 56 ? 16 : least;
+        auto least_of = [&](int S) { return t == fg::TILE_64x64_KG2_DEEP && force_tile < 0 && prices.last_round && tiles * S < 56 ? 16 : least; };
         auto consider = [&](int S, int tail, int32_t share, double cost) {
-            if (cost >= best_cost || nk < (S * tail > 1 ? least : least_whole) * S * tail || sum_length(prices, t, share) > longest) return;
+            if (cost >= best_cost || nk < least_of(S) * S * tail || sum_length(prices, t, S, share) > longest) return;
             best = Plan{t, S, tail};
             best_cost = cost;
         };
@@ -337,7 +340,7 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
             if (rest * S > slots || rest * S * slot_bytes > scratch_bytes) break;
             const double cost = in_front + share_time(rest * S, S, ranges.share[i]) + (2.0 * S + 2.0) * (double)(rest * slot_bytes) * (1 / tail_bw);
             consider(1, S, nk, cost);
-            if (t == fg::TILE_256x256 && sum_length(prices, t, nk) <= longest && cost < large_tail_cost) { large_tail = Plan{t, 1, S}; large_tail_cost = cost; }
+            if (t == fg::TILE_256x256 && sum_length(prices, t, 1, nk) <= longest && cost < large_tail_cost) { large_tail = Plan{t, 1, S}; large_tail_cost = cost; }
         }
     }
     // Of two plans with whole rounds in front of a split tail, the 256x256 tile's runs 4 % faster than the 256x128 tile's whose
@@ -379,16 +382,17 @@ Former former_plan(int64_t M, int64_t N, int64_t K, const KRanges &ranges, bool 
     const int lines = promised > 0 && K > 3904 ? straddling : 0;
     Plan former = plan_of(lines);
     if (lines > 0 && former.splits == 1 && former.tail_splits == 1) former = plan_of(0);
-    return Former{limit_of(scratch_need(former, M, N)), sum_length(kFormerPrices, former.tile, (ranges.nk + former.splits - 1) / former.splits)};
+    return Former{limit_of(scratch_need(former, M, N)), sum_length(kFormerPrices, former.tile, former.splits, (ranges.nk + former.splits - 1) / former.splits)};
 }
 
 // Plan of a real product without a diagonal operand.  Two things that the former planner chose hold still:
 // - Which scratch memory a call needs is part of what it promises: a call that needed none can be captured before the
 //   workspace exists and beside others, one whose partial products fit the static array can be made without allocation.  So no plan
 //   leaves the class (none, static array, workspace) of the former one (6 % of random shapes).
-// - No sum over K is longer: fewer partial sums mean a larger error (0.7 % of random shapes, sums 1.33 to 3 times as long; of 48 of them
-//   the error against 64 bits grew by 19 % on average, 408x8792x12960 4.2e-7 -> 7.2e-7, and they were 6 % slower than by the former
-//   plan; held to it they are 3 % faster and their error is 8 % smaller).
+// - No sum is longer (sum_length): fewer partial sums of a long K (0.7 % of random shapes) had an error against 64 bits 19 % larger on
+//   average, 408x8792x12960 4.2e-7 -> 7.2e-7, and were 6 % slower than by the former plan; held to it 48 of them are 3 % faster
+//   with an error 8 % smaller.  Twice as many ranges as before, whose partial products are added up one after the other (9 % of
+//   random shapes, small outputs with a long K), had one 3 to 20 % larger; those are as fast as before on average (0.88 to 1.16), 22 % more exact.
 // The former plan's own tile and split are always among the candidates (the larger ring with two groups of two sums in place of
 // the four groups).  Products of fewer than eight K tiles have neither splits nor groups and need not ask.  Costs about 1 us on the host.
 Plan plan_product(int64_t M, int64_t N, int64_t K, bool may_split, int k32, int straddling, const Prices &prices) {

@@ -422,7 +422,8 @@ def test_tails_of_the_256x128_tile_give_way_to_the_256x256_tile_only():
 
 def test_no_sum_over_k_is_longer_than_before_the_larger_rings():
     """Products that were split into more ranges before the planner was fitted again: fewer would mean longer sums and a larger error
-    (408x8792x12960: 4.2e-7 in three ranges, 7.2e-7 in one pass).  (sizes, A and B K-contiguous, variant, K tiles in a range at most)"""
+    (408x8792x12960: 4.2e-7 in three ranges, 7.2e-7 in one pass).  (sizes, A and B K-contiguous, variant, K tiles in a range at most)
+    Nor are more ranges added up than before where that is the longer sum (241x15x16544: 64 ranges 1.80e-7, 32 1.55e-7)."""
     import re
     real, bf16 = fg.FG_PLAN_REAL, fg.FG_PLAN_REAL_BF16
     for (M, N, K, a_kc, b_kc, variant, most) in ((832, 4928, 15680, 0, 0, real, 82), (8815, 161, 15696, 1, 1, bf16, 41), (8768, 192, 15296, 0, 0, real, 40),
@@ -433,6 +434,10 @@ def test_no_sum_over_k_is_longer_than_before_the_larger_rings():
         split = re.search(r"\+splitk(\d+)$", plan)
         ranges = int(split.group(1)) if split else 1
         assert -(-(-(-K // 64)) // ranges) <= most * (2 if "_deep" in plan else 1), (M, N, K, plan)        # deep: two sums of half the length
+    for (M, N, K, a_kc, b_kc, variant, most) in ((241, 15, 16544, 1, 0, real, 32), (27, 24, 16496, 0, 0, bf16, 32), (167, 37, 14432, 1, 0, bf16, 24),
+                                                 (83, 803, 16696, 0, 1, real, 8), (13, 87, 5872, 1, 1, bf16, 8)):
+        plan = fg.fg_gemm_plan(M, N, K, fg.FG_ROW if a_kc else fg.FG_COL, fg.FG_COL if b_kc else fg.FG_ROW, fg.FG_COL, variant)
+        assert int(re.search(r"\+splitk(\d+)$", plan).group(1)) <= most, (M, N, K, plan)
 
 
 def test_tiles_of_binary16_results():
