@@ -38,9 +38,10 @@ inline bool keeps_real_cd(int64_t ab, int64_t cd, bool has_c, int64_t ldc, int64
 }
 
 // The same for complex and dual products, whose planes or pairs double all of it.  Up to 80 MB in all: with C they are kept
-// (1536^2 x 512 24.4 -> 21.6 us, dual 2048^2 x 512 32.0 -> 29.4), but for a pass over at most 16 MB with a short K whose
-// columns are on the lines, which the L2s turn over faster streamed (K 72 to 200, 8 to 14 MB: 3 to 14 % slower kept, complex 1440x613x136
-// 8.8 / 7.7; with K from 336 on 2 to 11 % faster); without C off the lines only (dual 1532x2368x1112 41.3 -> 34.2; on them 22.4 streamed and
+// (1536^2 x 512 24.4 -> 21.6 us, dual 2048^2 x 512 32.0 -> 29.4), but for a pass over 7 to 16 MB with a short K whose
+// columns are on the lines, which the L2s turn over faster streamed (20 products with K 32 to 216: 0.96 to 1.14 of the time kept,
+// 1.04 on average, complex 1440x613x136 8.8 / 7.7; smaller ones equal within 1 %, interleaved ones up to 5 % faster kept; with K from
+// 336 on 2 to 11 % faster kept); without C off the lines only (dual 1532x2368x1112 41.3 -> 34.2; on them 22.4 streamed and
 // 23.6 kept, complex 2048^3, 100 MB, 77.4 and 78.4).  Above 80 MB: off the lines while A and B are small (4040x2048x400 complex 72.3 -> 62.9):
 // larger ones stay in the memory-side cache only if C and D do not push them out, and the K loop waits for memory (dual 899x3562x3832,
 // A and B 68 MB: 124 streamed, 156 kept).  Off the lines: planar ones off 128 bytes, interleaved ones off 64 (on half lines
@@ -50,7 +51,7 @@ inline bool keeps_complex_cd(int64_t ab, int64_t cd, int64_t K, bool interleaved
     const int64_t line = interleaved ? 64 : 128;
     const bool off = ldd % line != 0 || (has_c && ldc % line != 0);
     if (ab + cd > (80ll << 20)) return off && ab <= (32ll << 20);
-    return off || (has_c && (K > 256 || ab + cd > (16ll << 20)));
+    return off || (has_c && (K > 256 || ab + cd > (16ll << 20) || ab + cd < (7ll << 20)));
 }
 
 }  // namespace fg

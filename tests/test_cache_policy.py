@@ -64,12 +64,13 @@ def test_real_results_above_the_memory_side_cache_are_kept_only_off_the_half_lin
 
 
 def test_complex_results_of_short_passes_stream(rule):
-    """Complex and dual results on the lines with C: kept up to 80 MB, but streamed where the whole pass is at most 16 MB and K at
+    """Complex and dual results on the lines with C: kept up to 80 MB, but streamed where the whole pass is 7 to 16 MB and K at
     most 256; off the lines kept; above 80 MB kept only off the lines beside small A and B."""
     def keeps(M, N, K, ilv=0, c=True, off=0):
         ld = M + off
         return rule("complex", (M * K + K * N) * 4, M * N * 8 * (2 if c else 1), K, ilv, c, ld * (8 if ilv else 4), ld * (8 if ilv else 4))
     assert keeps(1440, 613, 136) == 0 and keeps(1216, 544, 200) == 0 and keeps(704, 810, 120, ilv=1) == 0       # 9 to 14 MB
+    assert keeps(640, 256, 176, ilv=1) == 1 and keeps(320, 1024, 120) == 1                                    # 3 and 6 MB
     assert keeps(1440, 613, 136, off=8) == 1                                                                 # the same off the lines
     assert keeps(736, 395, 848, ilv=1) == 1 and keeps(2592, 200, 360, ilv=1) == 1                            # 8 and 11 MB, longer K
     assert keeps(544, 2711, 192) == 1 and keeps(1408, 2907, 160) == 1                                        # 24 and 65 MB

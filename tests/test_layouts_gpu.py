@@ -117,8 +117,8 @@ TILES = ["0", "1", "2", "3"]           # 256x128, 128x128, 64x64, 64x64 with two
 @pytest.mark.parametrize("tile", TILES)
 def test_cache_policies_of_complex_results(monkeypatch, kind, tile):
     """C and D of complex and dual products are kept in the caches or streamed past them: the same results on interior and edge
-    tiles of every tile shape, with C and without, for columns on the lines, on half lines and off them.  Small passes on
-    the lines stream up to K = 256 and are kept above; of the large ones (over 80 MB), those beside large A and B stream and those
+    tiles of every tile shape, with C and without, for columns on the lines, on half lines and off them.  Passes of 7 to
+    16 MB on the lines stream up to K = 256 and are kept above; of the large ones (over 80 MB), those beside large A and B stream and those
     off the lines beside small ones are kept (test_cache_policy.py has the rule)."""
     from tests.parity import delenv, setenv
     setenv(monkeypatch, "FG_FORCE_TILE", tile)
@@ -126,7 +126,7 @@ def test_cache_policies_of_complex_results(monkeypatch, kind, tile):
         say("tile %s M=%d N=%d K=%d C=%d %s" % (tile, M, N, K, with_c, kind))
         run_cgemm_case(M, N, K, ints=True, alpha=2.0, beta=-1.0, with_c=with_c, **kind)
     run_cgemm_case(133, 264, 72, fg.FG_ROW, fg.FG_ROW, fg.FG_ROW, ints=True, **kind)
-    for M, N, K in ((1504, 2003, 2800), (1507, 2003, 2800), (2052, 2603, 72)):
+    for M, N, K in ((1440, 613, 136), (1440, 613, 328), (1504, 2003, 2800), (1507, 2003, 2800), (2052, 2603, 72)):
         say("tile %s M=%d N=%d K=%d C=1 %s" % (tile, M, N, K, kind))
         run_cgemm_case(M, N, K, fg.FG_ROW, fg.FG_COL, ints=True, alpha=2.0, beta=-1.0, samples=3000, **kind)
     delenv(monkeypatch, "FG_FORCE_TILE")
