@@ -129,8 +129,8 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 // when forced (A and B both M/N-contiguous: measured 0 to -5 %).
 // allow_groups: the family has the tiles with K groups.  The rates, the cost of a split and the prices of rows off the
 // lines are fitted to the times of replayed graphs of every tile and split forced over 190 products (64x64x32768 to
-// 4876x7518x2448): the choice is on average 1.7 % slower than the fastest (5 % with the rates before the larger rings),
-// at most 42 % (6708x5150x96), and over 16 % only with K up to 224.
+// 4876x7518x2448): the choice by them alone is on average 1.7 % slower than the fastest (5 % with the rates before the larger
+// rings), at most 42 % (6708x5150x96), and over 16 % only with K up to 224; held to what plan_product promises, 3.4 % (4.7 %).
 constexpr int kTileM[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64, 64};
 constexpr int kTileN[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64, 128};
 constexpr int kTilesPerCU[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1, 1};
@@ -216,7 +216,8 @@ constexpr Prices priced(const Rates &r) {
     p.last_round = r.last_round;
     return p;
 }
-constexpr Prices kPrices = priced(kRates), kPrices16 = priced(kRates16), kPromisedPrices = priced(kPromisedRates), kFormerPrices = priced(kFormerRates), kContractPrices = priced(kContractRates);
+constexpr Prices kPrices = priced(kRates), kPrices16 = priced(kRates16), kContractPrices = priced(kContractRates);
+constexpr Prices kPromisedPrices = priced(kPromisedRates), kFormerPrices = priced(kFormerRates);
 
 // The K ranges that a product may be split into: at least four K tiles (256 k) each.
 struct KRanges {
@@ -241,7 +242,11 @@ struct Shifts { int m[fg::TILE_COUNT], n[fg::TILE_COUNT], slots[fg::TILE_COUNT],
 constexpr Shifts shifts_of_tiles() {
     Shifts s{};
     s.cu = log2_of(kNumCU);
-    for (int t = 0; t < fg::TILE_COUNT; ++t) { s.m[t] = log2_of(kTileM[t]); s.n[t] = log2_of(kTileN[t]); s.slots[t] = s.cu + log2_of(kTilesPerCU[t]); }
+    for (int t = 0; t < fg::TILE_COUNT; ++t) {
+        s.m[t] = log2_of(kTileM[t]);
+        s.n[t] = log2_of(kTileN[t]);
+        s.slots[t] = s.cu + log2_of(kTilesPerCU[t]);
+    }
     return s;
 }
 constexpr Shifts kShifts = shifts_of_tiles();
@@ -340,7 +345,10 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
             if (rest * S > slots || rest * S * slot_bytes > scratch_bytes) break;
             const double cost = in_front + share_time(rest * S, S, ranges.share[i]) + (2.0 * S + 2.0) * (double)(rest * slot_bytes) * (1 / tail_bw);
             consider(1, S, nk, cost);
-            if (t == fg::TILE_256x256 && sum_length(prices, t, 1, nk) <= longest && cost < large_tail_cost) { large_tail = Plan{t, 1, S}; large_tail_cost = cost; }
+            if (t == fg::TILE_256x256 && sum_length(prices, t, 1, nk) <= longest && cost < large_tail_cost) {
+                large_tail = Plan{t, 1, S};
+                large_tail_cost = cost;
+            }
         }
     }
     // Of two plans with whole rounds in front of a split tail, the 256x256 tile's runs 4 % faster than the 256x128 tile's whose
@@ -367,7 +375,8 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
 int64_t scratch_need(const Plan &plan, int64_t M, int64_t N) {
     if (plan.splits <= 1 && plan.tail_splits <= 1) return 0;
     const int t = plan.tile;
-    const int64_t tiles = ((M + kTileM[t] - 1) >> kShifts.m[t]) * ((N + kTileN[t] - 1) >> kShifts.n[t]), tile_bytes = (int64_t)kTileM[t] * kTileN[t] * 4;
+    const int64_t tiles = ((M + kTileM[t] - 1) >> kShifts.m[t]) * ((N + kTileN[t] - 1) >> kShifts.n[t]);
+    const int64_t tile_bytes = (int64_t)kTileM[t] * kTileN[t] * 4;
     return (plan.splits > 1 ? tiles * plan.splits : (tiles & ((1ll << kShifts.slots[t]) - 1)) * plan.tail_splits) * tile_bytes;
 }
 
@@ -376,13 +385,15 @@ int64_t scratch_need(const Plan &plan, int64_t M, int64_t N) {
 struct Former { int64_t scratch; int32_t longest; };
 Former former_plan(int64_t M, int64_t N, int64_t K, const KRanges &ranges, bool may_split, int k32, int straddling) {
     auto limit_of = [](int64_t bytes) { return bytes == 0 ? 0 : bytes <= kStaticScratchBytes ? kStaticScratchBytes : kWorkspaceBytes; };
-    const int64_t promised = !may_split ? 0 : limit_of(scratch_need(choose_plan(M, N, ranges, true, true, 1, true, k32, false, kWorkspaceBytes, kPromisedPrices), M, N));
+    int64_t promised = 0;
+    if (may_split) promised = limit_of(scratch_need(choose_plan(M, N, ranges, true, true, 1, true, k32, false, kWorkspaceBytes, kPromisedPrices), M, N));
     // (the best plan within the promised class; rows off the lines counted in long K loops only, and only for a split)
     auto plan_of = [&](int lines) { return choose_plan(M, N, ranges, promised > 0, true, 1, true, k32, true, promised, kFormerPrices, lines); };
     const int lines = promised > 0 && K > 3904 ? straddling : 0;
     Plan former = plan_of(lines);
     if (lines > 0 && former.splits == 1 && former.tail_splits == 1) former = plan_of(0);
-    return Former{limit_of(scratch_need(former, M, N)), sum_length(kFormerPrices, former.tile, former.splits, (ranges.nk + former.splits - 1) / former.splits)};
+    const int32_t share = (ranges.nk + former.splits - 1) / former.splits;
+    return Former{limit_of(scratch_need(former, M, N)), sum_length(kFormerPrices, former.tile, former.splits, share)};
 }
 
 // Plan of a real product without a diagonal operand.  Two things that the former planner chose hold still:
@@ -414,9 +425,9 @@ Plan plan_product(int64_t M, int64_t N, int64_t K, bool may_split, int k32, int 
 // such products the 64x64 tile is more than 2 % slower than another in five, at most 14 %, 6528x2560x24).
 // The 64x64 tile with two K groups: one tile per unit and K steps for both groups, 1024^3 22.4 -> 15.9 us against the tile with
 // one group, 500x700x3000 interleaved 53.5 -> 33.5, and sums half as long: the error against 64 bits is 0.73 to 0.78 of one group's.
-// For that it is taken from K = 168 on, though up to 216 the second group costs planar operands 3 to 10 % (196x702x176 5.6, 6.1; around 250
-// it is even, interleaved ones gain from 216 on; 42 products); to 160 it costs up to 35 %, in a second round it does not pay (1300x1300x800
-// 21.8, 26.4; 1536^2 x 512 21.5, 29.7).
+// For that it is taken from K = 168 on, though up to 216 the second group costs planar operands 3 to 14 % (195x702x176 5.6, 6.1; around
+// 250 it is even, interleaved ones gain from 216 on; 42 products); from 136 to 160 it costs 8 to 18 %, in a second round it does not
+// pay (1300x1300x800 21.8, 26.4; 1536^2 x 512 21.5, 29.7).
 int choose_ctile(int64_t M, int64_t N, int64_t K) {
     static const int bm[fg::CTILE_COUNT] = {256, 128, 64, 64};
     static const int bn[fg::CTILE_COUNT] = {128, 128, 64, 64};

@@ -1510,7 +1510,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
                         }
                         if constexpr (Cfg::SPREAD) {
                             // one refill load after the MFMAs of sub-tile row i, evenly over the slice
-        #pragma unroll
+#pragma unroll
                             for (int n = 0; n < Cfg::A_SLABS; ++n)
                                 if (refill_a && i == n * TI / Cfg::A_SLABS) {
 #pragma unroll
