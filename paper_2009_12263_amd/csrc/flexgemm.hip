@@ -612,7 +612,7 @@ struct Scratch {
         ptr = by_stream ? guard->of_default : guard->ptr;
         if (by_stream) return FG_OK;                           // (this stream cannot be captured)
         if (stream_is_capturing(stream)) guard = nullptr;      // a captured call is ordered by its graph's caller
-        else if (guard->used && guard->last_stream != stream) {
+        else if (guard->used && (guard->last_stream != stream || stream == hipStreamPerThread)) {      // (one handle, a stream for each thread)
             hipError_t e = hipStreamWaitEvent(stream, guard->last_use, 0);
             if (e != hipSuccess) return fail(FG_ERR_LAUNCH, "hipStreamWaitEvent on the workspace's last use failed: %s", hipGetErrorString(e));
         }

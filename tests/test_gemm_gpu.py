@@ -665,6 +665,29 @@ def test_split_k_calls_on_the_default_stream_and_another():
             assert torch.equal(D, ref), "round %d: call %d differs from the serial result" % (rep, i)
 
 
+def test_split_k_calls_of_several_threads_on_their_per_thread_streams():
+    """hipStreamPerThread is one handle for a stream of each thread: split calls made on it by several threads are ordered like
+    those of different streams.  Each call has operands of its own; every entry equals the call made alone."""
+    import threading
+    calls = _split_calls(12, 500)
+    per_thread = 2
+    for _, D, _ in calls: D.fill_(float("nan"))
+    torch.cuda.synchronize()
+    failed = []
+    def work(mine):
+        try:
+            for call, D, _ in mine: call(D, per_thread)
+        except Exception as e:
+            failed.append(e)
+    threads = [threading.Thread(target=work, args=(calls[i::3],)) for i in range(3)]
+    for t in threads: t.start()
+    for t in threads: t.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    for i, (_, D, ref) in enumerate(calls):
+        assert torch.equal(D, ref), "call %d differs from the serial result" % i
+
+
 def test_split_k_call_does_not_wait_for_unrelated_work_of_the_default_stream():
     """After a split call on the default stream, one on another stream has nothing there to wait for: it ends while a
     long kernel that was issued on the default stream meanwhile still runs."""
