@@ -26,6 +26,7 @@
 #include <stdint.h>
 
 #include <type_traits>
+#include <utility>
 
 namespace fg {
 
@@ -114,7 +115,7 @@ __device__ __forceinline__ int tile_row(int pos, int rows, int z_count) {
 // B column-major) rather than M/N-contiguous.  STAGES LDS buffers per operand form a ring over K.
 template <int BM_, int BN_, int BK_, int STAGES_, int WGM_, int WGN_, bool A_KC_, bool B_KC_, bool STRIDED_,
           int DIAG_ = 0, int CPLX_ = 0, bool SPREAD_ = false, bool BF16_ = false, bool XFORM_ = false, bool ILV_ = false,
-          bool CSTREAM_ = false, bool CD16_ = false, bool M16_ = false, int KG_ = 1, bool KTURNS_ = false, int WAVES_ = 1>
+          bool CSTREAM_ = false, bool CD16_ = false, bool M16_ = false, int KG_ = 1, bool KTURNS_ = false, int WAVES_ = 1, bool WIDE_ = false>
 struct TileCfg {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, STAGES = STAGES_;
     // M16: the product is made of v_mfma_f32_16x16x32 instructions (16x16 results, 32 k per
@@ -131,6 +132,9 @@ struct TileCfg {
     // that what a unit fetches at a time lies side by side (192x2496x5368, A and B row-major: 21.3 -> 18.0 us).
     static constexpr bool KTURNS = KTURNS_;
     static constexpr int WAVES = WAVES_;                            // waves per SIMD that the registers are to leave room for
+    // WIDE: one wave per SIMD, accumulators in the accumulation registers (wide_loop.hpp).  A's ring has RING_A buffers.
+    static constexpr bool WIDE = WIDE_;
+    static constexpr int RING_A = WIDE_ && STAGES_ == 2 ? 3 : STAGES_;
     static constexpr int KINC = KTURNS_ ? KG_ : 1;
     static constexpr int NWAVES = WGM * WGN, NTHREADS = 64 * NWAVES * KG;
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;
@@ -166,7 +170,7 @@ struct TileCfg {
     // groups of two sets, as with the four K groups that served it before, 1.5e-7 with two groups of one; no time is lost
     // (64x64 tile with two buffers: 81 -> 87 registers, 24 products equal within 1 %).
     static constexpr bool PLAIN_REAL = !STRIDED_ && DIAG_ == 0 && CPLX_ == 0 && !M16_;
-    static constexpr int ACC_SETS = PLAIN_REAL && (KG_ > 1 || STAGES_ == 4) ? 2 : 1;
+    static constexpr int ACC_SETS = WIDE_ ? (8 * FI * FJ <= 256 ? 2 : 1) : PLAIN_REAL && (KG_ > 1 || STAGES_ == 4) ? 2 : 1;
     // ONCE: the kernel has K loops whose loads of A or of B carry the streaming policy, for operands that are read once:
     // narrow products, bound by reading their large operand (128x16384x12288 122 -> 113 us; where other tiles read the
     // operand again it costs: 8192x1024x4096 72 -> 76).  From which size on, and why: streams_once (cache_policy.hpp).
@@ -183,7 +187,7 @@ struct TileCfg {
     // direct loads per wave and K step (a diagonal operand is synthesised, not loaded)
     static constexpr int LOADS_PER_TILE = ((DIAG == 1 ? 0 : A_SLABS) + (DIAG == 2 ? 0 : B_SLABS)) * PLANES;
     // LDS map: [A plane 0: stage 0 .. S-1 | A plane 1 ... | B plane 0: stage 0 .. S-1 | B plane 1 ...]
-    static constexpr int A_PLANE_BYTES = A_TILE_BYTES * STAGES, B_PLANE_BYTES = B_TILE_BYTES * STAGES;
+    static constexpr int A_PLANE_BYTES = A_TILE_BYTES * RING_A, B_PLANE_BYTES = B_TILE_BYTES * STAGES;
     static constexpr int A_BYTES = A_PLANE_BYTES * PLANES;
     static constexpr int GROUP_BYTES = A_BYTES + B_PLANE_BYTES * PLANES, LDS_BYTES = GROUP_BYTES * KG;
     static_assert(BK == 32 || BK == 64, "BK must be 32 or 64");
@@ -205,6 +209,7 @@ struct TileCfg {
     static_assert(!XFORM || (DIAG == 0 && CPLX == 0 && !BF16 && !STRIDED), "element-wise addition on A and B: plain real FP16 matrices");
     static_assert(!CSTREAM || STRIDED, "the streaming variant is a contraction kernel");
     static_assert(!CD16 || (CPLX == 0 && DIAG == 0 && !STRIDED && !ILV), "binary16 C and D: plain real matrix kernels");
+    static_assert(!WIDE || (M16 && NWAVES == 4 && KG == 1 && !STRIDED && !XFORM && 4 * FI * FJ * ACC_SETS <= 256), "one wave per SIMD: plain real matrix kernels on 16x16x32 instructions");
     static_assert(!ILV || (CPLX == 1 && STAGES == 2 && !SPREAD && !STRIDED && DIAG == 0), "interleaved storage: plain complex products");
 };
 
@@ -1127,6 +1132,12 @@ __device__ __forceinline__ floatx16 gather_block(const floatx4 (&a16)[Cfg::FI][C
     return out;
 }
 
+}  // namespace fg
+
+#include "wide_loop.hpp"
+
+namespace fg {
+
 template <class Cfg>
 __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const typename Cfg::Params p) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
@@ -1155,6 +1166,8 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
     using LoaderB = typename std::conditional<Cfg::DIAG == 2, DiagLoader<BN, BK, Cfg::B_SLABS>, PlainB>::type;
     LoaderA la[P];
     LoaderB lb[P];
+    [[maybe_unused]] WideLoader<BM, Cfg::A_KC> wide_a;      // TileCfg::WIDE, in place of la and lb
+    [[maybe_unused]] WideLoader<BN, Cfg::B_KC> wide_b;
     FragReader<BM, BK, Cfg::A_KC, TI, Cfg::M16> fa;
     FragReader<BN, BK, Cfg::B_KC, TJ, Cfg::M16> fb;
     if constexpr (Cfg::STRIDED && !Cfg::A_KC) fa.init(wm * Cfg::WTM, lane, p.perm_z);
@@ -1210,6 +1223,31 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
             ap[0] += group_offset(tp.a_b, split);
             bp[0] += group_offset(tp.b_b, split);
         }
+        if constexpr (Cfg::WIDE) {
+            // a last K tile that hangs over the end of K comes first (see wide_loop.hpp), the others follow in order
+            const int rest = tp.K - (nk - 1) * BK;
+            const bool last_first = rest < BK && kt1 == nk && nkt > 0;
+            const uint32_t to_a = (uint32_t)(uintptr_t)lds_a + (uint32_t)wave * (Cfg::A_SLABS * 1024u);
+            const uint32_t to_b = (uint32_t)(uintptr_t)lds_b + (uint32_t)wave * (Cfg::B_SLABS * 1024u);
+            wide_a.init(wave, lane, tp.a_rs, tp.a_ks);
+            wide_b.init(wave, lane, tp.b_rs, tp.b_ks);
+            wide_a.at(ap[0], m0, tp.a_rs, tp.a_ks, tp.a_span, last_first ? nk - 1 : kt0, nkt > 0);
+            wide_b.at(bp[0], n0, tp.b_rs, tp.b_ks, tp.b_span, last_first ? nk - 1 : kt0, nkt > 0);
+            wide_a.issue(to_a, last_first ? rest : BK, lane);
+            wide_b.issue(to_b, last_first ? rest : BK, lane);
+            const int second = last_first ? kt0 : kt0 + 1;
+            wide_a.at(ap[0], m0, tp.a_rs, tp.a_ks, tp.a_span, second, nkt > 1);
+            wide_b.at(bp[0], n0, tp.b_rs, tp.b_ks, tp.b_span, second, nkt > 1);
+            // A's ring is filled but for one buffer, B's whole
+#pragma unroll
+            for (int st = 1; st < S; ++st) {
+                if (st < Cfg::RING_A - 1) { wide_a.issue(to_a + st * Cfg::A_TILE_BYTES, BK, lane); wide_a.next_base(); wide_a.next_size(nkt - st - 1); }
+                wide_b.issue(to_b + st * Cfg::B_TILE_BYTES, BK, lane);
+                wide_b.next_base();
+                wide_b.next_size(nkt - st - 1);
+            }
+            return;
+        }
         [[maybe_unused]] const ModeGroup none = {};
 #pragma unroll
         for (int q = 0; q < NLOADERS; ++q) {
@@ -1259,6 +1297,10 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
         using AccT = typename std::conditional<Cfg::M16, floatx4, floatx16>::type;
         constexpr int SETS = Cfg::ACC_SETS;         // (one plane only if there are two)
         AccT acc[P * SETS][TI][TJ];
+        if constexpr (Cfg::WIDE) {
+            own_acc();
+            static_for<4 * TI * TJ * SETS>([](auto r) { acc_zero<decltype(r)::value>(); });
+        }
 #pragma unroll
         for (int q = 0; q < P * SETS; ++q)
 #pragma unroll
@@ -1269,6 +1311,11 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
                     for (int r = 0; r < (Cfg::M16 ? 4 : 16); ++r) acc[q][i][j][r] = 0.f;
 
         if (nkt > 0) {
+            if constexpr (Cfg::WIDE) {
+                wait_tile<(Cfg::RING_A - 2) * Cfg::A_SLABS + (S - 1) * Cfg::B_SLABS>();     // all but the first K tile may be in flight
+                __builtin_amdgcn_s_barrier();
+                k_loop_wide<Cfg>(wide_a, wide_b, fa, fb, lds_a, lds_b, wave, nkt);
+            } else {
             wait_tiles<L, S - 1>(nkt - 1);
             __builtin_amdgcn_s_barrier();
 
@@ -1577,9 +1624,12 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
             }
             tile_body(nkt - 1, F, F, F, O);
             }
+            }
+        } else if constexpr (Cfg::WIDE) {
+            wait_tile<0>();                             // (an empty K range: no load stays behind)
         }
 
-        if constexpr (SETS == 2) {
+        if constexpr (SETS == 2 && !Cfg::WIDE) {
 #pragma unroll
             for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -1643,7 +1693,14 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
             }
             // the matrix kernels that stream C and D have a second copy of the epilogue without the hint
             constexpr bool TWO_POLICIES = !Cfg::STRIDED && Cfg::DIAG == 0;
-            if constexpr (Cfg::M16) {
+            if constexpr (Cfg::WIDE) {
+                if (ep.cd_cached) {
+                    if (ep.has_c) epilogue_wide<Cfg, true, true>(ep, mb, nb, lane);
+                    else epilogue_wide<Cfg, false, true>(ep, mb, nb, lane);
+                } else
+                if (ep.has_c) epilogue_wide<Cfg, true, false>(ep, mb, nb, lane);
+                else epilogue_wide<Cfg, false, false>(ep, mb, nb, lane);
+            } else if constexpr (Cfg::M16) {
                 auto blocks = [&](int i, int j) { return gather_block<Cfg>(acc[0], i, j); };
                 if (TWO_POLICIES && ep.cd_cached) {
                     if (ep.has_c) epilogue<Cfg, true, decltype(blocks), true>(ep, ep.C, ep.D, blocks, mb, nb, lane);

@@ -16,11 +16,9 @@ namespace fg {
 // (one set, from the memory-side cache: 69.0 -> 67.2), with C 93.5 -> 80.0, 3000^3 94.1 -> 88.4, 2329x3267x5104 127.8 -> 111;
 // a pass over C and D as before (8192^2 x 64: 97.3, 96.5).  A fourth does not fit.  Contractions measured 0 to 4 % slower
 // with three (extents 192, 72, 200 over 208: 11.3, 11.7) and keep two.
-// TILE_256x256_K32: the 256x256 tile computed with 16x16x32 matrix instructions (TileCfg::M16), for
-// products that fill (most of) the GPU: there the chip runs at its power limit and that instruction shape
-// sustains a higher rate on the same data; on a partly filled GPU the 32x32x16 kernels are faster.
-// Plain, BF16 and binary16-result matrix kernels, and the A/B-addition kernels of two layout pairs
-// (other tables leave the entry empty).
+// TILE_256x256_K32: the 256x256 tile computed with 16x16x32 matrix instructions (TileCfg::M16), which on a chip at its power limit
+// sustain a higher rate on the same data.  Plain, BF16 and binary16-result matrix kernels: one wave per SIMD (TileCfg::WIDE,
+// wide_loop.hpp); the A/B-addition kernels of two layout pairs: eight waves (other tables leave the entry empty).
 // TILE_64x64_KG2, TILE_64x64_KG2_DEEP: the 64x64 tile with two groups of four waves that share its K tiles
 // (TileCfg::KG), for outputs of at most two such tiles per unit: one group alone spends most of a K tile in barrier
 // and LDS latency.  DEEP: rings of four, for outputs of at most one tile per unit, whose two-buffer rings wait for
@@ -109,8 +107,8 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
     { (const void *)gemm_kernel<FG_CFG_KG(AKC, BKC, BF, XF, H, BN, ST, TURNS)>, NAME, 64, BN,      \
       FG_CFG_KG(AKC, BKC, BF, XF, H, BN, ST, TURNS)::NTHREADS, FG_CFG_KG(AKC, BKC, BF, XF, H, BN, ST, TURNS)::LDS_BYTES, 2 }
 #define FG_EMPTY_ENTRY { nullptr, nullptr, 0, 0, 0, 0, 0 }
-// the same with 16x16x32 matrix instructions (TileCfg::M16); BF: bfloat16 inputs, H: binary16 C and D
-#define FG_CFG_K32(BM, BN, BK, ST, WGM, WGN, AKC, BKC, BF, H) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, 0, 0, true, BF, false, false, false, H, true>
+// the same with 16x16x32 matrix instructions and one wave per SIMD (TileCfg::M16, WIDE); BF: bfloat16 inputs, H: binary16 C and D
+#define FG_CFG_K32(BM, BN, BK, ST, WGM, WGN, AKC, BKC, BF, H) TileCfg<BM, BN, BK, ST, WGM, WGN, AKC, BKC, false, 0, 0, true, BF, false, false, false, H, true, 1, false, 1, true>
 #define FG_ENTRY_K32(BM, BN, BK, ST, WGM, WGN, AKC, BKC, BF, H, NAME)                              \
     { (const void *)gemm_kernel<FG_CFG_K32(BM, BN, BK, ST, WGM, WGN, AKC, BKC, BF, H)>, NAME, BM, BN,            \
       FG_CFG_K32(BM, BN, BK, ST, WGM, WGN, AKC, BKC, BF, H)::NTHREADS,                             \
@@ -141,7 +139,7 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
             FG_ENTRY_BF16(128, 128, 64, 2, 2, 2, AKC, BKC, "gemm_bf16_" TAG "_128x128x64"),        \
             FG_ENTRY_BF16(64, 64, 64, 2, 2, 2, AKC, BKC, "gemm_bf16_" TAG "_64x64x64"),            \
             FG_ENTRY_BF16(128, 128, 64, 4, 4, 2, AKC, BKC, "gemm_bf16_" TAG "_128x128x64_deep"),   \
-            FG_ENTRY_K32(256, 256, 64, 2, 2, 4, AKC, BKC, true, false, "gemm_bf16_" TAG "_256x256x64_k32"), \
+            FG_ENTRY_K32(256, 256, 64, 2, 2, 2, AKC, BKC, true, false, "gemm_bf16_" TAG "_256x256x64_k32"), \
             FG_ENTRY_KG(AKC, BKC, true, false, false, 64, 2, false, "gemm_bf16_" TAG "_64x64x64"),            \
             FG_ENTRY_KG(AKC, BKC, true, false, false, 64, 4, true, "gemm_bf16_" TAG "_64x64x64"),            \
             FG_ENTRY_KG(AKC, BKC, true, false, false, 128, 3, true, "gemm_bf16_" TAG "_64x128x64"),\
@@ -163,7 +161,7 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
             FG_ENTRY_H16(128, 128, 64, 2, 2, 2, AKC, BKC, "gemm_h16_" TAG "_128x128x64"),          \
             FG_ENTRY_H16(64, 64, 64, 2, 2, 2, AKC, BKC, "gemm_h16_" TAG "_64x64x64"),              \
             FG_ENTRY_H16(128, 128, 64, 4, 4, 2, AKC, BKC, "gemm_h16_" TAG "_128x128x64_deep"),     \
-            FG_ENTRY_K32(256, 256, 64, 2, 2, 4, AKC, BKC, false, true, "gemm_h16_" TAG "_256x256x64_k32"), \
+            FG_ENTRY_K32(256, 256, 64, 2, 2, 2, AKC, BKC, false, true, "gemm_h16_" TAG "_256x256x64_k32"), \
             FG_ENTRY_KG(AKC, BKC, false, false, true, 64, 2, false, "gemm_h16_" TAG "_64x64x64"),             \
             FG_ENTRY_KG(AKC, BKC, false, false, true, 64, 4, true, "gemm_h16_" TAG "_64x64x64"),             \
             FG_ENTRY_KG(AKC, BKC, false, false, true, 128, 3, true, "gemm_h16_" TAG "_64x128x64"), \
@@ -237,7 +235,7 @@ inline KernelEntry xf_k32_entry(const char *name) {
             FG_ENTRY(128, 128, 64, 4, 4, 2, AKC, BKC, false, "gemm_" TAG "_128x128x64_deep"),      \
             FG_ENTRY(128, 128, 64, 4, 4, 2, AKC, BKC, true, "gett_" TAG "_128x128x64_deep"),       \
             FG_ENTRY_GS(128, 128, 64, 4, 4, 2, AKC, BKC, "gett_stream_" TAG "_128x128x64_deep"),   \
-            FG_ENTRY_K32(256, 256, 64, 2, 2, 4, AKC, BKC, false, false, "gemm_" TAG "_256x256x64_k32"), \
+            FG_ENTRY_K32(256, 256, 64, 2, 2, 2, AKC, BKC, false, false, "gemm_" TAG "_256x256x64_k32"), \
             FG_EMPTY_ENTRY, FG_EMPTY_ENTRY,                                                        \
             FG_ENTRY_KG(AKC, BKC, false, false, false, 64, 2, false, "gemm_" TAG "_64x64x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
             FG_ENTRY_KG(AKC, BKC, false, false, false, 64, 4, true, "gemm_" TAG "_64x64x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
