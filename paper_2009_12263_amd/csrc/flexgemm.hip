@@ -121,14 +121,12 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 // share a unit and one for a workgroup that has a unit to itself.  Edge tiles are predicated, so
 // a tile need not divide the problem.  K is split only when the output has too few tiles to fill
 // the GPU and K is long (may_split: plain real products).
-// k32: the kernel family has a 256x256 tile with 16x16x32 matrix instructions (TILE_256x256_K32).  It is not a candidate of its
-// own.  k32 == 3: that kernel has one wave per SIMD (TileCfg::WIDE) and replaces the 256x256 tile whenever that one is chosen
-// (3000x3000x2000 with C 71.5 -> 59.4 us, 6144x2048x4096 116 -> 98, 4096x4096x320 40.4 -> 38.8; the other way round only a streamed C
-// and D with K up to 768, see select_kernel, and 3072x4096x512, 35.2 and 36.3).  k32 == 2 (addition on A and B): it has eight waves and
-// replaces the 256x256 tile when the output has such a tile for at least three quarters of the
-// compute units (measured +1 to +5 % from 192 tiles up, K from 1024 to 8192; equal at 176 tiles,
-// -1 to -6 % at 160 and fewer: a partly busy chip is not at its power limit).  k32 == 1: only
-// when forced.
+// k32: the kernel family has a 256x256 kernel named for its 16x16x32 matrix instructions (TILE_256x256_K32).  It is not a candidate
+// of its own.  k32 == 2: it replaces the 256x256 tile
+// when that one is chosen and the output has such a tile for at least three quarters of the
+// compute units (addition on A and B, whose two 256x256 kernels differ: measured +1 to +5 % from 192 tiles up, K from 1024
+// to 8192; equal at 176 tiles, -1 to -6 % at 160 and fewer: a partly busy chip is not at its power limit; in the other
+// families both entries are one kernel).  k32 == 1: only when forced (A and B both M/N-contiguous).
 // allow_groups: the family has the tiles with K groups.  The rates, the cost of a split and the prices of rows off the
 // lines are fitted to the times of replayed graphs of every tile and split forced over 190 products (64x64x32768 to
 // 4876x7518x2448): the choice by them alone is on average 1.7 % slower than the fastest (5 % with the rates before the larger
@@ -368,7 +366,7 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
         best.tile = fg::TILE_256x128;
     if (best.tile == fg::TILE_256x256 && k32 > 0 && !forced_plain) {
         const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256) * batches;
-        if (force_k32 || k32 == 3 || (k32 == 2 && tiles >= kNumCU * 3 / 4)) best.tile = fg::TILE_256x256_K32;
+        if (force_k32 || (k32 == 2 && tiles >= kNumCU * 3 / 4)) best.tile = fg::TILE_256x256_K32;
     }
     return best;
 }
@@ -473,7 +471,7 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
         return &(q.dual ? fg::kernel_table_dual() : fg::kernel_table_cplx())[t * 4 + v];
     }
     const bool may_split = plan_out && !q.a_diag && !q.b_diag && !q.cd16;   // the reduction pass writes FP32
-    const int k32 = (q.a_diag || q.b_diag) ? 0 : q.ab_add ? (q.a_kc != q.b_kc ? 2 : 0) : 3;
+    const int k32 = (q.a_diag || q.b_diag) ? 0 : q.ab_add ? (q.a_kc != q.b_kc ? 2 : 0) : ((q.a_kc || q.b_kc) ? 2 : 1);
     // Rows off a line: by the extents (a row is whole 16-byte pieces), so that the plan query, which knows no leading
     // dimensions, says the same.  Rows that begin on half a line are not counted: 8192x243 over 4256, both K-contiguous,
     // 33.8 us in one pass, 41.7 split in two; 443x4534 33.8, and 35.4.
@@ -491,12 +489,10 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     // more in memory than they gain (8192^2: 180 us against 135 us), and the estimate above decides.
     if ((q.a_diag || q.b_diag) && g_force_tile.load(std::memory_order_relaxed) < 0 && q.M * q.N * 10 <= (256ll << 20))
         tile = fg::TILE_64x64;
-    if (tile == fg::TILE_256x256_K32 && k32 == 3 && g_force_tile.load(std::memory_order_relaxed) < 0) {
-        // Its loaders count the rest of an M/N-contiguous operand in 32 bits of 16 bytes.
-        if ((!q.a_kc && q.lda * q.K >= (1ll << 35)) || (!q.b_kc && q.ldb * q.K >= (1ll << 35))) tile = fg::TILE_256x256;
+    if (!q.ab_add && !q.a_diag && !q.b_diag && (tile == fg::TILE_256x256 || tile == fg::TILE_256x256_K32) && g_force_tile.load(std::memory_order_relaxed) < 0) {
         // A pass over C and D that stream: the stores of four waves fall behind those of eight (8192^2 with C, K = 384: 135.9 us,
         // 124.0 on the 256x128 tile; 512: 147 and 137; 768: 166.5 and 165.2; 1024: 187 and 193).
-        else if (q.C && q.K <= 512 && plan.splits == 1 && plan.tail_splits == 1 && q.M * q.N * 8 > fg::kMemorySideCache) tile = fg::TILE_256x128;
+        if (q.C && q.K <= 512 && q.M * q.N * 8 > fg::kMemorySideCache && plan.splits == 1 && plan.tail_splits == 1) tile = fg::TILE_256x128;
     }
     if (plan_out) { *plan_out = plan; plan_out->tile = tile; }
     if (q.a_diag) return &fg::kernel_table_diag()[tile * 4 + (q.b_kc ? 0 : 1)];

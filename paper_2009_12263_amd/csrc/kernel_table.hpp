@@ -16,9 +16,12 @@ namespace fg {
 // (one set, from the memory-side cache: 69.0 -> 67.2), with C 93.5 -> 80.0, 3000^3 94.1 -> 88.4, 2329x3267x5104 127.8 -> 111;
 // a pass over C and D as before (8192^2 x 64: 97.3, 96.5).  A fourth does not fit.  Contractions measured 0 to 4 % slower
 // with three (extents 192, 72, 200 over 208: 11.3, 11.7) and keep two.
-// TILE_256x256_K32: the 256x256 tile computed with 16x16x32 matrix instructions (TileCfg::M16), which on a chip at its power limit
-// sustain a higher rate on the same data.  Plain, BF16 and binary16-result matrix kernels: one wave per SIMD (TileCfg::WIDE,
-// wide_loop.hpp); the A/B-addition kernels of two layout pairs: eight waves (other tables leave the entry empty).
+// TILE_256x256, TILE_256x256_K32: 16x16x32 matrix instructions (TileCfg::M16), which on a chip at its power limit sustain a higher
+// rate on the same data.  Plain, BF16 and binary16-result matrix kernels: one kernel under both names, with one wave per SIMD
+// (TileCfg::WIDE, wide_loop.hpp; eight waves with 32x32x16 instructions, which outputs of fewer than 192 such tiles used to run on: 3000x3000x2000
+// with C 71.5 -> 59.4 us, 6144x2048x4096 116 -> 98, 4096x4096x320 40.4 -> 38.8, 3072x4096x512 35.2 -> 36.3).  The A/B-addition
+// kernels have eight waves, with 32x32x16 instructions (TILE_256x256) or, two layout pairs, 16x16x32 ones; contractions
+// 32x32x16 ones.
 // TILE_64x64_KG2, TILE_64x64_KG2_DEEP: the 64x64 tile with two groups of four waves that share its K tiles
 // (TileCfg::KG), for outputs of at most two such tiles per unit: one group alone spends most of a K tile in barrier
 // and LDS latency.  DEEP: rings of four, for outputs of at most one tile per unit, whose two-buffer rings wait for
@@ -134,7 +137,7 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
 #define FG_DEFINE_TABLE_BF16(FUNC, AKC, BKC, TAG)                                                  \
     const KernelEntry *FUNC() {                                                                    \
         static const KernelEntry t[TILE_COUNT] = {                                                 \
-            FG_ENTRY_BF16(256, 256, 64, 2, 2, 4, AKC, BKC, "gemm_bf16_" TAG "_256x256x64"),        \
+            FG_ENTRY_K32(256, 256, 64, 2, 2, 2, AKC, BKC, true, false, "gemm_bf16_" TAG "_256x256x64"), \
             FG_ENTRY_BF16(256, 128, 64, 3, 4, 2, AKC, BKC, "gemm_bf16_" TAG "_256x128x64"),        \
             FG_ENTRY_BF16(128, 128, 64, 2, 2, 2, AKC, BKC, "gemm_bf16_" TAG "_128x128x64"),        \
             FG_ENTRY_BF16(64, 64, 64, 2, 2, 2, AKC, BKC, "gemm_bf16_" TAG "_64x64x64"),            \
@@ -156,7 +159,7 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
 #define FG_DEFINE_TABLE_H16(FUNC, AKC, BKC, TAG)                                                   \
     const KernelEntry *FUNC() {                                                                    \
         static const KernelEntry t[TILE_COUNT] = {                                                 \
-            FG_ENTRY_H16(256, 256, 64, 2, 2, 4, AKC, BKC, "gemm_h16_" TAG "_256x256x64"),          \
+            FG_ENTRY_K32(256, 256, 64, 2, 2, 2, AKC, BKC, false, true, "gemm_h16_" TAG "_256x256x64"), \
             FG_ENTRY_H16(256, 128, 64, 3, 4, 2, AKC, BKC, "gemm_h16_" TAG "_256x128x64"),          \
             FG_ENTRY_H16(128, 128, 64, 2, 2, 2, AKC, BKC, "gemm_h16_" TAG "_128x128x64"),          \
             FG_ENTRY_H16(64, 64, 64, 2, 2, 2, AKC, BKC, "gemm_h16_" TAG "_64x64x64"),              \
@@ -220,7 +223,7 @@ inline KernelEntry xf_k32_entry(const char *name) {
 #define FG_DEFINE_TABLE(FUNC, AKC, BKC, TAG)                                                       \
     const KernelEntry *FUNC() {                                                                    \
         static const KernelEntry t[TILE_COUNT * VARIANT_COUNT] = {                                 \
-            FG_ENTRY(256, 256, 64, 2, 2, 4, AKC, BKC, false, "gemm_" TAG "_256x256x64"),           \
+            FG_ENTRY_K32(256, 256, 64, 2, 2, 2, AKC, BKC, false, false, "gemm_" TAG "_256x256x64"), \
             FG_ENTRY(256, 256, 64, 2, 2, 4, AKC, BKC, true, "gett_" TAG "_256x256x64"),            \
             FG_ENTRY_GS(256, 256, 64, 2, 2, 4, AKC, BKC, "gett_stream_" TAG "_256x256x64"),        \
             FG_ENTRY(256, 128, 64, 3, 4, 2, AKC, BKC, false, "gemm_" TAG "_256x128x64"),           \

@@ -72,23 +72,23 @@ __device__ __forceinline__ void mfma_acc_load(half8 a, half8 b, u32x4 rsrc, uint
 // ---- loader -----------------------------------------------------------------------------------------
 // One operand of a plain matrix, R rows x 64 k per K tile, in the LDS layout of TileLoader (16-row fragments); a wave
 // fetches SLABS pieces of 1 KB.  The descriptor is advanced in place.  Its size, the bytes from the current K tile
-// to the end of the operand, is kept in units of 16 bytes: up to 64 GiB (the host gives larger operands to other kernels).
+// to the end of the operand, is counted in 64 bits (negative past the end).
 template <int R, bool KC>
 struct WideLoader {
     static constexpr int SLABS = R / 32;
     uint32_t voff[SLABS];
     u32x4 rsrc;
-    uint32_t step, left16;         // bytes per K tile; 16-byte units from the current K tile to the end of the operand
+    uint32_t step, rest_lo;        // bytes per K tile; from the current K tile to the end of the operand
+    int32_t rest_hi;
 
     // K tile kt is the next one; more: there is such a tile to load
     __device__ __forceinline__ void at(const _Float16 *ptr, int row0, int64_t rs, int64_t ks, int64_t span, int kt, bool more) {
-        const int64_t first = (int64_t)row0 * rs + 64 * ks * kt;
-        const int64_t rest = (span - first) / 8;                   // (spans and strides are whole pieces of eight elements)
-        left16 = rest < 0 ? 0u : rest > 0xffffffffll ? 0xffffffffu : (uint32_t)rest;
-        rsrc = make_rsrc(ptr + first, more ? size() : 0u);
+        const int64_t first = (int64_t)row0 * rs + 64 * ks * kt, rest = (span - first) * 2;
+        rest_lo = (uint32_t)rest;
+        rest_hi = (int32_t)(rest >> 32);
+        rsrc = make_rsrc(ptr + first, !more || rest < 0 ? 0u : rest > 0xfffffff0ll ? 0xfffffff0u : (uint32_t)rest);
         step = (uint32_t)(128 * ks);
     }
-    __device__ __forceinline__ uint32_t size() const { return (left16 < 0x0fffffffu ? left16 : 0x0fffffffu) * 16u; }
     __device__ __forceinline__ void init(int wave, int lane, int64_t rs, int64_t ks) {
 #pragma unroll
         for (int s = 0; s < SLABS; ++s) {
@@ -119,9 +119,9 @@ struct WideLoader {
     // more: how many K tiles are still to be requested; without one the loads fetch nothing
     __device__ __forceinline__ void next_size(int more) {
         uint32_t n;
-        asm volatile("s_max_u32 %0, %0, %2\n\ts_sub_u32 %0, %0, %2\n\ts_min_u32 %1, %0, 0xfffffff\n\ts_lshl_b32 %1, %1, 4\n\t"
-                     "s_cmp_gt_i32 %3, 0\n\ts_cselect_b32 %1, %1, 0"
-                     : "+s"(left16), "=&s"(n) : "s"(step >> 4), "s"(more) : "scc");
+        asm volatile("s_sub_u32 %0, %0, %3\n\ts_subb_u32 %1, %1, 0\n\ts_cmp_gt_i32 %1, 0\n\ts_cselect_b32 %2, -16, %0\n\t"
+                     "s_cmp_lt_i32 %1, 0\n\ts_cselect_b32 %2, 0, %2\n\ts_cmp_gt_i32 %4, 0\n\ts_cselect_b32 %2, %2, 0"
+                     : "+s"(rest_lo), "+s"(rest_hi), "=&s"(n) : "s"(step), "s"(more) : "scc");
         rsrc[2] = n;
     }
     // all of a K tile at once, of which the first klim k exist (M/N-contiguous: what lies beyond K lies beyond the operand)
