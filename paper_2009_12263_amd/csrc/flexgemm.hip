@@ -49,10 +49,10 @@ void note_relaxed(fg_status st, const char *fmt, ...) {
 
 constexpr int kNumCU = 256;   // MI355X: 8 XCDs x 32 compute units
 
-// Tuning overrides of the planner, from the environment: FG_FORCE_TILE=0..8 picks a tile shape (0..3
+// Tuning overrides of the planner, from the environment: FG_FORCE_TILE=0..9 picks a tile shape (0..3
 // for the four tiles of the complex and dual kernels)
 // (5: the 256x256 tile with the k32 kernel where the family has one; 6, 7: the 64x64 tile with two K
-// groups and rings of two or four buffers, 8: the 64x128 tile with two), FG_FORCE_SPLIT=n a split of K
+// groups and rings of two or four buffers, 8: the 64x128 tile with two, 9: the 256x128 tile with eight waves), FG_FORCE_SPLIT=n a split of K
 // for every tile, FG_FORCE_TAIL=n a split of K for the tiles of the last round (1: never).  Read
 // when the library is loaded and again by fg_reload_tuning(), not on every call.
 std::atomic<int> g_force_tile{-1}, g_force_split{0}, g_force_tail{0};
@@ -131,9 +131,9 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 // lines are fitted to the times of replayed graphs of every tile and split forced over 190 products (64x64x32768 to
 // 4876x7518x2448): the choice by them alone is on average 1.7 % slower than the fastest (5 % with the rates before the larger
 // rings), at most 42 % (6708x5150x96), and over 16 % only with K up to 224; held to what plan_product promises, 3.4 % (4.7 %).
-constexpr int kTileM[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64, 64};
-constexpr int kTileN[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64, 128};
-constexpr int kTilesPerCU[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1, 1};
+constexpr int kTileM[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64, 64, 256};
+constexpr int kTileN[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64, 128, 128};
+constexpr int kTilesPerCU[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1, 1, 1};
 constexpr int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}, kSplitCount = sizeof kSplits / sizeof *kSplits;
 struct Rates {
     double shared[fg::TILE_COUNT], alone[fg::TILE_COUNT];
@@ -144,15 +144,21 @@ struct Rates {
     double off_line[fg::TILE_COUNT];
     bool last_round;         // the last, partly filled round is priced with the workgroups that it has
     // K groups and sets of accumulators per group, which share a workgroup's sum over K (TileCfg::KG, ACC_SETS)
-    int groups[fg::TILE_COUNT] = {1, 1, 1, 1, 1, 1, 1, 1, 1}, sets[fg::TILE_COUNT] = {1, 1, 1, 1, 1, 1, 1, 1, 1};
+    int groups[fg::TILE_COUNT] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1}, sets[fg::TILE_COUNT] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1};
 };
-constexpr Rates kRates = {{1, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
-                          {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
+constexpr Rates kRates = {{1.12, 0.95, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
+                          {1.12, 0.95, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
                           2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
                           {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true,
-                          {1, 1, 1, 1, 1, 1, 2, 2, 2}, {1, 1, 1, 1, 2, 1, 2, 2, 2}};
+                          {1, 1, 1, 1, 1, 1, 2, 2, 2, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1}};
+// Addition on A and B, whose kernels of the large tiles have eight waves.
+constexpr Rates kRatesAdd = {{1, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
+                             {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
+                             2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
+                             {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true,
+                             {1, 1, 1, 1, 1, 1, 2, 2, 2, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1}};
 using fg::TileCfg;
-static_assert(FG_CFG(128, 128, 64, 4, 4, 2, false, true, false)::ACC_SETS == 2 && FG_CFG(256, 128, 64, 3, 4, 2, false, true, false)::ACC_SETS == 1 &&
+static_assert(FG_CFG_K32(128, 128, 64, 4, 2, 2, false, true, false, false)::ACC_SETS == 2 && FG_CFG(128, 128, 64, 4, 4, 2, false, true, false)::ACC_SETS == 2 && FG_CFG(256, 128, 64, 3, 4, 2, false, true, false)::ACC_SETS == 1 &&
               FG_CFG_KG(false, true, false, false, false, 64, 2, false)::ACC_SETS == 2 && FG_CFG_KG(false, true, false, false, false, 64, 4, true)::ACC_SETS == 2 &&
               FG_CFG_KG(false, true, false, false, false, 128, 3, true)::ACC_SETS == 2, "Rates::sets");
 // Binary16 C and D with K from 512 on: a tile's C and D at three quarters of the bytes (they are half, in lines that are accessed
@@ -165,13 +171,13 @@ constexpr Rates kRates16 = {{1, 0.88, 0.732, 0.40, 0.74, 1, 0.373, 0.367, 0.384}
                             {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
                             2.07e-6, 26.8e9 * 4 / 3, 6.92e-6, 8.7e12,
                             {0, 0.022, 0, 0.0446, 0.0395, 0, 0, 0, 0}, true,
-                            {1, 1, 1, 1, 1, 1, 2, 2, 2}, {1, 1, 1, 1, 2, 1, 2, 2, 2}};
+                            {1, 1, 1, 1, 1, 1, 2, 2, 2, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1}};
 // The rates that decided what a call needs scratch memory for before the 64x64 tile had K groups
 // (see plan_product).
 constexpr Rates kPromisedRates = {{1.0, 0.8, 0.73, 0.45, 0.57, 1.0, 0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0, 0}, 2e-6, 25e9, 6e-6, 3e12, {}, false};
 // The rates of the planner before the larger rings (four K groups as tile 7, no 64x128 tile): see plan_product.
 constexpr Rates kFormerRates = {{1.0, 0.8, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29, 0}, {1.0, 0.8, 0.43, 0.135, 0.645, 1.0, 0.27, 0.29, 0}, 1.6e-6, 27e9, 12.3e-6, 7.2e12,
-                                {0, 0, 0, 0, 0, 0, 0.1, 0.1, 0}, false, {1, 1, 1, 1, 1, 1, 2, 4, 1}};
+                                {0, 0, 0, 0, 0, 0, 0.1, 0.1, 0}, false, {1, 1, 1, 1, 1, 1, 2, 4, 1, 1}};
 // Contractions have neither K groups nor splits, which the rates above were fitted with: over 320 contractions those
 // picked the fastest tile to within 2.4 % on average and 44 % at most (192 x 960 rows and columns over 2560: 33.8 us
 // with the deep 128x128 tile, 23.6 with the 64x64 tile), these to within 0.5 % and 43 %, and no tile slower than
@@ -216,7 +222,7 @@ constexpr Prices priced(const Rates &r) {
     p.last_round = r.last_round;
     return p;
 }
-constexpr Prices kPrices = priced(kRates), kPrices16 = priced(kRates16), kContractPrices = priced(kContractRates);
+constexpr Prices kPrices = priced(kRates), kPrices16 = priced(kRates16), kPricesAdd = priced(kRatesAdd), kContractPrices = priced(kContractRates);
 constexpr Prices kPromisedPrices = priced(kPromisedRates), kFormerPrices = priced(kFormerRates);
 
 // The K ranges that a product may be split into: at least four K tiles (256 k) each.
@@ -273,6 +279,7 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
         int t = g_force_tile.load(std::memory_order_relaxed);
         if (t == fg::TILE_256x256_K32) { t = fg::TILE_256x256; force_k32 = true; }
         else forced_plain = (t == fg::TILE_256x256);
+        if (t == fg::TILE_256x128_PASS) t = fg::TILE_256x128;
         if (t >= 0 && t < fg::TILE_COUNT) force_tile = t;
     }
     const int32_t nk = ranges.nk;
@@ -357,12 +364,13 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
     if (prices.last_round && force_tile < 0 && force_split < 1 && best.tile == fg::TILE_256x128 && best.tail_splits > 1 &&
         large_tail_cost <= 1.09 * best_cost)
         best = large_tail;
-    // A short K (up to 256) makes the product a pass over C and D: there the 256x128 tile measured
-    // 4 to 15 % faster than the 256x256 tile the estimate picks (8192^2 x 64: 95.7 against 100.3 us,
-    // 4096^2 x 128: 27.9 against 29.8, 8192^2 x 256: 107.1 against 112.1; at K = 384 and 512 it
-    // wins with a C operand and loses without one, from K = 768 on it loses).  Matrix kernels only,
-    // which is what k32 > 0 says: contraction 5a, K = 256, is faster on the larger tile.
-    if (best.tile == fg::TILE_256x256 && k32 > 0 && force_tile < 0 && nk <= 4 && best.splits == 1 && best.tail_splits == 1)
+    // A short K (up to 256) makes a product whose C and D stream a pass over them: there the 256x128 tile with eight waves
+    // (TILE_256x128_PASS) is faster than the 256x256 tile the estimate picks (8192^2 x 128 with C 98.2 against 115.1 us, without 56.3 and
+    // 60.0, 256: 110.9, 127.7, 77.1, 73.3; at K = 384 and 512 it wins with a C operand, see select_kernel).  Not where they stay in
+    // the caches (4096^2 x 256 38.9 and 38.1, without C 26.7 and 20.3; 3000x5000x256 45.9, 42.8, 24.9, 20.4; x 128 40.3, 39.9, 19.3, 17.5).
+    // Matrix kernels only, which is what k32 > 0 says: contraction 5a, K = 256, is faster on the larger tile.
+    if (best.tile == fg::TILE_256x256 && k32 > 0 && force_tile < 0 && nk <= 4 && best.splits == 1 && best.tail_splits == 1 &&
+        M * N * 8 > fg::kMemorySideCache)
         best.tile = fg::TILE_256x128;
     if (best.tile == fg::TILE_256x256 && k32 > 0 && !forced_plain) {
         const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256) * batches;
@@ -479,7 +487,7 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     const bool long16 = q.cd16 && q.K >= 512;               // (see kRates16)
     const int straddling = may_split || long16 ? (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N) : 0;
     const Plan plan = q.a_diag || q.b_diag ? choose_plan(q.M, q.N, KRanges(q.K), false, true, 1, false)
-                                           : plan_product(q.M, q.N, q.K, may_split, k32, straddling, long16 ? kPrices16 : kPrices);
+                                           : plan_product(q.M, q.N, q.K, may_split, k32, straddling, long16 ? kPrices16 : q.ab_add ? kPricesAdd : kPrices);
     int tile = plan.tile;
     // A product with a diagonal operand is bound by its memory traffic (one pass over the dense
     // operand, C and D; a tile row only meets the K tiles on the diagonal).  While all of it fits the
@@ -489,10 +497,17 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     // more in memory than they gain (8192^2: 180 us against 135 us), and the estimate above decides.
     if ((q.a_diag || q.b_diag) && g_force_tile.load(std::memory_order_relaxed) < 0 && q.M * q.N * 10 <= (256ll << 20))
         tile = fg::TILE_64x64;
-    if (!q.ab_add && !q.a_diag && !q.b_diag && (tile == fg::TILE_256x256 || tile == fg::TILE_256x256_K32) && g_force_tile.load(std::memory_order_relaxed) < 0) {
-        // A pass over C and D that stream: the stores of four waves fall behind those of eight (8192^2 with C, K = 384: 135.9 us,
-        // 124.0 on the 256x128 tile; 512: 147 and 137; 768: 166.5 and 165.2; 1024: 187 and 193).
-        if (q.C && q.K <= 512 && q.M * q.N * 8 > fg::kMemorySideCache && plan.splits == 1 && plan.tail_splits == 1) tile = fg::TILE_256x128;
+    if (!q.ab_add && !q.a_diag && !q.b_diag) {
+        const int forced = g_force_tile.load(std::memory_order_relaxed);
+        // A pass over C and D that stream: the stores of four waves fall behind those of eight (8192^2 with C, K = 384: 135.9 us on the
+        // 256x256 tile, 124.0 on the 256x128 one with eight; 512: 147 and 137; 768: 166.5 and 165.2; 1024: 187 and 193).
+        if ((tile == fg::TILE_256x256 || tile == fg::TILE_256x256_K32) && forced < 0 && q.C && q.K <= 512 &&
+            q.M * q.N * 8 > fg::kMemorySideCache && plan.splits == 1 && plan.tail_splits == 1)
+            tile = fg::TILE_256x128;
+        // Short K, where loading, multiplying and storing hardly overlap within a tile: eight waves on the 256x128 tile (2560^2 x 128 with
+        // C 14.9 us with four, 12.9 with eight, 8192x1024x128 without 11.3 and 10.7, at K = 512 18.6 and 17.7, 16.0 and 17.1; at 768
+        // 21.0 and 20.9, 18.9 and 20.7; binary16 results with C 19.3 and 18.3, 22.1 and 21.9; 1000: 23.7, 24.2, 25.4, 26.4).
+        if (tile == fg::TILE_256x128 && (forced == fg::TILE_256x128_PASS || (forced < 0 && q.K <= (q.C ? 768 : 512)))) tile = fg::TILE_256x128_PASS;
     }
     if (plan_out) { *plan_out = plan; plan_out->tile = tile; }
     if (q.a_diag) return &fg::kernel_table_diag()[tile * 4 + (q.b_kc ? 0 : 1)];

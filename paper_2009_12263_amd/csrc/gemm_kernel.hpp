@@ -174,7 +174,7 @@ struct TileCfg {
     // ONCE: the kernel has K loops whose loads of A or of B carry the streaming policy, for operands that are read once:
     // narrow products, bound by reading their large operand (128x16384x12288 122 -> 113 us; where other tiles read the
     // operand again it costs: 8192x1024x4096 72 -> 76).  From which size on, and why: streams_once (cache_policy.hpp).
-    static constexpr bool ONCE = PLAIN_REAL && (KTURNS_ || STAGES_ == 4);
+    static constexpr bool ONCE = (PLAIN_REAL && (KTURNS_ || STAGES_ == 4)) || (WIDE_ && STAGES_ == 4);
     // SPREAD: the refill loads of a ring buffer are issued one at a time between the MFMAs of two
     // k-slices (A's part in the slice after the buffer is retired, B's part in the next one)
     // instead of as one burst: a burst from all waves queues up in the compute unit's single
@@ -1233,16 +1233,17 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
             wide_b.init(wave, lane, tp.b_rs, tp.b_ks);
             wide_a.at(ap[0], m0, tp.a_rs, tp.a_ks, tp.a_span, last_first ? nk - 1 : kt0, nkt > 0);
             wide_b.at(bp[0], n0, tp.b_rs, tp.b_ks, tp.b_span, last_first ? nk - 1 : kt0, nkt > 0);
-            wide_a.issue(to_a, last_first ? rest : BK, lane);
-            wide_b.issue(to_b, last_first ? rest : BK, lane);
+            const bool a_once = Cfg::ONCE && tp.once == 2, b_once = Cfg::ONCE && tp.once == 1;
+            wide_a.issue(to_a, last_first ? rest : BK, lane, a_once);
+            wide_b.issue(to_b, last_first ? rest : BK, lane, b_once);
             const int second = last_first ? kt0 : kt0 + 1;
             wide_a.at(ap[0], m0, tp.a_rs, tp.a_ks, tp.a_span, second, nkt > 1);
             wide_b.at(bp[0], n0, tp.b_rs, tp.b_ks, tp.b_span, second, nkt > 1);
             // A's ring is filled but for one buffer, B's whole
 #pragma unroll
             for (int st = 1; st < S; ++st) {
-                if (st < Cfg::RING_A - 1) { wide_a.issue(to_a + st * Cfg::A_TILE_BYTES, BK, lane); wide_a.next_base(); wide_a.next_size(nkt - st - 1); }
-                wide_b.issue(to_b + st * Cfg::B_TILE_BYTES, BK, lane);
+                if (st < Cfg::RING_A - 1) { wide_a.issue(to_a + st * Cfg::A_TILE_BYTES, BK, lane, a_once); wide_a.next_base(); wide_a.next_size(nkt - st - 1); }
+                wide_b.issue(to_b + st * Cfg::B_TILE_BYTES, BK, lane, b_once);
                 wide_b.next_base();
                 wide_b.next_size(nkt - st - 1);
             }
@@ -1314,7 +1315,10 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
             if constexpr (Cfg::WIDE) {
                 wait_tile<(Cfg::RING_A - 2) * Cfg::A_SLABS + (S - 1) * Cfg::B_SLABS>();     // all but the first K tile may be in flight
                 __builtin_amdgcn_s_barrier();
-                k_loop_wide<Cfg>(wide_a, wide_b, fa, fb, lds_a, lds_b, wave, nkt);
+                const int once = Cfg::ONCE ? load_param<int32_t>(offsetof(GemmParams, once)) : 0;
+                if (Cfg::ONCE && once == 1) { if constexpr (Cfg::ONCE) k_loop_wide<Cfg, 1>(wide_a, wide_b, fa, fb, lds_a, lds_b, wave, nkt); }
+                else if (Cfg::ONCE && once == 2) { if constexpr (Cfg::ONCE) k_loop_wide<Cfg, 2>(wide_a, wide_b, fa, fb, lds_a, lds_b, wave, nkt); }
+                else k_loop_wide<Cfg, 0>(wide_a, wide_b, fa, fb, lds_a, lds_b, wave, nkt);
             } else {
             wait_tiles<L, S - 1>(nkt - 1);
             __builtin_amdgcn_s_barrier();

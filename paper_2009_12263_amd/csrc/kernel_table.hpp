@@ -34,7 +34,8 @@ namespace fg {
 // with two groups, 15.5; 1895x714x1256: 15.3, 14.0; 128x64 tiles 15.7 and 14.9).
 // All three: matrix kernels of real products.
 enum TileId { TILE_256x256 = 0, TILE_256x128 = 1, TILE_128x128 = 2, TILE_64x64 = 3, TILE_128x128_DEEP = 4,
-              TILE_256x256_K32 = 5, TILE_64x64_KG2 = 6, TILE_64x64_KG2_DEEP = 7, TILE_64x128_KG2 = 8, TILE_COUNT = 9, DIAG_TILE_COUNT = 4 };
+              TILE_256x256_K32 = 5, TILE_64x64_KG2 = 6, TILE_64x64_KG2_DEEP = 7, TILE_64x128_KG2 = 8,
+              TILE_256x128_PASS = 9, TILE_COUNT = 10, DIAG_TILE_COUNT = 4 };
 
 struct KernelEntry {
     const void *fn;           // void (*)(const GemmParams), contractions: (const ContractParams)
@@ -138,14 +139,15 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
     const KernelEntry *FUNC() {                                                                    \
         static const KernelEntry t[TILE_COUNT] = {                                                 \
             FG_ENTRY_K32(256, 256, 64, 2, 2, 2, AKC, BKC, true, false, "gemm_bf16_" TAG "_256x256x64"), \
-            FG_ENTRY_BF16(256, 128, 64, 3, 4, 2, AKC, BKC, "gemm_bf16_" TAG "_256x128x64"),        \
+            FG_ENTRY_K32(256, 128, 64, 3, 2, 2, AKC, BKC, true, false, "gemm_bf16_" TAG "_256x128x64"), \
             FG_ENTRY_BF16(128, 128, 64, 2, 2, 2, AKC, BKC, "gemm_bf16_" TAG "_128x128x64"),        \
             FG_ENTRY_BF16(64, 64, 64, 2, 2, 2, AKC, BKC, "gemm_bf16_" TAG "_64x64x64"),            \
-            FG_ENTRY_BF16(128, 128, 64, 4, 4, 2, AKC, BKC, "gemm_bf16_" TAG "_128x128x64_deep"),   \
+            FG_ENTRY_K32(128, 128, 64, 4, 2, 2, AKC, BKC, true, false, "gemm_bf16_" TAG "_128x128x64_deep"), \
             FG_ENTRY_K32(256, 256, 64, 2, 2, 2, AKC, BKC, true, false, "gemm_bf16_" TAG "_256x256x64_k32"), \
             FG_ENTRY_KG(AKC, BKC, true, false, false, 64, 2, false, "gemm_bf16_" TAG "_64x64x64"),            \
             FG_ENTRY_KG(AKC, BKC, true, false, false, 64, 4, true, "gemm_bf16_" TAG "_64x64x64"),            \
-            FG_ENTRY_KG(AKC, BKC, true, false, false, 128, 3, true, "gemm_bf16_" TAG "_64x128x64"),\
+            FG_ENTRY_KG(AKC, BKC, true, false, false, 128, 3, true, "gemm_bf16_" TAG "_64x128x64"), \
+            FG_ENTRY_BF16(256, 128, 64, 3, 4, 2, AKC, BKC, "gemm_bf16_" TAG "_256x128x64"),        \
         };                                                                                         \
         return t;                                                                                  \
     }
@@ -160,14 +162,15 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
     const KernelEntry *FUNC() {                                                                    \
         static const KernelEntry t[TILE_COUNT] = {                                                 \
             FG_ENTRY_K32(256, 256, 64, 2, 2, 2, AKC, BKC, false, true, "gemm_h16_" TAG "_256x256x64"), \
-            FG_ENTRY_H16(256, 128, 64, 3, 4, 2, AKC, BKC, "gemm_h16_" TAG "_256x128x64"),          \
+            FG_ENTRY_K32(256, 128, 64, 3, 2, 2, AKC, BKC, false, true, "gemm_h16_" TAG "_256x128x64"), \
             FG_ENTRY_H16(128, 128, 64, 2, 2, 2, AKC, BKC, "gemm_h16_" TAG "_128x128x64"),          \
             FG_ENTRY_H16(64, 64, 64, 2, 2, 2, AKC, BKC, "gemm_h16_" TAG "_64x64x64"),              \
-            FG_ENTRY_H16(128, 128, 64, 4, 4, 2, AKC, BKC, "gemm_h16_" TAG "_128x128x64_deep"),     \
+            FG_ENTRY_K32(128, 128, 64, 4, 2, 2, AKC, BKC, false, true, "gemm_h16_" TAG "_128x128x64_deep"), \
             FG_ENTRY_K32(256, 256, 64, 2, 2, 2, AKC, BKC, false, true, "gemm_h16_" TAG "_256x256x64_k32"), \
             FG_ENTRY_KG(AKC, BKC, false, false, true, 64, 2, false, "gemm_h16_" TAG "_64x64x64"),             \
             FG_ENTRY_KG(AKC, BKC, false, false, true, 64, 4, true, "gemm_h16_" TAG "_64x64x64"),             \
             FG_ENTRY_KG(AKC, BKC, false, false, true, 128, 3, true, "gemm_h16_" TAG "_64x128x64"), \
+            FG_ENTRY_H16(256, 128, 64, 3, 4, 2, AKC, BKC, "gemm_h16_" TAG "_256x128x64"),          \
         };                                                                                         \
         return t;                                                                                  \
     }
@@ -202,7 +205,8 @@ inline KernelEntry xf_k32_entry(const char *name) {
             xf_k32_entry<AKC, BKC>("gemm_abadd_" TAG "_256x256x64_k32"),                           \
             FG_ENTRY_KG(AKC, BKC, false, true, false, 64, 2, false, "gemm_abadd_" TAG "_64x64x64"),           \
             FG_ENTRY_KG(AKC, BKC, false, true, false, 64, 4, true, "gemm_abadd_" TAG "_64x64x64"),           \
-            FG_ENTRY_KG(AKC, BKC, false, true, false, 128, 3, true, "gemm_abadd_" TAG "_64x128x64"),\
+            FG_ENTRY_KG(AKC, BKC, false, true, false, 128, 3, true, "gemm_abadd_" TAG "_64x128x64"), \
+            FG_EMPTY_ENTRY,                                                                        \
         };                                                                                         \
         return t;                                                                                  \
     }
@@ -226,7 +230,7 @@ inline KernelEntry xf_k32_entry(const char *name) {
             FG_ENTRY_K32(256, 256, 64, 2, 2, 2, AKC, BKC, false, false, "gemm_" TAG "_256x256x64"), \
             FG_ENTRY(256, 256, 64, 2, 2, 4, AKC, BKC, true, "gett_" TAG "_256x256x64"),            \
             FG_ENTRY_GS(256, 256, 64, 2, 2, 4, AKC, BKC, "gett_stream_" TAG "_256x256x64"),        \
-            FG_ENTRY(256, 128, 64, 3, 4, 2, AKC, BKC, false, "gemm_" TAG "_256x128x64"),           \
+            FG_ENTRY_K32(256, 128, 64, 3, 2, 2, AKC, BKC, false, false, "gemm_" TAG "_256x128x64"), \
             FG_ENTRY(256, 128, 64, 2, 4, 2, AKC, BKC, true, "gett_" TAG "_256x128x64"),            \
             FG_ENTRY_GS(256, 128, 64, 2, 4, 2, AKC, BKC, "gett_stream_" TAG "_256x128x64"),        \
             FG_ENTRY(128, 128, 64, 2, 2, 2, AKC, BKC, false, "gemm_" TAG "_128x128x64"),           \
@@ -235,14 +239,15 @@ inline KernelEntry xf_k32_entry(const char *name) {
             FG_ENTRY(64, 64, 64, 2, 2, 2, AKC, BKC, false, "gemm_" TAG "_64x64x64"),               \
             FG_ENTRY(64, 64, 64, 2, 2, 2, AKC, BKC, true, "gett_" TAG "_64x64x64"),                \
             FG_ENTRY_GS(64, 64, 64, 2, 2, 2, AKC, BKC, "gett_stream_" TAG "_64x64x64"),            \
-            FG_ENTRY(128, 128, 64, 4, 4, 2, AKC, BKC, false, "gemm_" TAG "_128x128x64_deep"),      \
+            FG_ENTRY_K32(128, 128, 64, 4, 2, 2, AKC, BKC, false, false, "gemm_" TAG "_128x128x64_deep"), \
             FG_ENTRY(128, 128, 64, 4, 4, 2, AKC, BKC, true, "gett_" TAG "_128x128x64_deep"),       \
             FG_ENTRY_GS(128, 128, 64, 4, 4, 2, AKC, BKC, "gett_stream_" TAG "_128x128x64_deep"),   \
             FG_ENTRY_K32(256, 256, 64, 2, 2, 2, AKC, BKC, false, false, "gemm_" TAG "_256x256x64_k32"), \
             FG_EMPTY_ENTRY, FG_EMPTY_ENTRY,                                                        \
             FG_ENTRY_KG(AKC, BKC, false, false, false, 64, 2, false, "gemm_" TAG "_64x64x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
             FG_ENTRY_KG(AKC, BKC, false, false, false, 64, 4, true, "gemm_" TAG "_64x64x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
-            FG_ENTRY_KG(AKC, BKC, false, false, false, 128, 3, true, "gemm_" TAG "_64x128x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY,\
+            FG_ENTRY_KG(AKC, BKC, false, false, false, 128, 3, true, "gemm_" TAG "_64x128x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
+            FG_ENTRY(256, 128, 64, 3, 4, 2, AKC, BKC, false, "gemm_" TAG "_256x128x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
         };                                                                                         \
         return t;                                                                                  \
     }

@@ -59,15 +59,18 @@ __device__ __forceinline__ void mfma_acc(half8 a, half8 b) {
     else asm volatile("v_mfma_f32_16x16x32_f16 a[%0:%1], %2, %3, a[%0:%1]" ::"n"(R), "n"(R + 3), "v"(a), "v"(b));
 }
 // the same, and a direct load to LDS address lds + OFF: the matrix instruction stands between the write of m0 and its use
-template <bool BF16, int R, int OFF>
+// (STREAM: the load carries the streaming policy)
+#define FG_MFMA_LOAD(TYPE, POLICY)                                                                                                      \
+    asm volatile("s_add_u32 m0, %6, %7\n\tv_mfma_f32_16x16x32_" TYPE " a[%0:%1], %2, %3, a[%0:%1]\n\tbuffer_load_dwordx4 %4, %5, 0 offen" POLICY " lds" \
+                 ::"n"(R), "n"(R + 3), "v"(a), "v"(b), "v"(voff), "s"(rsrc), "s"(lds), "n"(OFF) : "memory", "m0", "scc")
+template <bool BF16, bool STREAM, int R, int OFF>
 __device__ __forceinline__ void mfma_acc_load(half8 a, half8 b, u32x4 rsrc, uint32_t lds, uint32_t voff) {
-    if constexpr (BF16)
-        asm volatile("s_add_u32 m0, %6, %7\n\tv_mfma_f32_16x16x32_bf16 a[%0:%1], %2, %3, a[%0:%1]\n\tbuffer_load_dwordx4 %4, %5, 0 offen lds"
-                     ::"n"(R), "n"(R + 3), "v"(a), "v"(b), "v"(voff), "s"(rsrc), "s"(lds), "n"(OFF) : "memory", "m0", "scc");
-    else
-        asm volatile("s_add_u32 m0, %6, %7\n\tv_mfma_f32_16x16x32_f16 a[%0:%1], %2, %3, a[%0:%1]\n\tbuffer_load_dwordx4 %4, %5, 0 offen lds"
-                     ::"n"(R), "n"(R + 3), "v"(a), "v"(b), "v"(voff), "s"(rsrc), "s"(lds), "n"(OFF) : "memory", "m0", "scc");
+    if constexpr (BF16 && STREAM) FG_MFMA_LOAD("bf16", " nt");
+    else if constexpr (BF16) FG_MFMA_LOAD("bf16", "");
+    else if constexpr (STREAM) FG_MFMA_LOAD("f16", " nt");
+    else FG_MFMA_LOAD("f16", "");
 }
+#undef FG_MFMA_LOAD
 
 // ---- loader -----------------------------------------------------------------------------------------
 // One operand of a plain matrix, R rows x 64 k per K tile, in the LDS layout of TileLoader (16-row fragments); a wave
@@ -125,14 +128,15 @@ struct WideLoader {
         rsrc[2] = n;
     }
     // all of a K tile at once, of which the first klim k exist (M/N-contiguous: what lies beyond K lies beyond the operand)
-    __device__ __forceinline__ void issue(uint32_t lds, int klim, int lane) const {
+    __device__ __forceinline__ void issue(uint32_t lds, int klim, int lane, bool stream) const {
 #pragma unroll
         for (int s = 0; s < SLABS; ++s) {
             uint32_t v = voff[s];
             if constexpr (KC) {
                 if (chunk(s, lane) * 8 >= klim) v = kOutOfRange;
             }
-            load16_to_lds(rsrc, lds + s * 1024u, v);
+            if (stream) load16_to_lds<true>(rsrc, lds + s * 1024u, v);
+            else load16_to_lds(rsrc, lds + s * 1024u, v);
         }
     }
 };
@@ -143,7 +147,8 @@ struct WideLoader {
 //                 barrier of tile kt - 1);
 //   second slice: after the barrier at slot BAR, which publishes tile kt + 1 and retires tile kt, the first
 //                 fragments of tile kt + 1 are read, and B's tile kt + RB is requested.
-template <class Cfg, class LA, class LB, class FA, class FB>
+// ONCE: GemmParams::once.
+template <class Cfg, int ONCE, class LA, class LB, class FA, class FB>
 __device__ __forceinline__ void k_loop_wide(LA &la, LB &lb, const FA &fa, const FB &fb, FG_LDS char *lds_a, FG_LDS char *lds_b, int wave, int nkt) {
     constexpr int TI = Cfg::FI, TJ = Cfg::FJ, SLOTS = TI * TJ, NR = TI + TJ, RA = Cfg::RING_A, RB = Cfg::STAGES;
     constexpr int NA = LA::SLABS, NB = LB::SLABS, SET2 = Cfg::ACC_SETS == 2 ? 4 * SLOTS : 0;
@@ -174,7 +179,7 @@ __device__ __forceinline__ void k_loop_wide(LA &la, LB &lb, const FA &fa, const 
         static_for<SLOTS>([&](auto s_tag) {
             constexpr int s = s_tag, i = s / TJ, j = s % TJ, l = (s - 1) / LOAD_A;
             if constexpr (s >= 1 && (s - 1) % LOAD_A == 0 && l < NA)
-                mfma_acc_load<Cfg::BF16, 4 * s, (ca + RA - 1) % RA * Cfg::A_TILE_BYTES + l * 1024>(b[0][j], a[0][i], la.rsrc, to_a, la.voff[l]);
+                mfma_acc_load<Cfg::BF16, ONCE == 2, 4 * s, (ca + RA - 1) % RA * Cfg::A_TILE_BYTES + l * 1024>(b[0][j], a[0][i], la.rsrc, to_a, la.voff[l]);
             else
                 mfma_acc<Cfg::BF16, 4 * s>(b[0][j], a[0][i]);
             if constexpr (s == 2 + (NA - 1) * LOAD_A) la.next_base();
@@ -192,7 +197,7 @@ __device__ __forceinline__ void k_loop_wide(LA &la, LB &lb, const FA &fa, const 
                 __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (s >= BAR && (s - BAR) % LOAD_B == 0 && l < NB)
-                mfma_acc_load<Cfg::BF16, 4 * s + SET2, cb * Cfg::B_TILE_BYTES + l * 1024>(b[1][j], a[1][i], lb.rsrc, to_b, lb.voff[l]);
+                mfma_acc_load<Cfg::BF16, ONCE == 1, 4 * s + SET2, cb * Cfg::B_TILE_BYTES + l * 1024>(b[1][j], a[1][i], lb.rsrc, to_b, lb.voff[l]);
             else
                 mfma_acc<Cfg::BF16, 4 * s + SET2>(b[1][j], a[1][i]);
             if constexpr (s == BAR + 1 + (NB - 1) * LOAD_B) lb.next_base();

@@ -524,22 +524,25 @@ def test_every_tile_shape_in_every_kernel_family(monkeypatch):
 
 @pytest.mark.parametrize("la,lb", list(itertools.product(LAYOUTS, LAYOUTS)))
 def test_one_wave_per_simd(monkeypatch, la, lb):
-    """The 256x256 kernels with four waves: K loops shorter than their rings, ending in each pair of buffers, with and without a
+    """The kernels with four waves (256x256, 256x128 and deep 128x128 tiles): K loops shorter than their rings, ending in each pair of buffers, with and without a
     K tail (whose K tile comes first), tiles that hang over M, N or both by any remainder, every family and epilogue, several tiles
     per workgroup, K ranges that are short or empty; integer data, every entry exact."""
-    setenv(monkeypatch, "FG_FORCE_TILE", "5")
-    for n, K in enumerate((8, 64, 72, 128, 136, 192, 248, 256, 320, 384, 448, 520)):
-        M, N = (300 + n, 264 + 3 * n) if n % 2 else (513 - n, 258 + n)
-        say("four waves, %dx%dx%d, A=%d B=%d" % (M, N, K, la, lb))
-        run_gemm_case(M, N, K, la, lb, ld_layout=LAYOUTS[n // 2 % 2], ints=True, pad=8, poison=True, with_c=n % 3 != 2, bias_dim=(None, 0, 1)[n % 3],
-                      act=fg.FG_ACT_RELU if n % 4 == 1 else fg.FG_ACT_NONE, c_act=fg.FG_ACT_RELU if n % 4 == 2 else fg.FG_ACT_NONE, bf16=n % 5 == 4, beta=-2.0)
-        run_gemm_case(M, N, K, la, lb, ints=True, pad=8, poison=True, with_c=n % 2 == 0, bias_dim=(0, 1, None)[n % 3], cd16=True)
-    say("several tiles per workgroup"); run_gemm_case(5000, 4400, 200, la, lb, ints=True, beta=-2.0, samples=4000)
-    say("streamed C and D"); run_gemm_case(6150, 5900, 136, la, lb, ints=True, samples=4000, bias_dim=1)
-    for S, K in ((3, 1096), (5, 392), (7, 520)):
-        setenv(monkeypatch, "FG_FORCE_SPLIT", str(S))
-        say("K = %d split in %d" % (K, S)); run_gemm_case(300, 264, K, la, lb, ints=True, bias_dim=1, act=fg.FG_ACT_RELU)
-    delenv(monkeypatch, "FG_FORCE_SPLIT")
+    for tile in ("5", "1", "4"):
+        setenv(monkeypatch, "FG_FORCE_TILE", tile)
+        for n, K in enumerate((8, 64, 72, 128, 136, 192, 248, 256, 320, 384, 448, 520)):
+            M, N = (300 + n, 264 + 3 * n) if n % 2 else (513 - n, 258 + n)
+            say("tile %s with four waves, %dx%dx%d, A=%d B=%d" % (tile, M, N, K, la, lb))
+            run_gemm_case(M, N, K, la, lb, ld_layout=LAYOUTS[n // 2 % 2], ints=True, pad=8, poison=True, with_c=n % 3 != 2, bias_dim=(None, 0, 1)[n % 3],
+                          act=fg.FG_ACT_RELU if n % 4 == 1 else fg.FG_ACT_NONE, c_act=fg.FG_ACT_RELU if n % 4 == 2 else fg.FG_ACT_NONE, bf16=n % 5 == 4, beta=-2.0)
+            run_gemm_case(M, N, K, la, lb, ints=True, pad=8, poison=True, with_c=n % 2 == 0, bias_dim=(0, 1, None)[n % 3], cd16=True)
+        say("several tiles per workgroup"); run_gemm_case(5000, 4400, 200, la, lb, ints=True, beta=-2.0, samples=4000)
+        say("streamed C and D"); run_gemm_case(6150, 5900, 136, la, lb, ints=True, samples=4000, bias_dim=1)
+        for S, K in ((3, 1096), (5, 392), (7, 520)):
+            setenv(monkeypatch, "FG_FORCE_SPLIT", str(S))
+            say("K = %d split in %d" % (K, S)); run_gemm_case(300, 264, K, la, lb, ints=True, bias_dim=1, act=fg.FG_ACT_RELU)
+        delenv(monkeypatch, "FG_FORCE_SPLIT")
+    setenv(monkeypatch, "FG_FORCE_TILE", "9")
+    say("256x128 tile with eight waves"); run_gemm_case(300, 264, 200, la, lb, ints=True, pad=8, poison=True, bias_dim=0)
     delenv(monkeypatch, "FG_FORCE_TILE")
 
 
