@@ -1308,6 +1308,7 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
         p.cd_cached = q.cplx ? fg::keeps_complex_cd(2 * ab, 2 * cd, q.K, q.ilv, q.C != nullptr, q.ldc * elem, q.ldd * elem)
                              : fg::keeps_real_cd(ab, cd, q.C != nullptr, q.ldc * elem, q.ldd * elem);
     }
+    p.rotate = (p.tiles_m == 1 && q.b_kc) || (p.tiles_n == 1 && q.a_kc);
     p.once = p.tiles_m == 1 && fg::streams_once((uintptr_t)q.B, q.ldb, q.N * q.K * 2) ? 1
            : p.tiles_n == 1 && fg::streams_once((uintptr_t)q.A, q.lda, q.M * q.K * 2) ? 2 : 0;
     hipStream_t stream = (hipStream_t)hip_stream;

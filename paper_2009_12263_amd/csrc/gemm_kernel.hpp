@@ -65,6 +65,13 @@ struct GemmParams {
     // Kernels of TileCfg::ONCE: 1: B is fetched by one row of tiles only, 2: A by one column of tiles (set by the host): its
     // loads carry the streaming policy.
     int32_t once;
+    // Kernels of TileCfg::ROTATE: workgroups walk their K range in a circle, those of an XCD from a place of its own (set by the host
+    // where one row or column of tiles reads a whole K-contiguous operand).  Side by side from the start of K, all of them
+    // read, of rows that lie a power of two apart, the same few address bits at a time, and those choose the memory channel:
+    // 128x4096x16384 46.7 -> 41.7 us, 128x8192x8192 48.5 -> 45.2, 120x6000x8192 38.9 -> 36.9, with rows 16448 apart 43.1 -> 41.9.  A place for each
+    // XCD and not for each workgroup: those of an XCD share the small operand in its L2 (48.5 us otherwise).  An
+    // M/N-contiguous operand is read in long pieces already (42.1 -> 49).
+    int32_t rotate;
     // transforms on loaded elements (Section 4.3): C_ij := act(C_ij); with TileCfg::XFORM also
     // A_ik := half(A_ik + a_add), B_kj := half(B_kj + b_add), the addend as two packed halves
     int32_t c_act;
@@ -175,6 +182,7 @@ struct TileCfg {
     // narrow products, bound by reading their large operand (128x16384x12288 122 -> 113 us; where other tiles read the
     // operand again it costs: 8192x1024x4096 72 -> 76).  From which size on, and why: streams_once (cache_policy.hpp).
     static constexpr bool ONCE = (PLAIN_REAL && (KTURNS_ || STAGES_ == 4)) || (WIDE_ && STAGES_ == 4);
+    static constexpr bool ROTATE = WIDE_ && STAGES_ == 4;            // see GemmParams::rotate
     // SPREAD: the refill loads of a ring buffer are issued one at a time between the MFMAs of two
     // k-slices (A's part in the slice after the buffer is retired, B's part in the next one)
     // instead of as one burst: a burst from all waves queues up in the compute unit's single
@@ -1178,12 +1186,14 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
     // where its row index equals k, so a tile row m0 needs just the K tiles that meet
     // [m0, m0 + BM): the "skip iterations off the diagonal" predicate of Section 5.2.
     int kt0 = 0, nkt = 0;
+    [[maybe_unused]] int turn = 0;          // TileCfg::ROTATE: where in the K tiles the walk begins
 
     // start the loads of a tile: point the loaders at its panels and fill the ring
     auto start_tile = [&](int tile_id, int &m0, int &n0, int &split) {
         // parameters are re-read here rather than kept in registers across the K loop
         const Params tp = load_param<Params>(0);
         int tm, tn;
+        [[maybe_unused]] const int item = tile_id;
         split = 0;
         if constexpr (Cfg::SPLITK) {
             // which K range of a split product, and which tile of this launch's range
@@ -1224,27 +1234,34 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
             bp[0] += group_offset(tp.b_b, split);
         }
         if constexpr (Cfg::WIDE) {
-            // a last K tile that hangs over the end of K comes first (see wide_loop.hpp), the others follow in order
+            // a last K tile that hangs over the end of K comes first (see wide_loop.hpp), the others follow in order, or in a circle
             const int rest = tp.K - (nk - 1) * BK;
             const bool last_first = rest < BK && kt1 == nk && nkt > 0;
+            const int circle = nkt - (last_first ? 1 : 0);
+            if constexpr (Cfg::ROTATE) turn = tp.rotate && circle > 0 ? (item & 7) * 5 % circle : 0;
             const uint32_t to_a = (uint32_t)(uintptr_t)lds_a + (uint32_t)wave * (Cfg::A_SLABS * 1024u);
             const uint32_t to_b = (uint32_t)(uintptr_t)lds_b + (uint32_t)wave * (Cfg::B_SLABS * 1024u);
             wide_a.init(wave, lane, tp.a_rs, tp.a_ks);
             wide_b.init(wave, lane, tp.b_rs, tp.b_ks);
-            wide_a.at(ap[0], m0, tp.a_rs, tp.a_ks, tp.a_span, last_first ? nk - 1 : kt0, nkt > 0);
-            wide_b.at(bp[0], n0, tp.b_rs, tp.b_ks, tp.b_span, last_first ? nk - 1 : kt0, nkt > 0);
+            const int first = last_first ? nk - 1 : kt0 + turn;
+            wide_a.at(ap[0], m0, tp.a_rs, tp.a_ks, tp.a_span, first, nkt > 0, circle);
+            wide_b.at(bp[0], n0, tp.b_rs, tp.b_ks, tp.b_span, first, nkt > 0, circle);
             const bool a_once = Cfg::ONCE && tp.once == 2, b_once = Cfg::ONCE && tp.once == 1;
             wide_a.issue(to_a, last_first ? rest : BK, lane, a_once);
             wide_b.issue(to_b, last_first ? rest : BK, lane, b_once);
-            const int second = last_first ? kt0 : kt0 + 1;
-            wide_a.at(ap[0], m0, tp.a_rs, tp.a_ks, tp.a_span, second, nkt > 1);
-            wide_b.at(bp[0], n0, tp.b_rs, tp.b_ks, tp.b_span, second, nkt > 1);
+            const int second = last_first ? kt0 + turn : turn + 1 == circle ? kt0 : kt0 + turn + 1;
+            wide_a.at(ap[0], m0, tp.a_rs, tp.a_ks, tp.a_span, second, nkt > 1, circle);
+            wide_b.at(bp[0], n0, tp.b_rs, tp.b_ks, tp.b_span, second, nkt > 1, circle);
             // A's ring is filled but for one buffer, B's whole
 #pragma unroll
             for (int st = 1; st < S; ++st) {
-                if (st < Cfg::RING_A - 1) { wide_a.issue(to_a + st * Cfg::A_TILE_BYTES, BK, lane, a_once); wide_a.next_base(); wide_a.next_size(nkt - st - 1); }
+                if (st < Cfg::RING_A - 1) {
+                    wide_a.issue(to_a + st * Cfg::A_TILE_BYTES, BK, lane, a_once);
+                    wide_a.template next_base<Cfg::ROTATE>(nkt - st - 1, turn);
+                    wide_a.next_size(nkt - st - 1);
+                }
                 wide_b.issue(to_b + st * Cfg::B_TILE_BYTES, BK, lane, b_once);
-                wide_b.next_base();
+                wide_b.template next_base<Cfg::ROTATE>(nkt - st - 1, turn);
                 wide_b.next_size(nkt - st - 1);
             }
             return;
@@ -1316,9 +1333,9 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
                 wait_tile<(Cfg::RING_A - 2) * Cfg::A_SLABS + (S - 1) * Cfg::B_SLABS>();     // all but the first K tile may be in flight
                 __builtin_amdgcn_s_barrier();
                 const int once = Cfg::ONCE ? load_param<int32_t>(offsetof(GemmParams, once)) : 0;
-                if (Cfg::ONCE && once == 1) { if constexpr (Cfg::ONCE) k_loop_wide<Cfg, 1>(wide_a, wide_b, fa, fb, lds_a, lds_b, wave, nkt); }
-                else if (Cfg::ONCE && once == 2) { if constexpr (Cfg::ONCE) k_loop_wide<Cfg, 2>(wide_a, wide_b, fa, fb, lds_a, lds_b, wave, nkt); }
-                else k_loop_wide<Cfg, 0>(wide_a, wide_b, fa, fb, lds_a, lds_b, wave, nkt);
+                if (Cfg::ONCE && once == 1) { if constexpr (Cfg::ONCE) k_loop_wide<Cfg, 1>(wide_a, wide_b, fa, fb, lds_a, lds_b, wave, nkt, turn); }
+                else if (Cfg::ONCE && once == 2) { if constexpr (Cfg::ONCE) k_loop_wide<Cfg, 2>(wide_a, wide_b, fa, fb, lds_a, lds_b, wave, nkt, turn); }
+                else k_loop_wide<Cfg, 0>(wide_a, wide_b, fa, fb, lds_a, lds_b, wave, nkt, turn);
             } else {
             wait_tiles<L, S - 1>(nkt - 1);
             __builtin_amdgcn_s_barrier();

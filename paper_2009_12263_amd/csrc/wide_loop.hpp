@@ -83,14 +83,19 @@ struct WideLoader {
     u32x4 rsrc;
     uint32_t step, rest_lo;        // bytes per K tile; from the current K tile to the end of the operand
     int32_t rest_hi;
+    uint32_t turn_lo, turn_hi;     // from the last K tile of a range walked in a circle to the first: (1 - its length) steps
 
     // K tile kt is the next one; more: there is such a tile to load
-    __device__ __forceinline__ void at(const _Float16 *ptr, int row0, int64_t rs, int64_t ks, int64_t span, int kt, bool more) {
+    // (circle: length of the range, see GemmParams::rotate)
+    __device__ __forceinline__ void at(const _Float16 *ptr, int row0, int64_t rs, int64_t ks, int64_t span, int kt, bool more, int circle) {
         const int64_t first = (int64_t)row0 * rs + 64 * ks * kt, rest = (span - first) * 2;
         rest_lo = (uint32_t)rest;
         rest_hi = (int32_t)(rest >> 32);
         rsrc = make_rsrc(ptr + first, !more || rest < 0 ? 0u : rest > 0xfffffff0ll ? 0xfffffff0u : (uint32_t)rest);
         step = (uint32_t)(128 * ks);
+        const int64_t turn = (1 - circle) * (128 * ks);
+        turn_lo = (uint32_t)turn;
+        turn_hi = (uint32_t)(turn >> 32);
     }
     __device__ __forceinline__ void init(int wave, int lane, int64_t rs, int64_t ks) {
 #pragma unroll
@@ -112,19 +117,30 @@ struct WideLoader {
     // KC: which chunk of eight k of its row a lane fetches (every wave's slabs begin at a multiple of 16 rows, the swizzle's period)
     static_assert(!KC || SLABS % 2 == 0, "");
     __device__ __forceinline__ int chunk(int s, int lane) const { return (lane & 7) ^ kc_swz<64>(s * 8 + lane / 8); }
-    // Written out: the compiler would do the saturating subtraction on the vector unit and move the descriptor there.
-    __device__ __forceinline__ void next_base() {
+    // On to the next K tile, from the end of the range to its start if left == turn (ROTATE).  more: how many K tiles are still to be
+    // requested; without one the loads fetch nothing.  Written out: the compiler would do it on the vector unit and move the
+    // descriptor there.
+    template <bool ROTATE>
+    __device__ __forceinline__ void next_base(int left, int turn) {
         uint32_t lo = rsrc[0], hi = rsrc[1];
-        asm volatile("s_add_u32 %0, %0, %2\n\ts_addc_u32 %1, %1, 0" : "+s"(lo), "+s"(hi) : "s"(step) : "scc");
+        if constexpr (ROTATE) {
+            uint32_t by_lo, by_hi;
+            asm volatile("s_cmp_eq_u32 %6, %7\n\ts_cselect_b32 %2, %8, %10\n\ts_cselect_b32 %3, %9, 0\n\t"
+                         "s_add_u32 %0, %0, %2\n\ts_addc_u32 %1, %1, %3\n\ts_sub_u32 %4, %4, %2\n\ts_subb_u32 %5, %5, %3"
+                         : "+s"(lo), "+s"(hi), "=&s"(by_lo), "=&s"(by_hi), "+s"(rest_lo), "+s"(rest_hi)
+                         : "s"(left), "s"(turn), "s"(turn_lo), "s"(turn_hi), "s"(step) : "scc");
+        } else {
+            asm volatile("s_add_u32 %0, %0, %4\n\ts_addc_u32 %1, %1, 0\n\ts_sub_u32 %2, %2, %4\n\ts_subb_u32 %3, %3, 0"
+                         : "+s"(lo), "+s"(hi), "+s"(rest_lo), "+s"(rest_hi) : "s"(step) : "scc");
+        }
         rsrc[0] = lo;
         rsrc[1] = hi;
     }
-    // more: how many K tiles are still to be requested; without one the loads fetch nothing
     __device__ __forceinline__ void next_size(int more) {
         uint32_t n;
-        asm volatile("s_sub_u32 %0, %0, %3\n\ts_subb_u32 %1, %1, 0\n\ts_cmp_gt_i32 %1, 0\n\ts_cselect_b32 %2, -16, %0\n\t"
-                     "s_cmp_lt_i32 %1, 0\n\ts_cselect_b32 %2, 0, %2\n\ts_cmp_gt_i32 %4, 0\n\ts_cselect_b32 %2, %2, 0"
-                     : "+s"(rest_lo), "+s"(rest_hi), "=&s"(n) : "s"(step), "s"(more) : "scc");
+        asm volatile("s_cmp_gt_i32 %1, 0\n\ts_cselect_b32 %0, -16, %2\n\ts_cmp_lt_i32 %1, 0\n\ts_cselect_b32 %0, 0, %0\n\t"
+                     "s_cmp_gt_i32 %3, 0\n\ts_cselect_b32 %0, %0, 0"
+                     : "=&s"(n) : "s"(rest_hi), "s"(rest_lo), "s"(more) : "scc");
         rsrc[2] = n;
     }
     // all of a K tile at once, of which the first klim k exist (M/N-contiguous: what lies beyond K lies beyond the operand)
@@ -147,9 +163,10 @@ struct WideLoader {
 //                 barrier of tile kt - 1);
 //   second slice: after the barrier at slot BAR, which publishes tile kt + 1 and retires tile kt, the first
 //                 fragments of tile kt + 1 are read, and B's tile kt + RB is requested.
-// ONCE: GemmParams::once.
+// ONCE: GemmParams::once.  turn: where in its range of K the walk began (GemmParams::rotate).
 template <class Cfg, int ONCE, class LA, class LB, class FA, class FB>
-__device__ __forceinline__ void k_loop_wide(LA &la, LB &lb, const FA &fa, const FB &fb, FG_LDS char *lds_a, FG_LDS char *lds_b, int wave, int nkt) {
+__device__ __forceinline__ void k_loop_wide(LA &la, LB &lb, const FA &fa, const FB &fb, FG_LDS char *lds_a, FG_LDS char *lds_b, int wave, int nkt,
+                                            [[maybe_unused]] int turn) {
     constexpr int TI = Cfg::FI, TJ = Cfg::FJ, SLOTS = TI * TJ, NR = TI + TJ, RA = Cfg::RING_A, RB = Cfg::STAGES;
     constexpr int NA = LA::SLABS, NB = LB::SLABS, SET2 = Cfg::ACC_SETS == 2 ? 4 * SLOTS : 0;
     // where the reads and loads of a slice stand (every third slot a read, with 64 of them)
@@ -182,7 +199,7 @@ __device__ __forceinline__ void k_loop_wide(LA &la, LB &lb, const FA &fa, const 
                 mfma_acc_load<Cfg::BF16, ONCE == 2, 4 * s, (ca + RA - 1) % RA * Cfg::A_TILE_BYTES + l * 1024>(b[0][j], a[0][i], la.rsrc, to_a, la.voff[l]);
             else
                 mfma_acc<Cfg::BF16, 4 * s>(b[0][j], a[0][i]);
-            if constexpr (s == 2 + (NA - 1) * LOAD_A) la.next_base();
+            if constexpr (s == 2 + (NA - 1) * LOAD_A) la.template next_base<Cfg::ROTATE>(left, turn + RA);
             if constexpr (s == 3 + (NA - 1) * LOAD_A) la.next_size(left - RA);
 #pragma unroll
             for (int n = 0; n < NR; ++n)
@@ -200,7 +217,7 @@ __device__ __forceinline__ void k_loop_wide(LA &la, LB &lb, const FA &fa, const 
                 mfma_acc_load<Cfg::BF16, ONCE == 1, 4 * s + SET2, cb * Cfg::B_TILE_BYTES + l * 1024>(b[1][j], a[1][i], lb.rsrc, to_b, lb.voff[l]);
             else
                 mfma_acc<Cfg::BF16, 4 * s + SET2>(b[1][j], a[1][i]);
-            if constexpr (s == BAR + 1 + (NB - 1) * LOAD_B) lb.next_base();
+            if constexpr (s == BAR + 1 + (NB - 1) * LOAD_B) lb.template next_base<Cfg::ROTATE>(left, turn + RB + 1);
             if constexpr (s == BAR + 2 + (NB - 1) * LOAD_B) lb.next_size(left - RB - 1);
 #pragma unroll
             for (int n = 0; n < NR; ++n)
