@@ -663,8 +663,8 @@ struct Scratch {
     }
 };
 
-// p: the parameters of kernel k, whose size the runtime takes from the kernel.
-fg_status launch(const fg::KernelEntry &k, const fg::GemmParams &p, hipStream_t stream, int batches = 1) {
+// p: the parameters of kernel k, whose size the runtime takes from the kernel; the divisions by its tile counts are filled in.
+fg_status launch(const fg::KernelEntry &k, fg::GemmParams &p, hipStream_t stream, int batches = 1) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return fail(FG_ERR_LAUNCH, "no HIP device is current");
     int per_cu = 0;
@@ -673,7 +673,9 @@ fg_status launch(const fg::KernelEntry &k, const fg::GemmParams &p, hipStream_t 
     const int ntiles = p.tile_count > 0 ? p.tile_count * (p.splits > 1 ? p.splits : 1) : p.tiles_m * p.tiles_n * batches;
     const int resident = per_cu * kNumCU;
     dim3 grid((unsigned)(ntiles < resident ? ntiles : resident)), block((unsigned)k.threads);
-    void *args[] = {const_cast<fg::GemmParams *>(&p)};
+    p.by_count = p.splits > 1 ? fg::division_by((uint32_t)p.tile_count) : fg::division_to_zero();
+    p.by_group = fg::tile_group(p.tiles_m, p.tiles_n);
+    void *args[] = {&p};
     hipError_t e = hipLaunchKernel(k.fn, grid, block, args, (size_t)k.lds_bytes, stream);
     if (e != hipSuccess) { (void)hipGetLastError(); return fail(FG_ERR_LAUNCH, "launch of %s failed: %s", k.name, hipGetErrorString(e)); }
     return FG_OK;

@@ -28,6 +28,8 @@
 #include <type_traits>
 #include <utility>
 
+#include "tile_map.hpp"
+
 namespace fg {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -82,6 +84,7 @@ struct GemmParams {
     // BM x BN partial result (alpha = 1, no C, bias or activation) to slot w of the workspace D.
     int32_t tile_begin, tile_count;
     int32_t splits, split_kt;
+    Division by_count, by_group;      // by tile_count and by the tiles of a group of tile rows (tile_map.hpp)
     // Matrix, complex and dual kernels: C and D are accessed with the default cache policy instead of the streaming
     // one (set by the host, gemm_impl; see stream_policy).
     int32_t cd_cached;
@@ -642,26 +645,6 @@ struct FragReader {
     }
 };
 
-// ---- workgroup -> tile map ----------------------------------------------------------------------
-// Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Give every XCD a
-// contiguous run of tiles (the first tiles mod 8 XCDs one more than the others), and walk tiles in
-// groups of 4 tile rows so that the workgroups resident on one XCD at a time share A row panels and
-// B column panels.  (Tile counts that are not multiples of 8 used to be dealt out one by one:
-// 1 to 5 % slower on ragged products.)
-__device__ __forceinline__ void block_to_tile(int bid, int tiles_m, int tiles_n, int &tm, int &tn) {
-    int nb = tiles_m * tiles_n;
-    const int x = bid & 7, left = nb & 7;
-    int id = x * (nb >> 3) + (x < left ? x : left) + (bid >> 3);
-    int gm = tiles_m >= 4 ? 4 : tiles_m;
-    int per_group = gm * tiles_n;
-    int group = id / per_group;
-    int first_m = group * gm;
-    int rows = (tiles_m - first_m) < gm ? (tiles_m - first_m) : gm;
-    int within = id - group * per_group;
-    tm = first_m + within % rows;
-    tn = within / rows;
-}
-
 // ---- epilogue fused into the register -> global store -------------------------------------------
 // D = act(alpha*acc + beta*C + bias) (Sections 4.2.3, 4.2.5, 5.3).  Accumulator (i, j), register r
 // of lane l holds D[m][n] with m = 32 i + l % 32 and n = 32 j + 8 (r / 4) + 4 (l / 32) + r % 4: one
@@ -1178,9 +1161,12 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
     [[maybe_unused]] WideLoader<BN, Cfg::B_KC> wide_b;
     FragReader<BM, BK, Cfg::A_KC, TI, Cfg::M16> fa;
     FragReader<BN, BK, Cfg::B_KC, TJ, Cfg::M16> fb;
-    if constexpr (Cfg::STRIDED && !Cfg::A_KC) fa.init(wm * Cfg::WTM, lane, p.perm_z);
-    else fa.init(wm * Cfg::WTM, lane);
-    fb.init(wn * Cfg::WTN, lane);
+    auto init_readers = [&] {
+        if constexpr (Cfg::STRIDED && !Cfg::A_KC) fa.init(wm * Cfg::WTM, lane, p.perm_z);
+        else fa.init(wm * Cfg::WTM, lane);
+        fb.init(wn * Cfg::WTN, lane);
+    };
+    if constexpr (!Cfg::WIDE) init_readers();
 
     // K tiles [kt0, kt0 + nkt) of the current output tile.  A diagonal operand has entries only
     // where its row index equals k, so a tile row m0 needs just the K tiles that meet
@@ -1197,7 +1183,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
         split = 0;
         if constexpr (Cfg::SPLITK) {
             // which K range of a split product, and which tile of this launch's range
-            split = tile_id / tp.tile_count;
+            split = divided(tile_id, tp.by_count);
             tile_id = tp.tile_begin + (tile_id - split * tp.tile_count);
         }
         if constexpr (Cfg::STRIDED) {
@@ -1206,7 +1192,8 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
             split = tile_id / per_batch;
             tile_id -= split * per_batch;
         }
-        block_to_tile(tile_id, tp.tiles_m, tp.tiles_n, tm, tn);
+        if constexpr (Cfg::STRIDED) block_to_tile(tile_id, tp.tiles_m, tp.tiles_n, tm, tn);
+        else block_to_tile(tile_id, tp.tiles_m, tp.tiles_n, tp.by_group, tm, tn);
         m0 = tm * BM;
         n0 = tn * BN;
         const int nk = (tp.K + BK - 1) / BK;
@@ -1238,29 +1225,36 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
             const int rest = tp.K - (nk - 1) * BK;
             const bool last_first = rest < BK && kt1 == nk && nkt > 0;
             const int circle = nkt - (last_first ? 1 : 0);
-            if constexpr (Cfg::ROTATE) turn = tp.rotate && circle > 0 ? (item & 7) * 5 % circle : 0;
+            turn = 0;
+            if (Cfg::ROTATE && tp.rotate && circle > 0) turn = (item & 7) * 5 % circle;
             const uint32_t to_a = (uint32_t)(uintptr_t)lds_a + (uint32_t)wave * (Cfg::A_SLABS * 1024u);
             const uint32_t to_b = (uint32_t)(uintptr_t)lds_b + (uint32_t)wave * (Cfg::B_SLABS * 1024u);
             wide_a.init(wave, lane, tp.a_rs, tp.a_ks);
             wide_b.init(wave, lane, tp.b_rs, tp.b_ks);
-            const int first = last_first ? nk - 1 : kt0 + turn;
+            const int first = kt0 + turn;
+            const bool a_once = Cfg::ONCE && tp.once == 2, b_once = Cfg::ONCE && tp.once == 1;
             wide_a.at(ap[0], m0, tp.a_rs, tp.a_ks, tp.a_span, first, nkt > 0, circle);
             wide_b.at(bp[0], n0, tp.b_rs, tp.b_ks, tp.b_span, first, nkt > 0, circle);
-            const bool a_once = Cfg::ONCE && tp.once == 2, b_once = Cfg::ONCE && tp.once == 1;
-            wide_a.issue(to_a, last_first ? rest : BK, lane, a_once);
-            wide_b.issue(to_b, last_first ? rest : BK, lane, b_once);
-            const int second = last_first ? kt0 + turn : turn + 1 == circle ? kt0 : kt0 + turn + 1;
-            wide_a.at(ap[0], m0, tp.a_rs, tp.a_ks, tp.a_span, second, nkt > 1, circle);
-            wide_b.at(bp[0], n0, tp.b_rs, tp.b_ks, tp.b_span, second, nkt > 1, circle);
+            if (last_first) {
+                wide_a.moved(nk - 1 - first).issue_part(to_a, rest, lane);
+                wide_b.moved(nk - 1 - first).issue_part(to_b, rest, lane);
+            } else {
+                wide_a.issue(to_a, a_once);
+                wide_b.issue(to_b, b_once);
+                wide_a.template next_base<Cfg::ROTATE>(nkt - 1, turn);
+                wide_b.template next_base<Cfg::ROTATE>(nkt - 1, turn);
+            }
+            wide_a.next_size(nkt - 1);
+            wide_b.next_size(nkt - 1);
             // A's ring is filled but for one buffer, B's whole
 #pragma unroll
             for (int st = 1; st < S; ++st) {
                 if (st < Cfg::RING_A - 1) {
-                    wide_a.issue(to_a + st * Cfg::A_TILE_BYTES, BK, lane, a_once);
+                    wide_a.issue(to_a + st * Cfg::A_TILE_BYTES, a_once);
                     wide_a.template next_base<Cfg::ROTATE>(nkt - st - 1, turn);
                     wide_a.next_size(nkt - st - 1);
                 }
-                wide_b.issue(to_b + st * Cfg::B_TILE_BYTES, BK, lane, b_once);
+                wide_b.issue(to_b + st * Cfg::B_TILE_BYTES, b_once);
                 wide_b.template next_base<Cfg::ROTATE>(nkt - st - 1, turn);
                 wide_b.next_size(nkt - st - 1);
             }
@@ -1309,6 +1303,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS, Cfg::WAVES) void gemm_kernel(const t
     if (tile >= ntiles) return;
     int m0, n0, sp0;
     start_tile(tile, m0, n0, sp0);
+    if constexpr (Cfg::WIDE) init_readers();            // (while the first loads are on their way)
 
     while (true) {
         const int m_base = m0 + wm * Cfg::WTM, n_base = n0 + wn * Cfg::WTN;

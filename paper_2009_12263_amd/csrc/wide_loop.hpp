@@ -85,38 +85,46 @@ struct WideLoader {
     int32_t rest_hi;
     uint32_t turn_lo, turn_hi;     // from the last K tile of a range walked in a circle to the first: (1 - its length) steps
 
-    // K tile kt is the next one; more: there is such a tile to load
-    // (circle: length of the range, see GemmParams::rotate)
+    // K tile kt is the next one; more: there is such a tile to load (circle: length of the range, see GemmParams::rotate)
     __device__ __forceinline__ void at(const _Float16 *ptr, int row0, int64_t rs, int64_t ks, int64_t span, int kt, bool more, int circle) {
         const int64_t first = (int64_t)row0 * rs + 64 * ks * kt, rest = (span - first) * 2;
-        rest_lo = (uint32_t)rest;
-        rest_hi = (int32_t)(rest >> 32);
-        rsrc = make_rsrc(ptr + first, !more || rest < 0 ? 0u : rest > 0xfffffff0ll ? 0xfffffff0u : (uint32_t)rest);
         step = (uint32_t)(128 * ks);
-        const int64_t turn = (1 - circle) * (128 * ks);
+        point(ptr + first, rest, more);
+        const int64_t turn = -(int64_t)(circle - 1) * step;
         turn_lo = (uint32_t)turn;
         turn_hi = (uint32_t)(turn >> 32);
     }
-    __device__ __forceinline__ void init(int wave, int lane, int64_t rs, int64_t ks) {
-#pragma unroll
-        for (int s = 0; s < SLABS; ++s) {
-            const int slab = wave * SLABS + s;
-            int64_t off;
-            if constexpr (KC) {
-                const int r = slab * 8 + lane / 8;
-                off = (int64_t)r * rs + chunk(s, lane) * 8;
-            } else {
-                constexpr int CH = R / 8;
-                const int kr = slab * (64 / CH) + lane / CH;
-                const int c = (lane % CH) ^ (mc_swz<R>(kr) << 2) ^ (((kr >> 3) & 1) << 1);
-                off = (int64_t)kr * ks + c * 8;
-            }
-            voff[s] = (uint32_t)(off * 2);
-        }
+    __device__ __forceinline__ void point(const void *p, int64_t rest, bool more) {
+        rest_lo = (uint32_t)rest;
+        rest_hi = (int32_t)(rest >> 32);
+        rsrc = make_rsrc(p, !more || rest < 0 ? 0u : rest > 0xfffffff0ll ? 0xfffffff0u : (uint32_t)rest);
     }
-    // KC: which chunk of eight k of its row a lane fetches (every wave's slabs begin at a multiple of 16 rows, the swizzle's period)
-    static_assert(!KC || SLABS % 2 == 0, "");
-    __device__ __forceinline__ int chunk(int s, int lane) const { return (lane & 7) ^ kc_swz<64>(s * 8 + lane / 8); }
+    // the loader `tiles` K tiles further on (back, if negative), for one K tile
+    __device__ __forceinline__ WideLoader moved(int tiles) const {
+        WideLoader o = *this;
+        const int64_t by = (int64_t)tiles * (int64_t)step;
+        o.point((const char *)(((uint64_t)rsrc[1] << 32) | rsrc[0]) + by, (int64_t)(((uint64_t)(uint32_t)rest_hi << 32) | rest_lo) - by, true);
+        return o;
+    }
+    // Which bits of a slab's chunk index differ from slab 0's: the swizzles are XORs of bits of the LDS row, and a wave's slabs begin at
+    // a multiple of 16 rows.  So a lane's offset in slab s is that of slab 0 with these bits flipped, plus as many rows.
+    static constexpr int SLAB_ROWS = KC ? 8 : 512 / R;
+    static constexpr int flips(int s) {
+        const int row = s * SLAB_ROWS;
+        return KC ? (row / 2) & 7 : ((R == 64 ? (row >> 1) & 1 : row & 3) << 2) ^ (((row >> 3) & 1) << 1);
+    }
+    static_assert(SLABS * SLAB_ROWS % 16 == 0, "");
+    __device__ __forceinline__ void init(int wave, int lane, int64_t rs, int64_t ks) {
+        const uint32_t pitch = (uint32_t)(KC ? rs : ks) * 2u;             // bytes from one LDS row's source to the next
+        constexpr int CH = KC ? 8 : R / 8;
+        const int row = lane / CH;                                        // of the first slab's
+        const int c = KC ? (lane & 7) ^ (lane >> 4) : (lane % CH) ^ (mc_swz<R>(row) << 2) ^ (((row >> 3) & 1) << 1);
+        const uint32_t first = (uint32_t)(wave * (SLABS * SLAB_ROWS) + row) * pitch;
+#pragma unroll
+        for (int s = 0; s < SLABS; ++s) voff[s] = first + (uint32_t)((c ^ flips(s)) * 16) + (uint32_t)(s * SLAB_ROWS) * pitch;
+    }
+    // KC: which chunk of eight k of its row a lane fetches
+    __device__ __forceinline__ int chunk(int s, int lane) const { return (lane & 7) ^ (lane >> 4) ^ flips(s); }
     // On to the next K tile, from the end of the range to its start if left == turn (ROTATE).  more: how many K tiles are still to be
     // requested; without one the loads fetch nothing.  Written out: the compiler would do it on the vector unit and move the
     // descriptor there.
@@ -143,17 +151,19 @@ struct WideLoader {
                      : "=&s"(n) : "s"(rest_hi), "s"(rest_lo), "s"(more) : "scc");
         rsrc[2] = n;
     }
-    // all of a K tile at once, of which the first klim k exist (M/N-contiguous: what lies beyond K lies beyond the operand)
-    __device__ __forceinline__ void issue(uint32_t lds, int klim, int lane, bool stream) const {
+    // All of a K tile at once.  klim < 64: only the first klim k exist (M/N-contiguous: what lies beyond K lies beyond the operand).
+    template <bool STREAM>
+    __device__ __forceinline__ void issue(uint32_t lds) const {
 #pragma unroll
-        for (int s = 0; s < SLABS; ++s) {
-            uint32_t v = voff[s];
-            if constexpr (KC) {
-                if (chunk(s, lane) * 8 >= klim) v = kOutOfRange;
-            }
-            if (stream) load16_to_lds<true>(rsrc, lds + s * 1024u, v);
-            else load16_to_lds(rsrc, lds + s * 1024u, v);
-        }
+        for (int s = 0; s < SLABS; ++s) load16_to_lds<STREAM>(rsrc, lds + s * 1024u, voff[s]);
+    }
+    __device__ __forceinline__ void issue(uint32_t lds, bool stream) const {
+        if (stream) issue<true>(lds);
+        else issue<false>(lds);
+    }
+    __device__ __forceinline__ void issue_part(uint32_t lds, int klim, int lane) const {
+#pragma unroll
+        for (int s = 0; s < SLABS; ++s) load16_to_lds(rsrc, lds + s * 1024u, KC && chunk(s, lane) * 8 >= klim ? kOutOfRange : voff[s]);
     }
 };
 
@@ -172,6 +182,7 @@ __device__ __forceinline__ void k_loop_wide(LA &la, LB &lb, const FA &fa, const 
     // where the reads and loads of a slice stand (every third slot a read, with 64 of them)
     constexpr int BAR = SLOTS / 8, LOAD_A = SLOTS * 7 / 8 / NA, LOAD_B = SLOTS * 5 / 8 / NB;
     constexpr auto read_at = [](int n, int first) { return first + n * (SLOTS * 3 / 4) / NR; };
+    constexpr int READ_1 = BAR + 2, NEXT_A = 2 + (NA - 1) * LOAD_A, SIZE_A = NEXT_A + 1;
     // Loads still in flight when tile kt + 1 must have landed: those requested after the younger of A's and B's tile kt + 1.
     constexpr int YOUNGER = RA == RB ? (RA - 2) * (NA + NB) : (RB - 1) * NA + (RB - 2) * NB;
     static_assert((RA == RB || RA == RB + 1) && RB >= 2 && YOUNGER <= 63 && LOAD_A >= 1 && LOAD_B >= 1, "");
@@ -199,8 +210,8 @@ __device__ __forceinline__ void k_loop_wide(LA &la, LB &lb, const FA &fa, const 
                 mfma_acc_load<Cfg::BF16, ONCE == 2, 4 * s, (ca + RA - 1) % RA * Cfg::A_TILE_BYTES + l * 1024>(b[0][j], a[0][i], la.rsrc, to_a, la.voff[l]);
             else
                 mfma_acc<Cfg::BF16, 4 * s>(b[0][j], a[0][i]);
-            if constexpr (s == 2 + (NA - 1) * LOAD_A) la.template next_base<Cfg::ROTATE>(left, turn + RA);
-            if constexpr (s == 3 + (NA - 1) * LOAD_A) la.next_size(left - RA);
+            if constexpr (s == NEXT_A) la.template next_base<Cfg::ROTATE>(left, turn + RA);
+            if constexpr (s == SIZE_A) la.next_size(left - RA);
 #pragma unroll
             for (int n = 0; n < NR; ++n)
                 if (s == read_at(n, 0)) read(ic<1>{}, ta, tb, 1, n);
@@ -221,12 +232,12 @@ __device__ __forceinline__ void k_loop_wide(LA &la, LB &lb, const FA &fa, const 
             if constexpr (s == BAR + 2 + (NB - 1) * LOAD_B) lb.next_size(left - RB - 1);
 #pragma unroll
             for (int n = 0; n < NR; ++n)
-                if (s == read_at(n, BAR + 2)) read(ic<0>{}, na, nb, 0, n);
+                if (s == read_at(n, READ_1)) read(ic<0>{}, na, nb, 0, n);
             __builtin_amdgcn_sched_barrier(0);
         });
         return --left == 0;
     };
-    static_assert(BAR + 2 + (NB - 1) * LOAD_B < SLOTS && 3 + (NA - 1) * LOAD_A < SLOTS && read_at(NR - 1, BAR + 2) < SLOTS, "");
+    static_assert(BAR + 2 + (NB - 1) * LOAD_B < SLOTS && SIZE_A < SLOTS && read_at(NR - 1, READ_1) < SLOTS, "");
     // unrolled over both rings
     if constexpr (RA == 3 && RB == 2) {
         for (;;) {
@@ -254,7 +265,8 @@ __device__ __forceinline__ void k_loop_wide(LA &la, LB &lb, const FA &fa, const 
     }
     // the last matrix instructions write their results this long after they were issued; no load stays behind
     __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory", FG_ACC_ALL);
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    own_acc();
     __builtin_amdgcn_sched_barrier(0);
 }
 
