@@ -14,6 +14,7 @@
 //   * C is read and D written straight from/to the accumulator registers with the epilogue
 //     (alpha, beta, bias, activation; Sections 4.2.3, 4.2.5, 5.3) fused into that store, so
 //     the paper's stages 1, 2, 4 and 5 (C and D through shared memory) do not exist here.
+// The large tiles of real matrix products have a K loop and an epilogue of their own (TileCfg::WIDE, wide_loop.hpp).
 //
 // The layout building block of Section 4.2.2 is the pair (row offset, k offset) of each
 // operand: element (r, k) of a tile lives at base + rowoff(r) + koff(k).  For a plain matrix

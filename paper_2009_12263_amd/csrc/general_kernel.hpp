@@ -14,7 +14,9 @@
 // an odd element costs 52 cache accesses per wave, one at an even element 22, an aligned one 15
 // (TCP_TOTAL_CACHE_ACCESSES per vector load at 1531x1021x2003, where both operands start odd: 51.8; at 1530x1018x2003
 // and 1536x1024x2003, whose A starts even or aligned and whose B is odd: 36.9 and 33.2; 27.9, 26.2 and 23.7 us;
-// the direct-to-LDS kernels take 20 to 22 us for 1536x1024x2048).  1531x1021x2003: 449 us with the element-wise FP32
+// the direct-to-LDS kernels take 20 to 22 us for 1536x1024x2048).  What costs is the lines rather than the accesses: pieces that
+// lie across two lines are filled at 54 GB/s per unit, others at 104, and with fewer accesses (the fifth word of an odd piece from
+// the neighbouring lane) the product takes as long (28.9 us).  1531x1021x2003: 449 us with the element-wise FP32
 // kernel that served these operands before.
 // 4095x4097x4099: 244 us, 563 TFLOP/s.
 #pragma once

@@ -6,16 +6,16 @@
 namespace fg {
 
 // TILE_128x128_DEEP: the 128x128 tile with a ring of four buffers (128 KB of LDS, one workgroup per
-// compute unit) and eight waves of 32x64 (two per SIMD, so that one wave's LDS and barrier latencies
-// are covered by the other's matrix instructions), for outputs of at most one such tile per unit: a
-// lone workgroup turns a K tile over too fast for a two-buffer ring to cover the memory latency.
-// (2048^3: 26.5 us against 28.8 us with four waves of 64x64 and the same ring.)  Matrix and
-// contraction kernels; no 16x16x32 form.
+// compute unit), for outputs of at most one such tile per unit: a
+// lone workgroup turns a K tile over too fast for a two-buffer ring to cover the memory latency.  Matrix kernels of real products: four
+// waves of 64x64, one per SIMD, on 16x16x32 instructions (TileCfg::WIDE; 2048^3 bfloat16 22.4 us with eight waves of 32x64,
+// which cover each other's latencies, 19.5 so).  Addition on A and B and contractions: eight waves on 32x32x16.
 // TILE_256x128: matrix kernels with a ring of three buffers (144 KB).  With two, a K tile has one tile's time to
 // arrive in (0.9 us), which data that comes from memory takes: 8192x1024x4096 with three operand sets in turn 82.5 -> 71.5 us
-// (one set, from the memory-side cache: 69.0 -> 67.2), with C 93.5 -> 80.0, 3000^3 94.1 -> 88.4, 2329x3267x5104 127.8 -> 111;
-// a pass over C and D as before (8192^2 x 64: 97.3, 96.5).  A fourth does not fit.  Contractions measured 0 to 4 % slower
-// with three (extents 192, 72, 200 over 208: 11.3, 11.7) and keep two.
+// (one set, from the memory-side cache: 69.0 -> 67.2), with C 93.5 -> 80.0, 3000^3 94.1 -> 88.4, 2329x3267x5104 127.8 -> 111.  A
+// fourth does not fit.  One wave per SIMD (four of 128x64) in place of eight of 64x64: 71.5 -> 64.5.  Contractions have eight, measured 0
+// to 4 % slower with three buffers (extents 192, 72, 200 over 208: 11.3, 11.7) and keep two.
+// TILE_256x128_PASS: the same tile with eight waves and 32x32x16 instructions, for products of short K (select_kernel).
 // TILE_256x256, TILE_256x256_K32: 16x16x32 matrix instructions (TileCfg::M16), which on a chip at its power limit sustain a higher
 // rate on the same data.  Plain, BF16 and binary16-result matrix kernels: one kernel under both names, with one wave per SIMD
 // (TileCfg::WIDE, wide_loop.hpp; eight waves with 32x32x16 instructions, which outputs of fewer than 192 such tiles used to run on: 3000x3000x2000

@@ -16,7 +16,7 @@
 //     kt + 2 is requested in the first half of K tile kt and B's in the second, so that requests go out all the time
 //     and have between 1.0 and 1.9 K tiles to land (rings of two: 660 us, this one 552).
 // Together, 8192^3 with C on random operands: 893 -> 806 us (TN), 902 -> 815 (NN), 911 -> 814 (NT), 898 -> 815 (TT), against eight
-// waves with two buffers; 4096^3 with three operand sets in turn 134 -> 122.
+// waves with two buffers; 4096^3 with three operand sets in turn 134 -> 122 (with the planner's other changes 117).
 #pragma once
 
 namespace fg {
