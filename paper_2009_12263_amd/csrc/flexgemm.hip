@@ -52,7 +52,7 @@ constexpr int kNumCU = 256;   // MI355X: 8 XCDs x 32 compute units
 // Tuning overrides of the planner, from the environment: FG_FORCE_TILE=0..9 picks a tile shape (0..3
 // for the four tiles of the complex and dual kernels)
 // (5: the 256x256 tile with the k32 kernel where the family has one; 6, 7: the 64x64 tile with two K
-// groups and rings of two or four buffers, 8: the 64x128 tile with two, 9: the 256x128 tile with eight waves), FG_FORCE_SPLIT=n a split of K
+// groups and rings of two or four buffers, 8: the 64x128 tile with two, 9 and 10: the 256x128 and the deep 128x128 tile with eight waves), FG_FORCE_SPLIT=n a split of K
 // for every tile, FG_FORCE_TAIL=n a split of K for the tiles of the last round (1: never).  Read
 // when the library is loaded and again by fg_reload_tuning(), not on every call.
 std::atomic<int> g_force_tile{-1}, g_force_split{0}, g_force_tail{0};
@@ -133,9 +133,9 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 // rings), at most 42 % (6708x5150x96), and over 16 % only with K up to 224; held to what plan_product promises, 3.4 % (4.7 %).
 // Since then the rates of the two large tiles went up with their K loops (1 -> 1.12, 0.88 -> 0.95): of the 190 products 21 take another
 // plan, at 0.83 to 1.05 of the time, 0.94 on average.
-constexpr int kTileM[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64, 64, 256};
-constexpr int kTileN[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64, 128, 128};
-constexpr int kTilesPerCU[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1, 1, 1};
+constexpr int kTileM[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64, 64, 256, 128};
+constexpr int kTileN[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64, 128, 128, 128};
+constexpr int kTilesPerCU[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1, 1, 1, 1};
 constexpr int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}, kSplitCount = sizeof kSplits / sizeof *kSplits;
 struct Rates {
     double shared[fg::TILE_COUNT], alone[fg::TILE_COUNT];
@@ -146,19 +146,19 @@ struct Rates {
     double off_line[fg::TILE_COUNT];
     bool last_round;         // the last, partly filled round is priced with the workgroups that it has
     // K groups and sets of accumulators per group, which share a workgroup's sum over K (TileCfg::KG, ACC_SETS)
-    int groups[fg::TILE_COUNT] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1}, sets[fg::TILE_COUNT] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1};
+    int groups[fg::TILE_COUNT] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1}, sets[fg::TILE_COUNT] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1};
 };
 constexpr Rates kRates = {{1.12, 0.95, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
                           {1.12, 0.95, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
                           2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
                           {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true,
-                          {1, 1, 1, 1, 1, 1, 2, 2, 2, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1}};
+                          {1, 1, 1, 1, 1, 1, 2, 2, 2, 1, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1, 2}};
 // Addition on A and B, whose kernels of the large tiles have eight waves.
 constexpr Rates kRatesAdd = {{1, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
                              {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
                              2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
                              {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true,
-                             {1, 1, 1, 1, 1, 1, 2, 2, 2, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1}};
+                             {1, 1, 1, 1, 1, 1, 2, 2, 2, 1, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1, 2}};
 using fg::TileCfg;
 static_assert(FG_CFG_K32(128, 128, 64, 4, 2, 2, false, true, false, false)::ACC_SETS == 2 && FG_CFG(128, 128, 64, 4, 4, 2, false, true, false)::ACC_SETS == 2 && FG_CFG(256, 128, 64, 3, 4, 2, false, true, false)::ACC_SETS == 1 &&
               FG_CFG_KG(false, true, false, false, false, 64, 2, false)::ACC_SETS == 2 && FG_CFG_KG(false, true, false, false, false, 64, 4, true)::ACC_SETS == 2 &&
@@ -173,13 +173,13 @@ constexpr Rates kRates16 = {{1, 0.88, 0.732, 0.40, 0.74, 1, 0.373, 0.367, 0.384}
                             {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
                             2.07e-6, 26.8e9 * 4 / 3, 6.92e-6, 8.7e12,
                             {0, 0.022, 0, 0.0446, 0.0395, 0, 0, 0, 0}, true,
-                            {1, 1, 1, 1, 1, 1, 2, 2, 2, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1}};
+                            {1, 1, 1, 1, 1, 1, 2, 2, 2, 1, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1, 2}};
 // The rates that decided what a call needs scratch memory for before the 64x64 tile had K groups
 // (see plan_product).
 constexpr Rates kPromisedRates = {{1.0, 0.8, 0.73, 0.45, 0.57, 1.0, 0, 0, 0}, {1.0, 0.8, 0.43, 0.17, 0.57, 1.0, 0, 0, 0}, 2e-6, 25e9, 6e-6, 3e12, {}, false};
 // The rates of the planner before the larger rings (four K groups as tile 7, no 64x128 tile): see plan_product.
 constexpr Rates kFormerRates = {{1.0, 0.8, 0.73, 0.40, 0.645, 1.0, 0.35, 0.29, 0}, {1.0, 0.8, 0.43, 0.135, 0.645, 1.0, 0.27, 0.29, 0}, 1.6e-6, 27e9, 12.3e-6, 7.2e12,
-                                {0, 0, 0, 0, 0, 0, 0.1, 0.1, 0}, false, {1, 1, 1, 1, 1, 1, 2, 4, 1, 1}};
+                                {0, 0, 0, 0, 0, 0, 0.1, 0.1, 0}, false, {1, 1, 1, 1, 1, 1, 2, 4, 1, 1, 1}};
 // Contractions have neither K groups nor splits, which the rates above were fitted with: over 320 contractions those
 // picked the fastest tile to within 2.4 % on average and 44 % at most (192 x 960 rows and columns over 2560: 33.8 us
 // with the deep 128x128 tile, 23.6 with the 64x64 tile), these to within 0.5 % and 43 %, and no tile slower than
@@ -282,6 +282,7 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
         if (t == fg::TILE_256x256_K32) { t = fg::TILE_256x256; force_k32 = true; }
         else forced_plain = (t == fg::TILE_256x256);
         if (t == fg::TILE_256x128_PASS) t = fg::TILE_256x128;
+        if (t == fg::TILE_128x128_PASS) t = fg::TILE_128x128_DEEP;
         if (t >= 0 && t < fg::TILE_COUNT) force_tile = t;
     }
     const int32_t nk = ranges.nk;
@@ -510,6 +511,11 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
         // C 14.9 us with four, 12.9 with eight, 8192x1024x128 without 11.3 and 10.7, at K = 512 18.6 and 17.7, 16.0 and 17.1; at 768
         // 21.0 and 20.9, 18.9 and 20.7; binary16 results with C 19.3 and 18.3, 22.1 and 21.9; 1000: 23.7, 24.2, 25.4, 26.4).
         if (tile == fg::TILE_256x128 && (forced == fg::TILE_256x128_PASS || (forced < 0 && q.K <= (q.C ? 768 : 512)))) tile = fg::TILE_256x128_PASS;
+        // The same on the deep 128x128 tile (2048^2 x 128 with C 11.8 us with four waves, 10.4 with eight, 960x4096x256 without 9.5 and 8.7, 1304x2200x512
+        // 13.0 and 12.4, 2000^2 x 760 17.1 and 16.6; 768: 15.8 and 16.0, 1536x2048x1024 12.8 and 14.0); a little longer where a last K tile
+        // hangs over, which four waves load first and by itself (1536x2048x1000: 15.9 and 15.4, 16.1 and 16.0; 2000^2 x 2024: 28.1 and 29.3).
+        const bool short_k = q.K <= 768 || (q.K < 1024 && q.K % 64 != 0);
+        if (tile == fg::TILE_128x128_DEEP && (forced == fg::TILE_128x128_PASS || (forced < 0 && short_k && plan.splits == 1))) tile = fg::TILE_128x128_PASS;
     }
     if (plan_out) { *plan_out = plan; plan_out->tile = tile; }
     if (q.a_diag) return &fg::kernel_table_diag()[tile * 4 + (q.b_kc ? 0 : 1)];

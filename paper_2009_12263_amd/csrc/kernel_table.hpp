@@ -15,7 +15,8 @@ namespace fg {
 // (one set, from the memory-side cache: 69.0 -> 67.2), with C 93.5 -> 80.0, 3000^3 94.1 -> 88.4, 2329x3267x5104 127.8 -> 111.  A
 // fourth does not fit.  One wave per SIMD (four of 128x64) in place of eight of 64x64: 71.5 -> 64.5.  Contractions have eight, measured 0
 // to 4 % slower with three buffers (extents 192, 72, 200 over 208: 11.3, 11.7) and keep two.
-// TILE_256x128_PASS: the same tile with eight waves and 32x32x16 instructions, for products of short K (select_kernel).
+// TILE_256x128_PASS, TILE_128x128_PASS: the 256x128 and the deep 128x128 tile with eight waves and 32x32x16 instructions, for products of short K
+// (select_kernel).
 // TILE_256x256, TILE_256x256_K32: 16x16x32 matrix instructions (TileCfg::M16), which on a chip at its power limit sustain a higher
 // rate on the same data.  Plain, BF16 and binary16-result matrix kernels: one kernel under both names, with one wave per SIMD
 // (TileCfg::WIDE, wide_loop.hpp; eight waves with 32x32x16 instructions, which outputs of fewer than 192 such tiles used to run on: 3000x3000x2000
@@ -35,7 +36,7 @@ namespace fg {
 // All three: matrix kernels of real products.
 enum TileId { TILE_256x256 = 0, TILE_256x128 = 1, TILE_128x128 = 2, TILE_64x64 = 3, TILE_128x128_DEEP = 4,
               TILE_256x256_K32 = 5, TILE_64x64_KG2 = 6, TILE_64x64_KG2_DEEP = 7, TILE_64x128_KG2 = 8,
-              TILE_256x128_PASS = 9, TILE_COUNT = 10, DIAG_TILE_COUNT = 4 };
+              TILE_256x128_PASS = 9, TILE_128x128_PASS = 10, TILE_COUNT = 11, DIAG_TILE_COUNT = 4 };
 
 struct KernelEntry {
     const void *fn;           // void (*)(const GemmParams), contractions: (const ContractParams)
@@ -148,6 +149,7 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
             FG_ENTRY_KG(AKC, BKC, true, false, false, 64, 4, true, "gemm_bf16_" TAG "_64x64x64"),            \
             FG_ENTRY_KG(AKC, BKC, true, false, false, 128, 3, true, "gemm_bf16_" TAG "_64x128x64"), \
             FG_ENTRY_BF16(256, 128, 64, 3, 4, 2, AKC, BKC, "gemm_bf16_" TAG "_256x128x64"),        \
+            FG_ENTRY_BF16(128, 128, 64, 4, 4, 2, AKC, BKC, "gemm_bf16_" TAG "_128x128x64_deep"),   \
         };                                                                                         \
         return t;                                                                                  \
     }
@@ -171,6 +173,7 @@ inline int entry_index(int tile, int variant) { return tile * VARIANT_COUNT + va
             FG_ENTRY_KG(AKC, BKC, false, false, true, 64, 4, true, "gemm_h16_" TAG "_64x64x64"),             \
             FG_ENTRY_KG(AKC, BKC, false, false, true, 128, 3, true, "gemm_h16_" TAG "_64x128x64"), \
             FG_ENTRY_H16(256, 128, 64, 3, 4, 2, AKC, BKC, "gemm_h16_" TAG "_256x128x64"),          \
+            FG_ENTRY_H16(128, 128, 64, 4, 4, 2, AKC, BKC, "gemm_h16_" TAG "_128x128x64_deep"),     \
         };                                                                                         \
         return t;                                                                                  \
     }
@@ -206,7 +209,7 @@ inline KernelEntry xf_k32_entry(const char *name) {
             FG_ENTRY_KG(AKC, BKC, false, true, false, 64, 2, false, "gemm_abadd_" TAG "_64x64x64"),           \
             FG_ENTRY_KG(AKC, BKC, false, true, false, 64, 4, true, "gemm_abadd_" TAG "_64x64x64"),           \
             FG_ENTRY_KG(AKC, BKC, false, true, false, 128, 3, true, "gemm_abadd_" TAG "_64x128x64"), \
-            FG_EMPTY_ENTRY,                                                                        \
+            FG_EMPTY_ENTRY, FG_EMPTY_ENTRY,                                                        \
         };                                                                                         \
         return t;                                                                                  \
     }
@@ -248,6 +251,7 @@ inline KernelEntry xf_k32_entry(const char *name) {
             FG_ENTRY_KG(AKC, BKC, false, false, false, 64, 4, true, "gemm_" TAG "_64x64x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
             FG_ENTRY_KG(AKC, BKC, false, false, false, 128, 3, true, "gemm_" TAG "_64x128x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
             FG_ENTRY(256, 128, 64, 3, 4, 2, AKC, BKC, false, "gemm_" TAG "_256x128x64"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
+            FG_ENTRY(128, 128, 64, 4, 4, 2, AKC, BKC, false, "gemm_" TAG "_128x128x64_deep"), FG_EMPTY_ENTRY, FG_EMPTY_ENTRY, \
         };                                                                                         \
         return t;                                                                                  \
     }

@@ -43,7 +43,7 @@ FG_HOST_DEVICE int divided(int x, Division d) { return (int)((uint32_t)(((uint64
 
 // The same tile with the division by the tiles of a group prepared by the host (tile_group): integer divisions on the scalar unit
 // are a hundred instructions in front of a workgroup's first load.  Bfloat16 2048^3 21.4 -> 20.3 us with the loader's shorter start
-// (WideLoader); 256^3 in replayed graphs 4.42 -> 4.33.  Contractions, which divide by their modes' extents all the same, measured 1 to 5 % slower with it
+// (WideLoader); 1024^3 TT 8.39 -> 8.17; 256^3 in replayed graphs 4.42 -> 4.24 (4.33 with a branch for a divisor of 1).  Contractions, which divide by their modes' extents all the same, measured 1 to 5 % slower with it
 // (aebf,dfce->abcd with a = c = 24, b = f = 32, d = e = 8: 19.2, 20.2 us) and keep the plain form.
 inline Division tile_group(int tiles_m, int tiles_n) { return tiles_m <= 4 ? division_to_zero() : division_by((uint32_t)(4 * tiles_n)); }
 FG_HOST_DEVICE void block_to_tile(int bid, int tiles_m, int tiles_n, Division per_group, int &tm, int &tn) {

@@ -541,8 +541,10 @@ def test_one_wave_per_simd(monkeypatch, la, lb):
             setenv(monkeypatch, "FG_FORCE_SPLIT", str(S))
             say("K = %d split in %d" % (K, S)); run_gemm_case(300, 264, K, la, lb, ints=True, bias_dim=1, act=fg.FG_ACT_RELU)
         delenv(monkeypatch, "FG_FORCE_SPLIT")
-    setenv(monkeypatch, "FG_FORCE_TILE", "9")
-    say("256x128 tile with eight waves"); run_gemm_case(300, 264, 200, la, lb, ints=True, pad=8, poison=True, bias_dim=0)
+    for tile in ("9", "10"):
+        setenv(monkeypatch, "FG_FORCE_TILE", tile)
+        say("tile %s with eight waves" % tile); run_gemm_case(300, 264, 200, la, lb, ints=True, pad=8, poison=True, bias_dim=0)
+        say("bfloat16, binary16 results"); run_gemm_case(300, 264, 328, la, lb, ints=True, bf16=True); run_gemm_case(300, 264, 328, la, lb, ints=True, cd16=True)
     delenv(monkeypatch, "FG_FORCE_TILE")
 
 
