@@ -29,6 +29,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "operand_window.hpp"
 #include "tile_map.hpp"
 
 namespace fg {
@@ -269,8 +270,6 @@ __device__ __forceinline__ u32x4 make_rsrc(const void *p, uint32_t bytes = 0x7ff
     r[3] = 0x00020000u;                     // 32-bit data format, no swizzle
     return r;
 }
-
-constexpr uint32_t kOutOfRange = 0x80000000u;   // a byte offset no descriptor of ours reaches
 
 // 64 lanes x 16 bytes from global memory straight into LDS: lane l's 16 bytes land at
 // lds_addr + 16*l.  lds_addr is wave-uniform (it goes to M0).  The load is tracked by vmcnt only;

@@ -97,7 +97,7 @@ struct WideLoader {
     __device__ __forceinline__ void point(const void *p, int64_t rest, bool more) {
         rest_lo = (uint32_t)rest;
         rest_hi = (int32_t)(rest >> 32);
-        rsrc = make_rsrc(p, !more || rest < 0 ? 0u : rest > 0xfffffff0ll ? 0xfffffff0u : (uint32_t)rest);
+        rsrc = make_rsrc(p, more ? window_bytes(rest) : 0u);
     }
     // the loader `tiles` K tiles further on (back, if negative), for one K tile
     __device__ __forceinline__ WideLoader moved(int tiles) const {
@@ -126,8 +126,8 @@ struct WideLoader {
     // KC: which chunk of eight k of its row a lane fetches
     __device__ __forceinline__ int chunk(int s, int lane) const { return (lane & 7) ^ (lane >> 4) ^ flips(s); }
     // On to the next K tile, from the end of the range to its start if left == turn (ROTATE).  more: how many K tiles are still to be
-    // requested; without one the loads fetch nothing.  Written out: the compiler would do it on the vector unit and move the
-    // descriptor there.
+    // requested; without one the loads fetch nothing.  No lane is masked here, so the size may be larger than that of
+    // window_bytes.  Written out: the compiler would do it on the vector unit and move the descriptor there.
     template <bool ROTATE>
     __device__ __forceinline__ void next_base(int left, int turn) {
         uint32_t lo = rsrc[0], hi = rsrc[1];

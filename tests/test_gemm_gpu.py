@@ -604,6 +604,40 @@ def test_operands_larger_than_2_gib():
     torch.cuda.empty_cache()
 
 
+def test_last_k_tile_of_operands_larger_than_2_gib(monkeypatch):
+    """K-contiguous operands of more than 2 GiB whose last K tile hangs over the end of K: the lanes beyond K load zeros and not what lies
+    2 GiB further on (the offset of a masked lane).  Ones, so that every sum is exact; then one such operand with a row of
+    infinities where the masked lanes of the first panel would read: times the other operand's zeros they would be NaN there."""
+    def ones(rows, K):
+        return torch.ones(rows * K, dtype=torch.float16, device="cuda")
+
+    def product(M, N, K, a, b):
+        D = torch.full((M * N,), float("nan"), device="cuda")
+        fg.fg_gemm(M, N, K, 1.0, fg.Matrix(a, fg.FG_ROW, K), fg.Matrix(b, fg.FG_COL, K), 0.0, None, fg.Matrix(D, fg.FG_COL, M))
+        torch.cuda.synchronize()
+        return D.view(N, M)
+    n, K = 320, 4194248
+    say("both 2.5 GiB: %dx%dx%d" % (n, n, K)); assert "256x256" in fg.fg_gemm_plan(n, n, K, fg.FG_ROW, fg.FG_COL)
+    assert (product(n, n, K, ones(n, K), ones(n, K)) == K).all()
+    torch.cuda.empty_cache()
+    M, N, K = 160000, 256, 8200
+    at = (1 << 30) + K // 64 * 64                # element that a masked lane of the first panel would begin at
+    big, small = ones(M, K), ones(N, K)
+    big.view(M, K)[at // K] = float("inf")
+    for tile in ("0", "1", "4"):
+        for flip in (False, True):
+            setenv(monkeypatch, "FG_FORCE_TILE", tile)
+            say("one of 2.4 GiB, tile %s, %s" % (tile, "B" if flip else "A"))
+            D = product(N, M, K, small, big).T if flip else product(M, N, K, big, small)
+            assert torch.isinf(D[:, at // K]).all()
+            D[:, at // K] = K
+            assert (D == K).all()
+            del D
+    delenv(monkeypatch, "FG_FORCE_TILE")
+    del big, small
+    torch.cuda.empty_cache()
+
+
 def test_split_k_results_do_not_depend_on_arrival_order(monkeypatch):
     """The K ranges of a tile are computed by workgroups on different XCDs and added up from the
     workspace.  Many launches in a row on fresh data (a stale read would return a previous
