@@ -308,7 +308,10 @@ __device__ __forceinline__ void epilogue_wide(const GemmParams &p, int m_base, i
     // The larger of a value and the floor: the instruction gives the other operand for a NaN, so that 0 makes it the ReLU of act_clamp (a NaN
     // becomes 0) and NaN lets everything through.  One instruction in place of three.
     const float floor_v = p.act == 1 ? 0.f : __builtin_nanf(""), floor_c = p.c_act == 1 ? 0.f : __builtin_nanf("");
-    auto act = [](float v, float floor) { float y; asm("v_max_f32 %0, %1, %2" : "=v"(y) : "v"(v), "v"(floor)); return y; };
+    // (Not as assembly: the compiler would not know it for a vector instruction and leave out the two wait states that a lane exchange of
+    // its result needs, as with binary16 results below.)
+    auto act = [](float v, float floor) { return __builtin_fmaxf(v, floor); };
+    auto act_c = [](float v, float floor) { float y; asm("v_max_f32 %0, %1, %2" : "=v"(y) : "v"(v), "v"(floor)); return y; };
     const int ldc_b = (int)p.ldc * ES, ldd_b = (int)p.ldd * ES;
     const char *Cb = (const char *)p.C, *Db = (const char *)p.D;
     __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
@@ -380,8 +383,8 @@ __device__ __forceinline__ void epilogue_wide(const GemmParams &p, int m_base, i
                     if constexpr (HAS_C) {
                         float c0 = cv[b % (AHEAD + 1)][2 * r], c1 = cv[b % (AHEAD + 1)][2 * r + 1];
                         exchange(c0, c1);
-                        v0 += p.beta * act(c0, floor_c);
-                        v1 += p.beta * act(c1, floor_c);
+                        v0 += p.beta * act_c(c0, floor_c);
+                        v1 += p.beta * act_c(c1, floor_c);
                     }
                     v0 = act(v0, floor_v);
                     v1 = act(v1, floor_v);
@@ -395,7 +398,7 @@ __device__ __forceinline__ void epilogue_wide(const GemmParams &p, int m_base, i
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     float v = p.alpha * acc[r] + (bias_n_on ? bn[r] : bias_m[i]);
-                    if constexpr (HAS_C) v += p.beta * act(cv[b % (AHEAD + 1)][r], floor_c);
+                    if constexpr (HAS_C) v += p.beta * act_c(cv[b % (AHEAD + 1)][r], floor_c);
                     y[r] = act(v, floor_v);
                 }
             }
