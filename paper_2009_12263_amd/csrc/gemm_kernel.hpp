@@ -277,17 +277,20 @@ __device__ __forceinline__ u32x4 make_rsrc(const void *p, uint32_t bytes = 0x7ff
 // publishes a tile.  (Written as assembly because the compiler, not knowing which LDS bytes a
 // direct load writes, otherwise drains every outstanding load before any LDS read, which would
 // serialise the prefetch of later tiles with the product of the current one.)
-template <bool STREAM = false>
+// SPILLS: the kernel keeps more in scalar registers than there are, so a descriptor may come back from a spill (v_readlane) right in
+// front of the load.  A vector memory instruction needs five wait states behind a vector instruction that writes a scalar register it
+// reads, and the compiler, which does not see one in assembly, leaves them out.
+template <bool STREAM = false, bool SPILLS = false>
 __device__ __forceinline__ void load16_to_lds(u32x4 rsrc, uint32_t lds_addr, uint32_t voff) {
     if constexpr (STREAM)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop %3\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
                      :
-                     : "s"(lds_addr), "v"(voff), "s"(rsrc)
+                     : "s"(lds_addr), "v"(voff), "s"(rsrc), "n"(SPILLS ? 3 : 0)
                      : "memory", "m0");
     else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop %3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                      :
-                     : "s"(lds_addr), "v"(voff), "s"(rsrc)
+                     : "s"(lds_addr), "v"(voff), "s"(rsrc), "n"(SPILLS ? 3 : 0)
                      : "memory", "m0");
 }
 
@@ -479,7 +482,7 @@ struct TileLoader {
             // multiple of BK the last step of each pass hangs over it: those k are zero-filled
             if (kdigit[0] + kchunk[s] >= kext[0]) v = kOutOfRange;
         }
-        load16_to_lds<STREAM>(rsrc_cur, dst, v);
+        load16_to_lds<STREAM, STRIDED>(rsrc_cur, dst, v);
     }
     __device__ __forceinline__ void advance() {
         if constexpr (!STRIDED) {

@@ -88,3 +88,21 @@ def test_lane_exchanges_wait_for_vector_results(kernels):
         bad = _too_close(code, writes, reads, 2)
         assert not bad, "%s: %d lane exchanges right behind the result they read, first %s" % (name, len(bad), bad[0])
     assert seen > 10000
+
+
+def test_loads_wait_for_descriptors_that_vector_instructions_write(kernels):
+    """A vector memory instruction needs five wait states after a vector instruction (the reload of a spill) that writes a scalar
+    register it reads."""
+    def writes(op, rest):
+        return {r for r in _registers(rest.split(",")[0]) if r[0] == "s"} if op.startswith("v_") else set()
+
+    def reads(op, rest):
+        if not op.startswith(("buffer_", "global_", "flat_", "scratch_")):
+            return set()
+        return {r for operand in rest.split(",") for r in _registers(operand.split()[0]) if r[0] == "s"}
+    seen = 0
+    for name, code in kernels.items():
+        seen += sum(op.startswith("buffer_") and rest.endswith(" lds") for op, rest in code)
+        bad = _too_close(code, writes, reads, 5)
+        assert not bad, "%s: %d accesses right behind the reload of a register they read, first %s" % (name, len(bad), bad[0])
+    assert seen > 10000
