@@ -33,7 +33,8 @@ __device__ __forceinline__ void static_for(F &&f) { static_for_seq(f, std::make_
 // The accumulators live in accumulation registers that are named in the assembly and known to nobody else: as variables the
 // compiler copied them about between the K tiles and spilled (564 registers).  Fragment (i, j) of set s holds registers
 // 4 ((s FI + i) FJ + j) .. + 3.  own_acc() marks all of them as written, so that the compiler keeps nothing of its
-// own in one across it.
+// own in one across it.  That leaves what lives between two of them; that nothing but this assembly touches an accumulation register is
+// checked in the compiled kernels (tests/test_compiled_kernels.py).
 #define FG_ACC10(d) "a" #d "0", "a" #d "1", "a" #d "2", "a" #d "3", "a" #d "4", "a" #d "5", "a" #d "6", "a" #d "7", "a" #d "8", "a" #d "9"
 #define FG_ACC_ALL                                                                                                                      \
     "a0", "a1", "a2", "a3", "a4", "a5", "a6", "a7", "a8", "a9", FG_ACC10(1), FG_ACC10(2), FG_ACC10(3), FG_ACC10(4), FG_ACC10(5),        \
@@ -303,6 +304,7 @@ __device__ __forceinline__ void epilogue_wide(const GemmParams &p, int m_base, i
     constexpr int kPolicy = CACHED ? 0 : stream_policy<Cfg>();
     constexpr bool H = Cfg::CD16;
     constexpr int ES = H ? 2 : 4, NB = Cfg::TI * Cfg::TJ, AHEAD = CACHED ? 2 : 3;
+    own_acc();
     const int lm = lane & 31, lh = lane >> 5;
     const bool bias_m_on = p.bias && p.bias_dim == 0, bias_n_on = p.bias && p.bias_dim != 0;
     // The larger of a value and the floor: the instruction gives the other operand for a NaN, so that 0 makes it the ReLU of act_clamp (a NaN
@@ -406,6 +408,7 @@ __device__ __forceinline__ void epilogue_wide(const GemmParams &p, int m_base, i
             for (int e = 0; e < 16; ++e)
                 store_cd<H, kPolicy>(y[e], rd, place(voff_d, b, e) + row_of(b) * ES, col_of(b, e) * ldd_b);
             __builtin_amdgcn_sched_barrier(0);
+            own_acc();
         });
     };
     if (m_base + Cfg::WTM <= p.M && n_base + Cfg::WTN <= p.N) run(std::false_type{});

@@ -106,3 +106,27 @@ def test_loads_wait_for_descriptors_that_vector_instructions_write(kernels):
         bad = _too_close(code, writes, reads, 5)
         assert not bad, "%s: %d accesses right behind the reload of a register they read, first %s" % (name, len(bad), bad[0])
     assert seen > 10000
+
+
+def test_accumulators_belong_to_the_assembly(kernels):
+    """The kernels with four waves keep their results in accumulation registers that the compiler knows nothing of (csrc/wide_loop.hpp): it
+    must have no use of its own for one.  All that touches them is their clearing, once each, the matrix instructions, which add
+    to what they hold, and the reads of the epilogues."""
+    wide = {name: code for name, code in kernels.items() if "11gemm_kernelI" in name and "Lb1EEEEEvNT_" in name}       # TileCfg::WIDE
+    assert len(wide) == 36                     # three tiles, four layouts; FP16, bfloat16 and binary16 results
+    for name, code in wide.items():
+        cleared, read = [], set()
+        for op, rest in code:
+            operands = [o.strip() for o in rest.split(",")]
+            touched = [o for o in operands if any(r[0] == "a" for r in _registers(o.split()[0] if o else o))]
+            if not touched:
+                continue
+            if op == "v_accvgpr_write_b32":
+                assert operands[1] == "0", (name, op, rest)
+                cleared += _registers(operands[0])
+            elif op == "v_accvgpr_read_b32":
+                read |= _registers(operands[1])
+            else:
+                assert op.startswith("v_mfma_f32_16x16x32_") and touched == [operands[0], operands[3]] and operands[0] == operands[3], (name, op, rest)
+        assert sorted(cleared) == [("a", i) for i in range(len(cleared))] and len(cleared) in (128, 256), name
+        assert read == set(cleared), name
