@@ -308,12 +308,10 @@ __device__ __forceinline__ void epilogue_wide(const GemmParams &p, int m_base, i
     const int lm = lane & 31, lh = lane >> 5;
     const bool bias_m_on = p.bias && p.bias_dim == 0, bias_n_on = p.bias && p.bias_dim != 0;
     // The larger of a value and the floor: the instruction gives the other operand for a NaN, so that 0 makes it the ReLU of act_clamp (a NaN
-    // becomes 0) and NaN lets everything through.  One instruction in place of three.
-    const float floor_v = p.act == 1 ? 0.f : __builtin_nanf(""), floor_c = p.c_act == 1 ? 0.f : __builtin_nanf("");
-    // (Not as assembly: the compiler would not know it for a vector instruction and leave out the two wait states that a lane exchange of
-    // its result needs, as with binary16 results below.)
+    // becomes 0) and NaN lets everything through.  One instruction in place of three.  Not as assembly: the compiler would not know it for a
+    // vector instruction and leave out the two wait states that a lane exchange of its result needs.
+    const float floor_v = p.act == 1 ? 0.f : __builtin_nanf("");
     auto act = [](float v, float floor) { return __builtin_fmaxf(v, floor); };
-    auto act_c = [](float v, float floor) { float y; asm("v_max_f32 %0, %1, %2" : "=v"(y) : "v"(v), "v"(floor)); return y; };
     const int ldc_b = (int)p.ldc * ES, ldd_b = (int)p.ldd * ES;
     const char *Cb = (const char *)p.C, *Db = (const char *)p.D;
     __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
@@ -374,6 +372,13 @@ __device__ __forceinline__ void epilogue_wide(const GemmParams &p, int m_base, i
                     bn[r] = p.bias[n_base + Cfg::ACC_LH * lh + (EDGE && col > n_last ? (n_last < 0 ? -(n_base + Cfg::ACC_LH * lh) : n_last) : col)];
                 }
             }
+            // The activation of C is a comparison: a loaded value can be a signalling NaN, and the larger of that and 0 is a NaN.
+            if constexpr (HAS_C) {
+                if (p.c_act == 1) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) cv[b % (AHEAD + 1)][e] = cv[b % (AHEAD + 1)][e] > 0.f ? cv[b % (AHEAD + 1)][e] : 0.f;
+                }
+            }
             float y[16];
             if constexpr (PAIR) {
                 constexpr int ip = ii(b);
@@ -385,8 +390,8 @@ __device__ __forceinline__ void epilogue_wide(const GemmParams &p, int m_base, i
                     if constexpr (HAS_C) {
                         float c0 = cv[b % (AHEAD + 1)][2 * r], c1 = cv[b % (AHEAD + 1)][2 * r + 1];
                         exchange(c0, c1);
-                        v0 += p.beta * act_c(c0, floor_c);
-                        v1 += p.beta * act_c(c1, floor_c);
+                        v0 += p.beta * c0;
+                        v1 += p.beta * c1;
                     }
                     v0 = act(v0, floor_v);
                     v1 = act(v1, floor_v);
@@ -400,7 +405,7 @@ __device__ __forceinline__ void epilogue_wide(const GemmParams &p, int m_base, i
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     float v = p.alpha * acc[r] + (bias_n_on ? bn[r] : bias_m[i]);
-                    if constexpr (HAS_C) v += p.beta * act_c(cv[b % (AHEAD + 1)][r], floor_c);
+                    if constexpr (HAS_C) v += p.beta * cv[b % (AHEAD + 1)][r];
                     y[r] = act(v, floor_v);
                 }
             }

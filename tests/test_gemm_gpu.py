@@ -177,6 +177,43 @@ def test_non_finite_values_propagate_like_the_definition():
     assert np.array_equal(np16(D).reshape(N, M).T.astype(np.float64), r["D"])
 
 
+@pytest.mark.parametrize("cd16", (False, True))
+def test_non_finite_values_on_every_tile(monkeypatch, cd16):
+    """The same for the epilogues of the larger tiles, inner and edge tiles, and for activations of C and of the result: infinities, NaN
+    and signalling NaN (of which a maximum instruction makes a NaN) in C, A, B and bias."""
+    import numpy as np
+    from oracle import cpu_oracle as O
+    from paper_2009_12263_amd import workloads as W
+    from tests.parity import np16
+    M, N, K = 300, 264, 72
+    lda, ldb = (M + 7) // 8 * 8, (K + 7) // 8 * 8
+    bits, special = (torch.int16, (0x7d00, -0x300, 0x7e00, 0x7c00, -0x400)) if cd16 else (torch.int32, (0x7fa00000, -0x600000, 0x7fc00000, 0x7f800000, -0x800000))
+    dtype = torch.float16 if cd16 else torch.float32
+    A = W.small_ints(lda * K, 1, device="cuda"); B = W.small_ints(ldb * N, 2, device="cuda")
+    A.view(K, lda)[5, 17] = float("nan"); A.view(K, lda)[K - 1, 260] = float("inf"); B.view(N, ldb)[7, 2] = float("-inf")
+    bias = W.small_ints(N, 4, device="cuda", dtype=torch.float32)
+    bias.view(torch.int32)[9] = 0x7fa00000; bias[263] = float("-inf")
+    Cm = W.small_ints(M * N, 3, device="cuda", dtype=dtype)
+    for n, b in enumerate(special):                     # signalling NaN of both signs, NaN, infinities; in inner and in edge tiles
+        for row, col in ((40 + n, 20 + n), (70 + n, 200 + n), (290 + n, 11 + n), (258 + n, 257 + n)):
+            Cm.view(bits).view(N, M)[col, row] = b
+    for tile in (0, 1, 2, 3, 4, 6, 7, 8, 9, 10):
+        setenv(monkeypatch, "FG_FORCE_TILE", str(tile))
+        for act, c_act in itertools.product((fg.FG_ACT_NONE, fg.FG_ACT_RELU), repeat=2):
+            say("tile %d act=%d c_act=%d" % (tile, act, c_act))
+            D = torch.full_like(Cm, 7.0)
+            fg.fg_gemm(M, N, K, 1.0, fg.Matrix(A, fg.FG_COL, lda), fg.Matrix(B, fg.FG_COL, ldb), 1.0, fg.Matrix(Cm, fg.FG_COL, M),
+                       fg.Matrix(D, fg.FG_COL, M), bias=bias, bias_dim=1, act=act, c_act=c_act)
+            torch.cuda.synchronize()
+            with np.errstate(invalid="ignore"):
+                r = O.gemm(M, N, K, 1.0, O.Operand(np16(A), O.COL, lda), O.Operand(np16(B), O.COL, ldb), 1.0, np16(Cm).astype(np.float32), None, O.COL, M,
+                           np16(bias), 1, act=act, c_act=c_act)
+                want = r["D"].astype(np.float16).astype(np.float64) if cd16 else r["D"]
+            same = np.array_equal(np16(D).reshape(N, M).T.astype(np.float64), want, equal_nan=True)
+            assert same, "non-finite entries differ from the definition"
+    delenv(monkeypatch, "FG_FORCE_TILE")
+
+
 def test_arbitrary_sizes_large():
     say("5000x3000x1000 ints sampled"); run_gemm_case(5000, 3000, 1000, ints=True, config=2, samples=6000)
     say("4100x4100x4104 floats sampled"); run_gemm_case(4100, 4100, 4104, fg.FG_ROW, fg.FG_COL, config=2, samples=6000)
