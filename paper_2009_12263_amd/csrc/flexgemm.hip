@@ -153,6 +153,14 @@ constexpr Rates kRates = {{1.12, 0.95, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.38
                           2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
                           {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true,
                           {1, 1, 1, 1, 1, 1, 2, 2, 2, 1, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1, 2}};
+// K up to 512, where the 256x128 tile has eight waves (select_kernel): its rate with those.  At the one above it took products from the
+// smaller tiles that these are faster on (47 random ones with K up to 256 from the 64x64 tile, which takes 0.84 of the time, at best
+// 0.74, 752x6032x144 with C 13.3 -> 9.8 us; 16 from the 128x128 tile, 0.92; 7 go to the 256x256 tile, 0.98).
+constexpr Rates kRatesShort = {{1.12, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
+                               {1.12, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
+                               2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
+                               {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true,
+                               {1, 1, 1, 1, 1, 1, 2, 2, 2, 1, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1, 2}};
 // Addition on A and B, whose kernels of the large tiles have eight waves.
 constexpr Rates kRatesAdd = {{1, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
                              {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
@@ -224,7 +232,7 @@ constexpr Prices priced(const Rates &r) {
     p.last_round = r.last_round;
     return p;
 }
-constexpr Prices kPrices = priced(kRates), kPrices16 = priced(kRates16), kPricesAdd = priced(kRatesAdd), kContractPrices = priced(kContractRates);
+constexpr Prices kPrices = priced(kRates), kPricesShort = priced(kRatesShort), kPrices16 = priced(kRates16), kPricesAdd = priced(kRatesAdd), kContractPrices = priced(kContractRates);
 constexpr Prices kPromisedPrices = priced(kPromisedRates), kFormerPrices = priced(kFormerRates);
 
 // The K ranges that a product may be split into: at least four K tiles (256 k) each.
@@ -490,7 +498,8 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     const bool long16 = q.cd16 && q.K >= 512;               // (see kRates16)
     const int straddling = may_split || long16 ? (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N) : 0;
     const Plan plan = q.a_diag || q.b_diag ? choose_plan(q.M, q.N, KRanges(q.K), false, true, 1, false)
-                                           : plan_product(q.M, q.N, q.K, may_split, k32, straddling, long16 ? kPrices16 : q.ab_add ? kPricesAdd : kPrices);
+                                           : plan_product(q.M, q.N, q.K, may_split, k32, straddling,
+                                                          long16 ? kPrices16 : q.ab_add ? kPricesAdd : q.K <= 512 ? kPricesShort : kPrices);
     int tile = plan.tile;
     // A product with a diagonal operand is bound by its memory traffic (one pass over the dense
     // operand, C and D; a tile row only meets the K tiles on the diagonal).  While all of it fits the
