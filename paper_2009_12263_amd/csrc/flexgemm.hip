@@ -148,6 +148,8 @@ struct Rates {
     // K groups and sets of accumulators per group, which share a workgroup's sum over K (TileCfg::KG, ACC_SETS)
     int groups[fg::TILE_COUNT] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1}, sets[fg::TILE_COUNT] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1};
 };
+// Sets of the 256x128 tile: it has two, but is counted with the one of eight waves.  With two the limit on sums (plan_product) admits it in
+// place of the 256x256 tile's twice as many ranges, which is slower (29 products 1.03, 8784x160x16016 90.4 and 122.6 us).
 constexpr Rates kRates = {{1.12, 0.95, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
                           {1.12, 0.95, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
                           2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
@@ -161,16 +163,18 @@ constexpr Rates kRatesShort = {{1.12, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367,
                                2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
                                {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true,
                                {1, 1, 1, 1, 1, 1, 2, 2, 2, 1, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1, 2}};
-// Addition on A and B, whose kernels of the large tiles have eight waves.
+// Addition on A and B, whose kernels of the large tiles have eight waves; what all real products were priced with before there were
+// others (see plan_product).
 constexpr Rates kRatesAdd = {{1, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
                              {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
                              2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
                              {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true,
                              {1, 1, 1, 1, 1, 1, 2, 2, 2, 1, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1, 2}};
 using fg::TileCfg;
-static_assert(FG_CFG_K32(128, 128, 64, 4, 2, 2, false, true, false, false)::ACC_SETS == 2 && FG_CFG(128, 128, 64, 4, 4, 2, false, true, false)::ACC_SETS == 2 && FG_CFG(256, 128, 64, 3, 4, 2, false, true, false)::ACC_SETS == 1 &&
-              FG_CFG_KG(false, true, false, false, false, 64, 2, false)::ACC_SETS == 2 && FG_CFG_KG(false, true, false, false, false, 64, 4, true)::ACC_SETS == 2 &&
-              FG_CFG_KG(false, true, false, false, false, 128, 3, true)::ACC_SETS == 2, "Rates::sets");
+static_assert(FG_CFG_K32(256, 256, 64, 2, 2, 2, false, true, false, false)::ACC_SETS == 1 && FG_CFG_K32(256, 128, 64, 3, 2, 2, false, true, false, false)::ACC_SETS == 2 &&
+              FG_CFG(256, 128, 64, 3, 4, 2, false, true, false)::ACC_SETS == 1 && FG_CFG_K32(128, 128, 64, 4, 2, 2, false, true, false, false)::ACC_SETS == 2 &&
+              FG_CFG(128, 128, 64, 4, 4, 2, false, true, false)::ACC_SETS == 2 && FG_CFG_KG(false, true, false, false, false, 64, 2, false)::ACC_SETS == 2 &&
+              FG_CFG_KG(false, true, false, false, false, 64, 4, true)::ACC_SETS == 2 && FG_CFG_KG(false, true, false, false, false, 128, 3, true)::ACC_SETS == 2, "Rates::sets");
 // Binary16 C and D with K from 512 on: a tile's C and D at three quarters of the bytes (they are half, in lines that are accessed
 // all the same), rows off the lines priced for the tiles without K groups (these products cannot be split, and were priced
 // without), and the 64x64 tile at its former shared rate.  216 random products: 0.6 % slower than the fastest tile on average, over 5 % for
@@ -425,13 +429,23 @@ Former former_plan(int64_t M, int64_t N, int64_t K, const KRanges &ranges, bool 
 //   random shapes, small outputs with a long K), had one 3 to 20 % larger; those are as fast as before on average (0.88 to 1.16), 22 % more exact.
 // The former plan's own tile and split are always among the candidates (the larger ring with two groups of two sums in place of
 // the four groups).  Products of fewer than eight K tiles have neither splits nor groups and need not ask.  Costs about 1 us on the host.
+// Nor is a sum longer than by the rates before the kernels with four waves (kRatesAdd).  These left to the deep 128x128 tile, with two
+// sums to an entry, what would run on the 256x256 tile's one now: 34 such products had an error against 64 bits 1.38 times as
+// large, 3360x2592x4288 2.82e-7 -> 4.23e-7.  Only a plan with that tile has to ask.
 Plan plan_product(int64_t M, int64_t N, int64_t K, bool may_split, int k32, int straddling, const Prices &prices) {
     const KRanges ranges(K);
     const bool forced = g_force_split.load(std::memory_order_relaxed) >= 1 || g_force_tail.load(std::memory_order_relaxed) > 1 ||
                         g_force_tile.load(std::memory_order_relaxed) >= 0;
-    if (forced || ranges.n == 1) return choose_plan(M, N, ranges, may_split, true, 1, true, k32, true, kWorkspaceBytes, prices, straddling);
-    const Former former = former_plan(M, N, K, ranges, may_split, k32, straddling);
-    return choose_plan(M, N, ranges, former.scratch > 0, true, 1, true, k32, true, former.scratch, prices, straddling, former.longest);
+    if (forced) return choose_plan(M, N, ranges, may_split, true, 1, true, k32, true, kWorkspaceBytes, prices, straddling);
+    const Former former = ranges.n == 1 ? Former{may_split ? kWorkspaceBytes : 0, INT32_MAX} : former_plan(M, N, K, ranges, may_split, k32, straddling);
+    auto plan_of = [&](const Prices &by, int32_t longest) {
+        return choose_plan(M, N, ranges, former.scratch > 0, true, 1, true, k32, true, former.scratch, by, straddling, longest);
+    };
+    const Plan plan = plan_of(prices, former.longest);
+    if ((plan.tile != fg::TILE_256x256 && plan.tile != fg::TILE_256x256_K32) || (&prices != &kPrices && &prices != &kPricesShort)) return plan;
+    const Plan before = plan_of(kPricesAdd, former.longest);
+    auto sum_of = [&](const Plan &p) { return sum_length(kPricesAdd, p.tile, p.splits, (ranges.nk + p.splits - 1) / p.splits); };
+    return sum_of(plan) <= sum_of(before) ? plan : plan_of(prices, sum_of(before));
 }
 
 // Tile of the complex and dual kernels (256x128, 128x128 with two workgroups per unit, 64x64 with

@@ -13,3 +13,14 @@ def test_short_k_is_left_to_small_tiles(M, N, K, la, lb, tile):
     """The 256x128 tile has eight waves where K is short, and is priced with their rate."""
     for variant in (fg.FG_PLAN_REAL, fg.FG_PLAN_REAL_BF16):
         assert fg.fg_gemm_plan(M, N, K, la, lb, variant=variant).endswith("_" + tile)
+
+
+@pytest.mark.parametrize("M,N,K,la,lb", [
+    (1440, 5832, 704, ROW, COL), (1824, 5104, 832, ROW, COL), (2528, 3520, 1024, ROW, COL), (3520, 2768, 1824, ROW, COL), (5280, 1888, 1312, ROW, COL),
+    (1792, 5232, 672, ROW, COL), (8128, 1464, 544, ROW, COL), (6080, 1408, 1424, COL, ROW), (4448, 2064, 1056, COL, COL), (5904, 2048, 1152, ROW, ROW),
+    (3360, 2592, 4288, COL, COL), (2832, 3008, 3136, ROW, ROW), (1552, 1792, 15776, ROW, COL), (2688, 1056, 12448, ROW, COL)])
+def test_no_sum_is_longer_than_before(M, N, K, la, lb):
+    """Products of the deep 128x128 tile, which adds an entry up in two sums, do not go to the 256x256 tile, which has one (their error against
+    64 bits was 1.38 times as large there)."""
+    for variant in (fg.FG_PLAN_REAL, fg.FG_PLAN_REAL_BF16):
+        assert "_256x256x64" not in fg.fg_gemm_plan(M, N, K, la, lb, variant=variant)
