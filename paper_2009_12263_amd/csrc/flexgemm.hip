@@ -379,14 +379,6 @@ Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bo
     if (prices.last_round && force_tile < 0 && force_split < 1 && best.tile == fg::TILE_256x128 && best.tail_splits > 1 &&
         large_tail_cost <= 1.09 * best_cost)
         best = large_tail;
-    // A short K (up to 256) makes a product whose C and D stream a pass over them: there the 256x128 tile with eight waves
-    // (TILE_256x128_PASS) is faster than the 256x256 tile the estimate picks (8192^2 x 128 with C 98.2 against 115.1 us, without 56.3 and
-    // 60.0, 256: 110.9, 127.7, 77.1, 73.3; at K = 384 and 512 it wins with a C operand, see select_kernel).  Not where they stay in
-    // the caches (4096^2 x 256 38.9 and 38.1, without C 26.7 and 20.3; 3000x5000x256 45.9, 42.8, 24.9, 20.4; x 128 40.3, 39.9, 19.3, 17.5).
-    // Matrix kernels only, which is what k32 > 0 says: contraction 5a, K = 256, is faster on the larger tile.
-    if (best.tile == fg::TILE_256x256 && k32 > 0 && force_tile < 0 && nk <= 4 && best.splits == 1 && best.tail_splits == 1 &&
-        M * N * 8 > fg::kMemorySideCache)
-        best.tile = fg::TILE_256x128;
     if (best.tile == fg::TILE_256x256 && k32 > 0 && !forced_plain) {
         const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256) * batches;
         if (force_k32 || (k32 == 2 && tiles >= kNumCU * 3 / 4)) best.tile = fg::TILE_256x256_K32;
@@ -493,6 +485,13 @@ int choose_ctile(int64_t M, int64_t N, int64_t K) {
     return best;
 }
 
+// Whether C and D stay in the caches (GemmParams::cd_cached).  (The plan query has neither a C nor leading dimensions.)
+bool keeps_cd(const Problem &q) {
+    const int64_t ab = (q.M * q.K + q.K * q.N) * 2, cd = q.M * q.N * (q.cd16 ? 2 : 4) * (q.C ? 2 : 1), elem = q.ilv ? 8 : q.cd16 ? 2 : 4;
+    return q.cplx ? fg::keeps_complex_cd(2 * ab, 2 * cd, q.K, q.ilv, q.C != nullptr, q.ldc * elem, q.ldd * elem)
+                  : fg::keeps_real_cd(ab, cd, q.C != nullptr, q.ldc * elem, q.ldd * elem);
+}
+
 // Kernel variant for a normalised problem.
 const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr) {
     if (plan_out) *plan_out = Plan{0, 1, 1};
@@ -523,13 +522,22 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     // more in memory than they gain (8192^2: 180 us against 135 us), and the estimate above decides.
     if ((q.a_diag || q.b_diag) && g_force_tile.load(std::memory_order_relaxed) < 0 && q.M * q.N * 10 <= (256ll << 20))
         tile = fg::TILE_64x64;
+    const int forced = g_force_tile.load(std::memory_order_relaxed);
+    // A short K makes a product a pass over C and D, on which eight waves and the 256x128 tile (TILE_256x128_PASS) can be faster than the
+    // 256x256 tile that the estimate picks.  Time on the former by that on the latter, 340 products:
+    // - K up to 128, 0.81 to 1.04, 0.93 on average (5408x5104x16 23.7 and 26.3 us); but with a C that stays in the caches 1.01 to 1.08 (5104x5344x96
+    //   50.1 and 46.5), binary16 0.9, and without one off the half lines 0.93 to 1.1 (5748x5376x128 35.7 and 32.5; by M, see off_line), binary16 0.85;
+    // - K up to 256 where C and D stream, 0.78 to 1.0 (6336x5824x256 with C 73.5 and 92.1), and binary16 results without C of more than 64 MB,
+    //   0.72 to 1.02 (smaller ones 1.0 to 1.1); others 0.91 to 1.37 (4260x6688x256 48.6 and 35.6);
+    // - K up to 512 with a C, where C and D stream, 0.78 to 0.97 (10272x4704x512 108.8 and 139.0; binary16 0.91 to 1.02); others 0.93 to 1.28
+    //   (binary16 6240x6704x512 94 and 78).
+    // Addition on A and B, whose 256x256 kernels have eight waves too: K up to 256 with one of the operands K-contiguous.
+    if ((tile == fg::TILE_256x256 || tile == fg::TILE_256x256_K32) && !q.a_diag && !q.b_diag && forced < 0 && plan.splits == 1 && plan.tail_splits == 1) {
+        const bool streams = !keeps_cd(q), large16 = q.cd16 && !q.C && q.M * q.N * 2 > (64ll << 20);
+        const int64_t longest = q.ab_add ? (k32 > 0 ? 256 : 0) : streams ? (q.C ? 512 : 256) : large16 ? 256 : q.cd16 || (!q.C && q.M % 16 == 0) ? 128 : 0;
+        if (q.K <= longest) tile = fg::TILE_256x128;
+    }
     if (!q.ab_add && !q.a_diag && !q.b_diag) {
-        const int forced = g_force_tile.load(std::memory_order_relaxed);
-        // A pass over C and D that stream: the stores of four waves fall behind those of eight (8192^2 with C, K = 384: 135.9 us on the
-        // 256x256 tile, 124.0 on the 256x128 one with eight; 512: 147 and 137; 768: 166.5 and 165.2; 1024: 187 and 193).
-        if ((tile == fg::TILE_256x256 || tile == fg::TILE_256x256_K32) && forced < 0 && q.C && q.K <= 512 &&
-            q.M * q.N * 8 > fg::kMemorySideCache && plan.splits == 1 && plan.tail_splits == 1)
-            tile = fg::TILE_256x128;
         // Short K, where loading, multiplying and storing hardly overlap within a tile: eight waves on the 256x128 tile (2560^2 x 128 with
         // C 14.9 us with four, 12.9 with eight, 8192x1024x128 without 11.3 and 10.7, at K = 512 18.6 and 17.7, 16.0 and 17.1; at 768
         // 21.0 and 20.9, 18.9 and 20.7; binary16 results with C 19.3 and 18.3, 22.1 and 21.9; 1000: 23.7, 24.2, 25.4, 26.4).
@@ -1336,11 +1344,7 @@ static fg_status gemm_impl(int64_t M, int64_t N, int64_t K, float alpha, const f
     if (tiles64 >= (1ll << 31) / 64) return fail(FG_ERR_UNSUPPORTED, "too many tiles");
     const int tiles = (int)tiles64;
     p.tile_begin = 0; p.tile_count = tiles; p.splits = 1;
-    {
-        const int64_t ab = (q.M * q.K + q.K * q.N) * 2, cd = q.M * q.N * (q.cd16 ? 2 : 4) * (q.C ? 2 : 1), elem = q.ilv ? 8 : q.cd16 ? 2 : 4;
-        p.cd_cached = q.cplx ? fg::keeps_complex_cd(2 * ab, 2 * cd, q.K, q.ilv, q.C != nullptr, q.ldc * elem, q.ldd * elem)
-                             : fg::keeps_real_cd(ab, cd, q.C != nullptr, q.ldc * elem, q.ldd * elem);
-    }
+    p.cd_cached = keeps_cd(q);
     p.rotate = (p.tiles_m == 1 && q.b_kc) || (p.tiles_n == 1 && q.a_kc);
     p.once = p.tiles_m == 1 && fg::streams_once((uintptr_t)q.B, q.ldb, q.N * q.K * 2) ? 1
            : p.tiles_n == 1 && fg::streams_once((uintptr_t)q.A, q.lda, q.M * q.K * 2) ? 2 : 0;

@@ -24,3 +24,13 @@ def test_no_sum_is_longer_than_before(M, N, K, la, lb):
     64 bits was 1.38 times as large there)."""
     for variant in (fg.FG_PLAN_REAL, fg.FG_PLAN_REAL_BF16):
         assert "_256x256x64" not in fg.fg_gemm_plan(M, N, K, la, lb, variant=variant)
+
+
+@pytest.mark.parametrize("variant,M,N,K,tile", [
+    (fg.FG_PLAN_REAL, 8192, 6000, 256, "256x256x64"), (fg.FG_PLAN_REAL, 8192, 8192, 256, "256x128x64"), (fg.FG_PLAN_REAL, 5408, 5104, 128, "256x128x64"), (fg.FG_PLAN_REAL, 5748, 5376, 128, "256x256x64"),
+    (fg.FG_PLAN_REAL, 5408, 5104, 192, "256x256x64"), (fg.FG_PLAN_REAL_BF16, 8192, 6000, 256, "256x256x64"), (fg.FG_PLAN_REAL_F16_CD, 2384, 5584, 128, "256x128x64"),
+    (fg.FG_PLAN_REAL_F16_CD, 9024, 6784, 256, "256x128x64"), (fg.FG_PLAN_REAL_F16_CD, 3524, 7968, 256, "256x256x64"),
+    (fg.FG_PLAN_REAL_AB_ADD, 4096, 4096, 256, "256x128x64"), (fg.FG_PLAN_REAL_AB_ADD, 4096, 4096, 320, "256x256x64")])
+def test_tile_of_a_short_k(variant, M, N, K, tile):
+    """The 256x128 tile in place of the 256x256 one: where C and D stream, by what decides that (keeps_real_cd), and not by M and N alone."""
+    assert fg.fg_gemm_plan(M, N, K, fg.FG_COL, fg.FG_COL, variant=variant).replace("_k32", "").endswith("_" + tile)
