@@ -509,7 +509,7 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     // 33.8 us in one pass, 41.7 split in two; 443x4534 33.8, and 35.4.
     auto off_line = [](int64_t extent) { return (extent + 7) / 8 % 4 != 0; };
     const bool long16 = q.cd16 && q.K >= 512;               // (see kRates16)
-    const int straddling = may_split || long16 ? (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N) : 0;
+    const int off = (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N), straddling = may_split || long16 ? off : 0;
     const Plan plan = q.a_diag || q.b_diag ? choose_plan(q.M, q.N, KRanges(q.K), false, true, 1, false)
                                            : plan_product(q.M, q.N, q.K, may_split, k32, straddling,
                                                           long16 ? kPrices16 : q.ab_add ? kPricesAdd : q.K <= 512 ? kPricesShort : kPrices);
@@ -540,12 +540,17 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     if (!q.ab_add && !q.a_diag && !q.b_diag) {
         // Short K, where loading, multiplying and storing hardly overlap within a tile: eight waves on the 256x128 tile (2560^2 x 128 with
         // C 14.9 us with four, 12.9 with eight, 8192x1024x128 without 11.3 and 10.7, at K = 512 18.6 and 17.7, 16.0 and 17.1; at 768
-        // 21.0 and 20.9, 18.9 and 20.7; binary16 results with C 19.3 and 18.3, 22.1 and 21.9; 1000: 23.7, 24.2, 25.4, 26.4).
-        if (tile == fg::TILE_256x128 && (forced == fg::TILE_256x128_PASS || (forced < 0 && q.K <= (q.C ? 768 : 512)))) tile = fg::TILE_256x128_PASS;
+        // 21.0 and 20.9, 18.9 and 20.7; binary16 results with C 19.3 and 18.3, 22.1 and 21.9; 1000: 23.7, 24.2, 25.4, 26.4).  Binary16 results
+        // without C, whose stores are exchanged into lines first, up to 1024 (K 520 to 800 0.935 of the time of four, 42 products, 4088x1184x576
+        // 14.7 -> 12.9; up to 1024 0.967, 21; forced, from 1152 on 0.96 to 1.03).
+        const int64_t pass_k = q.C ? 768 : q.cd16 ? 1024 : 512;
+        if (tile == fg::TILE_256x128 && (forced == fg::TILE_256x128_PASS || (forced < 0 && q.K <= pass_k))) tile = fg::TILE_256x128_PASS;
         // The same on the deep 128x128 tile (2048^2 x 128 with C 11.8 us with four waves, 10.4 with eight, 960x4096x256 without 9.5 and 8.7, 1304x2200x512
         // 13.0 and 12.4, 2000^2 x 760 17.1 and 16.6; 768: 15.8 and 16.0, 1536x2048x1024 12.8 and 14.0); a little longer where a last K tile
-        // hangs over, which four waves load first and by itself (1536x2048x1000: 15.9 and 15.4, 16.1 and 16.0; 2000^2 x 2024: 28.1 and 29.3).
-        const bool short_k = q.K <= 768 || (q.K < 1024 && q.K % 64 != 0);
+        // hangs over, which four waves load first and by itself (1536x2048x1000: 15.9 and 15.4, 16.1 and 16.0; 2000^2 x 2024: 28.1 and 29.3), and for
+        // binary16 results with both operands off the lines, whose fills a second wave per SIMD covers better (K 1024 to 2560 0.965 of the time of
+        // four, 78 products; up to 4096 0.99; FP32 results 0.93 to 1.1, 0.99 on average).
+        const bool short_k = q.K <= 768 || (q.K < 1024 && q.K % 64 != 0) || (q.cd16 && off == 2 && q.K <= 2560);
         if (tile == fg::TILE_128x128_DEEP && (forced == fg::TILE_128x128_PASS || (forced < 0 && short_k && plan.splits == 1))) tile = fg::TILE_128x128_PASS;
     }
     if (plan_out) { *plan_out = plan; plan_out->tile = tile; }
