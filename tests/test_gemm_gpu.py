@@ -585,6 +585,22 @@ def test_one_wave_per_simd(monkeypatch, la, lb):
     delenv(monkeypatch, "FG_FORCE_TILE")
 
 
+@pytest.mark.parametrize("M,N,la,lb", [(100, 700, fg.FG_COL, fg.FG_COL), (128, 1300, fg.FG_ROW, fg.FG_COL), (700, 100, fg.FG_ROW, fg.FG_ROW), (1030, 67, fg.FG_ROW, fg.FG_COL)])
+def test_walks_in_a_circle(monkeypatch, M, N, la, lb):
+    """One row (column) of deep 128x128 tiles whose long operand is K-contiguous: each XCD walks its range of K from a place of its own
+    (GemmParams::rotate).  Circles shorter than the ring, as long, and longer than one for each XCD, with and without a last K tile that hangs
+    over (which is outside the circle), and ranges of a split; several operands' worth of tiles, so that every place is taken."""
+    setenv(monkeypatch, "FG_FORCE_TILE", "4")
+    for K in (8, 64, 72, 128, 136, 192, 200, 256, 264, 320, 328, 576, 584, 1000, 1088):
+        say("circle %dx%dx%d A=%d B=%d" % (M, N, K, la, lb))
+        run_gemm_case(M, N, K, la, lb, ints=True, pad=8, poison=True, with_c=K % 3 == 0, bias_dim=0, cd16=K % 5 == 0, bf16=K % 5 == 1)
+    for S, K in ((2, 192), (3, 392), (3, 512), (4, 520), (5, 1000), (6, 1536), (7, 904)):
+        setenv(monkeypatch, "FG_FORCE_SPLIT", str(S))
+        say("circles of K = %d split in %d" % (K, S)); run_gemm_case(M, N, K, la, lb, ints=True, poison=True, bias_dim=1, act=fg.FG_ACT_RELU)
+    delenv(monkeypatch, "FG_FORCE_SPLIT")
+    delenv(monkeypatch, "FG_FORCE_TILE")
+
+
 @pytest.mark.parametrize("la,lb", list(itertools.product(LAYOUTS, LAYOUTS)))
 def test_ring_of_three_buffers(monkeypatch, la, lb):
     """The 256x128 tile's ring is no power of two: K loops shorter than the ring, as long, and ending in each of its
