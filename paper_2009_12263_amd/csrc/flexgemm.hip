@@ -155,9 +155,10 @@ constexpr Rates kRates = {{1.12, 0.95, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.38
                           2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
                           {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true,
                           {1, 1, 1, 1, 1, 1, 2, 2, 2, 1, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1, 2}};
-// K up to 512, where the 256x128 tile has eight waves (select_kernel): its rate with those.  At the one above it took products from the
-// smaller tiles that these are faster on (47 random ones with K up to 256 from the 64x64 tile, which takes 0.84 of the time, at best
-// 0.74, 752x6032x144 with C 13.3 -> 9.8 us; 16 from the 128x128 tile, 0.92; 7 go to the 256x256 tile, 0.98).
+// K up to 512, with C 768, where the 256x128 tile has eight waves (select_kernel): its rate with those.  At the one above it took products
+// from the smaller tiles that these are faster on (47 random ones with K up to 256 from the 64x64 tile, which takes 0.84 of the time, at best
+// 0.74, 752x6032x144 with C 13.3 -> 9.8 us; 16 from the 128x128 tile, 0.92, with C and K from 512 to 768 on it 0.87 to 0.97; 7 go to the 256x256
+// tile, 0.98).
 constexpr Rates kRatesShort = {{1.12, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
                                {1.12, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
                                2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
@@ -512,7 +513,7 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     const int off = (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N), straddling = may_split || long16 ? off : 0;
     const Plan plan = q.a_diag || q.b_diag ? choose_plan(q.M, q.N, KRanges(q.K), false, true, 1, false)
                                            : plan_product(q.M, q.N, q.K, may_split, k32, straddling,
-                                                          long16 ? kPrices16 : q.ab_add ? kPricesAdd : q.K <= 512 ? kPricesShort : kPrices);
+                                                          long16 ? kPrices16 : q.ab_add ? kPricesAdd : q.K <= (q.C ? 768 : 512) ? kPricesShort : kPrices);
     int tile = plan.tile;
     // A product with a diagonal operand is bound by its memory traffic (one pass over the dense
     // operand, C and D; a tile row only meets the K tiles on the diagonal).  While all of it fits the
@@ -529,12 +530,12 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     //   50.1 and 46.5), binary16 0.9, and without one off the half lines 0.93 to 1.1 (5748x5376x128 35.7 and 32.5; by M, see off_line), binary16 0.85;
     // - K up to 256 where C and D stream, 0.78 to 1.0 (6336x5824x256 with C 73.5 and 92.1), and binary16 results without C of more than 64 MB,
     //   0.72 to 1.02 (smaller ones 1.0 to 1.1); others 0.91 to 1.37 (4260x6688x256 48.6 and 35.6);
-    // - K up to 512 with a C, where C and D stream, 0.78 to 0.97 (10272x4704x512 108.8 and 139.0; binary16 0.91 to 1.02); others 0.93 to 1.28
-    //   (binary16 6240x6704x512 94 and 78).
+    // - K up to 768 with a C, where C and D stream, 0.78 to 1.0 (10272x4704x512 108.8 and 139.0, 3104x11680x768 109.9 and 123.0); binary16 up to 512
+    //   0.91 to 1.02, from 640 on 1.01 to 1.08; others 0.93 to 1.28 (binary16 6240x6704x512 94 and 78).
     // Addition on A and B, whose 256x256 kernels have eight waves too: K up to 256 with one of the operands K-contiguous.
     if ((tile == fg::TILE_256x256 || tile == fg::TILE_256x256_K32) && !q.a_diag && !q.b_diag && forced < 0 && plan.splits == 1 && plan.tail_splits == 1) {
         const bool streams = !keeps_cd(q), large16 = q.cd16 && !q.C && q.M * q.N * 2 > (64ll << 20);
-        const int64_t longest = q.ab_add ? (k32 > 0 ? 256 : 0) : streams ? (q.C ? 512 : 256) : large16 ? 256 : q.cd16 || (!q.C && q.M % 16 == 0) ? 128 : 0;
+        const int64_t longest = q.ab_add ? (k32 > 0 ? 256 : 0) : streams ? (!q.C ? 256 : q.cd16 ? 512 : 768) : large16 ? 256 : q.cd16 || (!q.C && q.M % 16 == 0) ? 128 : 0;
         if (q.K <= longest) tile = fg::TILE_256x128;
     }
     if (!q.ab_add && !q.a_diag && !q.b_diag) {
