@@ -306,10 +306,13 @@ fg_status fg_init(void);
  * Name of the kernel variant and block tile that fg_gemm would use for this problem, written as
  * a NUL-terminated string into `buf` (at most `buf_len` bytes), followed by "+splitk<n>" when K
  * is split into n ranges for every tile, or "+tailsplitk<n>" when only the tiles of the last round
- * are split.  A name ending in "_k32" is the kernel built on 16x16x32 matrix instructions, used for
- * outputs with a 256x256 tile for at least three quarters of the compute units; the others use 32x32x16 instructions.  Both
- * accumulate the same FP16 products in FP32, in a different order: results agree within the stated
+ * are split.  A name ending in "_k32" is given to outputs with a 256x256 tile for at least three quarters of the compute
+ * units where A or B is K-contiguous; for real FP16, BF16 and FG_F16-result products it is the kernel of the same name without it, with a
+ * constant added to A and B one built on 16x16x32 matrix instructions in place of 32x32x16 ones.  All tiles
+ * accumulate the same FP16 products in FP32, in different orders: results agree within the stated
  * tolerance and are bit-identical on integer-valued data.
+ * The query has no C: with one and K up to 768 a call may take another tile than it names (256x128 for 256x256 where C and D
+ * are too large for the caches, a smaller one for 256x128).  Whether K is split does not depend on C.
  * A name with "_64x64x64" stands for the 64x64 tile whichever number of wave groups (one, two or
  * four) shares its K.  "gemm_general_64x64x32" and "gemm_general_128x128x64" are the general kernel (K % 8 != 0; both take
  * K steps of 64); a product that only misses an alignment, which this query does not know, runs there too.

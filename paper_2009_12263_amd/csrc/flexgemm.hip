@@ -49,9 +49,9 @@ void note_relaxed(fg_status st, const char *fmt, ...) {
 
 constexpr int kNumCU = 256;   // MI355X: 8 XCDs x 32 compute units
 
-// Tuning overrides of the planner, from the environment: FG_FORCE_TILE=0..9 picks a tile shape (0..3
+// Tuning overrides of the planner, from the environment: FG_FORCE_TILE=0..10 picks a tile shape (0..3
 // for the four tiles of the complex and dual kernels)
-// (5: the 256x256 tile with the k32 kernel where the family has one; 6, 7: the 64x64 tile with two K
+// (5: the 256x256 tile by its k32 name, another kernel than 0 for addition on A and B only; 6, 7: the 64x64 tile with two K
 // groups and rings of two or four buffers, 8: the 64x128 tile with two, 9 and 10: the 256x128 and the deep 128x128 tile with eight waves), FG_FORCE_SPLIT=n a split of K
 // for every tile, FG_FORCE_TAIL=n a split of K for the tiles of the last round (1: never).  Read
 // when the library is loaded and again by fg_reload_tuning(), not on every call.
@@ -131,8 +131,8 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 // lines are fitted to the times of replayed graphs of every tile and split forced over 190 products (64x64x32768 to
 // 4876x7518x2448): the choice by them alone is on average 1.7 % slower than the fastest (5 % with the rates before the larger
 // rings), at most 42 % (6708x5150x96), and over 16 % only with K up to 224; held to what plan_product promises, 3.4 % (4.7 %).
-// Since then the rates of the two large tiles went up with their K loops (1 -> 1.12, 0.88 -> 0.95): of the 190 products 21 take another
-// plan, at 0.83 to 1.05 of the time, 0.94 on average.
+// Since then the rates of the two large tiles went up with their K loops (1 -> 1.12, 0.88 -> 0.95): 2 of the 190 products take another
+// plan, and 650 of 60000 random ones, 300 of which at 0.93 of the time by the rates before, 0.76 to 1.15.
 constexpr int kTileM[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64, 64, 256, 128};
 constexpr int kTileN[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64, 128, 128, 128};
 constexpr int kTilesPerCU[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1, 1, 1, 1};
@@ -510,10 +510,14 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     // 33.8 us in one pass, 41.7 split in two; 443x4534 33.8, and 35.4.
     auto off_line = [](int64_t extent) { return (extent + 7) / 8 % 4 != 0; };
     const bool long16 = q.cd16 && q.K >= 512;               // (see kRates16)
-    const int off = (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N), straddling = may_split || long16 ? off : 0;
-    const Plan plan = q.a_diag || q.b_diag ? choose_plan(q.M, q.N, KRanges(q.K), false, true, 1, false)
-                                           : plan_product(q.M, q.N, q.K, may_split, k32, straddling,
-                                                          long16 ? kPrices16 : q.ab_add ? kPricesAdd : q.K <= (q.C ? 768 : 512) ? kPricesShort : kPrices);
+    const int off = (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N);
+    auto product = [&](bool split, const Prices &prices) { return plan_product(q.M, q.N, q.K, split, k32, may_split || long16 ? off : 0, prices); };
+    Plan plan = q.a_diag || q.b_diag ? choose_plan(q.M, q.N, KRanges(q.K), false, true, 1, false)
+                                     : product(may_split, long16 ? kPrices16 : q.ab_add ? kPricesAdd : q.K <= 512 ? kPricesShort : kPrices);
+    // With C the 256x128 tile has eight waves up to K = 768 (below).  Only a plan of one pass is made again, for one pass: whether a product
+    // is split does not depend on C, which the plan query does not know.
+    if (q.C && !q.cd16 && !q.ab_add && q.K > 512 && q.K <= 768 && plan.tile == fg::TILE_256x128 && plan.splits == 1 && plan.tail_splits == 1)
+        plan = product(false, kPricesShort);
     int tile = plan.tile;
     // A product with a diagonal operand is bound by its memory traffic (one pass over the dense
     // operand, C and D; a tile row only meets the K tiles on the diagonal).  While all of it fits the

@@ -5,8 +5,8 @@
 // with 128x64 each (16 KB instead of 24 per 64 instructions), and every other instruction of a K tile is needed half as often.
 // The price: no second wave covers what a wave waits for, so the loop is written as one straight line of slots, a
 // matrix instruction each (16 cycles), with at most a fragment read and a direct load beside it:
-//   * what a K tile costs besides is kept to about 35 scalar and 2 vector instructions per wave (the loaders of the other kernels
-//     take 62 and 34 per 64 matrix instructions): descriptors are advanced in place, m0 is written by one addition with the
+//   * what a K tile costs besides is kept to 58 scalar (16 write m0, 18 copy a descriptor's words) and up to 9 vector instructions per
+//     wave and 128 matrix instructions (the loaders of the other kernels take 62 and 34 per 64): descriptors are advanced in place, m0 is written by one addition with the
 //     matrix instruction as the wait between it and its use, and there is no branch but one per K tile.  A taken branch, or the
 //     twenty scalar instructions of a descriptor computed in one go, stall the matrix unit (8192^3 on zeros, a branch
 //     around the masking of a last K tile in every K tile: 704 us, without it 660);
