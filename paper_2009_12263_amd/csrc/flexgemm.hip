@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdarg>
 #include <cstdio>
@@ -396,20 +397,22 @@ int64_t scratch_need(const Plan &plan, int64_t M, int64_t N) {
     return (plan.splits > 1 ? tiles * plan.splits : (tiles & ((1ll << kShifts.slots[t]) - 1)) * plan.tail_splits) * tile_bytes;
 }
 
+// The most that a product with this need may take: none, the static array, the workspace.
+int64_t scratch_class(int64_t bytes) { return bytes == 0 ? 0 : bytes <= kStaticScratchBytes ? kStaticScratchBytes : kWorkspaceBytes; }
+
 // What the planner before the larger rings chose (kFormerRates, four K groups as tile 7, itself held to the scratch classes of
 // kPromisedRates), as far as calls still depend on it.
 struct Former { int64_t scratch; int32_t longest; };
 Former former_plan(int64_t M, int64_t N, int64_t K, const KRanges &ranges, bool may_split, int k32, int straddling) {
-    auto limit_of = [](int64_t bytes) { return bytes == 0 ? 0 : bytes <= kStaticScratchBytes ? kStaticScratchBytes : kWorkspaceBytes; };
     int64_t promised = 0;
-    if (may_split) promised = limit_of(scratch_need(choose_plan(M, N, ranges, true, true, 1, true, k32, false, kWorkspaceBytes, kPromisedPrices), M, N));
+    if (may_split) promised = scratch_class(scratch_need(choose_plan(M, N, ranges, true, true, 1, true, k32, false, kWorkspaceBytes, kPromisedPrices), M, N));
     // (the best plan within the promised class; rows off the lines counted in long K loops only, and only for a split)
     auto plan_of = [&](int lines) { return choose_plan(M, N, ranges, promised > 0, true, 1, true, k32, true, promised, kFormerPrices, lines); };
     const int lines = promised > 0 && K > 3904 ? straddling : 0;
     Plan former = plan_of(lines);
     if (lines > 0 && former.splits == 1 && former.tail_splits == 1) former = plan_of(0);
     const int32_t share = (ranges.nk + former.splits - 1) / former.splits;
-    return Former{limit_of(scratch_need(former, M, N)), sum_length(kFormerPrices, former.tile, former.splits, share)};
+    return Former{scratch_class(scratch_need(former, M, N)), sum_length(kFormerPrices, former.tile, former.splits, share)};
 }
 
 // Plan of a real product without a diagonal operand.  Two things that the former planner chose hold still:
@@ -422,23 +425,27 @@ Former former_plan(int64_t M, int64_t N, int64_t K, const KRanges &ranges, bool 
 //   random shapes, small outputs with a long K), had one 3 to 20 % larger; those are as fast as before on average (0.88 to 1.16), 22 % more exact.
 // The former plan's own tile and split are always among the candidates (the larger ring with two groups of two sums in place of
 // the four groups).  Products of fewer than eight K tiles have neither splits nor groups and need not ask.  Costs about 1 us on the host.
-// Nor is a sum longer than by the rates before the kernels with four waves (kRatesAdd).  These left to the deep 128x128 tile, with two
-// sums to an entry, what would run on the 256x256 tile's one now: 34 such products had an error against 64 bits 1.38 times as
-// large, 3360x2592x4288 2.82e-7 -> 4.23e-7.  Only a plan with that tile has to ask.
+// Both hold as well against the rates before the kernels with four waves (kRatesAdd).  These left to the deep 128x128 tile, with two sums
+// to an entry, what would run on the 256x256 tile's one now: 34 such products had an error against 64 bits 1.38 times as
+// large, 3360x2592x4288 2.82e-7 -> 4.23e-7; and 81 of 60000 random products would need scratch memory where they needed none, or more than
+// the static array (2960x6976x5680, 696x2002x8416).  Only a plan with that tile or with a split has to ask.
 Plan plan_product(int64_t M, int64_t N, int64_t K, bool may_split, int k32, int straddling, const Prices &prices) {
     const KRanges ranges(K);
     const bool forced = g_force_split.load(std::memory_order_relaxed) >= 1 || g_force_tail.load(std::memory_order_relaxed) > 1 ||
                         g_force_tile.load(std::memory_order_relaxed) >= 0;
     if (forced) return choose_plan(M, N, ranges, may_split, true, 1, true, k32, true, kWorkspaceBytes, prices, straddling);
     const Former former = ranges.n == 1 ? Former{may_split ? kWorkspaceBytes : 0, INT32_MAX} : former_plan(M, N, K, ranges, may_split, k32, straddling);
-    auto plan_of = [&](const Prices &by, int32_t longest) {
-        return choose_plan(M, N, ranges, former.scratch > 0, true, 1, true, k32, true, former.scratch, by, straddling, longest);
+    auto plan_of = [&](const Prices &by, int64_t scratch, int32_t longest) {
+        return choose_plan(M, N, ranges, scratch > 0, true, 1, true, k32, true, scratch, by, straddling, longest);
     };
-    const Plan plan = plan_of(prices, former.longest);
-    if ((plan.tile != fg::TILE_256x256 && plan.tile != fg::TILE_256x256_K32) || (&prices != &kPrices && &prices != &kPricesShort)) return plan;
-    const Plan before = plan_of(kPricesAdd, former.longest);
+    const Plan plan = plan_of(prices, former.scratch, former.longest);
+    const bool large = plan.tile == fg::TILE_256x256 || plan.tile == fg::TILE_256x256_K32, split = plan.splits > 1 || plan.tail_splits > 1;
+    if ((!large && !split) || (&prices != &kPrices && &prices != &kPricesShort)) return plan;
+    const Plan before = plan_of(kPricesAdd, former.scratch, former.longest);
     auto sum_of = [&](const Plan &p) { return sum_length(kPricesAdd, p.tile, p.splits, (ranges.nk + p.splits - 1) / p.splits); };
-    return sum_of(plan) <= sum_of(before) ? plan : plan_of(prices, sum_of(before));
+    const int64_t allowed = scratch_class(scratch_need(before, M, N));
+    if (scratch_need(plan, M, N) <= allowed && (!large || sum_of(plan) <= sum_of(before))) return plan;
+    return plan_of(prices, allowed, std::min(former.longest, sum_of(before)));
 }
 
 // Tile of the complex and dual kernels (256x128, 128x128 with two workgroups per unit, 64x64 with

@@ -1,4 +1,6 @@
 """Plans of products (fg_gemm_plan) on whose tile a measured rule decides; CPU, no launch."""
+import re
+
 import pytest
 
 from paper_2009_12263_amd import binding as fg
@@ -34,3 +36,23 @@ def test_no_sum_is_longer_than_before(M, N, K, la, lb):
 def test_tile_of_a_short_k(variant, M, N, K, tile):
     """The 256x128 tile in place of the 256x256 one: where C and D stream, by what decides that (keeps_real_cd), and not by M and N alone."""
     assert fg.fg_gemm_plan(M, N, K, fg.FG_COL, fg.FG_COL, variant=variant).replace("_k32", "").endswith("_" + tile)
+
+
+def _scratch(M, N, plan):
+    """Bytes of partial products of a plan with one workgroup per compute unit."""
+    tm, tn = (int(v) for v in re.search(r"_(\d+)x(\d+)x", plan).groups())
+    tiles = -(-M // tm) * -(-N // tn)
+    split, tail = re.search(r"\+splitk(\d+)", plan), re.search(r"\+tailsplitk(\d+)", plan)
+    return (tiles * int(split[1]) if split else tiles % 256 * int(tail[1]) if tail else 0) * tm * tn * 4
+
+
+@pytest.mark.parametrize("M,N,K,la,lb,limit", [
+    (6832, 3408, 12000, ROW, COL, 0), (2528, 6432, 13552, ROW, ROW, 0), (7627, 5147, 6160, ROW, ROW, 0), (8059, 5054, 7592, COL, ROW, 0),
+    (2960, 6976, 5680, COL, COL, 0), (5824, 2864, 1952, ROW, COL, 0), (7436, 1060, 3736, COL, ROW, 0), (3270, 5114, 1144, ROW, COL, 0),
+    (7248, 176, 9328, COL, COL, 16 << 20), (1481, 708, 12568, COL, ROW, 16 << 20), (696, 2002, 8416, ROW, COL, 16 << 20), (1056, 7835, 8024, COL, ROW, 16 << 20),
+    (368, 4096, 12832, ROW, COL, 16 << 20), (1855, 746, 10848, COL, COL, 16 << 20)])
+def test_no_call_needs_more_scratch_memory_than_before(M, N, K, la, lb, limit):
+    """What needed none can be captured without the workspace, what fitted the static array can be made by fg_gemm_noalloc: the kernels with
+    four waves and their rates change neither."""
+    for variant in (fg.FG_PLAN_REAL, fg.FG_PLAN_REAL_BF16):
+        assert _scratch(M, N, fg.fg_gemm_plan(M, N, K, la, lb, variant=variant)) <= limit
