@@ -133,7 +133,7 @@ const fg::KernelEntry *table_for(bool a_kc, bool b_kc) {
 // 4876x7518x2448): the choice by them alone is on average 1.7 % slower than the fastest (5 % with the rates before the larger
 // rings), at most 42 % (6708x5150x96), and over 16 % only with K up to 224; held to what plan_product promises, 3.4 % (4.7 %).
 // Since then the rates of the two large tiles went up with their K loops (1 -> 1.12, 0.88 -> 0.95): 2 of the 190 products take another
-// plan, and 650 of 60000 random ones, 300 of which at 0.93 of the time by the rates before, 0.76 to 1.15.
+// plan, and 572 of 60000 random ones, 266 of which at 0.93 of the time by the rates before, 0.76 to 1.14.
 constexpr int kTileM[fg::TILE_COUNT] = {256, 256, 128, 64, 128, 256, 64, 64, 64, 256, 128};
 constexpr int kTileN[fg::TILE_COUNT] = {256, 128, 128, 64, 128, 256, 64, 64, 128, 128, 128};
 constexpr int kTilesPerCU[fg::TILE_COUNT] = {1, 1, 2, 4, 1, 1, 2, 1, 1, 1, 1};

@@ -90,6 +90,21 @@ def test_lane_exchanges_wait_for_vector_results(kernels):
     assert seen > 10000
 
 
+def test_matrix_instructions_wait_for_vector_results(kernels):
+    """A matrix instruction needs two wait states after another vector instruction that writes what it reads; those of the kernels with
+    four waves are assembly."""
+    def writes(op, rest):
+        if not op.startswith("v_") or op.startswith(("v_cmp", "v_nop", "v_mfma")):
+            return set()
+        return {r for r in _registers(rest.split(",")[0]) if r[0] != "s"}
+
+    def reads(op, rest):
+        return set().union(*(_registers(r) for r in rest.split(",")[1:])) if op.startswith("v_mfma") else set()
+    for name, code in kernels.items():
+        bad = _too_close(code, writes, reads, 2)
+        assert not bad, "%s: %d matrix instructions right behind the result they read, first %s" % (name, len(bad), bad[0])
+
+
 def test_loads_wait_for_descriptors_that_vector_instructions_write(kernels):
     """A vector memory instruction needs five wait states after a vector instruction (the reload of a spill) that writes a scalar
     register it reads."""
