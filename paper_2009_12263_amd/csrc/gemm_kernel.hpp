@@ -279,7 +279,8 @@ __device__ __forceinline__ u32x4 make_rsrc(const void *p, uint32_t bytes = 0x7ff
 // serialise the prefetch of later tiles with the product of the current one.)
 // SPILLS: the kernel keeps more in scalar registers than there are, so a descriptor may come back from a spill (v_readlane) right in
 // front of the load.  A vector memory instruction needs five wait states behind a vector instruction that writes a scalar register it
-// reads, and the compiler, which does not see one in assembly, leaves them out.
+// reads, and the compiler, which does not see one in assembly, leaves them out.  (On every load of these kernels instead of the first
+// of a K step only: contractions of 5.6 to 127 us equal within 0.4 %.)
 template <bool STREAM = false, bool SPILLS = false>
 __device__ __forceinline__ void load16_to_lds(u32x4 rsrc, uint32_t lds_addr, uint32_t voff) {
     if constexpr (STREAM)
