@@ -165,8 +165,9 @@ constexpr Rates kRatesShort = {{1.12, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367,
                                2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
                                {0, 0.022, 0, 0.0446, 0.0395, 0, 0.09, 0.142, 0.098}, true,
                                {1, 1, 1, 1, 1, 1, 2, 2, 2, 1, 1}, {1, 1, 1, 1, 2, 1, 2, 2, 2, 1, 2}};
-// Addition on A and B, whose kernels of the large tiles have eight waves; what all real products were priced with before there were
-// others (see plan_product).
+// Addition on A and B and diagonal operands, whose kernels of the large tiles have eight waves (170 diagonal products above 256 MB took the 256x256
+// tile by the rates above, at 1.085 of the time, 11888x2800 with A diagonal 78.7 and 96.1 us); what all real products were priced with
+// before there were others (see plan_product).
 constexpr Rates kRatesAdd = {{1, 0.88, 0.732, 0.596, 0.74, 1, 0.373, 0.367, 0.384},
                              {1, 0.88, 0.527, 0.169, 0.74, 1, 0.233, 0.367, 0.384},
                              2.07e-6, 26.8e9, 6.92e-6, 8.7e12,
@@ -283,9 +284,8 @@ int32_t sum_length(const Prices &prices, int tile, int S, int32_t share) {
 }
 
 // longest: no plan whose sums are longer (sum_length).
-Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bool allow_smallest = true, int64_t batches = 1,
-                 bool allow_deep = true, int k32 = 0, bool allow_groups = false, int64_t scratch_bytes = kWorkspaceBytes,
-                 const Prices &prices = kPrices, int straddling = 0, int32_t longest = INT32_MAX) {
+Plan choose_plan(int64_t M, int64_t N, const KRanges &ranges, bool may_split, bool allow_smallest, int64_t batches,
+                 bool allow_deep, int k32, bool allow_groups, int64_t scratch_bytes, const Prices &prices, int straddling = 0, int32_t longest = INT32_MAX) {
     constexpr double tail_launch = 6e-6, tail_bw = 3e12;      // the leftover tiles' reduction follows a full round
     // tuning overrides (see read_tuning_from_environment)
     int force_tile = -1;
@@ -519,7 +519,7 @@ const fg::KernelEntry *select_kernel(const Problem &q, Plan *plan_out = nullptr)
     const bool long16 = q.cd16 && q.K >= 512;               // (see kRates16)
     const int off = (int)off_line(q.a_kc ? q.K : q.M) + (int)off_line(q.b_kc ? q.K : q.N);
     auto product = [&](bool split, const Prices &prices) { return plan_product(q.M, q.N, q.K, split, k32, may_split || long16 ? off : 0, prices); };
-    Plan plan = q.a_diag || q.b_diag ? choose_plan(q.M, q.N, KRanges(q.K), false, true, 1, false)
+    Plan plan = q.a_diag || q.b_diag ? choose_plan(q.M, q.N, KRanges(q.K), false, true, 1, false, 0, false, 0, kPricesAdd)      // (eight waves)
                                      : product(may_split, long16 ? kPrices16 : q.ab_add ? kPricesAdd : q.K <= 512 ? kPricesShort : kPrices);
     // With C the 256x128 tile has eight waves up to K = 768 (below).  Only a plan of one pass is made again, for one pass: whether a product
     // is split does not depend on C, which the plan query does not know.

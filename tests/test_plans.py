@@ -56,3 +56,11 @@ def test_no_call_needs_more_scratch_memory_than_before(M, N, K, la, lb, limit):
     four waves and their rates change neither."""
     for variant in (fg.FG_PLAN_REAL, fg.FG_PLAN_REAL_BF16):
         assert _scratch(M, N, fg.fg_gemm_plan(M, N, K, la, lb, variant=variant)) <= limit
+
+
+@pytest.mark.parametrize("M,N,la,lb,tile", [
+    (1584, 29072, ROW, fg.FG_DIAG, "256x128x64"), (14488, 3552, fg.FG_DIAG, ROW, "256x128x64"), (10848, 4736, ROW, fg.FG_DIAG, "256x128x64"), (12192, 4512, fg.FG_DIAG, COL, "256x128x64"),
+    (10384, 4960, COL, fg.FG_DIAG, "256x128x64"), (17816, 3032, COL, fg.FG_DIAG, "256x128x64"), (7272, 7360, fg.FG_DIAG, ROW, "256x128x64"), (3952, 12816, fg.FG_DIAG, ROW, "256x128x64")])
+def test_diagonal_products_by_rates_of_their_own(M, N, la, lb, tile):
+    """Their kernels have eight waves: the rates of the kernels with four are not theirs."""
+    assert fg.fg_gemm_plan(M, N, M if la == fg.FG_DIAG else N, la, lb).endswith("_" + tile)
